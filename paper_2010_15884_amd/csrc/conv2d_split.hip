@@ -1,0 +1,444 @@
+// 2-D valid convolution (paper Eq. 3) for filters whose multiply-adds outweigh their bytes, on the
+// matrix cores and in full fp32: no promise about the inputs is asked of the caller.
+//
+// Contraction.  One v_mfma_f32_16x16x32_bf16 multiplies a 16 x 32 by a 32 x 16 matrix.  The
+// contraction is made from the filter's own extent (a doubly blocked Toeplitz form):
+//
+//   N (16)  "bases": 16 output positions (r, c0 + JC i), i = 0..15, of one output row
+//   M (16)  "offsets": the JR x JC outputs (r + jr, c + jc) next to a base, j = JC jr + jc
+//   K       input offsets (dr, dc), dc < 16, two rows (32 values) = one "unit" per instruction
+//
+// 4 x 4 offsets serve filters up to 13 columns, 8 x 2 offsets 14 and 15 columns (kw + JC - 1 <= 16).
+// A group of JR output rows takes NS = ceil((kh + JR - 1) / 2) units.
+//
+// Precision.  Every input and tap is the exact sum of three bf16 numbers, v = v1 + v2 + v3, each the
+// rest rounded to nearest (8 + 8 + 8 bits: nothing of the 24 is lost).  Six of the nine products are
+// taken -- x1f1, x1f2, x2f1, x2f2, x1f3, x3f1 -- and accumulated in fp32; the three dropped ones are
+// below 2^-25 of the term and of either sign.  bf16 has the exponent range of fp32, so nothing is
+// scaled.  What the split cannot carry is looked for in every input: infinities, NaN (the zeros of the
+// Toeplitz form would spread them to outputs whose window does not hold them), magnitudes from 2^80 on
+// and non-zero ones below 2^-40 (parts or products of parts could become subnormal, which the matrix
+// cores read as 0).  The 16 input rows x 272 columns that hold such a value are noted, and the outputs
+// they reach are taken again with ordinary multiply-adds before the workgroup ends.
+//
+// Data path.  A workgroup of four wavefronts walks down a block of rows of a 256-column strip, 16 input
+// rows (a "chunk") at a time.  A chunk is loaded into registers two chunks ahead of its use, split once
+// (not once per overlapping window) and written to LDS as three bf16 planes one chunk ahead; a lane's
+// operand is then 16 bytes of a plane.  Every unit is read from LDS once and applied to all output
+// groups it belongs to, whose sums wait in registers: no halo row is loaded or split twice within a
+// block, one barrier per chunk, and all indices of the sums are compile-time constants.
+//
+// What bounds it: instruction issue.  A chunk of 11x11 takes a workgroup 4.0 us with two of them on a CU: 168 matrix
+// instructions (1.1 us a wavefront at 16 clocks) and about 350 vector instructions of split, checks and addresses
+// (0.6 us), which do not overlap between the two wavefronts of a SIMD.  Measured (us, the vector kernels before /
+// this): 11x11 on 8192^2 243 / 147, 15x15 on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 42.
+// Tried: 272 input columns per chunk (one wavefront splits a fifth piece and the others wait: 11x11 190 us with two
+// accumulators an output), one accumulator (145 us, but errors of 1.8e-7 instead of 6e-8), stores behind per-lane
+// branches (every chunk then waits for the stores of the one before), three workgroups a CU (spills at NS = 7, level
+// below).  Reads of 16 bytes from LDS at 8-byte alignment are slow: a window is two 8-byte (8 x 2: four 4-byte) reads.
+#include "launch.h"
+#include "systolic.h"
+#include "tiling.h"
+
+#include <type_traits>
+
+namespace sysconv {
+namespace {
+
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+typedef const float __attribute__((address_space(4)))* kernarg_floats;
+
+constexpr int kCols = 240;                  // output columns of a workgroup's strip (64 for three wavefronts, 48 for the last)
+constexpr int kInCols = 256;                // input columns of a chunk (a filter is at most 15 wide)
+constexpr int kChunk = 16;                  // input rows of a chunk: 8 units
+constexpr int kUnits = kChunk / 2;
+constexpr int kRow = 3 * kInCols;           // a row in LDS, in bf16 numbers: 256 first parts, 256 second, 256 third
+constexpr int kBuf = kChunk * kRow;
+constexpr int kMaxChunks = 64;              // chunks of a row block
+constexpr int kNonTemporal = 2;             // the nt bit of a buffer store
+constexpr unsigned kTiny = ((127u - 40u) << 24) - 1;       // (bits << 1) - 1 of 2^-40
+constexpr unsigned short kHuge = (127 + 80) << 7;          // upper half of the bits of 2^80
+
+// Three bf16 parts of two numbers; every part is the remainder rounded to nearest.
+__device__ __forceinline__ void split2(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3)
+{
+    p1 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{a, b}, b2));
+    const float ra = a - __builtin_bit_cast(float, p1 << 16), rb = b - __builtin_bit_cast(float, p1 & 0xffff0000u);
+    p2 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{ra, rb}, b2));
+    const float sa = ra - __builtin_bit_cast(float, p2 << 16), sb = rb - __builtin_bit_cast(float, p2 & 0xffff0000u);
+    p3 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{sa, sb}, b2));
+}
+
+// Barrier for what the workgroup exchanges through LDS: the loads from global memory that are in flight stay so.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int JC, int NS>
+struct SplitShape {
+    static constexpr int JR = 16 / JC;                     // output rows of a group
+    static constexpr int NB = 64 / (16 * JC);       // instruction columns (16 bases) of a wavefront's 64 columns
+    static constexpr int UG = JR / 2;                      // units from one group to the next
+    static constexpr int GROUPS = kChunk / JR;             // groups that start in a chunk
+    static constexpr int LIVE = 4;                         // sums of a group live in slot (group mod LIVE)
+    static constexpr int PARTS = JC == 4 ? 2 : 1;          // sums of an output: x1f1 apart from the small products
+    static constexpr int TROWS = 2 * NS + JR - 1;          // rows of the zero-padded taps
+    static constexpr int TCOLS = 16 + JC - 1;
+    static_assert(NS - 1 < LIVE * UG, "a slot is free again before its next group starts");
+    static_assert((LIVE % GROUPS) == 0 || GROUPS == LIVE, "slots repeat over the chunks");
+};
+
+constexpr int kPlaces = 512;                // workgroups the device holds: two a CU (registers allow 256 a lane)
+
+// The outputs rows [ra, rb) x columns [c0, c0 + 256) of the image with plain multiply-adds.
+__device__ __forceinline__ void plain_rows(kernarg_floats taps_f, const float* __restrict__ x, float* __restrict__ y,
+                                           int w_img, long long xp, int ow, long long yp, int kh, int kw, int c0,
+                                           int ra, int rb, int wave, int lane)
+{
+    const int col = c0 + kTile * lane;
+    for (int r = ra + wave; r < rb; r += kBlock / kWave) {
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int p = 0; p < kh; ++p) {
+            const float* row = x + (long long)(r + p) * xp;
+            float win[4];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) win[i] = row[min(col + i, w_img - 1)];
+            for (int q = 0; q < kw; ++q) {
+                win[3] = row[min(col + q + 3, w_img - 1)];
+                const float wv = taps_f[p * kw + q];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(wv, win[i], acc[i]);
+                win[0] = win[1]; win[1] = win[2]; win[2] = win[3];
+            }
+        }
+        store4_guarded<false>(y + (long long)r * yp, col, ow, acc);
+    }
+}
+
+template <int JC, int NS>
+__global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
+    Taps2D taps, const float* __restrict__ x, float* __restrict__ y, int h, int w_img, long long xp, int oh, int ow,
+    long long yp, int kh, int kw, int rows, int row_blocks, int strips, int per_xcd)
+{
+    (void)taps;
+    using S = SplitShape<JC, NS>;
+    constexpr int JR = S::JR, NB = S::NB, UG = S::UG, LIVE = S::LIVE, GROUPS = S::GROUPS;
+    kernarg_floats taps_f = (kernarg_floats)__builtin_amdgcn_kernarg_segment_ptr();
+
+    __shared__ __attribute__((aligned(16))) __bf16 parts[2 * kBuf + 32];     // (windows of the last wavefront reach past a row)
+    __shared__ float tpad[S::TROWS * S::TCOLS];
+    __shared__ int bad_chunk[kMaxChunks];
+
+    const int g = xcd_contiguous(blockIdx.x, per_xcd);
+    if (g >= row_blocks * strips) return;                                  // (the whole workgroup)
+    const int rblk = g / strips, strip = g - rblk * strips;                // workgroups walk along the rows of the image
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = wave_in_block();
+    const int c0 = strip * kCols;
+    const int r0 = rblk * rows;
+    const int ow_strip = min(ow, c0 + kCols);                              // columns the strip stores: up to here
+    const int rows_out = min(rows, oh - r0);
+    // chunks 0 .. chunks-1 start groups; one more holds the units that only finish them
+    const int chunks = (rows_out + kChunk - 1) / kChunk;
+    const int last_row = h - 1;
+    const bool edge = c0 + kInCols > w_img;                                // uniform
+
+    // ---------------------------------------------------------------- a chunk into registers
+    // Wavefront v takes rows v, v+4, v+8, v+12 (1 KB each).  Loads that would reach past the row's end start at its last
+    // four columns instead and are put right before the split.
+    const int col_m = min(c0 + kTile * lane, w_img - 4), off_m = c0 + kTile * lane - col_m;
+    const unsigned col_b = (unsigned)col_m * (unsigned)sizeof(float);
+    f4u raw[4];
+    auto load_chunk = [&](int c) {
+        const int rbase = r0 + c * kChunk;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            raw[k] = *reinterpret_cast<const f4u*>(reinterpret_cast<const char*>(x + (long long)min(rbase + wave + 4 * k, last_row) * xp) + col_b);
+    };
+    auto put_right = [&](f4u& v, int off) {                                // columns past the image read as 0
+        if (off & 1) v = f4u{v.y, v.z, v.w, 0.0f};
+        if (off & 2) v = f4u{v.z, v.w, 0.0f, 0.0f};
+        if (off > 3) v = f4u{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    unsigned tiny;
+    us2 huge;
+    auto put = [&](const f4u& v, __bf16* dst) {
+        u2 p1, p2, p3;
+        unsigned a, b, c;
+        split2(v.x, v.y, a, b, c);
+        p1.x = a; p2.x = b; p3.x = c;
+        split2(v.z, v.w, a, b, c);
+        p1.y = a; p2.y = b; p3.y = c;
+        *reinterpret_cast<u2*>(dst) = p1;
+        *reinterpret_cast<u2*>(dst + kInCols) = p2;
+        *reinterpret_cast<u2*>(dst + 2 * kInCols) = p3;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tiny = min(tiny, (__builtin_bit_cast(unsigned, (float)v[i]) << 1) - 1u);   // +-0: the largest
+        huge = __builtin_elementwise_max(huge, __builtin_bit_cast(us2, p1.x & 0x7fff7fffu));
+        huge = __builtin_elementwise_max(huge, __builtin_bit_cast(us2, p1.y & 0x7fff7fffu));
+    };
+    auto store_chunk = [&](int c, auto edge_tag) {
+        __bf16* buf = parts + (c & 1) * kBuf;
+        tiny = 0xffffffffu;
+        huge = us2{0, 0};
+        if constexpr (decltype(edge_tag)::value) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) put_right(raw[k], off_m);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) put(raw[k], buf + (wave + 4 * k) * kRow + kTile * lane);
+        if (tiny < kTiny || huge.x >= kHuge || huge.y >= kHuge) bad_chunk[c] = 1;
+    };
+
+    load_chunk(0);
+    for (int e = threadIdx.x; e < S::TROWS * S::TCOLS; e += kBlock) {
+        const int p = e / S::TCOLS - (JR - 1), q = e % S::TCOLS - (JC - 1);
+        tpad[e] = p >= 0 && p < kh && q >= 0 && q < kw ? taps_f[p * kw + q] : 0.0f;
+    }
+    if (threadIdx.x < kMaxChunks) bad_chunk[threadIdx.x] = 0;
+    __syncthreads();
+
+    // A operands: the Toeplitz form of the taps, constant for the whole kernel
+    const int i16 = lane & 15, kb = lane >> 4;                             // operand coordinates of the lane
+    b8 fa[NS][3];
+    {
+        const int jr = i16 / JC, jc = i16 % JC;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const float* t = tpad + (2 * s + (kb >> 1) - jr + JR - 1) * S::TCOLS + 8 * (kb & 1) - jc + JC - 1;
+            u4 p[3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                unsigned a, b, c;
+                split2(t[2 * i], t[2 * i + 1], a, b, c);
+                p[0][i] = a; p[1][i] = b; p[2][i] = c;
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) fa[s][j] = __builtin_bit_cast(b8, p[j]);
+        }
+    }
+    if (edge) store_chunk(0, std::true_type{});
+    else store_chunk(0, std::false_type{});
+    load_chunk(1);
+    __syncthreads();
+
+    f4 acc[LIVE][NB][S::PARTS];
+    const int win0 = (kb >> 1) * kRow + wave * 64 + JC * i16 + 8 * (kb & 1);
+    const int out_col = c0 + wave * 64 + JC * i16;
+
+    // Outputs of group `grp` of the block: lane (i16, kb) holds offsets j = 4 kb .. 4 kb + 3.  Buffer stores drop the
+    // lanes whose offset is out of range, so no store hides behind a branch: the compiler can then count the stores
+    // that are younger than the loads in flight and wait for the loads alone.
+    const unsigned pitch_b = (unsigned)yp * (unsigned)sizeof(float);
+    auto store_group = [&](int grp, const f4 (&sums)[NB][S::PARTS], auto edge_tag) {
+        constexpr unsigned kNowhere = 0xffffff00u;
+        float* base = y + (long long)(r0 + grp * JR) * yp;                 // uniform
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const u4 ob = __builtin_bit_cast(u4, S::PARTS == 2 ? sums[nb][0] + sums[nb][S::PARTS - 1] : sums[nb][0]);
+            const int col = out_col + nb * 16 * JC;
+            constexpr int kRows = 4 / JC;                                  // rows of the lane's four outputs
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const int rr = kb * kRows + k;
+                const unsigned off = (unsigned)rr * pitch_b + (unsigned)col * 4u;
+                const bool row_ok = grp * JR + rr < rows_out;
+                if constexpr (!decltype(edge_tag)::value) {                // 256 input columns: 240 outputs at least
+                    const unsigned to = row_ok && col < c0 + kCols ? off : kNowhere;
+                    if constexpr (JC == 4)
+                        __builtin_amdgcn_raw_buffer_store_b128(ob, rsrc, to, 0, kNonTemporal);
+                    else
+                        __builtin_amdgcn_raw_buffer_store_b64(u2{ob[2 * k], ob[2 * k + 1]}, rsrc, to, 0, kNonTemporal);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < JC; ++i)
+                        __builtin_amdgcn_raw_buffer_store_b32(ob[JC * k + i], rsrc,
+                                                              row_ok && col + i < ow_strip ? off + 4u * i : kNowhere, 0, kNonTemporal);
+                }
+            }
+        }
+    };
+
+    // One chunk: FIRST has no groups from before it, LAST starts none.  SLOT0: slot of the chunk's first group.
+    auto compute = [&](int c, auto edge_tag, auto first_tag, auto last_tag, auto slot_tag) {
+        constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
+        constexpr int SLOT0 = decltype(slot_tag)::value;
+        int at = (c & 1) * kBuf + win0;
+#pragma unroll
+        for (int u = 0; u < (LAST ? NS - UG : kUnits); ++u, at += 2 * kRow) {
+            __builtin_amdgcn_sched_barrier(0);                             // (else the reads of many units are hoisted and registers spill)
+            asm("" : "+v"(at));                                            // one running address, not one per unit kept for the loop
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                b8 b[3];
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    __builtin_memcpy(&b[j], __builtin_assume_aligned(parts + at + nb * 16 * JC + j * kInCols, 2 * JC), 16);
+#pragma unroll
+                for (int lg = -LIVE; lg < GROUPS; ++lg) {
+                    const int s = u - UG * lg;
+                    if (s < 0 || s >= NS || (FIRST && lg < 0) || (LAST && lg >= 0)) continue;
+                    constexpr int kLo = S::PARTS - 1;
+                    f4& hi = acc[(lg + SLOT0 + LIVE) % LIVE][nb][0];
+                    f4& lo = acc[(lg + SLOT0 + LIVE) % LIVE][nb][kLo];
+                    if (s == 0) hi = lo = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][2], b[0], lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[2], lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][1], b[1], lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][1], b[0], lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[1], lo, 0, 0, 0);
+                    hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[0], hi, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int lg = -LIVE; lg < GROUPS; ++lg) {
+                if (u - UG * lg != NS - 1 || (FIRST && lg < 0) || (LAST && lg >= 0)) continue;
+                store_group(c * GROUPS + lg, acc[(lg + SLOT0 + LIVE) % LIVE], edge_tag);
+            }
+        }
+    };
+    // Chunk c+1 goes to LDS and chunk c+2 is asked for while chunk c is used; the buffer that chunk c+1
+    // takes was last read before the barrier that ended chunk c-1.
+    auto run = [&](auto edge_tag) {
+        auto advance = [&](int c, auto first_tag, auto slot_tag) {
+            store_chunk(c + 1, edge_tag);
+            load_chunk(c + 2);
+            compute(c, edge_tag, first_tag, std::false_type{}, slot_tag);
+            lds_barrier();
+        };
+        using Slot0 = std::integral_constant<int, 0>;
+        using Slot1 = std::integral_constant<int, GROUPS % LIVE>;          // slots of the odd chunks
+        advance(0, std::true_type{}, Slot0{});
+        int c = 1;
+        for (; c + 2 <= chunks; c += 2) {
+            advance(c, std::false_type{}, Slot1{});
+            advance(c + 1, std::false_type{}, Slot0{});
+        }
+        if (c < chunks) {
+            advance(c, std::false_type{}, Slot1{});
+            compute(c + 1, edge_tag, std::false_type{}, std::true_type{}, Slot0{});
+        } else {
+            compute(c, edge_tag, std::false_type{}, std::true_type{}, Slot1{});
+        }
+    };
+    if (edge) run(std::true_type{});
+    else run(std::false_type{});
+
+    // Chunks with values that the split does not carry: the groups of rows they belong to once more.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                       // the stores above are done before any of these
+    __syncthreads();
+    for (int k = 0; k <= chunks; ++k) {
+        if (!__builtin_amdgcn_readfirstlane(bad_chunk[k])) continue;
+        const int first = k * kChunk - (2 * NS - 1);                       // group at row R: input rows R .. R + 2 NS - 1
+        const int ra = first <= 0 ? 0 : (first + JR - 1) / JR * JR;
+        const int rb = min((k + 1) * kChunk, rows_out);
+        plain_rows(taps_f, x, y, w_img, xp, ow_strip, yp, kh, kw, c0, r0 + ra, r0 + rb, wave, lane);
+        __syncthreads();
+    }
+}
+
+template <int JC, int NS>
+hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
+                        hipStream_t s)
+{
+    Taps2D taps;
+    for (int i = 0; i < kTaps2DLen; ++i) taps.f[i] = i < kh * kw ? f[i] : 0.0f;
+    const int oh = h - kh + 1, ow = w - kw + 1;
+    const int strips = (ow + kCols - 1) / kCols;
+    // Rows of a workgroup's block: whole chunks, so many that the rounds of resident workgroups take the
+    // least time.  A block costs its chunks and about 1.5 more for the taps, the first loads and the units
+    // that only finish groups (11x11: 4.0 us a chunk in every round, on images of 2048^2 to 8192^2).
+    const int all_chunks = (oh + kChunk - 1) / kChunk;
+    int best = 1;
+    double best_cost = 0;
+    for (int m = 1; m < kMaxChunks && m <= all_chunks; ++m) {
+        const long long wgs = (long long)((all_chunks + m - 1) / m) * strips;
+        const double cost = (double)((wgs + kPlaces - 1) / kPlaces) * (m + 1.5);
+        if (m == 1 || cost < best_cost) { best = m; best_cost = cost; }
+    }
+    const long long rows = (long long)best * kChunk;
+    const int row_blocks = (int)((oh + rows - 1) / rows);
+    const long long groups = (long long)row_blocks * strips;
+    const long long per_xcd = (groups + kXcds - 1) / kXcds;
+    const long long blocks = per_xcd * kXcds;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((conv2d_split_kernel<JC, NS>), dim3((unsigned)blocks), dim3(kBlock), 0, s, taps, x, y, h, w,
+                       (long long)xp, oh, ow, (long long)yp, kh, kw, (int)rows, row_blocks, strips, (int)per_xcd);
+    return hipGetLastError();
+}
+
+int split_units(int kh, int kw)                 // NS of the kernel that serves the filter
+{
+    if (kh <= 13 && kw <= 13) return kh <= 5 ? 4 : (kh + 4) / 2;           // ceil((kh + 3) / 2), at least 4
+    return kh <= 7 ? 8 : (kh + 8) / 2;                                     // ceil((kh + 7) / 2), at least 8
+}
+
+}  // namespace
+
+// Filters and images the kernel takes: taps 0 or 2^-60 .. 2^40 in magnitude (so that no part of a tap and no
+// product of parts is subnormal or infinite), rows of at least four columns (the loads are 16 bytes), output
+// pitches whose rows of a group lie within the 2 GB of a buffer descriptor.
+bool conv2d_split_takes(int w, size_t yp, const float* f, int kh, int kw)
+{
+    if (w < 4 || yp > ((size_t)1 << 25) || kh > kMaxK2D || kw > kMaxK2D) return false;
+    for (int i = 0; i < kh * kw; ++i) {
+        const float a = __builtin_fabsf(f[i]);
+        if (!(a == 0.0f || (a >= 0x1p-60f && a <= 0x1p40f))) return false;         // NaN fails too
+    }
+    return true;
+}
+
+// Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units NS, theirs with
+// the kh*kw taps, so the line is drawn in taps per unit; measured on 300x400 .. 8192x8192 images (us, vector / split):
+//   filters that only the run-time-sized FBS kernel serves (a side above 11, or 8 .. 11 and not square): from 12 taps
+//   a unit at every size (5x13 7.8 / 6.0 on 300x400, 49 / 41 on 4096^2; 9x13 76 / 42; 12x12 11.0 / 7.3, 100 / 46), from 8
+//   on images of 2 M outputs (13x5 9.7 / 10.2 on 1000^2, 19.4 / 17.6 on 2048^2, 56 / 44 on 4096^2).  With 14 or 15 rows or
+//   columns: from 10 taps a unit (15x15 14.9 / 8.9 on 300x400, 150 / 59 on 4096^2; 6x14 10.9 / 10.4 on 1000^2; 3x15 32 / 37
+//   on 3001x4003), but not tall narrow ones, whose sums over 11 units in one accumulator are no more exact than the
+//   vector kernel's (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
+//   8x8 .. 11x11 (SBM) and other sides up to 11 (compile-time FBS): those kernels are quick on small images, and the
+//   split kernel wins once the image is large enough, the sooner the more taps a unit has: 11x11 (17.3) 9.9 / 9.6 on
+//   1000^2, 258 / 147 on 8192^2; 10x10 (14.3) 20.0 / 16.7 on 2048^2; 9x9 (13.5) 17.2 / 16.1 on 2048^2; 8x8 (10.7) 18.3 / 19.5
+//   on 2000x3000, 33.6 / 32.1 on 3001x4003; 7x11 (15.4) 8.8 / 8.1 on 1000^2; 11x7 (11) 9.7 / 10.0 on 1500x1100, 55 / 42 on
+//   4096^2; 7x7 25.5 / 32.5 on 3001x4003.
+bool conv2d_split_pays(int oh, int ow, int kh, int kw)
+{
+    const int taps = kh * kw, units = split_units(kh, kw);
+    const double outputs = (double)oh * ow;
+    if (kh > 13 || kw > 13) return kw >= 11 && taps >= 10 * units;
+    const bool run_time_sized = kh > 11 || kw > 11 || (kh >= 8 && kw >= 8 && kh != kw);
+    if (run_time_sized) return taps >= 12 * units || (taps >= 8 * units && outputs >= 2e6);
+    return taps >= 64 && outputs * (taps - 9 * units) >= 12e6 * units;
+}
+
+hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
+                               size_t yp, hipStream_t s)
+{
+    const int units = split_units(kh, kw);
+    if (kh <= 13 && kw <= 13) {
+        switch (units) {
+        case 4: return launch_split<4, 4>(x, h, w, xp, f, kh, kw, y, yp, s);
+        case 5: return launch_split<4, 5>(x, h, w, xp, f, kh, kw, y, yp, s);
+        case 6: return launch_split<4, 6>(x, h, w, xp, f, kh, kw, y, yp, s);
+        case 7: return launch_split<4, 7>(x, h, w, xp, f, kh, kw, y, yp, s);
+        default: return launch_split<4, 8>(x, h, w, xp, f, kh, kw, y, yp, s);
+        }
+    }
+    switch (units) {
+    case 8: return launch_split<2, 8>(x, h, w, xp, f, kh, kw, y, yp, s);
+    case 9: return launch_split<2, 9>(x, h, w, xp, f, kh, kw, y, yp, s);
+    case 10: return launch_split<2, 10>(x, h, w, xp, f, kh, kw, y, yp, s);
+    default: return launch_split<2, 11>(x, h, w, xp, f, kh, kw, y, yp, s);
+    }
+}
+
+}  // namespace sysconv

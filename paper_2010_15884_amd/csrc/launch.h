@@ -71,6 +71,12 @@ bool conv2d_mfma_taps_in_range(const float* f, int n);      // largest |f| is 0 
 hipError_t launch_conv2d_mfma(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                               float* y, size_t yp, hipStream_t s);
 
+// Matrix-core path without conditions on the input (conv2d_split.hip).
+bool conv2d_split_takes(int w, size_t yp, const float* f, int kh, int kw);
+bool conv2d_split_pays(int oh, int ow, int kh, int kw);     // where it is the fastest kernel
+hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
+                               float* y, size_t yp, hipStream_t s);
+
 hipError_t launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t s);
 hipError_t launch_alu_yardstick(float* out, int workgroups, int trips, hipStream_t s);
 long long alu_yardstick_fmas(int workgroups, int trips);
