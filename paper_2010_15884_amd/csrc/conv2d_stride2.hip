@@ -13,6 +13,8 @@
 #include "systolic.h"
 #include "tiling.h"
 
+#include <utility>
+
 namespace sysconv {
 namespace {
 
@@ -242,6 +244,140 @@ hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f,
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------ strip form ----
+// Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 512
+// input columns and walks down its 2*(ROWS-1)+kh input rows, kAhead of them in flight in registers.  Each row's two
+// windows are built once and applied to every output row whose filter covers it, where the tiles build them again for
+// every (output row, filter row) and step through the taps four at a time.  Small filters are bound by the requests for
+// input rows ((2 (ROWS-1) + kh) / (2 ROWS) times the image, mostly from L2), large ones by the vector ALUs.
+constexpr int kAhead = 4;
+
+template <int KW, int ROWS, bool EDGE>
+__device__ __forceinline__ void stride2_strip_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
+                                                   float* __restrict__ yrow, int in_col, int out_col, int w_img,
+                                                   long long xp, int ow, long long yp, int kh, int rows_out,
+                                                   bool lane_valid)
+{
+    constexpr int KE = (KW + 1) / 2, KO = KW / 2;
+    const int rows_in = 2 * (rows_out - 1) + kh;
+
+    float v[kAhead][8];
+    auto load_row = [&](int rho, float (&d)[8]) {                          // past the last row: the last row again
+        const float* p = xrow + (long long)min(rho, rows_in - 1) * xp;
+        if (EDGE) {
+            float lo[4], hi[4];
+            load4_guarded<false>(p, in_col, w_img, lo);
+            load4_guarded<false>(p, in_col + 4, w_img, hi);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { d[i] = lo[i]; d[4 + i] = hi[i]; }
+        } else {
+            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + 4);
+            d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
+            d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load_row(i, v[i]);
+
+    float acc[ROWS][4];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r][0] = acc[r][1] = acc[r][2] = acc[r][3] = 0.0f;
+
+    for (int rho0 = 0; rho0 < rows_in; rho0 += kAhead) {
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const int rho = rho0 + j;
+            if (rho >= rows_in) break;                                     // uniform
+            // the filter rows this input row meets, asked for together
+            float wv[ROWS][KW];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                kernarg_floats fp = taps_f + min(max(rho - 2 * r, 0), kh - 1) * KW;
+#pragma unroll
+                for (int q = 0; q < KW; ++q) wv[r][q] = fp[q];
+            }
+            float ev[KE + 3], od[KO + 3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ev[i] = v[j][2 * i];
+#pragma unroll
+            for (int i = 0; i < KO + 3 && i < 4; ++i) od[i] = v[j][2 * i + 1];
+            load_row(rho + kAhead, v[j]);
+#pragma unroll
+            for (int m = 4; m < KE + 3; ++m) ev[m] = from_lane_above(ev[m - 4]);
+#pragma unroll
+            for (int m = 4; m < KO + 3; ++m) od[m] = from_lane_above(od[m - 4]);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const int p = rho - 2 * r;
+                if (p < 0 || p >= kh) continue;                            // uniform
+#pragma unroll
+                for (int q = 0; q < KW; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        acc[r][i] = __builtin_fmaf(wv[r][q], (q & 1) ? od[q / 2 + i] : ev[q / 2 + i], acc[r][i]);
+            }
+        }
+    }
+    if (!lane_valid) return;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        if (r < rows_out) store4_guarded(yrow + (long long)r * yp, out_col, ow, acc[r]);
+}
+
+template <int KW, int ROWS>
+__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_strip_kernel(Taps2D taps, const float* __restrict__ x,
+                                                                          float* __restrict__ y, int w_img,
+                                                                          long long xp, int oh, int ow, long long yp,
+                                                                          int kh, int row_blocks, int strips, int side,
+                                                                          int per_xcd)
+{
+    (void)taps;
+    kernarg_floats tf = (kernarg_floats)__builtin_amdgcn_kernarg_segment_ptr();
+    int rb, strip;
+    if (!wave_tile(per_xcd, row_blocks, strips, side, rb, strip)) return;
+    constexpr int valid_lanes = kWave - halo_lanes((KW + 1) / 2);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int out_col0 = strip * kTile * valid_lanes;
+    const int r0 = rb * ROWS;
+    const int rows_out = min(ROWS, oh - r0);
+    const float* xrow = x + (long long)(2 * r0) * xp;
+    float* yrow = y + (long long)r0 * yp;
+    const bool lane_valid = lane < valid_lanes;
+    const int in_col = 2 * out_col0 + 2 * kTile * lane, out_col = out_col0 + kTile * lane;
+    if (2 * out_col0 + kCols <= w_img)
+        stride2_strip_rows<KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+    else
+        stride2_strip_rows<KW, ROWS, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+}
+
+template <int KW, int ROWS>
+hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f, int kh, float* y, size_t yp, hipStream_t s)
+{
+    Taps2D taps;
+    for (int i = 0; i < kTaps2DLen; ++i) taps.f[i] = i < kh * KW ? f[i] : 0.0f;
+    const int oh = (h - kh) / 2 + 1, ow = (w - KW) / 2 + 1;
+    const int cols = kTile * (kWave - halo_lanes((KW + 1) / 2));
+    const int strips = (ow + cols - 1) / cols;
+    const int row_blocks = (oh + ROWS - 1) / ROWS;
+    long long per_xcd;
+    const long long blocks = tile_workgroups(row_blocks, strips, per_xcd);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((conv2d_fbs_stride2_strip_kernel<KW, ROWS>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+                       taps, x, y, w, (long long)xp, oh, ow, (long long)yp, kh, row_blocks, strips, band_width(xp),
+                       (int)per_xcd);
+    return hipGetLastError();
+}
+
+typedef hipError_t (*LaunchStrip)(const float*, int, int, size_t, const float*, int, float*, size_t, hipStream_t);
+template <int ROWS, int... KW>
+hipError_t launch_strip_by_kw(std::integer_sequence<int, KW...>, const float* x, int h, int w, size_t xp, const float* f,
+                              int kh, int kw, float* y, size_t yp, hipStream_t s)
+{
+    static constexpr LaunchStrip table[] = {launch_strip<KW + 1, ROWS>...};
+    if (kw < 1 || kw > (int)sizeof...(KW)) return hipErrorInvalidValue;
+    return table[kw - 1](x, h, w, xp, f, kh, y, yp, s);
+}
+
 template <int RPW>
 hipError_t launch_tiles(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
                         hipStream_t s)
@@ -271,9 +407,8 @@ hipError_t launch_tiles(const float* x, int h, int w, size_t xp, const float* f,
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                      float* y, size_t yp, hipStream_t s)
 {
-    // Square filters up to 5x5 run the block form, two output rows per wavefront (8192^2, 5x5: 70 us
-    // against 88 us for the LDS tiles and 56 us for a copy of the same bytes; 1, 3 and 4 rows: 83, 68, 74 us;
-    // 2x2: 58.6 against 64.8 us); everything else the tiles.
+    // Square filters up to 5x5 run the block form, two output rows per wavefront (8192^2, 5x5: 68 us against 75 - 82 us
+    // for the strips, 88 us for the LDS tiles and 56 us for a copy of the same bytes; 1, 3 and 4 rows: 83, 68, 74 us).
     if (kh == kw) {
         switch (kh) {
         case 2: return launch_block<2, 2, 2>(x, h, w, xp, f, y, yp, s);
@@ -283,7 +418,16 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         default: break;
         }
     }
-    return launch_tiles<2>(x, h, w, xp, f, kh, kw, y, yp, s);
+    // The rest runs the strips (us, tiles / strips of 2 / of 3 rows): 8192^2 7x7 126 / 92 / 85, 11x11 165 / 125 / 117, 15x15 303 /
+    // 167 / 179, 13x4 198 / 118 / 108, 2x15 78 / 73 / 78; 4095x6001 7x7 51 / 39 / 37; 2048^2 7x7 12.0 / 11.7 / 12.9, 13x13 30 / 20 / 24.
+    // Three rows read fewer halo rows and need images large enough to fill the chip with fewer wavefronts, and taps of
+    // three filter rows that fit the scalar registers.  Narrow filters on small images stay with the tiles, where four
+    // wavefronts share the staging of one tile's rows (300x400: 7x3 6.9 / 7.4, 13x4 9.5 / 10.4, 15x2 10.2 / 10.7).
+    using AllKw = std::make_integer_sequence<int, kMaxK2D>;
+    const double outputs = (double)((h - kh) / 2 + 1) * ((w - kw) / 2 + 1);
+    if (kw <= 4 && outputs < 4e5) return launch_tiles<2>(x, h, w, xp, f, kh, kw, y, yp, s);
+    if (kw > 1 && kw <= 11 && outputs >= 4e6) return launch_strip_by_kw<3>(AllKw{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    return launch_strip_by_kw<2>(AllKw{}, x, h, w, xp, f, kh, kw, y, yp, s);
 }
 
 }  // namespace sysconv

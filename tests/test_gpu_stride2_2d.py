@@ -121,3 +121,34 @@ def test_stride2_2d_unsupported_requests_launch_nothing():
     assert e.value.status == B.SYS_ERR_SIZE
     torch.cuda.synchronize()
     assert (y == 7.0).all()
+
+
+@pytest.mark.parametrize("kh,kw", [(6, 6), (7, 7), (1, 6), (9, 2), (4, 11), (11, 11), (2, 12), (15, 15), (13, 3)])
+@pytest.mark.parametrize("h,w", [(4003, 4099), (700, 2301)])
+def test_stride2_2d_strips_of_two_and_three_rows(kh, kw, h, w):
+    """Images of 4 M outputs (strips of three rows, the last block of one or two) and smaller ones (two rows), whole
+    strips and the cut one at the right edge, into a pitched output whose surroundings stay untouched."""
+    x, f = W.random_case(kh * 100 + kw, (h, w), (kh, kw), x_range=(0.0, 1.0))
+    oh, ow = (h - kh) // 2 + 1, (w - kw) // 2 + 1
+    big = torch.full((oh + 2, ow + 5), float("nan"), dtype=torch.float32, device="cuda")
+    B.sys_conv2d_strided(dev(x), f, 2, big[1:1 + oh, 2:2 + ow])
+    torch.cuda.synchronize()
+    out = big.cpu().numpy()
+    assert err(np.ascontiguousarray(out[1:1 + oh, 2:2 + ow]), x, f) <= TOL
+    out[1:1 + oh, 2:2 + ow] = np.nan
+    assert np.isnan(out).all()
+
+
+@pytest.mark.parametrize("kh,kw", [(6, 6), (13, 3), (15, 15)])
+def test_stride2_2d_strips_keep_infinities_in_their_windows(kh, kw):
+    h, w = 700, 1301
+    x, f = W.random_case(kh, (h, w), (kh, kw), x_range=(0.0, 1.0))
+    bad = [(0, 0), (h - 1, w - 1), (350, 511), (351, 512)]
+    for r, c in bad:
+        x[r, c] = np.inf
+    y = run(x, f)
+    want = np.zeros(y.shape, bool)
+    for r, c in bad:
+        rr, cc = np.arange(y.shape[0]) * 2, np.arange(y.shape[1]) * 2
+        want |= np.outer((rr <= r) & (r < rr + kh), (cc <= c) & (c < cc + kw))
+    assert np.array_equal(~np.isfinite(y), want)
