@@ -15,6 +15,8 @@
 #include "launch.h"
 #include "systolic.h"
 
+#include <utility>
+
 namespace sysconv {
 namespace {
 
@@ -123,16 +125,24 @@ hipError_t launch_stride2(const float* x, size_t n, const float* w, int k, float
     return hipGetLastError();
 }
 
+// Tap counts known at compile time up to 22, where the loop's counters and its waits for taps show
+// (2^26 inputs, us, loop / unrolled: k = 8 76.4 / 74.7, 13 77.2 / 74.2, 17 79.7 / 75.4, 20 81.0 / 77.9); from there on the
+// unrolled code loses to the loop, which stays in the instruction cache (24 80.7 / 83.4, 36 91 / 114, 64 103 / 206).
+constexpr int kUnrolled = 22;
+typedef hipError_t (*Launch)(const float*, size_t, const float*, int, float*, hipStream_t);
+template <int... K>
+hipError_t launch_by_k(std::integer_sequence<int, K...>, const float* x, size_t n, const float* w, int k, float* y,
+                       hipStream_t s)
+{
+    static constexpr Launch table[] = {launch_stride2<K>...};              // [0]: the loop
+    return table[k <= kUnrolled ? k : 0](x, n, w, k, y, s);
+}
+
 }  // namespace
 
 hipError_t launch_conv1d_fbs_stride2(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
 {
-    switch (k) {                                // the paper's filter sizes (Section 6) and the headline's are unrolled
-    case 2: return launch_stride2<2>(x, n, w, k, y, s);
-    case 5: return launch_stride2<5>(x, n, w, k, y, s);
-    case 16: return launch_stride2<16>(x, n, w, k, y, s);
-    default: return launch_stride2<0>(x, n, w, k, y, s);
-    }
+    return launch_by_k(std::make_integer_sequence<int, kUnrolled + 1>{}, x, n, w, k, y, s);
 }
 
 }  // namespace sysconv
