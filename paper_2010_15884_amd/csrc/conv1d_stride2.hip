@@ -7,8 +7,8 @@
 // The hand-over rule splits the inputs of a PE into two chains that never mix: the
 // even taps see x(2c), x(2c+2), ... and the odd taps x(2c+1), x(2c+3), ...  Each is an
 // ordinary stride-1 FBS array over the de-interleaved signal, E(c) = x(2c) resp.
-// O(c) = x(2c+1), both adding into the same partial sums.  A lane loads eight
-// consecutive inputs (two dwordx4), which are E and O of its four PEs, and the two
+// O(c) = x(2c+1), both adding into the same partial sums.  A lane gets eight
+// consecutive inputs, which are E and O of its four PEs, and the two
 // chains then run the stride-1 time steps with the even resp. the odd taps.  The
 // chains are independent, so they are issued one after the other (all even steps,
 // then all odd steps) rather than alternating.
@@ -76,18 +76,32 @@ __global__ __launch_bounds__(kBlock) void conv1d_fbs_stride2_kernel(TapsStride2 
     const long long base = wave * kGroups * per_group;                     // first output of the wavefront
     if (base >= m) return;                                                 // uniform per wavefront
 
+    // A group's 512 inputs come in as two loads of 1 KB; a round trip through LDS, private to the wavefront, then gives
+    // each lane the eight consecutive inputs of its four PEs.  (Loaded straight by the lanes that need them, every cache
+    // line was asked for by two instructions and the non-temporal hint could not be used: 2^26 inputs, k = 2 72 -> 62 us,
+    // 16 75 -> 64, 31 82 -> 67; a copy of the same bytes takes 65 us.  From k = 50 on the vector ALUs bound both.)
+    __shared__ __attribute__((aligned(16))) float stage[kBlock / kWave][kGroups * 2 * kWave * kTile];
+    float* const lds = stage[wave_in_block()];
     float ev[kGroups][4], od[kGroups][4], acc[kGroups][4];
 #pragma unroll
     for (int r = 0; r < kGroups; ++r) {
-        const long long c0 = base + r * per_group + kTile * lane;          // this lane's first PE
-        float lo[4], hi[4];
-        // The two loads of a lane split every 64 bytes of x between them, so each cache line
-        // is asked for twice in a row: the loads stay cacheable, and the second one hits
-        // (n = 2^27, k = 5: 145 us against 214 us with the non-temporal hint).
-        load4_guarded<false>(x, 2 * c0, n, lo);
-        load4_guarded<false>(x, 2 * c0 + 4, n, hi);
-        ev[r][0] = lo[0]; od[r][0] = lo[1]; ev[r][1] = lo[2]; od[r][1] = lo[3];
-        ev[r][2] = hi[0]; od[r][2] = hi[1]; ev[r][3] = hi[2]; od[r][3] = hi[3];
+        const long long c0 = 2 * (base + r * per_group) + kTile * lane;
+        load4_guarded(x, c0, n, ev[r]);
+        load4_guarded(x, c0 + kWave * kTile, n, od[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < kGroups; ++r) {
+        float* row = lds + r * 2 * kWave * kTile + kTile * lane;
+        *reinterpret_cast<f4*>(row) = f4{ev[r][0], ev[r][1], ev[r][2], ev[r][3]};
+        *reinterpret_cast<f4*>(row + kWave * kTile) = f4{od[r][0], od[r][1], od[r][2], od[r][3]};
+    }
+    wave_exchange();
+#pragma unroll
+    for (int r = 0; r < kGroups; ++r) {
+        const float* own = lds + r * 2 * kWave * kTile + 2 * kTile * lane;
+        const f4 lo = *reinterpret_cast<const f4*>(own), hi = *reinterpret_cast<const f4*>(own + 4);
+        ev[r][0] = lo.x; od[r][0] = lo.y; ev[r][1] = lo.z; od[r][1] = lo.w;
+        ev[r][2] = hi.x; od[r][2] = hi.y; ev[r][3] = hi.z; od[r][3] = hi.w;
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[r][i] = 0.0f;
     }

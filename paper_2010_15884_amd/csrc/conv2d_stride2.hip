@@ -123,9 +123,25 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_kernel(TapsStride2D
     }
 }
 
+// Row of a strip from the lanes' load order (lane l: columns 4l .. 4l+3 of the strip's first and second half, so that a
+// load is 1 KB of consecutive addresses) to the array's (lane l: columns 8l .. 8l+7, four PEs), through 2 KB of LDS that
+// belong to the wavefront.  Loaded straight by the lanes that need them, every cache line was asked for twice (us,
+// before / with the exchange: 8192^2 5x5 68.4 / 62.0, 4x4 65.3 / 59.8; 4095x6001 5x5 30.6 / 26.3).  In the strip form
+// below, whose row loop waits for each exchange, it costs more than it gives (4095x6001 7x7 35.9 / 38.1).
+__device__ __forceinline__ void exchange_row(float* __restrict__ slot, int lane, float (&v)[8])
+{
+    *reinterpret_cast<f4*>(slot + kTile * lane) = f4{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<f4*>(slot + kStrip + kTile * lane) = f4{v[4], v[5], v[6], v[7]};
+    wave_exchange();
+    const f4 lo = *reinterpret_cast<const f4*>(slot + 2 * kTile * lane), hi = *reinterpret_cast<const f4*>(slot + 2 * kTile * lane + 4);
+    v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
+    v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+    wave_exchange();
+}
+
 // ------------------------------------------------------------ block form ----
 // For the small square filters of the paper's experiment (Section 6) the same array
-// without LDS: a wavefront takes ROWS output rows of a strip of 512 input columns,
+// without LDS tiles: a wavefront takes ROWS output rows of a strip of 512 input columns,
 // requests all 2*(ROWS-1)+KH input rows up front (eight consecutive inputs per lane and
 // row) and then, input row by input row, builds the shifted windows of the even and of
 // the odd chain once and applies them to every output row whose filter covers that input
@@ -134,7 +150,8 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_kernel(TapsStride2D
 template <int KH, int KW, int ROWS, bool EDGE>
 __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
                                                    float* __restrict__ yrow, int in_col, int out_col, int w_img,
-                                                   long long xp, int ow, long long yp, int rows_out, bool lane_valid)
+                                                   long long xp, int ow, long long yp, int rows_out, bool lane_valid,
+                                                   float* __restrict__ slots, int lane)
 {
     constexpr int NIN = 2 * (ROWS - 1) + KH;
     constexpr int KE = (KW + 1) / 2, KO = KW / 2;
@@ -149,11 +166,11 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
         if (EDGE) {
             float lo[4], hi[4];
             load4_guarded<false>(p, in_col, w_img, lo);
-            load4_guarded<false>(p, in_col + 4, w_img, hi);
+            load4_guarded<false>(p, in_col + kStrip, w_img, hi);
 #pragma unroll
             for (int i = 0; i < 4; ++i) { v[rho][i] = lo[i]; v[rho][4 + i] = hi[i]; }
         } else {
-            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + 4);
+            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + kStrip);
             v[rho][0] = lo.x; v[rho][1] = lo.y; v[rho][2] = lo.z; v[rho][3] = lo.w;
             v[rho][4] = hi.x; v[rho][5] = hi.y; v[rho][6] = hi.z; v[rho][7] = hi.w;
         }
@@ -162,6 +179,7 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
     float acc[ROWS][4];
 #pragma unroll
     for (int rho = 0; rho < NIN; ++rho) {
+        exchange_row(slots + (rho & 1) * kCols, lane, v[rho]);
         float ev[KE + 3], od[KO + 3];
 #pragma unroll
         for (int i = 0; i < 4; ++i) { ev[i] = v[rho][2 * i]; od[i] = v[rho][2 * i + 1]; }
@@ -207,6 +225,7 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D
                                                                           int per_xcd)
 {
     (void)taps;
+    __shared__ __attribute__((aligned(16))) float slots[kBlock / kWave][2 * kCols];
     kernarg_floats tf = (kernarg_floats)__builtin_amdgcn_kernarg_segment_ptr();
     int rb, strip;
     if (!wave_tile(per_xcd, row_blocks, strips, side, rb, strip)) return;
@@ -218,12 +237,12 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D
     const float* xrow = x + (long long)(2 * r0) * xp;
     float* yrow = y + (long long)r0 * yp;
     const bool lane_valid = lane < valid_lanes;
-    const int in_col = 2 * out_col0 + 2 * kTile * lane, out_col = out_col0 + kTile * lane;
+    const int in_col = 2 * out_col0 + kTile * lane, out_col = out_col0 + kTile * lane;
     // interior strips: all 512 input columns exist, and then so do the valid lanes' outputs
     if (2 * out_col0 + kCols <= w_img)
-        stride2_block_rows<KH, KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid);
+        stride2_block_rows<KH, KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, slots[wave_in_block()], lane);
     else
-        stride2_block_rows<KH, KW, ROWS, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid);
+        stride2_block_rows<KH, KW, ROWS, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, slots[wave_in_block()], lane);
 }
 
 template <int KH, int KW, int ROWS>

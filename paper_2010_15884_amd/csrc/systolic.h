@@ -59,6 +59,14 @@ __device__ __forceinline__ float from_lane_below(float v)
         __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kDppWaveShr1, 0xf, 0xf, true));
 }
 
+// Between the lanes of one wavefront writing LDS and reading each other's values back: the wavefront's LDS operations
+// complete in order, so the compiler alone has to keep them in order.
+__device__ __forceinline__ void wave_exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Streamed data is touched once, so by default the 16-byte accesses carry the
 // non-temporal hint (measured on MI355X: a copy moves ~6.0 TB/s with it and
 // ~5.4-5.9 TB/s without).
