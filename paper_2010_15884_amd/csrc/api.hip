@@ -180,6 +180,7 @@ int sys_conv2d(const float* d_x, int h, int w, size_t x_pitch, const float* h_f,
     if (proj == SYS_PROJ_AUTO && sysconv::conv2d_split_pays(oh, ow, kh, kw)
         && sysconv::conv2d_split_takes(w, y_pitch, h_f, kh, kw))
         return hip_status(sysconv::launch_conv2d_split(d_x, h, w, x_pitch, h_f, kh, kw, d_y, y_pitch, stream));
+    // What the split kernel does not take (conv2d_split_pays has the line and both sides' figures):
     // Measured on MI355X, square images of 1000 .. 10240 columns (us, 5x5: BFS / SBM / FBS): 2996^2 15.8 / 14.3 / 14.3,
     // 4092^2 25.9 / 28.7 / 27.1, 4604^2 33.9 / 36.4 / 32.5, 5996^2 57.2 / 57.0 / 51.1, 7164^2 81.0 / 83.6 / 75.1,
     // 8188^2 103 / 104 / 95.5, 10236^2 166 / 170 / 155.  Up to 6x6 the FBS tile kernels win by 3 - 17 % except where

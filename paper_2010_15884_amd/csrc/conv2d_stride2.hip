@@ -445,7 +445,8 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
     using AllKw = std::make_integer_sequence<int, kMaxK2D>;
     const double outputs = (double)((h - kh) / 2 + 1) * ((w - kw) / 2 + 1);
     if (kw <= 4 && outputs < 4e5) return launch_tiles<2>(x, h, w, xp, f, kh, kw, y, yp, s);
-    if (kw > 1 && kw <= 11 && outputs >= 4e6) return launch_strip_by_kw<3>(AllKw{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    if (kw > 1 && kw <= 11 && outputs >= 4e6)
+        return launch_strip_by_kw<3>(std::make_integer_sequence<int, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
     return launch_strip_by_kw<2>(AllKw{}, x, h, w, xp, f, kh, kw, y, yp, s);
 }
 
