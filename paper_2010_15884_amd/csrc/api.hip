@@ -178,7 +178,7 @@ int sys_conv2d(const float* d_x, int h, int w, size_t x_pitch, const float* h_f,
 
     int proj = projection;
     if (proj == SYS_PROJ_AUTO && sysconv::conv2d_split_pays(oh, ow, kh, kw)
-        && sysconv::conv2d_split_takes(w, y_pitch, h_f, kh, kw))
+        && sysconv::conv2d_split_takes(h, w, y_pitch, h_f, kh, kw))
         return hip_status(sysconv::launch_conv2d_split(d_x, h, w, x_pitch, h_f, kh, kw, d_y, y_pitch, stream));
     // What the split kernel does not take (conv2d_split_pays has the line and both sides' figures):
     // Measured on MI355X, square images of 1000 .. 10240 columns (us, 5x5: BFS / SBM / FBS): 2996^2 15.8 / 14.3 / 14.3,

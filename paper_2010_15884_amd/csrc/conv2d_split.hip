@@ -40,6 +40,8 @@
 #include "systolic.h"
 #include "tiling.h"
 
+#include <limits.h>
+
 #include <type_traits>
 
 namespace sysconv {
@@ -386,9 +388,12 @@ int split_units(int kh, int kw)                 // NS of the kernel that serves 
 
 // Filters and images the kernel takes: taps 0 or 2^-60 .. 2^40 in magnitude (so that no part of a tap and no
 // product of parts is subnormal or infinite), rows of at least four columns (the loads are 16 bytes), output
-// pitches whose rows of a group lie within the 2 GB of a buffer descriptor.
-bool conv2d_split_takes(int w, size_t yp, const float* f, int kh, int kw)
+// pitches whose rows of a group lie within the 2 GB of a buffer descriptor, heights whose row numbers stay in an
+// int: the chunks that a block asks for in advance reach up to three chunks past its last output row, and they are
+// clamped to the image only after that sum.
+bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 {
+    if (h > INT_MAX - 4 * kChunk) return false;
     if (w < 4 || yp > ((size_t)1 << 25) || kh > kMaxK2D || kw > kMaxK2D) return false;
     for (int i = 0; i < kh * kw; ++i) {
         const float a = __builtin_fabsf(f[i]);

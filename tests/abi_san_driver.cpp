@@ -15,6 +15,12 @@
 #define SYSCONV_NO_HIP_HEADER
 #include "sysconv.h"
 
+// The library's own rules for the matrix-core kernel behind AUTO (host code without a HIP call).
+namespace sysconv {
+bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw);
+bool conv2d_split_pays(int oh, int ow, int kh, int kw);
+}
+
 static int failures = 0;
 #define EXPECT(expr, want) do { const int got_ = (expr); if (got_ != (want)) { \
     fprintf(stderr, "line %d: %s = %d (%s), expected %d\n", __LINE__, #expr, got_, sys_status_string(got_), (int)(want)); \
@@ -146,6 +152,31 @@ int main()
                    kh * kw > 1 ? SYS_ERR_UNSUPPORTED : SYS_ERR_ALIAS);
             f.front() = NAN; f.back() = -0.5f;
             EXPECT(sys_conv2d(X, 100, 100, 100, f.data(), kh, kw, X + 5000, 100 - kw + 1, SYS_PROJ_MFMA, nullptr), SYS_ERR_ALIAS);
+        }
+
+    // ---- images the split kernel takes: rows of at least four columns, output pitches up to 2^25, and heights whose
+    //      row numbers (up to three chunks of 16 rows past the last output row) stay in an int
+    EXPECT(sysconv::conv2d_split_takes(INT_MAX, 5, 1, taps.data(), 13, 5), 0);
+    EXPECT(sysconv::conv2d_split_takes(INT_MAX - 63, 5, 1, taps.data(), 13, 5), 0);
+    EXPECT(sysconv::conv2d_split_takes(INT_MAX - 64, 5, 1, taps.data(), 13, 5), 1);
+    EXPECT(sysconv::conv2d_split_takes(100, 3, 1, taps.data(), 15, 3), 0);
+    EXPECT(sysconv::conv2d_split_takes(100, 4, 1, taps.data(), 15, 4), 1);
+    EXPECT(sysconv::conv2d_split_takes(100, 100, (size_t)1 << 25, taps.data(), 15, 15), 1);
+    EXPECT(sysconv::conv2d_split_takes(100, 100, ((size_t)1 << 25) + 1, taps.data(), 15, 15), 0);
+    for (int kh = 1; kh <= SYS_MAX_K2D; ++kh)                      // every tap is read, none beyond
+        for (int kw = 1; kw <= SYS_MAX_K2D; ++kw) {
+            std::vector<float> f((size_t)kh * kw, 0.0f);
+            EXPECT(sysconv::conv2d_split_takes(100, 100, 100, f.data(), kh, kw), 1);
+            for (float in : {0x1p-60f, -0x1p-60f, 0x1p40f, -0x1p40f, -0.0f}) {
+                f.back() = in;
+                EXPECT(sysconv::conv2d_split_takes(100, 100, 100, f.data(), kh, kw), 1);
+            }
+            for (float out : {0x1.fffffep-61f, 0x1.000002p40f, INFINITY, -INFINITY, NAN, 1e-45f}) {
+                f.back() = out;
+                EXPECT(sysconv::conv2d_split_takes(100, 100, 100, f.data(), kh, kw), 0);
+            }
+            for (int oh : {1, 15, 16, 1000, INT_MAX})
+                for (int ow : {1, 240, 241, INT_MAX}) (void)sysconv::conv2d_split_pays(oh, ow, kh, kw);
         }
 
     // ---- queries over their whole domain and beyond
