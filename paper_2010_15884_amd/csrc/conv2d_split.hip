@@ -17,9 +17,12 @@
 // below 2^-25 of the term and of either sign.  bf16 has the exponent range of fp32, so nothing is
 // scaled.  What the split cannot carry is looked for in every input: infinities, NaN (the zeros of the
 // Toeplitz form would spread them to outputs whose window does not hold them), magnitudes from 2^80 on
-// and non-zero ones below 2^-40 (parts or products of parts could become subnormal, which the matrix
-// cores read as 0).  The 16 input rows x 272 columns that hold such a value are noted, and the outputs
-// they reach are taken again with ordinary multiply-adds before the workgroup ends.
+// and non-zero ones so small that parts or products of parts could fall below 2^-126, where a bf16 part
+// has fewer than its 8 bits (tiny_limit(): below 2^-40 for taps down to 2^-60, below 2^-90 for taps from 2^-10 on).
+// A chunk (16 input rows x 256 columns) that holds such a value is marked, and the outputs it reaches are
+// taken again with ordinary multiply-adds before the workgroup ends (plain_rows).  Measured (us; the vector kernel / no such
+// value / one in the image / one in every twelfth chunk down a column / in every chunk): 11x11 on 4096^2 73 / 45 / 55 / 58 / 95, on
+// 8192^2 255 / 142 / 149 / 189 / 329; 15x15 on 3001x4003 114 / 44 / 52 / 70 / 110; on 300x400 15 / 8.7 / 19 / 19 / 15.
 //
 // Data path.  A workgroup of four wavefronts walks down a block of rows of a 256-column strip, 16 input
 // rows (a "chunk") at a time.  A chunk is loaded into registers two chunks ahead of its use, split once
@@ -61,9 +64,9 @@ constexpr int kChunk = 16;                  // input rows of a chunk: 8 units
 constexpr int kUnits = kChunk / 2;
 constexpr int kRow = 3 * kInCols;           // a row in LDS, in bf16 numbers: 256 first parts, 256 second, 256 third
 constexpr int kBuf = kChunk * kRow;
-constexpr int kMaxChunks = 64;              // chunks of a row block
+constexpr int kMaxChunks = 64;              // chunks of a row block, the one that only finishes groups among them (marks fill 64 bits)
 constexpr int kNonTemporal = 2;             // the nt bit of a buffer store
-constexpr unsigned kTiny = ((127u - 40u) << 24) - 1;       // (bits << 1) - 1 of 2^-40
+constexpr int kPlainRows = 4;               // output rows a wavefront takes together in plain_rows, and input rows in flight
 constexpr unsigned short kHuge = (127 + 80) << 7;          // upper half of the bits of 2^80
 
 // Three bf16 parts of two numbers; every part is the remainder rounded to nearest.
@@ -100,35 +103,90 @@ struct SplitShape {
 
 constexpr int kPlaces = 512;                // workgroups the device holds: two a CU (registers allow 256 a lane)
 
-// The outputs rows [ra, rb) x columns [c0, c0 + 256) of the image with plain multiply-adds.
-__device__ __forceinline__ void plain_rows(kernarg_floats taps_f, const float* __restrict__ x, float* __restrict__ y,
-                                           int w_img, long long xp, int ow, long long yp, int kh, int kw, int c0,
-                                           int ra, int rb, int wave, int lane)
+// Where the marked chunks of a row block make the matrix cores' work pointless: the block then ends with plain_rows for
+// all rows from the present chunk on.  A marked chunk costs 2.7 (11x11) to 5 (15x15) chunk times, since it takes 28 to 37
+// output rows again, and plain_rows alone 1.5 to 2.3 a chunk: level where one chunk in 4 to 6 is marked.  One marked
+// chunk alone ends only blocks so short that it is a sixth of them.
+__device__ __forceinline__ bool too_many(unsigned long long marks, int seen, int chunks)
 {
-    const int col = c0 + kTile * lane;
-    for (int r = ra + wave; r < rb; r += kBlock / kWave) {
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int p = 0; p < kh; ++p) {
-            const float* row = x + (long long)(r + p) * xp;
-            float win[4];
+    const int marked = __builtin_popcountll(marks);
+    return marked * 6 > seen && (marked > 1 || chunks <= 6);
+}
+
+// The output rows [ra, rb) of the strip with plain multiply-adds, as an FBS array whose width is known at compile time:
+// a wavefront walks down the input rows of kPlainRows output rows, builds each row's window once and applies it to every
+// output row whose filter covers it.  The filter rows in use are in registers (from tap0, row 0 of the taps in LDS, one
+// a step ahead of its use): two wavefronts a SIMD do not hide the latency of scalar loads (11x11 on 4096^2, a marked value in
+// every chunk: 127 us with taps in scalar registers, 95 this way; 1263 with one output row a wavefront and a load a tap).
+// It takes 1.0 to 1.35 times the vector kernels' time.  (col_b, off): the lane's load.
+template <int KW, int TapPitch, class PutRight>
+__device__ __forceinline__ void plain_rows(const float* tap0, const float* __restrict__ x, float* __restrict__ y,
+                                           unsigned col_b, int off, long long xp, int col, int ow_strip, long long yp, int kh,
+                                           int ra, int rb, bool edge, int wave, PutRight put_right)
+{
+    for (int r = ra + kPlainRows * wave; r < rb; r += kPlainRows * (kBlock / kWave)) {
+        const int rows_out = min(kPlainRows, rb - r), rows_in = rows_out - 1 + kh;
+        const float* xrow = x + (long long)r * xp;
+        f4u v[kPlainRows];
+        auto load_row = [&](int rho, f4u& d) {                             // past the last row: the last row again
+            d = *reinterpret_cast<const f4u*>(reinterpret_cast<const char*>(xrow + (long long)min(rho, rows_in - 1) * xp) + col_b);
+        };
+        float wv[kPlainRows][KW];                                          // filter row p in slot p mod kPlainRows
+        auto load_taps = [&](int p, float (&w)[KW]) {
+            int at = min(p, kh - 1) * TapPitch;
+            asm("" : "+v"(at));                                            // one address for all taps of the row
+            const float* t = tap0 + at;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) win[i] = row[min(col + i, w_img - 1)];
-            for (int q = 0; q < kw; ++q) {
-                win[3] = row[min(col + q + 3, w_img - 1)];
-                const float wv = taps_f[p * kw + q];
+            for (int q = 0; q < KW; ++q) w[q] = t[q];
+        };
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(wv, win[i], acc[i]);
-                win[0] = win[1]; win[1] = win[2]; win[2] = win[3];
+        for (int i = 0; i < kPlainRows; ++i) load_row(i, v[i]);
+        load_taps(0, wv[0]);
+        float acc[kPlainRows][4];
+#pragma unroll
+        for (int j = 0; j < kPlainRows; ++j) acc[j][0] = acc[j][1] = acc[j][2] = acc[j][3] = 0.0f;
+#pragma nounroll
+        for (int rho0 = 0; rho0 < rows_in; rho0 += kPlainRows) {
+#pragma unroll
+            for (int i = 0; i < kPlainRows; ++i) {
+                const int rho = rho0 + i;
+                if (rho >= rows_in) break;                                 // uniform
+                f4u t = v[i];
+                load_row(rho + kPlainRows, v[i]);
+                if (edge) {
+                    asm volatile("");                                      // a branch, not selects in every strip
+                    put_right(t, off);
+                }
+                float win[KW + 3] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+                for (int m = 4; m < KW + 3; ++m) win[m] = from_lane_above(win[m - 4]);
+#pragma unroll
+                for (int j = kPlainRows - 1; j >= 0; --j) {
+                    if (rho - j >= 0 && rho - j < kh) {                    // uniform
+#pragma unroll
+                        for (int q = 0; q < KW; ++q)
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                acc[j][k] = __builtin_fmaf(wv[(i - j + kPlainRows) % kPlainRows][q], win[q + k], acc[j][k]);
+                    }
+                    if (j == kPlainRows - 1) load_taps(rho + 1, wv[(i + 1) % kPlainRows]);     // that slot is free now
+                }
             }
         }
-        store4_guarded<false>(y + (long long)r * yp, col, ow, acc);
+#pragma unroll
+        for (int j = 0; j < kPlainRows; ++j)
+            if (j < rows_out) store4_guarded<false>(y + (long long)(r + j) * yp, col, ow_strip, acc[j]);
     }
 }
+
+// Filter widths the kernels are built for: all that pay (conv2d_split_pays).
+__host__ __device__ constexpr int least_width(int jc) { return jc == 4 ? 5 : 11; }
+__host__ __device__ constexpr int most_width(int jc) { return jc == 4 ? 13 : 15; }
 
 template <int JC, int NS>
 __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
     Taps2D taps, const float* __restrict__ x, float* __restrict__ y, int h, int w_img, long long xp, int oh, int ow,
-    long long yp, int kh, int kw, int rows, int row_blocks, int strips, int per_xcd)
+    long long yp, int kh, int kw, int rows, int row_blocks, int strips, int per_xcd, unsigned tiny_below)
 {
     (void)taps;
     using S = SplitShape<JC, NS>;
@@ -137,7 +195,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
 
     __shared__ __attribute__((aligned(16))) __bf16 parts[2 * kBuf + 32];     // (windows of the last wavefront reach past a row)
     __shared__ float tpad[S::TROWS * S::TCOLS];
-    __shared__ int bad_chunk[kMaxChunks];
+    __shared__ unsigned marks[kMaxChunks / 32];                            // a bit per chunk
 
     const int g = xcd_contiguous(blockIdx.x, per_xcd);
     if (g >= row_blocks * strips) return;                                  // (the whole workgroup)
@@ -197,7 +255,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) put(raw[k], buf + (wave + 4 * k) * kRow + kTile * lane);
-        if (tiny < kTiny || huge.x >= kHuge || huge.y >= kHuge) bad_chunk[c] = 1;
+        if (tiny < tiny_below || huge.x >= kHuge || huge.y >= kHuge) atomicOr(marks + c / 32, 1u << (c % 32));
     };
 
     load_chunk(0);
@@ -205,7 +263,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         const int p = e / S::TCOLS - (JR - 1), q = e % S::TCOLS - (JC - 1);
         tpad[e] = p >= 0 && p < kh && q >= 0 && q < kw ? taps_f[p * kw + q] : 0.0f;
     }
-    if (threadIdx.x < kMaxChunks) bad_chunk[threadIdx.x] = 0;
+    if (threadIdx.x < kMaxChunks / 32) marks[threadIdx.x] = 0;
     __syncthreads();
 
     // A operands: the Toeplitz form of the taps, constant for the whole kernel
@@ -309,8 +367,13 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         }
     };
     // Chunk c+1 goes to LDS and chunk c+2 is asked for while chunk c is used; the buffer that chunk c+1
-    // takes was last read before the barrier that ended chunk c-1.
-    auto run = [&](auto edge_tag) {
+    // takes was last read before the barrier that ended chunk c-1.  Returns the chunk at which the block was given up
+    // (too_many), or chunks + 1.
+    auto marked_up_to = [&](int c) {                                       // final, and the same to all wavefronts, once chunk c begins
+        const unsigned lo = __builtin_amdgcn_readfirstlane(marks[0]), hi = __builtin_amdgcn_readfirstlane(marks[1]);
+        return ((unsigned long long)hi << 32 | lo) & (~0ull >> (kMaxChunks - 1 - c));
+    };
+    auto run = [&](auto edge_tag) -> int {
         auto advance = [&](int c, auto first_tag, auto slot_tag) {
             store_chunk(c + 1, edge_tag);
             load_chunk(c + 2);
@@ -319,9 +382,11 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         };
         using Slot0 = std::integral_constant<int, 0>;
         using Slot1 = std::integral_constant<int, GROUPS % LIVE>;          // slots of the odd chunks
+        if (too_many(marked_up_to(0), 1, chunks)) return 0;
         advance(0, std::true_type{}, Slot0{});
         int c = 1;
         for (; c + 2 <= chunks; c += 2) {
+            if (too_many(marked_up_to(c), c + 1, chunks)) return c;
             advance(c, std::false_type{}, Slot1{});
             advance(c + 1, std::false_type{}, Slot0{});
         }
@@ -331,21 +396,46 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         } else {
             compute(c, edge_tag, std::false_type{}, std::true_type{}, Slot1{});
         }
+        return chunks + 1;
     };
-    if (edge) run(std::true_type{});
-    else run(std::false_type{});
+    const int stop = edge ? run(std::true_type{}) : run(std::false_type{});
 
-    // Chunks with values that the split does not carry: the groups of rows they belong to once more.
+    // The output rows that marked chunks reach, once more; neighbouring marked chunks together.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                       // the stores above are done before any of these
     __syncthreads();
-    for (int k = 0; k <= chunks; ++k) {
-        if (!__builtin_amdgcn_readfirstlane(bad_chunk[k])) continue;
+    auto again = [&](int ra, int rb) {
+        auto with = [&](auto kw_tag, auto self) {
+            constexpr int KW = decltype(kw_tag)::value;
+            if (kw == KW)
+                plain_rows<KW, S::TCOLS>(tpad + (JR - 1) * S::TCOLS + JC - 1, x, y, col_b, off_m, xp, c0 + kTile * lane, ow_strip, yp, kh, r0 + ra, r0 + rb, edge, wave, put_right);
+            else if constexpr (KW < most_width(JC))
+                self(std::integral_constant<int, KW + 1>{}, self);
+        };
+        with(std::integral_constant<int, least_width(JC)>{}, with);
+    };
+    unsigned long long todo = marked_up_to(chunks);
+    if (stop <= chunks) todo |= ~0ull << stop;
+    while (todo) {
+        const int k = __builtin_ctzll(todo);
+        const int run = __builtin_ctzll(~(todo >> k) | 1ull << 63), last = min(k + run - 1, chunks);     // marked: chunks k .. last
         const int first = k * kChunk - (2 * NS - 1);                       // group at row R: input rows R .. R + 2 NS - 1
-        const int ra = first <= 0 ? 0 : (first + JR - 1) / JR * JR;
-        const int rb = min((k + 1) * kChunk, rows_out);
-        plain_rows(taps_f, x, y, w_img, xp, ow_strip, yp, kh, kw, c0, r0 + ra, r0 + rb, wave, lane);
-        __syncthreads();
+        again(first <= 0 ? 0 : (first + JR - 1) / JR * JR, min((last + 1) * kChunk, rows_out));
+        todo = last < chunks ? todo & ~0ull << (last + 1) : 0;
     }
+}
+
+// Inputs below this magnitude (0 apart) are not for the split: with a smallest tap of 2^t, below 2^(-100 - t) products of
+// parts that are more than a 2^-26th of the term could fall below 2^-126, and below 2^-103 the parts themselves.  In the form
+// the kernel compares, (bits << 1) - 1.
+unsigned tiny_limit(const float* f, int n)
+{
+    float least = 0x1p40f;
+    for (int i = 0; i < n; ++i)
+        if (f[i] != 0.0f) least = __builtin_fminf(least, __builtin_fabsf(f[i]));
+    int t = 0;
+    (void)__builtin_frexpf(least, &t);                                     // least = m 2^t with 1/2 <= m < 1
+    const int e = -100 - (t - 1) > -103 ? -100 - (t - 1) : -103;
+    return ((unsigned)(127 + e) << 24) - 1u;
 }
 
 template <int JC, int NS>
@@ -374,7 +464,7 @@ hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f,
     const long long blocks = per_xcd * kXcds;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((conv2d_split_kernel<JC, NS>), dim3((unsigned)blocks), dim3(kBlock), 0, s, taps, x, y, h, w,
-                       (long long)xp, oh, ow, (long long)yp, kh, kw, (int)rows, row_blocks, strips, (int)per_xcd);
+                       (long long)xp, oh, ow, (long long)yp, kh, kw, (int)rows, row_blocks, strips, (int)per_xcd, tiny_limit(f, kh * kw));
     return hipGetLastError();
 }
 
@@ -387,14 +477,15 @@ int split_units(int kh, int kw)                 // NS of the kernel that serves 
 }  // namespace
 
 // Filters and images the kernel takes: taps 0 or 2^-60 .. 2^40 in magnitude (so that no part of a tap and no
-// product of parts is subnormal or infinite), rows of at least four columns (the loads are 16 bytes), output
-// pitches whose rows of a group lie within the 2 GB of a buffer descriptor, heights whose row numbers stay in an
+// product of parts is subnormal or infinite), widths that plain_rows is built for (and with them rows of at least four
+// columns, the 16 bytes of a load), output pitches whose rows of a group lie within the 2 GB of a buffer descriptor, heights whose row numbers stay in an
 // int: the chunks that a block asks for in advance reach up to three chunks past its last output row, and they are
 // clamped to the image only after that sum.
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 {
     if (h > INT_MAX - 4 * kChunk) return false;
-    if (w < 4 || yp > ((size_t)1 << 25) || kh > kMaxK2D || kw > kMaxK2D) return false;
+    if (yp > ((size_t)1 << 25) || kh > kMaxK2D || kw > kMaxK2D || w < kw) return false;
+    if (kw < least_width(kh <= 13 && kw <= 13 ? 4 : 2)) return false;
     for (int i = 0; i < kh * kw; ++i) {
         const float a = __builtin_fabsf(f[i]);
         if (!(a == 0.0f || (a >= 0x1p-60f && a <= 0x1p40f))) return false;         // NaN fails too

@@ -71,9 +71,89 @@ def test_values_the_split_does_not_carry(value, kh, kw, h, w):
     assert ((want[ok] - got[ok]).abs() <= TOL * scale).all()
 
 
+def _same_as_fbs(d, f):
+    """AUTO against the FBS projection where both are finite, and the same infinities and NaN."""
+    want, got = B.sys_conv2d(d, f, projection="FBS"), B.sys_conv2d(d, f)
+    assert torch.equal(torch.isnan(want), torch.isnan(got)) and torch.equal(torch.isinf(want), torch.isinf(got))
+    ok = torch.isfinite(want)
+    scale = B.sys_conv2d(d.nan_to_num(0.0, 0.0, 0.0).abs(), np.abs(f), projection="FBS")
+    assert ((want - got).abs()[ok] <= TOL * scale[ok]).all()
+
+
+# Row blocks of 1 .. 63 chunks (the rule takes so many that the workgroups fill the chip in whole rounds), with one marked
+# chunk early, late or in the last place, neighbouring ones, and so many that a block is given up at once or half way.
+@pytest.mark.parametrize("rows", [[3], [16 * 30], [16 * 62 + 5], [16 * 63], [40, 60, 900], list(range(500, 600, 16)), list(range(0, 1100, 16)),
+                                  list(range(0, 1100, 96)), list(range(15, 1100, 112))])
+@pytest.mark.parametrize("kh,kw,h,w", [(13, 13, 300, 500), (13, 13, 2900, 600), (10, 12, 30000, 600), (13, 13, 104000, 600), (15, 15, 171000, 600)])
+def test_marked_chunks_in_blocks_of_every_length(rows, kh, kw, h, w):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(kh)
+    d = torch.rand((h, w), dtype=torch.float32, device="cuda", generator=gen)
+    f = _case(kh, kw, kh, kw)[1]
+    for i, r in enumerate(rows):
+        if r < h:
+            d[r, (97 * i) % w] = float("nan")
+    if h > 20000:                                                          # a block far down, and the last rows of the image
+        d[h - 1100:h - 1100 + len(rows) * 16:16, 5] = float("inf")
+        d[h - 2, w - 1] = float("nan")
+    _same_as_fbs(d, f)
+
+
+def _scaled(shape, lo, seed):
+    """Numbers of either sign with magnitudes in [lo, 2 lo)."""
+    rng = np.random.default_rng(seed)
+    return (np.ldexp(rng.uniform(1.0, 1.999, shape), int(np.log2(lo))) * rng.choice([-1.0, 1.0], shape)).astype(np.float32)
+
+
+@pytest.mark.parametrize("kh,kw", [(13, 13), (15, 15)])
+@pytest.mark.parametrize("tap,inputs", [
+    # either side of the lower limit, 2^-100 over the smallest tap, and so far below it that the split alone would show
+    (0.0, [-99, -100, -101, -130]), (-8.0, [-91, -92, -93, -122]), (-60.0, [-39, -40, -41, -58]),
+    (5.0, [-102, -103, -104, -122]),                                       # large taps: 2^-103
+    (0.0, [79, 80, 81]), (40.0, [79])])                                    # either side of the upper limit: sums just below 2^128
+def test_either_side_of_the_limits(kh, kw, tap, inputs):
+    f = _scaled((kh, kw), 2.0 ** tap, seed=8)
+    f[1, 2] = 0.0
+    for e in inputs:
+        x = _scaled((150, 500), 2.0 ** e, seed=9)
+        if e + tap > 100:
+            x, f = (np.abs(x) / 2 + np.float32(2.0) ** (e - 1)).astype(np.float32), np.full((kh, kw), 2.0 ** tap, np.float32)
+        assert err2d(run2d(x, f, "AUTO"), x, f) <= TOL, (tap, e)
+
+
+def _us(fn, launches=6, best_of=5):
+    fn()
+    times = []
+    for _ in range(best_of):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(launches):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / launches)
+    return min(times)
+
+
+@pytest.mark.parametrize("kh,kw,vector", [(11, 11, "SBM"), (15, 15, "FBS")])
+def test_no_input_makes_auto_much_slower_than_the_vector_kernels(kh, kw, vector):
+    """Small values cost nothing; a NaN in every chunk costs what the vector kernels take and the chunks looked at before a
+    block is given up (measured: 1.0 .. 1.3 times the vector kernel; the bound leaves room for another box's clocks)."""
+    x, f = _case(4096, 4096, kh, kw, seed=10)
+    d = dev(x)
+    y = torch.empty(4097 - kh, 4097 - kw, dtype=torch.float32, device="cuda")
+    plain, small, bound = (_us(lambda: B.sys_conv2d(d, f, y)), _us(lambda: B.sys_conv2d(d * 1e-15, f, y)),
+                           _us(lambda: B.sys_conv2d(d, f, y, projection=vector)))
+    scale = _us(lambda: d * 1e-15)
+    assert small <= 1.5 * (plain + scale), f"{plain} {small}"
+    d[5::16, 7::200] = float("nan")
+    marked = _us(lambda: B.sys_conv2d(d, f, y))
+    assert marked <= 2.0 * bound, f"a NaN per chunk: {marked:.1f} us, {vector} {bound:.1f} us"
+
+
 def test_small_numbers_keep_their_precision():
     x, f = _case(80, 500, 13, 13, seed=4)
-    for s in (1e-9, 1e-15, 1e-30, 1e15, 1e25):
+    for s in (1e-9, 1e-15, 1e-30, 1e-36, 1e15, 1e25):
         xs = (x * s).astype(np.float32)
         assert err2d(run2d(xs, f, "AUTO"), xs, f) <= TOL
 
