@@ -181,6 +181,19 @@ int main()
             }
         }
 
+    // ---- shapes on either side of the rule's line, both kernels timed there
+    EXPECT(sysconv::conv2d_split_pays(8182, 8182, 11, 11), 1);
+    EXPECT(sysconv::conv2d_split_pays(286, 386, 15, 15), 1);
+    EXPECT(sysconv::conv2d_split_pays(4084, 4092, 13, 5), 1);
+    EXPECT(sysconv::conv2d_split_pays(8237, 244, 13, 5), 0);       // a second strip for four columns
+    EXPECT(sysconv::conv2d_split_pays(929, 2371, 13, 5), 0);
+    EXPECT(sysconv::conv2d_split_pays(8, 200000, 11, 11), 0);      // half of every chunk is padding
+    EXPECT(sysconv::conv2d_split_pays(1275, 1606, 3, 12), 0);
+    EXPECT(sysconv::conv2d_split_pays(866, 4759, 3, 12), 0);       // three rows: half of the units are empty
+    EXPECT(sysconv::conv2d_split_pays(4673, 1074, 3, 13), 1);
+    EXPECT(sysconv::conv2d_split_pays(370, 6223, 10, 10), 0);
+    EXPECT(sysconv::conv2d_split_pays(2039, 2039, 10, 10), 1);
+
     // ---- queries over their whole domain and beyond
     for (int p = -2; p <= 10; ++p)
         for (int k = -1; k <= 70; ++k) {
