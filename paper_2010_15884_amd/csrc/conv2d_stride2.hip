@@ -9,6 +9,11 @@
 // inputs of image row 2r+p -- x(2c) and x(2c+1) of its four PEs -- and the even and the
 // odd taps of that filter row then run as two stride-1 FBS chains over the
 // de-interleaved values (the hand-over X(c,q) = X(c+1,q-2) never mixes the two).
+//
+//   conv2d_fbs_stride2_kernel<RPW>            any filter up to 15x15: the LDS tiles described above
+//   conv2d_fbs_stride2_block_kernel<K,K,ROWS> 2x2 .. 5x5: all input rows of two output rows up front
+//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  any height: rows streamed through registers, where the tiles do not
+//                                             fit the chip in one round (conv2d_stride2_strip_rows)
 #include "launch.h"
 #include "systolic.h"
 #include "tiling.h"
@@ -141,20 +146,22 @@ __device__ __forceinline__ void exchange_row(float* __restrict__ slot, int lane,
 
 // ------------------------------------------------------------ block form ----
 // For the small square filters of the paper's experiment (Section 6) the same array
-// without LDS tiles: a wavefront takes ROWS output rows of a strip of 512 input columns,
-// requests all 2*(ROWS-1)+KH input rows up front (eight consecutive inputs per lane and
-// row) and then, input row by input row, builds the shifted windows of the even and of
-// the odd chain once and applies them to every output row whose filter covers that input
+// without staged tiles: a wavefront takes ROWS output rows of a strip of 512 input columns,
+// requests all 2*(ROWS-1)+KH input rows up front (four consecutive inputs of either half of
+// a row per lane) and then, input row by input row, passes the row through its own 2 KB of
+// LDS (exchange_row), builds the shifted windows of the even and of the odd chain once and applies them to every output row whose filter covers that input
 // row (p = rho - 2r).  Strips overlap like the tiles above: the PEs whose even chain
 // would reach past lane 63 compute values that are never stored.
 template <int KH, int KW, int ROWS, bool EDGE>
 __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
-                                                   float* __restrict__ yrow, int in_col, int out_col, int w_img,
+                                                   float* __restrict__ yrow, int in_col0, int out_col, int w_img,
                                                    long long xp, int ow, long long yp, int rows_out, bool lane_valid,
                                                    float* __restrict__ slots, int lane)
 {
     constexpr int NIN = 2 * (ROWS - 1) + KH;
     constexpr int KE = (KW + 1) / 2, KO = KW / 2;
+    const int in_col = in_col0 + kTile * lane;
+    constexpr int kSecond = kStrip;                                         // columns from a lane's first four to its other four
     const int rows_in = 2 * (rows_out - 1) + KH;
 
     float v[NIN][8];
@@ -166,11 +173,11 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
         if (EDGE) {
             float lo[4], hi[4];
             load4_guarded<false>(p, in_col, w_img, lo);
-            load4_guarded<false>(p, in_col + kStrip, w_img, hi);
+            load4_guarded<false>(p, in_col + kSecond, w_img, hi);
 #pragma unroll
             for (int i = 0; i < 4; ++i) { v[rho][i] = lo[i]; v[rho][4 + i] = hi[i]; }
         } else {
-            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + kStrip);
+            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + kSecond);
             v[rho][0] = lo.x; v[rho][1] = lo.y; v[rho][2] = lo.z; v[rho][3] = lo.w;
             v[rho][4] = hi.x; v[rho][5] = hi.y; v[rho][6] = hi.z; v[rho][7] = hi.w;
         }
@@ -237,7 +244,7 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D
     const float* xrow = x + (long long)(2 * r0) * xp;
     float* yrow = y + (long long)r0 * yp;
     const bool lane_valid = lane < valid_lanes;
-    const int in_col = 2 * out_col0 + kTile * lane, out_col = out_col0 + kTile * lane;
+    const int in_col = 2 * out_col0, out_col = out_col0 + kTile * lane;
     // interior strips: all 512 input columns exist, and then so do the valid lanes' outputs
     if (2 * out_col0 + kCols <= w_img)
         stride2_block_rows<KH, KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, slots[wave_in_block()], lane);
@@ -388,14 +395,18 @@ hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f,
 }
 
 typedef hipError_t (*LaunchStrip)(const float*, int, int, size_t, const float*, int, float*, size_t, hipStream_t);
-template <int ROWS, int... KW>
-hipError_t launch_strip_by_kw(std::integer_sequence<int, KW...>, const float* x, int h, int w, size_t xp, const float* f,
+template <int ROWS, int KW0, int... KW>
+hipError_t launch_strip_by_kw(std::integer_sequence<int, KW0, KW...>, const float* x, int h, int w, size_t xp, const float* f,
                               int kh, int kw, float* y, size_t yp, hipStream_t s)
 {
-    static constexpr LaunchStrip table[] = {launch_strip<KW + 1, ROWS>...};
-    if (kw < 1 || kw > (int)sizeof...(KW)) return hipErrorInvalidValue;
-    return table[kw - 1](x, h, w, xp, f, kh, y, yp, s);
+    static constexpr LaunchStrip table[] = {launch_strip<KW0, ROWS>, launch_strip<KW, ROWS>...};    // widths KW0 and on
+    if (kw < KW0 || kw > KW0 + (int)sizeof...(KW)) return hipErrorInvalidValue;
+    return table[kw - KW0](x, h, w, xp, f, kh, y, yp, s);
 }
+
+constexpr int kTileRpw = 2;                              // output rows of a wavefront in the tiles
+constexpr int kTileOutRows = kTileRpw * (kBlock / kWave);
+constexpr int kCus = 256, kLdsPerCu = 160 * 1024;
 
 template <int RPW>
 hipError_t launch_tiles(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
@@ -423,11 +434,36 @@ hipError_t launch_tiles(const float* x, int h, int w, size_t xp, const float* f,
 
 }  // namespace
 
+// Filters without a block form: 0 = tiles, else the rows of the strips.  Tiles as long as their workgroups fit the chip in one
+// round, else strips (us, tiles / strips of 2 / of 3 rows).  A tile takes 2 (4 RPW - 1) + kh rows of 2 KB of the 160 KB of LDS
+// of a CU: five workgroups (kh = 2) to two (kh = 13 and more), so a round ends at 2.5 M to 1.0 M outputs, and there the tiles'
+// time jumps: 7x7 on 769x1865 outputs 18.2 / 13.7 / 14.7, 13x13 on 654x1920 30.3 / 21.6 / 24.7.  Below, four wavefronts share the
+// staging of a tile's rows: 6x3 on 1137x1676 outputs 11.8 / 14.5 / 15.6, 2x5 on 2910x100 6.0 / 7.2 / 8.5, 10x1 on 1529x800
+// 10.4 / 12.6 / 13.5.  Wide filters on about a workgroup a CU, or up to two with many taps, are the exception, as a row's windows
+// are built once instead of per filter row (300x400 inputs: 15x15 16.6 / 14.4 / 21.0, 9x9 9.9 / 9.1 / 10.9; outputs 109x3025 6x8
+// 9.6 / 8.1, 257x1857 14x14 19.3 / 17.1, but 822x416 6x6 9.3 / 8.8 and 1024x518 10x7 12.5 / 11.9 are left to the tiles: smaller
+// filters and more tiles lose as often).  Above: 8192^2 inputs 7x7 126 / 92 / 85, 11x11 165 / 125 / 117, 15x15 303 / 167 / 179, 13x4 198 / 118 / 108, 2x15 78 / 73 / 78.
+// Three rows read fewer halo rows and need images large enough to fill the chip with fewer wavefronts, and not too many taps
+// (4 M to 20 M outputs, 2 rows / 3 rows: up to 11 columns 1.01 to 1.07, 10 and 11 among them although up to nine scalar
+// registers of taps spill; 12 columns and more 0.9 to 1.0).  Of 2250 random shapes 29 are slower by 3 % or more than with tiles
+// alone, most of them within the noise of two runs; with a line at 0.4 M outputs and four columns it was 419, by up to 18 %.
+int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw)
+{
+    const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
+    const long long tiles = (((long long)oh + kTileOutRows - 1) / kTileOutRows) * (((long long)ow + cols - 1) / cols);
+    const int tiles_a_cu = kLdsPerCu / ((2 * (kTileOutRows - 1) + kh) * kCols * (int)sizeof(float));
+    const double few = 2.4 * kh * kw;                                      // tiles
+    const bool heavy = kw >= 6 && kh * kw >= 42 && (tiles <= kCus || (tiles <= 2 * kCus && (double)tiles <= few));
+    if (tiles <= (long long)kCus * tiles_a_cu && !heavy) return 0;
+    return kw > 1 && kw <= 11 && (double)oh * ow >= 4e6 ? 3 : 2;
+}
+
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                      float* y, size_t yp, hipStream_t s)
 {
-    // Square filters up to 5x5 run the block form, two output rows per wavefront (8192^2, 5x5: 68 us against 75 - 82 us
-    // for the strips, 88 us for the LDS tiles and 56 us for a copy of the same bytes; 1, 3 and 4 rows: 83, 68, 74 us).
+    // Square filters up to 5x5 run the block form, two output rows per wavefront (8192^2, 5x5: 62 us against 75 - 82 us
+    // for the strips, 88 us for the LDS tiles and 56 us for a copy of the same bytes; 1, 3 and 4 rows, before the exchange of
+    // the loads took two rows from 68 to 62 us: 83, 68, 74).
     if (kh == kw) {
         switch (kh) {
         case 2: return launch_block<2, 2, 2>(x, h, w, xp, f, y, yp, s);
@@ -437,17 +473,11 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         default: break;
         }
     }
-    // The rest runs the strips (us, tiles / strips of 2 / of 3 rows): 8192^2 7x7 126 / 92 / 85, 11x11 165 / 125 / 117, 15x15 303 /
-    // 167 / 179, 13x4 198 / 118 / 108, 2x15 78 / 73 / 78; 4095x6001 7x7 51 / 39 / 37; 2048^2 7x7 12.0 / 11.7 / 12.9, 13x13 30 / 20 / 24.
-    // Three rows read fewer halo rows and need images large enough to fill the chip with fewer wavefronts, and taps of
-    // three filter rows that fit the scalar registers.  Narrow filters on small images stay with the tiles, where four
-    // wavefronts share the staging of one tile's rows (300x400: 7x3 6.9 / 7.4, 13x4 9.5 / 10.4, 15x2 10.2 / 10.7).
-    using AllKw = std::make_integer_sequence<int, kMaxK2D>;
-    const double outputs = (double)((h - kh) / 2 + 1) * ((w - kw) / 2 + 1);
-    if (kw <= 4 && outputs < 4e5) return launch_tiles<2>(x, h, w, xp, f, kh, kw, y, yp, s);
-    if (kw > 1 && kw <= 11 && outputs >= 4e6)
-        return launch_strip_by_kw<3>(std::make_integer_sequence<int, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
-    return launch_strip_by_kw<2>(AllKw{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    switch (conv2d_stride2_strip_rows((h - kh) / 2 + 1, (w - kw) / 2 + 1, kh, kw)) {
+    case 0: return launch_tiles<kTileRpw>(x, h, w, xp, f, kh, kw, y, yp, s);
+    case 3: return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    default: return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    }
 }
 
 }  // namespace sysconv

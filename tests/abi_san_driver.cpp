@@ -15,10 +15,11 @@
 #define SYSCONV_NO_HIP_HEADER
 #include "sysconv.h"
 
-// The library's own rules for the matrix-core kernel behind AUTO (host code without a HIP call).
+// The library's own rules for the kernels behind AUTO (host code without a HIP call).
 namespace sysconv {
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw);
 bool conv2d_split_pays(int oh, int ow, int kh, int kw);
+int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);
 }
 
 static int failures = 0;
@@ -193,6 +194,26 @@ int main()
     EXPECT(sysconv::conv2d_split_pays(4673, 1074, 3, 13), 1);
     EXPECT(sysconv::conv2d_split_pays(370, 6223, 10, 10), 0);
     EXPECT(sysconv::conv2d_split_pays(2039, 2039, 10, 10), 1);
+
+    // ---- stride 2: tiles (0) or strips of two or three rows, all three timed at each shape
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1137, 1676, 6, 3), 0);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(2910, 100, 2, 5), 0);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1529, 800, 10, 1), 0);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1982, 1115, 1, 14), 0);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(143, 193, 15, 15), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(109, 3025, 6, 8), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(257, 1857, 14, 14), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(769, 1865, 7, 7), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(654, 1920, 13, 13), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(2045, 2998, 7, 7), 3);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(4089, 4089, 15, 15), 2);
+    for (int kh = 1; kh <= SYS_MAX_K2D; ++kh)
+        for (int kw = 1; kw <= SYS_MAX_K2D; ++kw)
+            for (int oh : {1, 8, 1000, 20000, INT_MAX / 2 + 1})
+                for (int ow : {1, 252, 1000, 20000, INT_MAX / 2 + 1}) {
+                    const int rows = sysconv::conv2d_stride2_strip_rows(oh, ow, kh, kw);
+                    if (rows != 0 && rows != 2 && !(rows == 3 && kw >= 2 && kw <= 11)) ++failures;
+                }
 
     // ---- queries over their whole domain and beyond
     for (int p = -2; p <= 10; ++p)
