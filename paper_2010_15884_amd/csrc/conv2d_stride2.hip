@@ -160,8 +160,12 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
 {
     constexpr int NIN = 2 * (ROWS - 1) + KH;
     constexpr int KE = (KW + 1) / 2, KO = KW / 2;
-    const int in_col = in_col0 + kTile * lane;
-    constexpr int kSecond = kStrip;                                         // columns from a lane's first four to its other four
+    // The right-hand strip of 2x2 filters loads straight to the lanes: where every load is checked, four rows do not make
+    // up for the exchange (us, straight / exchanged: 647x510 outputs 4.7 / 5.6, 266x1790 5.1 / 6.1, 1211x673 6.2 / 6.8, 442x3324
+    // 7.5 / 8.2; level on 4 M outputs).
+    constexpr bool EXCHANGE = !(EDGE && KH == 2);
+    const int in_col = EXCHANGE ? in_col0 + kTile * lane : in_col0 + 2 * kTile * lane;
+    constexpr int kSecond = EXCHANGE ? kStrip : kTile;                     // columns from a lane's first four to its other four
     const int rows_in = 2 * (rows_out - 1) + KH;
 
     float v[NIN][8];
@@ -186,7 +190,7 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
     float acc[ROWS][4];
 #pragma unroll
     for (int rho = 0; rho < NIN; ++rho) {
-        exchange_row(slots + (rho & 1) * kCols, lane, v[rho]);
+        if constexpr (EXCHANGE) exchange_row(slots + (rho & 1) * kCols, lane, v[rho]);
         float ev[KE + 3], od[KO + 3];
 #pragma unroll
         for (int i = 0; i < 4; ++i) { ev[i] = v[rho][2 * i]; od[i] = v[rho][2 * i + 1]; }
