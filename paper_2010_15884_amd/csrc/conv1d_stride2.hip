@@ -61,8 +61,9 @@ __device__ __forceinline__ void run_chain(float (&e)[kGroups][4], float (&acc)[k
     }
 }
 
-// The taps are the first kernel argument (offset 0 of the kernel-argument segment).
-template <int KT>
+// The taps are the first kernel argument (offset 0 of the kernel-argument segment).  STREAM: the signal is read with the
+// non-temporal hint.
+template <int KT, bool STREAM>
 __global__ __launch_bounds__(kBlock) void conv1d_fbs_stride2_kernel(TapsStride2 taps, const float* __restrict__ x,
                                                                     float* __restrict__ y, long long n, long long m,
                                                                     int k_rt, int valid_lanes)
@@ -79,15 +80,15 @@ __global__ __launch_bounds__(kBlock) void conv1d_fbs_stride2_kernel(TapsStride2 
     // A group's 512 inputs come in as two loads of 1 KB; a round trip through LDS, private to the wavefront, then gives
     // each lane the eight consecutive inputs of its four PEs.  (Loaded straight by the lanes that need them, every cache
     // line was asked for by two instructions and the non-temporal hint could not be used: 2^26 inputs, k = 2 72 -> 62 us,
-    // 16 75 -> 64, 31 82 -> 67; a copy of the same bytes takes 65 us.  From k = 50 on the vector ALUs bound both.)
+    // 16 75 -> 64, 31 82 -> 65; a copy of the same bytes takes 65 us.  From k = 50 on the vector ALUs bound both.)
     __shared__ __attribute__((aligned(16))) float stage[kBlock / kWave][kGroups * 2 * kWave * kTile];
     float* const lds = stage[wave_in_block()];
     float ev[kGroups][4], od[kGroups][4], acc[kGroups][4];
 #pragma unroll
     for (int r = 0; r < kGroups; ++r) {
         const long long c0 = 2 * (base + r * per_group) + kTile * lane;
-        load4_guarded(x, c0, n, ev[r]);
-        load4_guarded(x, c0 + kWave * kTile, n, od[r]);
+        load4_guarded<STREAM>(x, c0, n, ev[r]);
+        load4_guarded<STREAM>(x, c0 + kWave * kTile, n, od[r]);
     }
 #pragma unroll
     for (int r = 0; r < kGroups; ++r) {
@@ -134,15 +135,21 @@ hipError_t launch_stride2(const float* x, size_t n, const float* w, int k, float
     const long long waves = (m + per_wave - 1) / per_wave;
     const long long blocks = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((conv1d_fbs_stride2_kernel<KT>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
-                       taps, x, y, (long long)n, m, k, valid_lanes);
+    // Signals of 14 to 44 MB are read without the non-temporal hint: several of them, as a program goes round its buffers, stay
+    // in the 256 MB memory-side cache (us, with / without: k = 5 4 M inputs 5.9 / 5.7, 6 M 8.0 / 7.1, 9 M 11.3 / 10.2; 11 8.1 / 6.9 on 6 M; shorter
+    // 2 M 4.0 / 4.2, longer 12 M 13.9 / 14.5, 40 M 38.6 / 41.5).  With long filters it makes no difference (50: 7 M 13.6 / 14.1, 8 M 16.2 / 16.2).
+    // (A choice inside the kernel made every group wait for its own loads: 2^26 inputs, k = 28 65 -> 76 us.)
+    const bool cacheable = KT > 0 && n > 3500000 && n < 11000000;
+    const auto kernel = cacheable ? conv1d_fbs_stride2_kernel<KT, KT == 0> : conv1d_fbs_stride2_kernel<KT, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, taps, x, y, (long long)n, m, k, valid_lanes);
     return hipGetLastError();
 }
 
-// Tap counts known at compile time up to 22, where the loop's counters and its waits for taps show
-// (2^26 inputs, us, loop / unrolled: k = 8 76.4 / 74.7, 13 77.2 / 74.2, 17 79.7 / 75.4, 20 81.0 / 77.9); from there on the
-// unrolled code loses to the loop, which stays in the instruction cache (24 80.7 / 83.4, 36 91 / 114, 64 103 / 206).
-constexpr int kUnrolled = 22;
+// Tap counts known at compile time up to 34: on short signals the loop's counters and its waits for taps show (us, loop /
+// unrolled: 70 K inputs k = 2 3.4 / 3.1, 16 3.8 / 3.4, 20 4.0 / 3.5, 34 4.8 / 4.0; 3 M 8 5.1 / 4.8, 20 6.1 / 5.6, 32 7.1 / 6.4), and from about 8 M
+// inputs on both are at the copy rate (2^26: 2 62 / 62, 20 64 / 65, 34 66 / 65).  With 35 taps and more the unrolled code leaves the
+// instruction cache on long signals (2^26: 35 68 / 77, 48 78 / 92, 64 99 / 160), though it still gains on short ones (70 K: 64 6.6 / 5.4).
+constexpr int kUnrolled = 34;
 typedef hipError_t (*Launch)(const float*, size_t, const float*, int, float*, hipStream_t);
 template <int... K>
 hipError_t launch_by_k(std::integer_sequence<int, K...>, const float* x, size_t n, const float* w, int k, float* y,

@@ -10,7 +10,7 @@ from paper_2010_15884_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-K_S2 = [1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64]
+K_S2 = list(range(1, 65))        # up to 34 taps each count has a kernel of its own
 
 
 def run_s2(x, w, proj="FBS", stride=2):
@@ -43,6 +43,13 @@ def test_stride2_random_all_sizes(proj, k):
         assert y.shape == ((n - k) // 2 + 1,)
         e = err_s2(y, x, w)
         assert e <= TOL, f"k={k} n={n}: rel err {e}"
+
+
+@pytest.mark.parametrize("k", [1, 2, 5, 34, 35])
+@pytest.mark.parametrize("n", [3_500_000, 3_500_001, 10_999_999, 11_000_000])      # either side of the sizes read without the non-temporal hint
+def test_stride2_both_kinds_of_loads(k, n):
+    x, w = W.random_case(k, (n,), (k,))
+    assert err_s2(run_s2(x, w, "AUTO"), x, w) <= TOL
 
 
 @pytest.mark.parametrize("k", [1, 2, 5, 16, 23, 64])
