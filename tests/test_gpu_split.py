@@ -26,6 +26,18 @@ def _case(h, w, kh, kw, seed=0, top=1.0):
 
 
 @pytest.mark.parametrize("kh,kw", FILTERS)
+def test_auto_runs_the_split_kernel(kh, kw):
+    """Every vector kernel takes an output's taps in an order of its own in fp32; the split's sums round elsewhere.  So on random
+    data AUTO's bits differ from those of every projection that could have run instead."""
+    x, f = _case(100 + kh - 1, 719 + kw - 1, kh, kw, seed=11, top=255.0)
+    d = dev(x)
+    auto = B.sys_conv2d(d, f)
+    for proj in ("FBS", "SBM", "BFS"):
+        if B.sys_conv2d_has(proj, kh, kw):
+            assert (auto != B.sys_conv2d(d, f, projection=proj)).float().mean() > 0.2, proj
+
+
+@pytest.mark.parametrize("kh,kw", FILTERS)
 @pytest.mark.parametrize("oh,ow", [(1, 1), (16, 240), (17, 241), (15, 243), (33, 482), (100, 719)])
 def test_edges_of_strips_and_chunks(kh, kw, oh, ow):
     x, f = _case(oh + kh - 1, ow + kw - 1, kh, kw, top=255.0)
@@ -69,6 +81,23 @@ def test_values_the_split_does_not_carry(value, kh, kw, h, w):
     ok = torch.isfinite(want)
     scale = B.sys_conv2d(d.abs(), np.abs(f), projection="FBS")[ok]
     assert ((want[ok] - got[ok]).abs() <= TOL * scale).all()
+
+
+@pytest.mark.parametrize("kh,kw,h,w", [(13, 13, 60, 500), (15, 15, 60, 500), (9, 13, 300, 700), (11, 11, 1500, 1700)])
+def test_numbers_of_two_and_three_parts_are_bit_exact(kh, kw, h, w):
+    rng = np.random.default_rng(12)
+    # 17 bits need two or three parts; 0 / 1 taps, at most 120 of them, keep every partial sum below 2^24
+    x = rng.integers(-(1 << 17), 1 << 17, (h, w)).astype(np.float32)
+    f = np.zeros(kh * kw, np.float32)
+    f[rng.permutation(kh * kw)[:min(120, kh * kw - 3)]] = 1.0
+    f = f.reshape(kh, kw)
+    assert np.array_equal(run2d(x, f, "AUTO"), oracle.conv2d(x, f, ORACLE_THREADS).astype(np.float32))
+    # a single tap of 1 picks an input out, all 24 bits of it
+    x = _scaled((h, w), 1.0, seed=13)
+    for p, q in [(0, 0), (kh - 1, kw - 1), (kh // 2, 3)]:
+        f = np.zeros((kh, kw), np.float32)
+        f[p, q] = 1.0
+        assert np.array_equal(run2d(x, f, "AUTO"), x[p:p + h - kh + 1, q:q + w - kw + 1])
 
 
 def _same_as_fbs(d, f):

@@ -33,7 +33,7 @@ def test_2d_workloads(name):
     x, f = W.make(wl)
     ref = oracle.conv2d(x, f, ORACLE_THREADS)
     scale = oracle.absdot2d(x, f, ORACLE_THREADS)
-    for proj in ("FBS", "BFS", "SBM"):
+    for proj in ("AUTO", "FBS", "BFS", "SBM"):
         if not B.sys_conv2d_has(proj, *wl.k_shape):
             continue
         y = run2d(x, f, proj)
