@@ -22,10 +22,12 @@ single JSON line printed at the end carries
                2 x multiply-adds / kernel time against the 78.6 TFLOP/s fp32 vector peak
   roofline_mfma that workload through the opt-in matrix-core projection: issued MFMA flops against
                the 2.5 PFLOP/s dense fp16 peak, with the fraction of them the definition needs
+  roofline_split  that workload through AUTO, which runs the split matrix-core kernel (no condition on the input): issued
+               MFMA flops against the 2.5 PFLOP/s dense bf16 peak, with the fraction of them the definition needs
   roofline_2d  the 4096^2, 5x5 workload (bound by HBM): its fastest projection against the 8 TB/s peak, with the
                output rows packed tightly and on 128-byte lines
   cpu_baseline the CPU oracle (plain C, fp64) timed here on the host cores
-  also         all five workloads and every projection built for them, each with
+  also         all five workloads and every projection built for them (and AUTO where it is none of them), each with
                GB/s, Gtap/s and its fraction of the HBM and fp32-FMA peaks, a plain
                dwordx4 copy of the same footprint, and for the launch-bound ones the
                time per launch when 100 launches are replayed from a HIP graph; for the
@@ -434,7 +436,9 @@ def main() -> int:
             _, c_mean, _ = time_launches(copy_launch, steps, 3)
             copy_gbs = 8 * n_copy / c_mean / 1e9
             del srcs, dsts
-            for proj in ("FBS", "SBM", "BFS", "BSM", "FSM", "FFS", "MFMA"):
+            # AUTO has a row of its own where its kernel is none of the named projections: the split matrix-core kernel
+            auto = ("AUTO",) if name == "conv2d_8k_11x11" else ()
+            for proj in ("FBS", "SBM", "BFS", "BSM", "FSM", "FFS", "MFMA", *auto):
                 has = B.sys_conv1d_has(proj, w2.k_shape[0]) if w2.ndim == 1 else B.sys_conv2d_has(proj, *w2.k_shape)
                 if not has:
                     continue
@@ -464,7 +468,7 @@ def main() -> int:
             # choose the pitch: the fastest projection again with the output rows on 128-byte lines (same algorithmic
             # bytes: the padding is never written).
             if w2.ndim == 2 and w2.y_shape[1] % 32 and w2.algorithmic_bytes > (16 << 20):
-                mine = [r for r in also if r["workload"] == name and r["projection"] != "MFMA"]
+                mine = [r for r in also if r["workload"] == name and r["projection"] != "MFMA"]      # (AUTO's among them)
                 best = min(mine, key=lambda r: r["kernel_us_mean"])
                 pitch = -(-w2.y_shape[1] // 32) * 32
                 ln, kp = make_launcher(w2, best["projection"], xh, tp, y_pitch=pitch)
@@ -481,7 +485,8 @@ def main() -> int:
         result["also"] = also
         # the one workload that is bound by the vector ALUs, not by HBM: its own roofline object
         # (121 multiply-adds per 8 bytes; peak = 256 CUs x 64 lanes x 2.4 GHz x 2 flop = 78.6 TFLOP/s fp32)
-        alu = [r for r in also if r["workload"] == "conv2d_8k_11x11" and r["projection"] != "MFMA" and "y_pitch_floats" not in r]
+        alu = [r for r in also if r["workload"] == "conv2d_8k_11x11" and r["projection"] not in ("MFMA", "AUTO")
+               and "y_pitch_floats" not in r]
         if alu:
             best = max(alu, key=lambda r: r["Gtap/s"])
             kern = {"SBM": "conv2d_sbm_kernel<11, 11, 1>", "BFS": "conv2d_bfs_kernel<11, 11, 1>",
@@ -527,6 +532,25 @@ def main() -> int:
                 "kernel_us_mean": r["kernel_us_mean"],
                 "note": "v_mfma_f32_16x16x32_f16 on split fp16 operands (3 products); useful_fraction = kh*kw "
                         "multiply-adds of the definition / multiply-adds issued (Toeplitz zeros and the split)"}
+        # the same workload through AUTO: the split kernel, six products of bf16 parts for any input
+        sp = [r for r in also if r["workload"] == "conv2d_8k_11x11" and r["projection"] == "AUTO" and "y_pitch_floats" not in r]
+        if sp:
+            r = sp[0]
+            w5 = W.WORKLOADS["conv2d_8k_11x11"]
+            ns = (w5.k_shape[0] + 4) // 2                    # units of two input rows per group of 4 x 4 x 16 outputs
+            issued_macs_per_output = 6 * ns * 16 * 16 * 32 / 256.0
+            achieved = 2 * issued_macs_per_output * w5.n_outputs / (r["kernel_us_mean"] * 1e-6) / 1e12
+            sp_traffic, sp_prov = _stored_traffic("conv2d_auto_11x11_8k")
+            result["roofline_split"] = {
+                "workload": "conv2d_8k_11x11", "projection": "AUTO", "kernel": f"conv2d_split_kernel<4, {ns}>",
+                "bound": "mfma", "achieved": round(achieved, 1), "peak": 2500.0, "unit": "TFLOP/s",
+                "frac": round(achieved / 2500.0, 4),
+                "useful_fraction": round(w5.k_shape[0] * w5.k_shape[1] / issued_macs_per_output, 4),
+                "useful_TFLOP/s": round(2 * r["Gtap/s"] / 1e3, 2),
+                "frac_hbm_peak": r["frac_hbm_peak"], "traffic": sp_traffic, "traffic_source": sp_prov,
+                "kernel_us_mean": r["kernel_us_mean"],
+                "note": "v_mfma_f32_16x16x32_bf16 on operands split exactly into three parts (6 of 9 products); "
+                        "useful_fraction = kh*kw multiply-adds of the definition / multiply-adds issued"}
 
         # the large 2-D workload that is bound by HBM: its own roofline object (best projection, tight and aligned pitch)
         c4 = [r for r in also if r["workload"] == "conv2d_4k_5x5" and r["projection"] != "MFMA"]

@@ -31,12 +31,15 @@
 // groups it belongs to, whose sums wait in registers: no halo row is loaded or split twice within a
 // block, one barrier per chunk, and all indices of the sums are compile-time constants.
 //
-// What bounds it: instruction issue.  A chunk of 11x11 takes a workgroup 4.0 us with two of them on a CU: 168 matrix
-// instructions (1.1 us a wavefront at 16 clocks) and about 350 vector instructions of split, checks and addresses
-// (0.6 us), which do not overlap between the two wavefronts of a SIMD.  Measured (us, the vector kernels before /
-// this): 11x11 on 8192^2 243 / 147, 15x15 on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 42.
+// What bounds it: matrix and vector instructions, which add up.  On 8192^2 11x11 the matrix cores are busy for 57 % of the
+// kernel's clocks (16 clocks an instruction) and other vector instructions for 17 %, with 1.41 of the two wavefronts a SIMD has
+// room for resident on average; on 3001x4003 15x15 45 %, 14 % and 1.17.  Per resident pair of wavefronts that is all of the time: what
+// is missing is the tail, in which row blocks of equal length end at different times.  LDS is busy for 21 to 23 %, its bank
+// conflicts are 1 to 5 % of that, HBM reads are 1.06 and 1.28 times the image.  Measured (us, the vector kernels before / this; the
+// best of eight batches, 11x11 on 8192^2 159 and 15x15 46 on average among other passes): 11x11 on 8192^2 243 / 142, 15x15
+// on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 41.
 // Tried: 272 input columns per chunk (one wavefront splits a fifth piece and the others wait: 11x11 190 us with two
-// accumulators an output), one accumulator (145 us, but errors of 1.8e-7 instead of 6e-8), stores behind per-lane
+// accumulators an output), one accumulator (2 % faster, but errors of 1.8e-7 instead of 6e-8), stores behind per-lane
 // branches (every chunk then waits for the stores of the one before), three workgroups a CU (spills at NS = 7, level
 // below).  Reads of 16 bytes from LDS at 8-byte alignment are slow: a window is two 8-byte (8 x 2: four 4-byte) reads.
 #include "launch.h"
@@ -506,7 +509,7 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 //   vector kernel's (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
 //   8x8 .. 11x11 (SBM) and other sides up to 11 (compile-time FBS): those kernels are quick on small images, and the
 //   split kernel wins once the image is large enough, the sooner the more taps a unit has: 11x11 (17.3) 9.9 / 9.6 on
-//   1000^2, 258 / 147 on 8192^2; 10x10 (14.3) 12.1 / 13.2 on 370x6223, 20.0 / 16.7 on 2048^2; 9x9 (13.5) 17.2 / 16.1 on 2048^2; 8x8
+//   1000^2, 243 / 142 on 8192^2; 10x10 (14.3) 12.1 / 13.2 on 370x6223, 20.0 / 16.7 on 2048^2; 9x9 (13.5) 17.2 / 16.1 on 2048^2; 8x8
 //   (10.7) 18.3 / 19.5 on 2000x3000, 33.6 / 32.1 on 3001x4003; 7x11 (15.4) 8.8 / 8.1 on 1000^2; 11x7 (11) 9.7 / 10.0 on 1500x1100,
 //   55 / 42 on 4096^2; 7x7 25.5 / 32.5 on 3001x4003.
 // Near the line what the kernels compute for padding decides: strips of 240 columns and chunks of 16 rows here, about 252

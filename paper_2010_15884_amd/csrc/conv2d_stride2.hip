@@ -278,8 +278,9 @@ hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f,
 // Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 512
 // input columns and walks down its 2*(ROWS-1)+kh input rows, kAhead of them in flight in registers.  Each row's two
 // windows are built once and applied to every output row whose filter covers it, where the tiles build them again for
-// every (output row, filter row) and step through the taps four at a time.  Small filters are bound by the requests for
-// input rows ((2 (ROWS-1) + kh) / (2 ROWS) times the image, mostly from L2), large ones by the vector ALUs.
+// every (output row, filter row) and step through the taps four at a time.  What bounds it is the latency of its input rows:
+// on 4095x6001 7x7 (three rows, 32.4 us) the vector ALUs are busy for 30 %, 1.9 wavefronts a SIMD are resident of the four that
+// 116 registers allow, and the rows requested, (2 (ROWS-1) + kh) / (2 ROWS) = 1.83 times the image, come from L2 but for 1.25 times.
 constexpr int kAhead = 4;
 
 template <int KW, int ROWS, bool EDGE>
@@ -446,7 +447,8 @@ hipError_t launch_tiles(const float* x, int h, int w, size_t xp, const float* f,
 // 10.4 / 12.6 / 13.5.  Wide filters on about a workgroup a CU, or up to two with many taps, are the exception, as a row's windows
 // are built once instead of per filter row (300x400 inputs: 15x15 16.6 / 14.4 / 21.0, 9x9 9.9 / 9.1 / 10.9; outputs 109x3025 6x8
 // 9.6 / 8.1, 257x1857 14x14 19.3 / 17.1, but 822x416 6x6 9.3 / 8.8 and 1024x518 10x7 12.5 / 11.9 are left to the tiles: smaller
-// filters and more tiles lose as often).  Above: 8192^2 inputs 7x7 126 / 92 / 85, 11x11 165 / 125 / 117, 15x15 303 / 167 / 179, 13x4 198 / 118 / 108, 2x15 78 / 73 / 78.
+// filters and more tiles lose as often).  Above: 8192^2 inputs 7x7 126 / 92 / 85, 11x11 165 / 125 / 117, 15x15 303 / 167 / 179,
+// 13x4 198 / 118 / 108, 2x15 78 / 73 / 78.
 // Three rows read fewer halo rows and need images large enough to fill the chip with fewer wavefronts, and not too many taps
 // (4 M to 20 M outputs, 2 rows / 3 rows: up to 11 columns 1.01 to 1.07, 10 and 11 among them although up to nine scalar
 // registers of taps spill; 12 columns and more 0.9 to 1.0).  Of 2250 random shapes 29 are slower by 3 % or more than with tiles
