@@ -498,7 +498,8 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 
 // Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units NS, theirs with
 // the kh*kw taps, so the line is drawn in taps per unit; measured on 300x400 .. 8192x8192 images (us, vector / split), then
-// held against 2100 random shapes of 30 K to 26 M outputs (two of them lose, by 4 %):
+// held against 2100 random shapes of 30 K to 26 M outputs (three of them lose more than 3 %: 10x10 on 370x6223, where
+// two rounds of workgroups leave most of the second empty, 12.1 / 13.2, and two by 4 %):
 //   filters that only the run-time-sized FBS kernel serves (a side above 11, or 8 .. 11 and not square): from 12 taps
 //   a unit at every size (5x13 7.8 / 6.0 on 300x400, 49 / 41 on 4096^2; 9x13 76 / 42; 12x12 11.0 / 7.3, 100 / 46), with fewer on
 //   images of 2 M outputs and more, the larger the closer they are to 7 (13x5 13.5 / 14.3 on 2.2 M, 56 / 44 on 4096^2; 12x6
@@ -509,11 +510,12 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 //   vector kernel's (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
 //   8x8 .. 11x11 (SBM) and other sides up to 11 (compile-time FBS): those kernels are quick on small images, and the
 //   split kernel wins once the image is large enough, the sooner the more taps a unit has: 11x11 (17.3) 9.9 / 9.6 on
-//   1000^2, 243 / 142 on 8192^2; 10x10 (14.3) 12.1 / 13.2 on 370x6223, 20.0 / 16.7 on 2048^2; 9x9 (13.5) 17.2 / 16.1 on 2048^2; 8x8
+//   1000^2, 243 / 142 on 8192^2; 10x10 (14.3) 20.0 / 16.7 on 2048^2; 9x9 (13.5) 17.2 / 16.1 on 2048^2; 8x8
 //   (10.7) 18.3 / 19.5 on 2000x3000, 33.6 / 32.1 on 3001x4003; 7x11 (15.4) 8.8 / 8.1 on 1000^2; 11x7 (11) 9.7 / 10.0 on 1500x1100,
 //   55 / 42 on 4096^2; 7x7 25.5 / 32.5 on 3001x4003.
-// Near the line what the kernels compute for padding decides: strips of 240 columns and chunks of 16 rows here, about 252
-// columns and 8 rows there (us: 13x5 on 8237x244 outputs 13.5 / 18.3, on 50000x250 22.3 / 27.7; 11x11 on 8x200000 12.7 / 16.3).
+// What the kernels compute for padding counts where it is a third or more beyond the others': strips of 240 columns and chunks of
+// 16 rows here, about 252 columns and 8 rows there (us: 13x5 on 8237x244 outputs 13.5 / 18.3, on 20000x250 22.3 / 27.7; 11x11 on
+// 8x200000 12.7 / 16.3; but 9x9 on 2828x989, a sixth, 14.2 / 13.0).
 bool conv2d_split_pays(int oh, int ow, int kh, int kw)
 {
     const int taps = kh * kw, units = split_units(kh, kw);
@@ -521,12 +523,12 @@ bool conv2d_split_pays(int oh, int ow, int kh, int kw)
     const int cols = kTile * (kWave - halo_lanes(kw));
     const double theirs = (double)(((long long)ow + cols - 1) / cols * 252) * (double)(((long long)oh + 7) / 8 * 8);
     const double ours = (double)(((long long)ow + kCols - 1) / kCols * kCols) * (double)(((long long)oh + kChunk - 1) / kChunk * kChunk);
-    const double worth = taps * (1.08 * theirs < ours ? 1.08 * theirs / ours : 1.0);       // (8 %: many strips and chunks, where it is level)
+    const double worth = taps * (1.5 * theirs < ours ? 1.5 * theirs / ours : 1.0);
     if (kh > 13 || kw > 13) return kw >= 11 && taps >= 10 * units;
     const bool run_time_sized = kh > 11 || kw > 11 || (kh >= 8 && kw >= 8 && kh != kw);
     if (run_time_sized && kh <= 3) return worth >= 8 * units && outputs >= 5e6;
     if (run_time_sized) return taps >= 12 * units || (worth >= 8 * units && outputs >= 2e6 && outputs * (worth - 7 * units) >= 4e6 * units);
-    return taps >= 64 && outputs * (worth - 9 * units) >= 12.2e6 * units;
+    return taps >= 64 && outputs * (worth - 9 * units) >= 12e6 * units;
 }
 
 hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,

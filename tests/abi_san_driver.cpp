@@ -192,7 +192,8 @@ int main()
     EXPECT(sysconv::conv2d_split_pays(1275, 1606, 3, 12), 0);
     EXPECT(sysconv::conv2d_split_pays(866, 4759, 3, 12), 0);       // three rows: half of the units are empty
     EXPECT(sysconv::conv2d_split_pays(4673, 1074, 3, 13), 1);
-    EXPECT(sysconv::conv2d_split_pays(370, 6223, 10, 10), 0);
+    EXPECT(sysconv::conv2d_split_pays(2828, 989, 9, 9), 1);
+    EXPECT(sysconv::conv2d_split_pays(3857, 380, 11, 11), 1);
     EXPECT(sysconv::conv2d_split_pays(2039, 2039, 10, 10), 1);
 
     // ---- stride 2: tiles (0) or strips of two or three rows, all three timed at each shape
