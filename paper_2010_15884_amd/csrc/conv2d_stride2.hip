@@ -152,7 +152,7 @@ __device__ __forceinline__ void exchange_row(float* __restrict__ slot, int lane,
 // LDS (exchange_row), builds the shifted windows of the even and of the odd chain once and applies them to every output row whose filter covers that input
 // row (p = rho - 2r).  Strips overlap like the tiles above: the PEs whose even chain
 // would reach past lane 63 compute values that are never stored.
-template <int KH, int KW, int ROWS, bool EDGE>
+template <int KH, int KW, int ROWS, bool EDGE, bool EXCHANGE>
 __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
                                                    float* __restrict__ yrow, int in_col0, int out_col, int w_img,
                                                    long long xp, int ow, long long yp, int rows_out, bool lane_valid,
@@ -160,10 +160,6 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
 {
     constexpr int NIN = 2 * (ROWS - 1) + KH;
     constexpr int KE = (KW + 1) / 2, KO = KW / 2;
-    // The right-hand strip of 2x2 filters loads straight to the lanes: where every load is checked, four rows do not make
-    // up for the exchange (us, straight / exchanged: 647x510 outputs 4.7 / 5.6, 266x1790 5.1 / 6.1, 1211x673 6.2 / 6.8, 442x3324
-    // 7.5 / 8.2; level on 4 M outputs).
-    constexpr bool EXCHANGE = !(EDGE && KH == 2);
     const int in_col = EXCHANGE ? in_col0 + kTile * lane : in_col0 + 2 * kTile * lane;
     constexpr int kSecond = EXCHANGE ? kStrip : kTile;                     // columns from a lane's first four to its other four
     const int rows_in = 2 * (rows_out - 1) + KH;
@@ -250,10 +246,16 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D
     const bool lane_valid = lane < valid_lanes;
     const int in_col = 2 * out_col0, out_col = out_col0 + kTile * lane;
     // interior strips: all 512 input columns exist, and then so do the valid lanes' outputs
+    // A right-hand strip more than half full of a 2x2 filter loads straight to the lanes: where every load is checked, four rows do
+    // not make up for the exchange (us, straight / exchanged: 266x1790 outputs 5.1 / 6.1, 1211x673 6.2 / 6.8, 442x3324 7.5 / 8.2; but
+    // half full and less 1221x284 6.1 / 5.3, 254x1656 5.2 / 4.9; level on 4 M outputs).
+    float* const own = slots[wave_in_block()];
     if (2 * out_col0 + kCols <= w_img)
-        stride2_block_rows<KH, KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, slots[wave_in_block()], lane);
+        stride2_block_rows<KH, KW, ROWS, false, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, own, lane);
+    else if (KH == 2 && 2 * out_col0 + kStrip < w_img)
+        stride2_block_rows<KH, KW, ROWS, true, KH != 2>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, own, lane);
     else
-        stride2_block_rows<KH, KW, ROWS, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, slots[wave_in_block()], lane);
+        stride2_block_rows<KH, KW, ROWS, true, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, own, lane);
 }
 
 template <int KH, int KW, int ROWS>
