@@ -135,10 +135,11 @@ hipError_t launch_stride2(const float* x, size_t n, const float* w, int k, float
     const long long waves = (m + per_wave - 1) / per_wave;
     const long long blocks = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    // Signals of 14 to 44 MB are read without the non-temporal hint: several of them, as a program goes round its buffers, stay
-    // in the 256 MB memory-side cache (us, with / without: k = 5 4 M inputs 5.9 / 5.7, 6 M 8.0 / 7.1, 9 M 11.3 / 10.2; 11 8.1 / 6.9 on 6 M; shorter
-    // 2 M 4.0 / 4.2, longer 12 M 13.9 / 14.5, 40 M 38.6 / 41.5).  With long filters it makes no difference (50: 7 M 13.6 / 14.1, 8 M 16.2 / 16.2).
-    // (A choice inside the kernel made every group wait for its own loads: 2^26 inputs, k = 28 65 -> 76 us.)
+    // Signals of 14 to 44 MB are read without the non-temporal hint: several of them, as a program goes round its buffers,
+    // stay in the 256 MB memory-side cache (us, with / without: k = 5 4 M inputs 5.9 / 5.7, 6 M 8.0 / 7.1, 9 M 11.3 / 10.2; k = 11
+    // 6 M 8.1 / 6.9; shorter 2 M 4.0 / 4.2, longer 12 M 13.9 / 14.5, 40 M 38.6 / 41.5).  With long filters it makes no difference
+    // (50: 7 M 13.6 / 14.1, 8 M 16.2 / 16.2).  (A choice inside the kernel made every group wait for its own loads: 2^26 inputs,
+    // k = 28 65 -> 76 us.)
     const bool cacheable = KT > 0 && n > 3500000 && n < 11000000;
     const auto kernel = cacheable ? conv1d_fbs_stride2_kernel<KT, KT == 0> : conv1d_fbs_stride2_kernel<KT, true>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, taps, x, y, (long long)n, m, k, valid_lanes);
@@ -146,9 +147,10 @@ hipError_t launch_stride2(const float* x, size_t n, const float* w, int k, float
 }
 
 // Tap counts known at compile time up to 34: on short signals the loop's counters and its waits for taps show (us, loop /
-// unrolled: 70 K inputs k = 2 3.4 / 3.1, 16 3.8 / 3.4, 20 4.0 / 3.5, 34 4.8 / 4.0; 3 M 8 5.1 / 4.8, 20 6.1 / 5.6, 32 7.1 / 6.4), and from about 8 M
-// inputs on both are at the copy rate (2^26: 2 62 / 62, 20 64 / 65, 34 66 / 65).  With 35 taps and more the unrolled code leaves the
-// instruction cache on long signals (2^26: 35 68 / 77, 48 78 / 92, 64 99 / 160), though it still gains on short ones (70 K: 64 6.6 / 5.4).
+// unrolled: 70 K inputs k = 2 3.4 / 3.1, 16 3.8 / 3.4, 20 4.0 / 3.5, 34 4.8 / 4.0; 3 M 8 5.1 / 4.8, 20 6.1 / 5.6, 32 7.1 / 6.4), and from
+// about 8 M inputs on both are at the copy rate (2^26: 2 62 / 62, 20 64 / 65, 34 66 / 65).  With 35 taps and more the unrolled
+// code leaves the instruction cache on long signals (2^26: 35 68 / 77, 48 78 / 92, 64 99 / 160), though it still gains on
+// short ones (70 K: 64 6.6 / 5.4).
 constexpr int kUnrolled = 34;
 typedef hipError_t (*Launch)(const float*, size_t, const float*, int, float*, hipStream_t);
 template <int... K>

@@ -19,10 +19,11 @@
 // Toeplitz form would spread them to outputs whose window does not hold them), magnitudes from 2^80 on
 // and non-zero ones so small that parts or products of parts could fall below 2^-126, where a bf16 part
 // has fewer than its 8 bits (tiny_limit(): below 2^-40 for taps down to 2^-60, below 2^-90 for taps from 2^-10 on).
-// A chunk (16 input rows x 256 columns) that holds such a value is marked, and the outputs it reaches are
-// taken again with ordinary multiply-adds before the workgroup ends (plain_rows).  Measured (us; the vector kernel / no such
-// value / one in the image / one in every twelfth chunk down a column / in every chunk): 11x11 on 4096^2 73 / 45 / 55 / 58 / 95, on
-// 8192^2 255 / 142 / 149 / 189 / 329; 15x15 on 3001x4003 114 / 44 / 52 / 70 / 110; on 300x400 15 / 8.7 / 19 / 19 / 15.
+// The chunk (16 input rows x 256 columns) that holds such a value is marked, and which four of its rows, and the outputs
+// these rows reach are taken again with ordinary multiply-adds before the workgroup ends (plain_rows).  Measured (us; the
+// vector kernel / no such value / one in the image / in every twelfth chunk down a column / in every fourth / in every one):
+// 11x11 on 4096^2 71 / 43 / 48 / 51 / 68 / 92, on 8192^2 242 / 148 / 155 / 174 / 230 / 326, on 1500^2 14.7 / 13.8 / 17 / 20 / 22 / 23;
+// 15x15 on 3001x4003 107 / 46 / 51 / 69 / 93 / 100, on 300x400 15 / 8.8 / 19 / 19 / 19 / 16.
 //
 // Data path.  A workgroup of four wavefronts walks down a block of rows of a 256-column strip, 16 input
 // rows (a "chunk") at a time.  A chunk is loaded into registers two chunks ahead of its use, split once
@@ -71,6 +72,7 @@ constexpr int kMaxChunks = 64;              // chunks of a row block, the one th
 constexpr int kNonTemporal = 2;             // the nt bit of a buffer store
 constexpr int kPlainRows = 4;               // output rows a wavefront takes together in plain_rows, and input rows in flight
 constexpr unsigned short kHuge = (127 + 80) << 7;          // upper half of the bits of 2^80
+constexpr unsigned kHugeBits = (kHuge << 16) - 0x8000u;    // the least number whose first part is 2^80
 
 // Three bf16 parts of two numbers; every part is the remainder rounded to nearest.
 __device__ __forceinline__ void split2(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3)
@@ -107,21 +109,23 @@ struct SplitShape {
 constexpr int kPlaces = 512;                // workgroups the device holds: two a CU (registers allow 256 a lane)
 
 // Where the marked chunks of a row block make the matrix cores' work pointless: the block then ends with plain_rows for
-// all rows from the present chunk on.  A marked chunk costs 2.7 (11x11) to 5 (15x15) chunk times, since it takes 28 to 37
-// output rows again, and plain_rows alone 1.5 to 2.3 a chunk: level where one chunk in 4 to 6 is marked.  One marked
-// chunk alone ends only blocks so short that it is a sixth of them.
+// all rows from the present chunk on.  Rows of a chunk that hold such values cost the 16 (11x11) to 24 (15x15) output rows they
+// reach, 2.3 to 3.8 chunk times, up to 4 to 6 where they are all over the chunk; plain_rows alone takes 2.3 to 2.5 a chunk: level
+// where between one chunk in 2 and one in 4 is marked.  An eighth of the block has to be: a margin of such values is no reason
+// (40 rows at the top and the bottom of 8192^2, 11x11: 322 us given up, 171 not).  One marked chunk alone ends only blocks of
+// one or two.
 __device__ __forceinline__ bool too_many(unsigned long long marks, int seen, int chunks)
 {
     const int marked = __builtin_popcountll(marks);
-    return marked * 6 > seen && (marked > 1 || chunks <= 6);
+    return marked * 3 > seen && marked * 8 > chunks && (marked > 1 || chunks <= 2);
 }
 
 // The output rows [ra, rb) of the strip with plain multiply-adds, as an FBS array whose width is known at compile time:
 // a wavefront walks down the input rows of kPlainRows output rows, builds each row's window once and applies it to every
 // output row whose filter covers it.  The filter rows in use are in registers (from tap0, row 0 of the taps in LDS, one
 // a step ahead of its use): two wavefronts a SIMD do not hide the latency of scalar loads (11x11 on 4096^2, a marked value in
-// every chunk: 127 us with taps in scalar registers, 95 this way; 1263 with one output row a wavefront and a load a tap).
-// It takes 1.0 to 1.35 times the vector kernels' time.  (col_b, off): the lane's load.
+// every chunk: 127 us with taps in scalar registers, 95 this way; 1263 with one output row a wavefront and a load a tap).  On
+// large images it issues 1.16 times the vector instructions of SBM.  (col_b, off): the lane's load.
 template <int KW, int TapPitch, class PutRight>
 __device__ __forceinline__ void plain_rows(const float* tap0, const float* __restrict__ x, float* __restrict__ y,
                                            unsigned col_b, int off, long long xp, int col, int ow_strip, long long yp, int kh,
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
 
     __shared__ __attribute__((aligned(16))) __bf16 parts[2 * kBuf + 32];     // (windows of the last wavefront reach past a row)
     __shared__ float tpad[S::TROWS * S::TCOLS];
-    __shared__ unsigned marks[kMaxChunks / 32];                            // a bit per chunk
+    __shared__ unsigned marks[kMaxChunks / 32], quads[kMaxChunks / 8];     // a bit per chunk, and per four rows of a chunk
 
     const int g = xcd_contiguous(blockIdx.x, per_xcd);
     if (g >= row_blocks * strips) return;                                  // (the whole workgroup)
@@ -258,7 +262,18 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) put(raw[k], buf + (wave + 4 * k) * kRow + kTile * lane);
-        if (tiny < tiny_below || huge.x >= kHuge || huge.y >= kHuge) atomicOr(marks + c / 32, 1u << (c % 32));
+        if (tiny < tiny_below || huge.x >= kHuge || huge.y >= kHuge) {     // rare: which of the lane's rows?
+            unsigned rows_hit = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned bits = __builtin_bit_cast(unsigned, (float)raw[k][i]);
+                    if ((bits << 1) - 1u < tiny_below || (bits & 0x7fffffffu) >= kHugeBits) rows_hit |= 1u << k;
+                }
+            atomicOr(marks + c / 32, 1u << (c % 32));
+            atomicOr(quads + c / 8, rows_hit << (4 * (c % 8)));
+        }
     };
 
     load_chunk(0);
@@ -267,6 +282,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         tpad[e] = p >= 0 && p < kh && q >= 0 && q < kw ? taps_f[p * kw + q] : 0.0f;
     }
     if (threadIdx.x < kMaxChunks / 32) marks[threadIdx.x] = 0;
+    if (threadIdx.x < kMaxChunks / 8) quads[threadIdx.x] = 0;
     __syncthreads();
 
     // A operands: the Toeplitz form of the taps, constant for the whole kernel
@@ -385,7 +401,8 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         };
         using Slot0 = std::integral_constant<int, 0>;
         using Slot1 = std::integral_constant<int, GROUPS % LIVE>;          // slots of the odd chunks
-        if (too_many(marked_up_to(0), 1, chunks)) return 0;
+        const bool full = (__builtin_amdgcn_readfirstlane(quads[0]) & 15u) == 15u;     // such values all over the first chunk
+        if ((full && chunks <= 6) || too_many(marked_up_to(0), 1, chunks)) return 0;
         advance(0, std::true_type{}, Slot0{});
         int c = 1;
         for (; c + 2 <= chunks; c += 2) {
@@ -403,27 +420,48 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
     };
     const int stop = edge ? run(std::true_type{}) : run(std::false_type{});
 
-    // The output rows that marked chunks reach, once more; neighbouring marked chunks together.
+    // The output rows that the marks reach, once more; neighbouring and overlapping ones together.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                       // the stores above are done before any of these
     __syncthreads();
     auto again = [&](int ra, int rb) {
         auto with = [&](auto kw_tag, auto self) {
             constexpr int KW = decltype(kw_tag)::value;
             if (kw == KW)
-                plain_rows<KW, S::TCOLS>(tpad + (JR - 1) * S::TCOLS + JC - 1, x, y, col_b, off_m, xp, c0 + kTile * lane, ow_strip, yp, kh, r0 + ra, r0 + rb, edge, wave, put_right);
+                plain_rows<KW, S::TCOLS>(tpad + (JR - 1) * S::TCOLS + JC - 1, x, y, col_b, off_m, xp, c0 + kTile * lane, ow_strip,
+                                         yp, kh, r0 + ra, r0 + rb, edge, wave, put_right);
             else if constexpr (KW < most_width(JC))
                 self(std::integral_constant<int, KW + 1>{}, self);
         };
         with(std::integral_constant<int, least_width(JC)>{}, with);
     };
     unsigned long long todo = marked_up_to(chunks);
-    if (stop <= chunks) todo |= ~0ull << stop;
-    while (todo) {
-        const int k = __builtin_ctzll(todo);
-        const int run = __builtin_ctzll(~(todo >> k) | 1ull << 63), last = min(k + run - 1, chunks);     // marked: chunks k .. last
-        const int first = k * kChunk - (2 * NS - 1);                       // group at row R: input rows R .. R + 2 NS - 1
-        again(first <= 0 ? 0 : (first + JR - 1) / JR * JR, min((last + 1) * kChunk, rows_out));
-        todo = last < chunks ? todo & ~0ull << (last + 1) : 0;
+    if (stop <= chunks) todo = (todo & ~(~0ull << stop)) | 1ull << stop;   // (from there on: all that is left)
+    int k = 0;
+    unsigned four = 0;                                                     // marked row quads of chunk k that are still to come
+    auto next = [&]() -> int {                                             // the next marked row quad of the block, or -1
+        while (four == 0) {
+            if (todo == 0) return -1;
+            k = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            four = k == stop ? 1u : (__builtin_amdgcn_readfirstlane(quads[k / 8]) >> (4 * (k % 8))) & 15u;
+        }
+        const int i = __builtin_ctz(four);
+        four &= four - 1;
+        return 4 * k + i;
+    };
+    auto first_row = [](int quad) {                                        // group at row R: input rows R .. R + 2 NS - 1
+        const int r = 4 * quad - (2 * NS - 1);
+        return r <= 0 ? 0 : (r + JR - 1) / JR * JR;
+    };
+    int quad = next();
+    while (quad >= 0) {
+        const int ra = first_row(quad);
+        int rb;
+        do {
+            rb = k == stop ? rows_out : (4 * quad + 3) / JR * JR + JR;
+            quad = next();
+        } while (quad >= 0 && first_row(quad) <= rb);
+        again(ra, min(rb, rows_out));
     }
 }
 
@@ -480,10 +518,10 @@ int split_units(int kh, int kw)                 // NS of the kernel that serves 
 }  // namespace
 
 // Filters and images the kernel takes: taps 0 or 2^-60 .. 2^40 in magnitude (so that no part of a tap and no
-// product of parts is subnormal or infinite), widths that plain_rows is built for (and with them rows of at least four
-// columns, the 16 bytes of a load), output pitches whose rows of a group lie within the 2 GB of a buffer descriptor, heights whose row numbers stay in an
-// int: the chunks that a block asks for in advance reach up to three chunks past its last output row, and they are
-// clamped to the image only after that sum.
+// product of parts is subnormal or infinite), widths that plain_rows is built for (and with them rows of at least
+// four columns, the 16 bytes of a load), output pitches whose rows of a group lie within the 2 GB of a buffer
+// descriptor, heights whose row numbers stay in an int: the chunks that a block asks for in advance reach up to
+// three chunks past its last output row, and they are clamped to the image only after that sum.
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 {
     if (h > INT_MAX - 4 * kChunk) return false;

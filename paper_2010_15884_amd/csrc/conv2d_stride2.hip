@@ -251,11 +251,14 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D
     // half full and less 1221x284 6.1 / 5.3, 254x1656 5.2 / 4.9; level on 4 M outputs).
     float* const own = slots[wave_in_block()];
     if (2 * out_col0 + kCols <= w_img)
-        stride2_block_rows<KH, KW, ROWS, false, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, own, lane);
+        stride2_block_rows<KH, KW, ROWS, false, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out,
+                                                      lane_valid, own, lane);
     else if (KH == 2 && 2 * out_col0 + kStrip < w_img)
-        stride2_block_rows<KH, KW, ROWS, true, KH != 2>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, own, lane);
+        stride2_block_rows<KH, KW, ROWS, true, KH != 2>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out,
+                                                        lane_valid, own, lane);
     else
-        stride2_block_rows<KH, KW, ROWS, true, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out, lane_valid, own, lane);
+        stride2_block_rows<KH, KW, ROWS, true, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out,
+                                                     lane_valid, own, lane);
 }
 
 template <int KH, int KW, int ROWS>
@@ -483,8 +486,11 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
     }
     switch (conv2d_stride2_strip_rows((h - kh) / 2 + 1, (w - kw) / 2 + 1, kh, kw)) {
     case 0: return launch_tiles<kTileRpw>(x, h, w, xp, f, kh, kw, y, yp, s);
-    case 3: return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
-    default: return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    case 3:
+        return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    default:
+        return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>{}, x, h, w, xp, f,
+                                     kh, kw, y, yp, s);
     }
 }
 
