@@ -401,8 +401,10 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         };
         using Slot0 = std::integral_constant<int, 0>;
         using Slot1 = std::integral_constant<int, GROUPS % LIVE>;          // slots of the odd chunks
-        const bool full = (__builtin_amdgcn_readfirstlane(quads[0]) & 15u) == 15u;     // such values all over the first chunk
-        if ((full && chunks <= 6) || too_many(marked_up_to(0), 1, chunks)) return 0;
+        if (__builtin_amdgcn_readfirstlane(marks[0]) & 1u) {
+            const bool full = (__builtin_amdgcn_readfirstlane(quads[0]) & 15u) == 15u;  // such values all over the first chunk
+            if ((full && chunks <= 6) || too_many(1, 1, chunks)) return 0;
+        }
         advance(0, std::true_type{}, Slot0{});
         int c = 1;
         for (; c + 2 <= chunks; c += 2) {
