@@ -17,14 +17,14 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsysconv.so")
-SOURCES = ["api.hip", "conv1d.hip", "conv1d_arrays.hip", "conv1d_stride2.hip", "conv1d_stt.hip", "conv2d.hip", "conv2d_mfma.hip", "conv2d_split.hip", "conv2d_stride2.hip", "copy.hip"]
+SOURCES = ["api.hip", "conv1d.hip", "conv1d_arrays.hip", "conv1d_split.hip", "conv1d_stride2.hip", "conv1d_stt.hip", "conv2d.hip", "conv2d_mfma.hip", "conv2d_split.hip", "conv2d_stride2.hip", "copy.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 # Per-file additions.  The matrix-core kernels keep their accumulators in ordinary vector registers
 # (the results go straight to the vector ALUs; from accumulation registers every value would
 # first need a v_accvgpr_read).
-FILE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("conv2d_mfma.hip", "conv2d_split.hip")}
+FILE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("conv1d_split.hip", "conv2d_mfma.hip", "conv2d_split.hip")}
 
 
 def _compile(src: str) -> str:
@@ -68,7 +68,7 @@ def build_c_demo(verbose: bool = True) -> str:
 
 SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-sanitize-recover=all", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
-HOST_LOGIC = ["api.hip", "conv1d_stt.hip", "conv2d_mfma.hip", "conv2d_split.hip"]      # argument checks, the design planner, the tap scaling
+HOST_LOGIC = ["api.hip", "conv1d_split.hip", "conv1d_stt.hip", "conv2d_mfma.hip", "conv2d_split.hip"]      # argument checks, the design planner, the tap scaling
 
 
 def build_host_sanitized(verbose: bool = True) -> str:

@@ -53,8 +53,10 @@ int sys_conv1d(const float* d_x, size_t n, const float* h_w, int k, float* d_y, 
 
     switch (projection) {
     case SYS_PROJ_AUTO:
-        // Long filters are bound by the VALUs, where BFS issues the fewest instructions
-        // (n = 2^26: k = 34: 110 / 109 us FBS / BFS, k = 36: 113 / 108, k = 48: 146 / 120,
+        if (sysconv::conv1d_split_takes(h_w, k))
+            return hip_status(sysconv::launch_conv1d_split(d_x, n, h_w, k, d_y, stream));
+        // What the matrix-core kernel does not take: long filters are bound by the VALUs, where BFS issues the fewest
+        // instructions (n = 2^26: k = 34: 110 / 109 us FBS / BFS, k = 36: 113 / 108, k = 48: 146 / 120,
         // k = 64: 208 / 142; up to k = 28 FBS sits on the copy rate and BFS 5-10 % above it).
         // On signals of 2 GB and more BFS, whose register groups do not overlap, is the
         // faster one at every k (n = 2^29: 739 / 709 us at k = 16, 744 / 708 at k = 5;

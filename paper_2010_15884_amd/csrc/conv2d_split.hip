@@ -11,14 +11,7 @@
 // 4 x 4 offsets serve filters up to 13 columns, 8 x 2 offsets 14 and 15 columns (kw + JC - 1 <= 16).
 // A group of JR output rows takes NS = ceil((kh + JR - 1) / 2) units.
 //
-// Precision.  Every input and tap is the exact sum of three bf16 numbers, v = v1 + v2 + v3, each the
-// rest rounded to nearest (8 + 8 + 8 bits: nothing of the 24 is lost).  Six of the nine products are
-// taken -- x1f1, x1f2, x2f1, x2f2, x1f3, x3f1 -- and accumulated in fp32; the three dropped ones are
-// below 2^-25 of the term and of either sign.  bf16 has the exponent range of fp32, so nothing is
-// scaled.  What the split cannot carry is looked for in every input: infinities, NaN (the zeros of the
-// Toeplitz form would spread them to outputs whose window does not hold them), magnitudes from 2^80 on
-// and non-zero ones so small that parts or products of parts could fall below 2^-126, where a bf16 part
-// has fewer than its 8 bits (tiny_limit(): below 2^-40 for taps down to 2^-60, below 2^-90 for taps from 2^-10 on).
+// Precision: three bf16 parts a number, six products (split_bf16.h), which also says which inputs the split does not carry.
 // The chunk (16 input rows x 256 columns) that holds such a value is marked, and which four of its rows, and the outputs
 // these rows reach are taken again with ordinary multiply-adds before the workgroup ends (plain_rows).  Measured (us; the
 // vector kernel / no such value / one in the image / in every twelfth chunk down a column / in every fourth / in every one):
@@ -44,6 +37,7 @@
 // branches (every chunk then waits for the stores of the one before), three workgroups a CU (spills at NS = 7, level
 // below).  Reads of 16 bytes from LDS at 8-byte alignment are slow: a window is two 8-byte (8 x 2: four 4-byte) reads.
 #include "launch.h"
+#include "split_bf16.h"
 #include "systolic.h"
 #include "tiling.h"
 
@@ -54,11 +48,6 @@
 namespace sysconv {
 namespace {
 
-typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef unsigned u2 __attribute__((ext_vector_type(2)));
-typedef unsigned u4 __attribute__((ext_vector_type(4)));
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 typedef const float __attribute__((address_space(4)))* kernarg_floats;
 
@@ -73,16 +62,6 @@ constexpr int kNonTemporal = 2;             // the nt bit of a buffer store
 constexpr int kPlainRows = 4;               // output rows a wavefront takes together in plain_rows, and input rows in flight
 constexpr unsigned short kHuge = (127 + 80) << 7;          // upper half of the bits of 2^80
 constexpr unsigned kHugeBits = (kHuge << 16) - 0x8000u;    // the least number whose first part is 2^80
-
-// Three bf16 parts of two numbers; every part is the remainder rounded to nearest.
-__device__ __forceinline__ void split2(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3)
-{
-    p1 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{a, b}, b2));
-    const float ra = a - __builtin_bit_cast(float, p1 << 16), rb = b - __builtin_bit_cast(float, p1 & 0xffff0000u);
-    p2 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{ra, rb}, b2));
-    const float sa = ra - __builtin_bit_cast(float, p2 << 16), sb = rb - __builtin_bit_cast(float, p2 & 0xffff0000u);
-    p3 = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{sa, sb}, b2));
-}
 
 // Barrier for what the workgroup exchanges through LDS: the loads from global memory that are in flight stay so.
 __device__ __forceinline__ void lds_barrier()
@@ -467,20 +446,6 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
     }
 }
 
-// Inputs below this magnitude (0 apart) are not for the split: with a smallest tap of 2^t, below 2^(-100 - t) products of
-// parts that are more than a 2^-26th of the term could fall below 2^-126, and below 2^-103 the parts themselves.  In the form
-// the kernel compares, (bits << 1) - 1.
-unsigned tiny_limit(const float* f, int n)
-{
-    float least = 0x1p40f;
-    for (int i = 0; i < n; ++i)
-        if (f[i] != 0.0f) least = __builtin_fminf(least, __builtin_fabsf(f[i]));
-    int t = 0;
-    (void)__builtin_frexpf(least, &t);                                     // least = m 2^t with 1/2 <= m < 1
-    const int e = -100 - (t - 1) > -103 ? -100 - (t - 1) : -103;
-    return ((unsigned)(127 + e) << 24) - 1u;
-}
-
 template <int JC, int NS>
 hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
                         hipStream_t s)
@@ -507,7 +472,7 @@ hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f,
     const long long blocks = per_xcd * kXcds;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((conv2d_split_kernel<JC, NS>), dim3((unsigned)blocks), dim3(kBlock), 0, s, taps, x, y, h, w,
-                       (long long)xp, oh, ow, (long long)yp, kh, kw, (int)rows, row_blocks, strips, (int)per_xcd, tiny_limit(f, kh * kw));
+                       (long long)xp, oh, ow, (long long)yp, kh, kw, (int)rows, row_blocks, strips, (int)per_xcd, split_tiny_limit(f, kh * kw));
     return hipGetLastError();
 }
 
@@ -519,9 +484,8 @@ int split_units(int kh, int kw)                 // NS of the kernel that serves 
 
 }  // namespace
 
-// Filters and images the kernel takes: taps 0 or 2^-60 .. 2^40 in magnitude (so that no part of a tap and no
-// product of parts is subnormal or infinite), widths that plain_rows is built for (and with them rows of at least
-// four columns, the 16 bytes of a load), output pitches whose rows of a group lie within the 2 GB of a buffer
+// Filters and images the kernel takes: taps that the split carries, widths that plain_rows is built for (and with them rows of at
+// least four columns, the 16 bytes of a load), output pitches whose rows of a group lie within the 2 GB of a buffer
 // descriptor, heights whose row numbers stay in an int: the chunks that a block asks for in advance reach up to
 // three chunks past its last output row, and they are clamped to the image only after that sum.
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
@@ -529,11 +493,7 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
     if (h > INT_MAX - 4 * kChunk) return false;
     if (yp > ((size_t)1 << 25) || kh > kMaxK2D || kw > kMaxK2D || w < kw) return false;
     if (kw < least_width(kh <= 13 && kw <= 13 ? 4 : 2)) return false;
-    for (int i = 0; i < kh * kw; ++i) {
-        const float a = __builtin_fabsf(f[i]);
-        if (!(a == 0.0f || (a >= 0x1p-60f && a <= 0x1p40f))) return false;         // NaN fails too
-    }
-    return true;
+    return split_takes_taps(f, kh * kw);
 }
 
 // Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units NS, theirs with

@@ -29,6 +29,10 @@ hipError_t launch_conv1d_fbs_stride2(const float* x, size_t n, const float* w, i
 bool has_conv1d_bfs(int k);
 hipError_t launch_conv1d_bfs(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s);
 
+// Matrix-core path without conditions on the input (conv1d_split.hip).
+bool conv1d_split_takes(const float* w, int k);
+hipError_t launch_conv1d_split(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s);
+
 // Generic space-time-transform kernel (conv1d_stt.hip).  A plan is what the host derives
 // from a design: the transform, its inverse's sign, the chunk of outputs one wavefront
 // takes, the lowest PE / time coordinates, and per passed variable its dependence and
