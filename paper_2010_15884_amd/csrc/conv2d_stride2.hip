@@ -4,16 +4,12 @@
 // columns, one 1-D pass per filter row as in the stride-1 2-D FBS kernel (Section 6.2),
 // all passes adding into the same partial sums.
 //
-// A workgroup stages a (2*(4*RPW-1) + kh) x 512 input tile in LDS; each of its four
-// wavefronts owns RPW output rows.  For filter row p a lane reads eight consecutive
-// inputs of image row 2r+p -- x(2c) and x(2c+1) of its four PEs -- and the even and the
-// odd taps of that filter row then run as two stride-1 FBS chains over the
-// de-interleaved values (the hand-over X(c,q) = X(c+1,q-2) never mixes the two).
+// For filter row p a lane holds eight consecutive inputs of image row 2r+p -- x(2c) and x(2c+1) of its four PEs -- and the
+// even and the odd taps of that filter row are two stride-1 FBS chains over the de-interleaved values (the hand-over
+// X(c,q) = X(c+1,q-2) never mixes the two).
 //
-//   conv2d_fbs_stride2_kernel<RPW>            any filter up to 15x15: the LDS tiles described above
 //   conv2d_fbs_stride2_block_kernel<K,K,ROWS> 2x2 .. 5x5: all input rows of two output rows up front
-//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  any height: rows streamed through registers, where the tiles do not
-//                                             fit the chip in one round (conv2d_stride2_strip_rows)
+//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  the rest: the input rows of one to three output rows streamed through registers
 #include "launch.h"
 #include "systolic.h"
 #include "tiling.h"
@@ -25,108 +21,7 @@ namespace {
 
 typedef const float __attribute__((address_space(4)))* kernarg_floats;
 
-constexpr int kCols = 2 * kStrip;                        // input columns of a tile (eight per lane)
-constexpr int kRowTaps = 20;                             // per filter row: 8 even taps, 8 odd taps, 4 of slack
-struct TapsStride2D { float f[kMaxK2D * kRowTaps]; };
-
-template <int NT, bool MORE, int RPW>
-__device__ __forceinline__ void chain_rows(float (&e)[RPW][4], float (&acc)[RPW][4], const float (&w)[4])
-{
-#pragma unroll
-    for (int j = 0; j < RPW; ++j) fbs_steps<NT, MORE>(e[j], acc[j], w);
-}
-
-// All kc >= 1 time steps of one chain of one filter row, for the RPW rows of a wavefront.
-template <int RPW>
-__device__ __forceinline__ void run_chain(float (&e)[RPW][4], float (&acc)[RPW][4], kernarg_floats w, int kc)
-{
-    int j = 0;
-#pragma nounroll
-    for (; j + 4 < kc; j += 4) {
-        const float wb[4] = {w[j], w[j + 1], w[j + 2], w[j + 3]};
-        chain_rows<4, true, RPW>(e, acc, wb);
-    }
-    const float wb[4] = {w[j], w[j + 1], w[j + 2], w[j + 3]};
-    switch (kc - j) {                                    // uniform across the wavefront
-    case 4: chain_rows<4, false, RPW>(e, acc, wb); break;
-    case 3: chain_rows<3, false, RPW>(e, acc, wb); break;
-    case 2: chain_rows<2, false, RPW>(e, acc, wb); break;
-    default: chain_rows<1, false, RPW>(e, acc, wb); break;
-    }
-}
-
-// The taps are the first kernel argument (offset 0 of the kernel-argument segment).
-template <int RPW>
-__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_kernel(TapsStride2D taps, const float* __restrict__ x,
-                                                                    float* __restrict__ y, int h, int w_img,
-                                                                    long long xp, int oh, int ow, long long yp,
-                                                                    int kh, int kw, int tiles_y, int n_tiles, int side,
-                                                                    int per_xcd)
-{
-    extern __shared__ __attribute__((aligned(16))) float tile[];           // (2*(kTileRows-1) + kh) x kCols
-    constexpr int kTileRows = RPW * (kBlock / kWave);                      // output rows per workgroup
-    (void)taps;
-    kernarg_floats tw = (kernarg_floats)__builtin_amdgcn_kernarg_segment_ptr();
-
-    const int t = xcd_contiguous(blockIdx.x, per_xcd);
-    if (t >= n_tiles) return;                                              // whole workgroup leaves together
-    int tile_y, tile_x;
-    band_order(t, tiles_y, n_tiles / tiles_y, side, tile_y, tile_x);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = wave_in_block();
-    const int ke = (kw + 1) / 2, ko = kw / 2;                              // even taps q = 0, 2, ..; odd taps q = 1, 3, ..
-    const int valid_lanes = kWave - halo_lanes(ke);
-    const int out_col0 = tile_x * kTile * valid_lanes;
-    const int out_row0 = tile_y * kTileRows;
-    const int in_col0 = 2 * out_col0, in_row0 = 2 * out_row0;
-
-    // stage: wavefront v copies input rows v, v+4, ... of the tile (2 KB each, coalesced)
-    const int in_rows = min(2 * (kTileRows - 1) + kh, h - in_row0);
-    for (int rr = wave; rr < in_rows; rr += kBlock / kWave) {
-        const float* src = x + (long long)(in_row0 + rr) * xp;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            float v[4];
-            load4_guarded<false>(src, in_col0 + half * kStrip + kTile * lane, w_img, v);
-            f4 t4;
-            t4.x = v[0]; t4.y = v[1]; t4.z = v[2]; t4.w = v[3];
-            *reinterpret_cast<f4*>(tile + rr * kCols + half * kStrip + kTile * lane) = t4;
-        }
-    }
-    __syncthreads();
-
-    float acc[RPW][4];
-#pragma unroll
-    for (int j = 0; j < RPW; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[j][i] = 0.0f;
-
-    const int lrow0 = wave * RPW;
-#pragma nounroll
-    for (int p = 0; p < kh; ++p) {
-        float ev[RPW][4], od[RPW][4];
-#pragma unroll
-        for (int j = 0; j < RPW; ++j) {
-            // rows below the staged part of the tile hold stale LDS; they only feed
-            // output rows >= oh, which are not stored
-            const float* row = tile + (2 * (lrow0 + j) + p) * kCols + 2 * kTile * lane;
-            const f4 lo = *reinterpret_cast<const f4*>(row), hi = *reinterpret_cast<const f4*>(row + 4);
-            ev[j][0] = lo.x; od[j][0] = lo.y; ev[j][1] = lo.z; od[j][1] = lo.w;
-            ev[j][2] = hi.x; od[j][2] = hi.y; ev[j][3] = hi.z; od[j][3] = hi.w;
-        }
-        kernarg_floats fp = tw + p * kRowTaps;
-        run_chain<RPW>(ev, acc, fp, ke);
-        if (ko > 0) run_chain<RPW>(od, acc, fp + 8, ko);
-    }
-
-    if (lane < valid_lanes) {
-#pragma unroll
-        for (int j = 0; j < RPW; ++j) {
-            const int r = out_row0 + lrow0 + j;
-            if (r < oh) store4_guarded(y + (long long)r * yp, out_col0 + kTile * lane, ow, acc[j]);
-        }
-    }
-}
+constexpr int kCols = 2 * kStrip;                        // input columns of a strip (eight per lane)
 
 // Row of a strip from the lanes' load order (lane l: columns 4l .. 4l+3 of the strip's first and second half, so that a
 // load is 1 KB of consecutive addresses) to the array's (lane l: columns 8l .. 8l+7, four PEs), through 2 KB of LDS that
@@ -163,6 +58,7 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
     const int in_col = EXCHANGE ? in_col0 + kTile * lane : in_col0 + 2 * kTile * lane;
     constexpr int kSecond = EXCHANGE ? kStrip : kTile;                     // columns from a lane's first four to its other four
     const int rows_in = 2 * (rows_out - 1) + KH;
+    const EdgeQuad first(in_col, w_img), second(in_col + kSecond, w_img);
 
     float v[NIN][8];
 #pragma unroll
@@ -170,22 +66,19 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
         // rows past the end of the block repeat its last row; they only feed output rows
         // that are not stored
         const float* p = xrow + (long long)min(rho, rows_in - 1) * xp;
-        if (EDGE) {
-            float lo[4], hi[4];
-            load4_guarded<false>(p, in_col, w_img, lo);
-            load4_guarded<false>(p, in_col + kSecond, w_img, hi);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { v[rho][i] = lo[i]; v[rho][4 + i] = hi[i]; }
-        } else {
-            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + kSecond);
-            v[rho][0] = lo.x; v[rho][1] = lo.y; v[rho][2] = lo.z; v[rho][3] = lo.w;
-            v[rho][4] = hi.x; v[rho][5] = hi.y; v[rho][6] = hi.z; v[rho][7] = hi.w;
-        }
+        const f4u lo = *reinterpret_cast<const f4u*>(p + (EDGE ? first.at : in_col));
+        const f4u hi = *reinterpret_cast<const f4u*>(p + (EDGE ? second.at : in_col + kSecond));
+        v[rho][0] = lo.x; v[rho][1] = lo.y; v[rho][2] = lo.z; v[rho][3] = lo.w;
+        v[rho][4] = hi.x; v[rho][5] = hi.y; v[rho][6] = hi.z; v[rho][7] = hi.w;
     }
 
     float acc[ROWS][4];
 #pragma unroll
     for (int rho = 0; rho < NIN; ++rho) {
+        if constexpr (EDGE) {
+            first.put_right(v[rho][0], v[rho][1], v[rho][2], v[rho][3]);
+            second.put_right(v[rho][4], v[rho][5], v[rho][6], v[rho][7]);
+        }
         if constexpr (EXCHANGE) exchange_row(slots + (rho & 1) * kCols, lane, v[rho]);
         float ev[KE + 3], od[KO + 3];
 #pragma unroll
@@ -282,13 +175,15 @@ hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f,
 // ------------------------------------------------------------ strip form ----
 // Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 512
 // input columns and walks down its 2*(ROWS-1)+kh input rows, kAhead of them in flight in registers.  Each row's two
-// windows are built once and applied to every output row whose filter covers it, where the tiles build them again for
-// every (output row, filter row) and step through the taps four at a time.  What bounds it is the latency of its input rows:
-// on 4095x6001 7x7 (three rows, 32.4 us) the vector ALUs are busy for 30 %, 1.9 wavefronts a SIMD are resident of the four that
-// 116 registers allow, and the rows requested, (2 (ROWS-1) + kh) / (2 ROWS) = 1.83 times the image, come from L2 but for 1.25 times.
+// windows are built once and applied to every output row whose filter covers it.  What bounds it is the latency of its input rows: the
+// rows requested, (2 (ROWS-1) + kh) / (2 ROWS) times the image, come from L2 for the most part.  A strip that reaches past
+// the right edge must not wait for each row by itself: with loads behind per-lane branches its wavefronts lived 28 us where the
+// others took 9, and the launch ended with them (4095x6001 7x7 37.1 us, with EdgeQuad's loads 30.5; 8192^2 11x11 118 / 94, 3000^2 9x9
+// 22.6 / 16.4).  Six or eight rows in flight are 1 to 5 % and 6 to 10 % slower than four.
 constexpr int kAhead = 4;
 
-template <int KW, int ROWS, bool EDGE>
+enum StripKind { kInside, kEdge, kNarrow };              // all 512 columns exist; not all do; fewer than four do
+template <int KW, int ROWS, StripKind KIND>
 __device__ __forceinline__ void stride2_strip_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
                                                    float* __restrict__ yrow, int in_col, int out_col, int w_img,
                                                    long long xp, int ow, long long yp, int kh, int rows_out,
@@ -296,18 +191,18 @@ __device__ __forceinline__ void stride2_strip_rows(kernarg_floats taps_f, const 
 {
     constexpr int KE = (KW + 1) / 2, KO = KW / 2;
     const int rows_in = 2 * (rows_out - 1) + kh;
+    constexpr bool EDGE = KIND == kEdge;
+    const EdgeQuad first(in_col, w_img), second(in_col + 4, w_img);
 
     float v[kAhead][8];
     auto load_row = [&](int rho, float (&d)[8]) {                          // past the last row: the last row again
         const float* p = xrow + (long long)min(rho, rows_in - 1) * xp;
-        if (EDGE) {
-            float lo[4], hi[4];
-            load4_guarded<false>(p, in_col, w_img, lo);
-            load4_guarded<false>(p, in_col + 4, w_img, hi);
+        if constexpr (KIND == kNarrow) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { d[i] = lo[i]; d[4 + i] = hi[i]; }
+            for (int i = 0; i < 8; ++i) d[i] = p[min(in_col + i, w_img - 1)];
         } else {
-            const f4u lo = *reinterpret_cast<const f4u*>(p + in_col), hi = *reinterpret_cast<const f4u*>(p + in_col + 4);
+            const f4u lo = *reinterpret_cast<const f4u*>(p + (EDGE ? first.at : in_col));
+            const f4u hi = *reinterpret_cast<const f4u*>(p + (EDGE ? second.at : in_col + 4));
             d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
             d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
         }
@@ -331,6 +226,10 @@ __device__ __forceinline__ void stride2_strip_rows(kernarg_floats taps_f, const 
                 kernarg_floats fp = taps_f + min(max(rho - 2 * r, 0), kh - 1) * KW;
 #pragma unroll
                 for (int q = 0; q < KW; ++q) wv[r][q] = fp[q];
+            }
+            if constexpr (EDGE) {
+                first.put_right(v[j][0], v[j][1], v[j][2], v[j][3]);
+                second.put_right(v[j][4], v[j][5], v[j][6], v[j][7]);
             }
             float ev[KE + 3], od[KO + 3];
 #pragma unroll
@@ -380,10 +279,17 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_strip_kernel(Taps2D
     float* yrow = y + (long long)r0 * yp;
     const bool lane_valid = lane < valid_lanes;
     const int in_col = 2 * out_col0 + 2 * kTile * lane, out_col = out_col0 + kTile * lane;
-    if (2 * out_col0 + kCols <= w_img)
-        stride2_strip_rows<KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
-    else
-        stride2_strip_rows<KW, ROWS, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+    if (2 * out_col0 + kCols <= w_img) {
+        stride2_strip_rows<KW, ROWS, kInside>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+    } else {
+        if constexpr (KW < 4) {
+            if (w_img < 4) {
+                stride2_strip_rows<KW, ROWS, kNarrow>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+                return;
+            }
+        }
+        stride2_strip_rows<KW, ROWS, kEdge>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+    }
 }
 
 template <int KW, int ROWS>
@@ -414,68 +320,31 @@ hipError_t launch_strip_by_kw(std::integer_sequence<int, KW0, KW...>, const floa
     return table[kw - KW0](x, h, w, xp, f, kh, y, yp, s);
 }
 
-constexpr int kTileRpw = 2;                              // output rows of a wavefront in the tiles
-constexpr int kTileOutRows = kTileRpw * (kBlock / kWave);
-constexpr int kCus = 256, kLdsPerCu = 160 * 1024;
-
-template <int RPW>
-hipError_t launch_tiles(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
-                        hipStream_t s)
-{
-    constexpr int tile_rows = RPW * (kBlock / kWave);
-    TapsStride2D taps;
-    for (int i = 0; i < kMaxK2D * kRowTaps; ++i) taps.f[i] = 0.0f;
-    for (int p = 0; p < kh; ++p)
-        for (int q = 0; q < kw; ++q) taps.f[p * kRowTaps + (q & 1) * 8 + q / 2] = f[p * kw + q];
-    const int oh = (h - kh) / 2 + 1, ow = (w - kw) / 2 + 1;
-    const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
-    const int tiles_x = (ow + cols - 1) / cols;
-    const int tiles_y = (oh + tile_rows - 1) / tile_rows;
-    const long long n_tiles = (long long)tiles_x * tiles_y;
-    const long long per_xcd = (n_tiles + kXcds - 1) / kXcds;
-    const long long blocks = per_xcd * kXcds;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const size_t lds = (size_t)(2 * (tile_rows - 1) + kh) * kCols * sizeof(float);
-    hipLaunchKernelGGL(conv2d_fbs_stride2_kernel<RPW>, dim3((unsigned)blocks), dim3(kBlock), lds, s,
-                       taps, x, y, h, w, (long long)xp, oh, ow, (long long)yp, kh, kw, tiles_y, (int)n_tiles,
-                       band_width(xp), (int)per_xcd);
-    return hipGetLastError();
-}
-
 }  // namespace
 
-// Filters without a block form: 0 = tiles, else the rows of the strips.  Tiles as long as their workgroups fit the chip in one
-// round, else strips (us, tiles / strips of 2 / of 3 rows).  A tile takes 2 (4 RPW - 1) + kh rows of 2 KB of the 160 KB of LDS
-// of a CU: five workgroups (kh = 2) to two (kh = 13 and more), so a round ends at 2.5 M to 1.0 M outputs, and there the tiles'
-// time jumps: 7x7 on 769x1865 outputs 18.2 / 13.7 / 14.7, 13x13 on 654x1920 30.3 / 21.6 / 24.7.  Below, four wavefronts share the
-// staging of a tile's rows: 6x3 on 1137x1676 outputs 11.8 / 14.5 / 15.6, 2x5 on 2910x100 6.0 / 7.2 / 8.5, 10x1 on 1529x800
-// 10.4 / 12.6 / 13.5.  Wide filters on about a workgroup a CU, or up to two with many taps, are the exception, as a row's windows
-// are built once instead of per filter row (300x400 inputs: 15x15 16.6 / 14.4 / 21.0, 9x9 9.9 / 9.1 / 10.9; outputs 109x3025 6x8
-// 9.6 / 8.1, 257x1857 14x14 19.3 / 17.1, but 822x416 6x6 9.3 / 8.8 and 1024x518 10x7 12.5 / 11.9 are left to the tiles: smaller
-// filters and more tiles lose as often).  Above: 8192^2 inputs 7x7 126 / 92 / 85, 11x11 165 / 125 / 117, 15x15 303 / 167 / 179,
-// 13x4 198 / 118 / 108, 2x15 78 / 73 / 78.
-// Three rows read fewer halo rows and need images large enough to fill the chip with fewer wavefronts, and not too many taps
-// (4 M to 20 M outputs, 2 rows / 3 rows: up to 11 columns 1.01 to 1.07, 10 and 11 among them although up to nine scalar
-// registers of taps spill; 12 columns and more 0.9 to 1.0).  Of 2250 random shapes 29 are slower by 3 % or more than with tiles
-// alone, most of them within the noise of two runs; with a line at 0.4 M outputs and four columns it was 419, by up to 18 %.
+// Output rows of a wavefront, filters with a block form aside.  One row reads the most halo rows and gives the most wavefronts and
+// the shortest, which decides while they do not fill the chip; 250 random shapes, two rows / one row by wavefronts of one row: filters of
+// more than 60 taps up to 2000 1.27 to 1.30, 2000 to 3000 1.21, 3000 to 4096 1.06, above 5000 0.92 to 1.02; 25 to 60 taps 1.24, 1.17, 1.0,
+// 0.88; fewer 1.10, 1.03, 0.93.  So filters of up to kFewTaps taps (0) take one row up to 3000 wavefronts, the others (2) up to one round of
+// the chip, and single-row filters, whose rows share nothing, always (1x14 on 3964x2242 inputs 10.1 / 7.6 us).  Three rows need images large
+// enough to fill the chip with fewer wavefronts and few enough columns that their taps stay in scalar registers (2 rows / 3
+// rows from 2 M outputs on: 8x8 on 892x2450 outputs 14.6 / 12.8 us, 7x7 on 2447^2 29.7 / 27.5).
+// LDS tiles shared by four wavefronts, which smaller images used to take, are slower than two rows on 399 of 400 random shapes
+// (1.37 times on average; with their loads in flight together too).
+constexpr int kOneRowFew = 3000, kOneRow = 4096, kFewTaps = 40;
 int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw)
 {
-    const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
-    const long long tiles = (((long long)oh + kTileOutRows - 1) / kTileOutRows) * (((long long)ow + cols - 1) / cols);
-    const int tiles_a_cu = kLdsPerCu / ((2 * (kTileOutRows - 1) + kh) * kCols * (int)sizeof(float));
-    const double few = 2.4 * kh * kw;                                      // tiles
-    const bool heavy = kw >= 6 && kh * kw >= 42 && (tiles <= kCus || (tiles <= 2 * kCus && (double)tiles <= few));
-    if (tiles <= (long long)kCus * tiles_a_cu && !heavy) return 0;
-    return kw > 1 && kw <= 11 && (double)oh * ow >= 4e6 ? 3 : 2;
+    if (kw > 1 && kw <= 11 && (double)oh * ow >= 2e6) return 3;
+    return kh * kw <= kFewTaps ? 0 : 2;
 }
 
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                      float* y, size_t yp, hipStream_t s)
 {
-    // Square filters up to 5x5 run the block form, two output rows per wavefront (8192^2, 5x5: 62 us against 75 - 82 us
-    // for the strips, 88 us for the LDS tiles and 56 us for a copy of the same bytes; 1, 3 and 4 rows, before the exchange of
-    // the loads took two rows from 68 to 62 us: 83, 68, 74).
-    if (kh == kw) {
+    // Square filters up to 5x5 run the block form, two output rows per wavefront (8192^2, 5x5: 62 us against 70 us for the strips and
+    // 56 us for a copy of the same bytes; 150 random shapes: strips of one / two / three rows are 1 to 3 % ahead below 0.3 M outputs in
+    // places, 6 to 20 % behind above).
+    if (kh == kw && w >= 4) {                                              // (it loads whole quads)
         switch (kh) {
         case 2: return launch_block<2, 2, 2>(x, h, w, xp, f, y, yp, s);
         case 3: return launch_block<3, 3, 2>(x, h, w, xp, f, y, yp, s);
@@ -484,13 +353,19 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         default: break;
         }
     }
-    switch (conv2d_stride2_strip_rows((h - kh) / 2 + 1, (w - kw) / 2 + 1, kh, kw)) {
-    case 0: return launch_tiles<kTileRpw>(x, h, w, xp, f, kh, kw, y, yp, s);
-    case 3:
-        return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    const int oh = (h - kh) / 2 + 1, ow = (w - kw) / 2 + 1;
+    int rows = conv2d_stride2_strip_rows(oh, ow, kh, kw);
+    if (rows != 3) {
+        const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
+        const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
+        rows = kh == 1 || wavefronts <= (rows == 0 ? kOneRowFew : kOneRow) ? 1 : 2;
+    }
+    using Widths = std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>;
+    switch (rows) {
+    case 1: return launch_strip_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    case 2: return launch_strip_by_kw<2>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
     default:
-        return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>{}, x, h, w, xp, f,
-                                     kh, kw, y, yp, s);
+        return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
     }
 }
 

@@ -93,6 +93,21 @@ __device__ __forceinline__ void load4_guarded(const float* __restrict__ row, lon
     }
 }
 
+// Columns [col, col+4) of the rows of an image of w >= 4 columns, for lanes that may reach past the right edge: the last
+// four columns are loaded instead and put right where they are used.  No branch, so the loads of many rows are in flight
+// together, where load4_guarded makes a wavefront whose lanes straddle the edge wait row by row.  What lies past the edge
+// holds other columns of the row: the 2-D kernels feed it only to outputs that are not stored.
+struct EdgeQuad {
+    int at;
+    bool by1, by2;
+    __device__ __forceinline__ EdgeQuad(int col, int w) : at(min(col, w - 4)), by1((col - at) & 1), by2((col - at) & 2) {}
+    __device__ __forceinline__ void put_right(float& a, float& b, float& c, float d) const
+    {
+        a = by1 ? b : a; b = by1 ? c : b; c = by1 ? d : c;
+        a = by2 ? c : a; b = by2 ? d : b;
+    }
+};
+
 // Store elements [idx, idx+4) of a row of `len` floats, clipped at the end.
 template <bool NT = (SYSCONV_NONTEMPORAL_STORE != 0)>
 __device__ __forceinline__ void store4_guarded(float* __restrict__ row, long long idx, long long len,

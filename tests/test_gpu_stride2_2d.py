@@ -165,3 +165,27 @@ def test_stride2_2d_2x2_right_hand_strip(w):
     """The last strip of 2x2 filters, which loads its lanes straight where it is more than half full (504 input columns a strip)."""
     x, f = W.random_case(w, (41, w), (2, 2), x_range=(0.0, 1.0))
     assert err(run(x, f), x, f) <= TOL
+
+
+# One-row and two-row wavefronts on either side of both lines (3000 and 4096 wavefronts of one row; strips of 248 to 252 outputs), the
+# single-row filter, and right-hand strips that end inside a lane's quad, with one whole strip and without.
+@pytest.mark.parametrize("kh,kw,oh,ow", [(4, 6, 2900, 200), (4, 6, 3100, 200), (9, 9, 4090, 130), (9, 9, 4102, 130), (1, 7, 5000, 90), (2, 1, 1501, 505),
+                                         (12, 12, 40, 253), (3, 5, 77, 250), (6, 6, 33, 1)])
+@pytest.mark.parametrize("extra", [0, 1])                       # an odd and an even number of columns
+def test_stride2_2d_rows_of_a_wavefront_and_right_edge(kh, kw, oh, ow, extra):
+    h, w = 2 * (oh - 1) + kh, 2 * (ow - 1) + kw + extra
+    x, f = W.random_case(kh * 100 + kw + extra, (h, w), (kh, kw), x_range=(0.0, 1.0))
+    big = torch.full((h, w + 9), float("nan"), dtype=torch.float32, device="cuda")     # a region of a wider image of NaN
+    big[:, :w] = dev(x)
+    y = B.sys_conv2d_strided(big[:, :w], f, 2)
+    torch.cuda.synchronize()
+    assert err(y.cpu().numpy(), x, f) <= TOL
+
+
+@pytest.mark.parametrize("kh,kw,w", [(2, 1, 1), (5, 1, 2), (2, 2, 2), (2, 2, 3), (7, 2, 3), (3, 3, 3), (15, 3, 3)])
+@pytest.mark.parametrize("h", [20, 9001])
+def test_stride2_2d_images_of_fewer_than_four_columns(kh, kw, w, h):
+    x, f = W.random_case(kh * 10 + kw, (h, w), (kh, kw), x_range=(0.0, 1.0))
+    y = B.sys_conv2d_strided(dev(x), f, 2)
+    torch.cuda.synchronize()
+    assert err(y.cpu().numpy(), x, f) <= TOL
