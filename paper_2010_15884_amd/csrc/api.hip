@@ -187,11 +187,14 @@ int sys_conv2d(const float* d_x, int h, int w, size_t x_pitch, const float* h_f,
     // 4092^2 25.9 / 28.7 / 27.1, 4604^2 33.9 / 36.4 / 32.5, 5996^2 57.2 / 57.0 / 51.1, 7164^2 81.0 / 83.6 / 75.1,
     // 8188^2 103 / 104 / 95.5, 10236^2 166 / 170 / 155.  Up to 6x6 the FBS tile kernels win by 3 - 17 % except where
     // the input pitch is a power of two of at most 16 KB (1024, 2048, 4096 columns): there single-strip order and the
-    // BFS block kernel's 1 KB-aligned strips win by 4 - 12 %.  7x7: SBM by 2 - 12 %.  8x8 .. 11x11: SBM.  The rest: FBS.
+    // BFS block kernel's 1 KB-aligned strips win by 4 - 12 %.  7x7: SBM by 2 - 12 % on large images and power-of-two
+    // pitches, FBS on others up to 3 M outputs (SBM / FBS: 345x390 5.8 / 4.8, 1494^2 9.05 / 8.67, 1704^2 9.64 / 9.19; but 2613^2 16.4 / 17.1,
+    // 2048^2 12.4 / 13.3).  8x8 .. 11x11: SBM.  The rest: FBS.
     if (proj == SYS_PROJ_AUTO) {
         const size_t pitch_bytes = x_pitch * sizeof(float);
         const bool short_pow2_pitch = (pitch_bytes & (pitch_bytes - 1)) == 0 && pitch_bytes <= 16384;
         if (kh == kw && kh >= 2 && kh <= 6) proj = short_pow2_pitch ? SYS_PROJ_BFS : SYS_PROJ_FBS;
+        else if (kh == 7 && kw == 7 && !short_pow2_pitch && (double)oh * ow <= 3e6) proj = SYS_PROJ_FBS;
         else if (sysconv::has_conv2d_sbm(kh, kw) && kh >= 7) proj = SYS_PROJ_SBM;
         else proj = SYS_PROJ_FBS;
     }

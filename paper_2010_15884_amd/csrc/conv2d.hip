@@ -59,12 +59,31 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_kernel(const float* __restr
 
     // stage: wavefront v copies input rows v, v+4, ... of the tile (1 KB each, coalesced)
     const int in_rows = min(kFbsTileRows + kh - 1, h - row0);
-    for (int rr = wave; rr < in_rows; rr += kBlock / kWave) {
-        float v[4];
-        load4_guarded<false>(x + (long long)(row0 + rr) * xp, col0 + kTile * lane, w_img, v);
-        f4 t4;
-        t4.x = v[0]; t4.y = v[1]; t4.z = v[2]; t4.w = v[3];
-        *reinterpret_cast<f4*>(tile + rr * kStrip + kTile * lane) = t4;
+    constexpr int kWaves = kBlock / kWave, kBatch = 4;                     // rows of a wavefront in flight
+    if (w_img >= 4) {                                                      // uniform
+        const EdgeQuad quad(col0 + kTile * lane, w_img);
+        const bool edge = col0 + kStrip > w_img;                           // uniform
+#pragma nounroll
+        for (int r0 = wave; r0 < in_rows; r0 += kWaves * kBatch) {
+            f4u v[kBatch];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k)                               // past the last row: the last row again
+                v[k] = *reinterpret_cast<const f4u*>(x + (long long)(row0 + min(r0 + k * kWaves, in_rows - 1)) * xp + quad.at);
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                const int rr = r0 + k * kWaves;
+                if (rr >= in_rows) break;                                  // uniform
+                float t[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+                if (edge) quad.put_right(t[0], t[1], t[2], t[3]);
+                *reinterpret_cast<f4*>(tile + rr * kStrip + kTile * lane) = f4{t[0], t[1], t[2], t[3]};
+            }
+        }
+    } else {
+        for (int rr = wave; rr < in_rows; rr += kWaves) {
+            float v[4];
+            load4_guarded<false>(x + (long long)(row0 + rr) * xp, col0 + kTile * lane, w_img, v);
+            *reinterpret_cast<f4*>(tile + rr * kStrip + kTile * lane) = f4{v[0], v[1], v[2], v[3]};
+        }
     }
     __syncthreads();
 
@@ -154,10 +173,23 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_static_kernel(Taps2D taps, 
     const int last_row = h - 1 - row0;                                     // rows past the image repeat its last row
     constexpr int kPerWave = (kInRows + 3) / 4;
     float stage[kPerWave][4];
+    auto stage_row = [&](int k) { return x + (long long)(row0 + min(wave + 4 * k, last_row)) * xp; };
+    if (KW >= 4 || w_img >= 4) {                                           // uniform
+        const EdgeQuad quad(col0 + kTile * lane, w_img);
 #pragma unroll
-    for (int k = 0; k < kPerWave; ++k)
-        load4_guarded<false>(x + (long long)(row0 + min(wave + 4 * k, last_row)) * xp, col0 + kTile * lane, w_img,
-                             stage[k]);
+        for (int k = 0; k < kPerWave; ++k) {
+            const f4u t = *reinterpret_cast<const f4u*>(stage_row(k) + quad.at);
+            stage[k][0] = t.x; stage[k][1] = t.y; stage[k][2] = t.z; stage[k][3] = t.w;
+        }
+        if (col0 + kStrip > w_img) {                                       // uniform
+            asm volatile("");                                              // a branch, not selects in every strip
+#pragma unroll
+            for (int k = 0; k < kPerWave; ++k) quad.put_right(stage[k][0], stage[k][1], stage[k][2], stage[k][3]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPerWave; ++k) load4_guarded<false>(stage_row(k), col0 + kTile * lane, w_img, stage[k]);
+    }
 #pragma unroll
     for (int k = 0; k < kPerWave; ++k) {
         const int rr = wave + 4 * k;
@@ -226,7 +258,7 @@ __device__ __forceinline__ int opaque_zero()
 // flight ahead of the one being consumed (PD divides KH so that the slot of a
 // row in the prefetch ring is a compile-time constant of the unrolled loop).
 // EDGE = the strip reaches past the right edge of the image: only then are
-// loads and stores bounds-checked per lane.
+// loads clamped to the row (EdgeQuad; at least 8 columns here) and stores bounds-checked per lane.
 enum BfsMode { kBfsFirst, kBfsMiddle, kBfsLast, kBfsChecked };
 
 template <int KH, int KW, int PD, bool EDGE>
@@ -255,24 +287,17 @@ struct BfsStrip {
         if (last_lane) {
 #pragma unroll
             for (int j = 0; j < NH; ++j) {
-                if (EDGE) {
-                    load4_guarded<false>(p, col + 4 * (j + 1), w_img, h[j]);
-                } else {
-                    const f4u t = *reinterpret_cast<const f4u*>(p + col + 4 * (j + 1));
-                    h[j][0] = t.x; h[j][1] = t.y; h[j][2] = t.z; h[j][3] = t.w;
-                }
+                const int at = col + 4 * (j + 1);
+                const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? EdgeQuad(at, w_img).at : at));
+                h[j][0] = t.x; h[j][1] = t.y; h[j][2] = t.z; h[j][3] = t.w;
             }
         }
-        if (EDGE) {
-            load4_guarded<false>(p, col, w_img, v);
-        } else {
-            // plain (cacheable) loads: the KH-1 halo rows are read again by the wavefront
-            // working on the next row block and should then come from L2 / the memory-side
-            // cache, not from HBM (measured on 4096^2, 5x5: 33 us against 43 us with the
-            // non-temporal hint)
-            const f4u t = *reinterpret_cast<const f4u*>(p + col);
-            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-        }
+        // plain (cacheable) loads: the KH-1 halo rows are read again by the wavefront
+        // working on the next row block and should then come from L2 / the memory-side
+        // cache, not from HBM (measured on 4096^2, 5x5: 33 us against 43 us with the
+        // non-temporal hint)
+        const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? EdgeQuad(col, w_img).at : col));
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
 
     // KH consecutive input rows rho0 .. rho0+KH-1 (rho0 a multiple of KH, so every slot
@@ -298,6 +323,11 @@ struct BfsStrip {
             for (int j = 0; j < NH; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) hin[j][i] = halo[ph % PD][j][i];
+            if (EDGE) {
+                EdgeQuad(col, w_img).put_right(win[0], win[1], win[2], win[3]);
+#pragma unroll
+                for (int j = 0; j < NH; ++j) EdgeQuad(col + 4 * (j + 1), w_img).put_right(hin[j][0], hin[j][1], hin[j][2], hin[j][3]);
+            }
             load_row(rho + PD, ring[ph % PD], halo[ph % PD]);
             // X(c) <- X(c+1): lanes 0..62 take the value of the lane above, lane 63 takes
             // the next halo element
@@ -432,18 +462,22 @@ struct SbmStrip {
     __device__ __forceinline__ void load_row(int row, float (&v)[4]) const
     {
         const float* p = xrow + (long long)min(row, rows_in - 1) * xp;
-        if (EDGE) {
-            load4_guarded<false>(p, col, w_img, v);
-        } else {
-            const f4u t = *reinterpret_cast<const f4u*>(p + col);
-            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-        }
+        const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? EdgeQuad(col, w_img).at : col));
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    }
+
+    // a row that has been loaded, where it is first used
+    __device__ __forceinline__ void arrived(float (&v)[4]) const
+    {
+        if (EDGE) EdgeQuad(col, w_img).put_right(v[0], v[1], v[2], v[3]);
     }
 
     __device__ __forceinline__ void run(kernarg_floats taps_t)
     {
 #pragma unroll
         for (int d = 0; d < RS - 1; ++d) load_row(d, ring[d]);
+#pragma unroll
+        for (int d = 0; d < KH - 1; ++d) arrived(ring[d]);
 
         for (int r0 = 0; r0 < rows_out; r0 += RS) {
 #pragma unroll
@@ -452,6 +486,7 @@ struct SbmStrip {
                 if (r >= rows_out) break;
                 // the slot of row r-1 is free now: fetch row r+KH+PD-1 into it
                 load_row(r + RS - 1, ring[(ph + RS - 1) % RS]);
+                arrived(ring[(ph + KH - 1) % RS]);
 
                 float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -528,7 +563,7 @@ __global__ __launch_bounds__(kBlock) void conv2d_sbm_kernel(Taps2D taps_t, const
 // one memory latency per block, and the compiler's wait counts are exact.
 // The KW-1 halo columns right of the strip are the same for all lanes, so they
 // are fetched with uniform (scalar) loads and enter the array in lane 63.
-template <int KH, int KW, int ROWS, bool EDGE>
+template <int KH, int KW, int ROWS, StripKind KIND>
 __device__ __forceinline__ void bfs_block_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
                                                float* __restrict__ yrow, int col0, int lane, int w_img,
                                                long long xp, int ow, long long yp, int rows_out)
@@ -537,6 +572,8 @@ __device__ __forceinline__ void bfs_block_rows(kernarg_floats taps_f, const floa
     constexpr int NH = (KW + 2) / 4;                                       // halo float4s
     const int col = col0 + kTile * lane;
     const int rows_in = rows_out + KH - 1;
+    constexpr bool EDGE = KIND != kInside;
+    const EdgeQuad quad(col, w_img);
 
     float v[NIN][4];
     float h[NIN][NH][4];
@@ -545,24 +582,28 @@ __device__ __forceinline__ void bfs_block_rows(kernarg_floats taps_f, const floa
         // rows past the end of the block repeat its last row; they only feed output rows
         // that are not stored
         const float* p = xrow + (long long)min(rho, rows_in - 1) * xp;
-        if (EDGE) {
+        if constexpr (KIND == kNarrow) {
             load4_guarded<false>(p, col, w_img, v[rho]);
-#pragma unroll
-            for (int j = 0; j < NH; ++j) load4_guarded<false>(p, col0 + kStrip + 4 * j, w_img, h[rho][j]);
         } else {
-            const f4u t = *reinterpret_cast<const f4u*>(p + col);
+            const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? quad.at : col));
             v[rho][0] = t.x; v[rho][1] = t.y; v[rho][2] = t.z; v[rho][3] = t.w;
-            const float* hp = p + col0 + kStrip;                           // wave-uniform address
+        }
+        const float* hp = p + col0 + kStrip;                               // wave-uniform address
 #pragma unroll
-            for (int j = 0; j < NH; ++j)
+        for (int j = 0; j < NH; ++j) {
+            if constexpr (EDGE) {
+                load4_guarded<false>(p, col0 + kStrip + 4 * j, w_img, h[rho][j]);
+            } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) h[rho][j][i] = hp[4 * j + i];
+            }
         }
     }
 
     float acc[ROWS][4];
 #pragma unroll
     for (int rho = 0; rho < NIN; ++rho) {
+        if constexpr (KIND == kEdge) quad.put_right(v[rho][0], v[rho][1], v[rho][2], v[rho][3]);
         float win[KW + 3];
 #pragma unroll
         for (int i = 0; i < 4; ++i) win[i] = v[rho][i];
@@ -620,9 +661,11 @@ __global__ __launch_bounds__(kBlock) void conv2d_bfs_block_kernel(Taps2D taps, c
     float* yrow = y + (long long)r0 * yp;
     constexpr int halo_cols = kTile * ((KW + 2) / 4);
     if (col0 + kStrip + halo_cols <= w_img)
-        bfs_block_rows<KH, KW, ROWS, false>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
+        bfs_block_rows<KH, KW, ROWS, kInside>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
+    else if (w_img >= 4 && (w_img & 3) != 0)                               // (whole quads up to the edge: nobody waits, 4096^2 5x5 24.0 / 24.9 us)
+        bfs_block_rows<KH, KW, ROWS, kEdge>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
     else
-        bfs_block_rows<KH, KW, ROWS, true>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
+        bfs_block_rows<KH, KW, ROWS, kNarrow>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
 }
 
 // ----------------------------------------------------- SBM 2-D, block form ---
@@ -630,7 +673,7 @@ __global__ __launch_bounds__(kBlock) void conv2d_bfs_block_kernel(Taps2D taps, c
 // bfs_block_rows: the ROWS+KH-1 input rows of a block of ROWS output rows are all
 // requested up front and the output rows are then computed one after the other in
 // straight-line code.  Taps arrive transposed (filter column q contiguous).
-template <int KH, int KW, int ROWS, bool EDGE>
+template <int KH, int KW, int ROWS, StripKind KIND>
 __device__ __forceinline__ void sbm_block_rows(kernarg_floats taps_t, const float* __restrict__ xrow,
                                                float* __restrict__ yrow, int col, int w_img, long long xp, int ow,
                                                long long yp, int rows_out, bool lane_valid)
@@ -638,6 +681,8 @@ __device__ __forceinline__ void sbm_block_rows(kernarg_floats taps_t, const floa
     constexpr int NIN = ROWS + KH - 1;
     constexpr bool kReloadTaps = KH * KW > 25;
     const int rows_in = rows_out + KH - 1;
+    constexpr bool EDGE = KIND != kInside;
+    const EdgeQuad quad(col, w_img);
 
     float v[NIN][4];
 #pragma unroll
@@ -645,16 +690,20 @@ __device__ __forceinline__ void sbm_block_rows(kernarg_floats taps_t, const floa
         // rows past the end of the block repeat its last row; they only feed output rows
         // that are not stored
         const float* p = xrow + (long long)min(rho, rows_in - 1) * xp;
-        if (EDGE) {
+        if constexpr (KIND == kNarrow) {
             load4_guarded<false>(p, col, w_img, v[rho]);
         } else {
-            const f4u t = *reinterpret_cast<const f4u*>(p + col);
+            const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? quad.at : col));
             v[rho][0] = t.x; v[rho][1] = t.y; v[rho][2] = t.z; v[rho][3] = t.w;
         }
     }
 
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
+        if constexpr (KIND == kEdge) {                                     // rows that this output row is the first to use
+#pragma unroll
+            for (int rho = r == 0 ? 0 : r + KH - 1; rho < r + KH; ++rho) quad.put_right(v[rho][0], v[rho][1], v[rho][2], v[rho][3]);
+        }
         float z[4];
 #pragma unroll
         for (int q = 0; q < KW; ++q) {
@@ -710,10 +759,13 @@ __global__ __launch_bounds__(kBlock) void conv2d_sbm_block_kernel(Taps2D taps_t,
     const float* xrow = x + (long long)r0 * xp;
     float* yrow = y + (long long)r0 * yp;
     const bool lane_valid = lane < valid_lanes;
+    const int col = col0 + kTile * lane;
     if (col0 + kStrip <= w_img)
-        sbm_block_rows<KH, KW, ROWS, false>(tf, xrow, yrow, col0 + kTile * lane, w_img, xp, ow, yp, rows_out, lane_valid);
-    else
-        sbm_block_rows<KH, KW, ROWS, true>(tf, xrow, yrow, col0 + kTile * lane, w_img, xp, ow, yp, rows_out, lane_valid);
+        sbm_block_rows<KH, KW, ROWS, kInside>(tf, xrow, yrow, col, w_img, xp, ow, yp, rows_out, lane_valid);
+    else if (KW >= 4 || w_img >= 4)
+        sbm_block_rows<KH, KW, ROWS, kEdge>(tf, xrow, yrow, col, w_img, xp, ow, yp, rows_out, lane_valid);
+    else if constexpr (KW < 4)
+        sbm_block_rows<KH, KW, ROWS, kNarrow>(tf, xrow, yrow, col, w_img, xp, ow, yp, rows_out, lane_valid);
 }
 
 // Lanes of an SBM strip that keep their results: 64 - halo_lanes(kw).  (Rounding the

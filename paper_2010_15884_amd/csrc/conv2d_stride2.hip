@@ -182,7 +182,6 @@ hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f,
 // 22.6 / 16.4).  Six or eight rows in flight are 1 to 5 % and 6 to 10 % slower than four.
 constexpr int kAhead = 4;
 
-enum StripKind { kInside, kEdge, kNarrow };              // all 512 columns exist; not all do; fewer than four do
 template <int KW, int ROWS, StripKind KIND>
 __device__ __forceinline__ void stride2_strip_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
                                                    float* __restrict__ yrow, int in_col, int out_col, int w_img,
