@@ -18,6 +18,14 @@ namespace {
 #endif
 constexpr int kGroups = SYSCONV_1D_GROUPS;     // register groups per wavefront (R)
 
+// The argument block of FBS and SBM: as long as the taps, in whole blocks of four and one more, where their count is known at
+// compile time (KT > 0).
+template <int KT>
+struct TapsFor {
+    static constexpr int kLen = KT ? (KT + 7) / 4 * 4 : kTaps1DLen;
+    float w[kLen];
+};
+
 // ---------------------------------------------------------------- FBS ------
 // Table 2, row 3 left: PE = c, time = q.  Partial sums and weights never move;
 // the inputs travel one PE towards lower c per step.  KT > 0 fixes the tap
@@ -45,7 +53,7 @@ __device__ __forceinline__ void fbs_groups_last(int nt, float (&e)[kGroups][4], 
 template <int KT, bool NT>
 __global__ __launch_bounds__(kBlock) void conv1d_fbs_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                             long long n, long long m, int k_rt, int valid_lanes,
-                                                            Taps1D taps)
+                                                            TapsFor<KT> taps)
 {
     const int k = KT ? KT : k_rt;
     const int lane = threadIdx.x & (kWave - 1);
@@ -152,7 +160,7 @@ __device__ __forceinline__ void sbm_readout_pe(float (&z)[kGroups][4])
 template <int KT>
 __global__ __launch_bounds__(kBlock) void conv1d_sbm_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                             long long n, long long m, int k_rt, int valid_lanes,
-                                                            Taps1D taps)
+                                                            TapsFor<KT> taps)
 {
     const int k = KT ? KT : k_rt;
     const int lane = threadIdx.x & (kWave - 1);
@@ -378,8 +386,8 @@ constexpr size_t kCachedFrom = 14u << 20, kCachedTo = 34u << 20;
 template <int KT, bool SBM>
 hipError_t launch_1d(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
 {
-    Taps1D taps;
-    for (int q = 0; q < kTaps1DLen; ++q) taps.w[q] = q < k ? w[q] : 0.0f;
+    TapsFor<KT> taps;
+    for (int q = 0; q < TapsFor<KT>::kLen; ++q) taps.w[q] = q < k ? w[q] : 0.0f;
     const long long m = (long long)n - k + 1;
     const int valid_lanes = group_valid_lanes(k);
     const long long per_wave = (long long)kGroups * kTile * valid_lanes;

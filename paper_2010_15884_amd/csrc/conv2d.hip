@@ -148,7 +148,7 @@ __host__ __device__ constexpr int fbs_static_valid_lanes(int kh, int kw)
 }
 
 template <int KH, int KW, int RPW>
-__global__ __launch_bounds__(kBlock) void conv2d_fbs_static_kernel(Taps2D taps, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_fbs_static_kernel(TapsOf<KH * KW> taps, const float* __restrict__ x,
                                                                    float* __restrict__ y, int h, int w_img,
                                                                    long long xp, int oh, int ow, long long yp,
                                                                    int tiles_y, int n_tiles, int side, int per_xcd)
@@ -405,7 +405,7 @@ struct BfsStrip {
 // run-time-indexed taps on the scalar load path (indexing the by-value struct
 // itself can make the compiler copy it to scratch).
 template <int KH, int KW, int PD>
-__global__ __launch_bounds__(kBlock) void conv2d_bfs_kernel(Taps2D taps, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_bfs_kernel(TapsOf<KH * KW> taps, const float* __restrict__ x,
                                                             float* __restrict__ y, int w_img, long long xp, int oh,
                                                             int ow, long long yp, int rows, int row_blocks,
                                                             int strips, int side, int per_xcd, int valid_lanes)
@@ -526,7 +526,7 @@ struct SbmStrip {
 };
 
 template <int KH, int KW, int PD>
-__global__ __launch_bounds__(kBlock) void conv2d_sbm_kernel(Taps2D taps_t, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_sbm_kernel(TapsOf<KH * KW> taps_t, const float* __restrict__ x,
                                                             float* __restrict__ y, int w_img, long long xp, int oh,
                                                             int ow, long long yp, int rows, int row_blocks,
                                                             int strips, int side, int per_xcd, int valid_lanes)
@@ -640,7 +640,7 @@ __device__ __forceinline__ void bfs_block_rows(kernarg_floats taps_f, const floa
 }
 
 template <int KH, int KW, int ROWS>
-__global__ __launch_bounds__(kBlock) void conv2d_bfs_block_kernel(Taps2D taps, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_bfs_block_kernel(TapsOf<KH * KW> taps, const float* __restrict__ x,
                                                                   float* __restrict__ y, int w_img, long long xp,
                                                                   int oh, int ow, long long yp, int row_blocks,
                                                                   int strips, int side, int per_xcd, int wide)
@@ -743,7 +743,7 @@ __device__ __forceinline__ void sbm_block_rows(kernarg_floats taps_t, const floa
 }
 
 template <int KH, int KW, int ROWS>
-__global__ __launch_bounds__(kBlock) void conv2d_sbm_block_kernel(Taps2D taps_t, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_sbm_block_kernel(TapsOf<KH * KW> taps_t, const float* __restrict__ x,
                                                                   float* __restrict__ y, int w_img, long long xp,
                                                                   int oh, int ow, long long yp, int row_blocks,
                                                                   int strips, int side, int per_xcd, int valid_lanes)
@@ -783,11 +783,10 @@ template <int KH, int KW, int PD, bool SBM>
 hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f, float* y, size_t yp, hipStream_t s)
 {
     // BFS reads its taps row by row, SBM column by column (transposed)
-    Taps2D taps;
     float ft[KH * KW];
     for (int p = 0; p < KH; ++p)
         for (int q = 0; q < KW; ++q) ft[SBM ? q * KH + p : p * KW + q] = f[p * KW + q];
-    fill_taps(taps, ft, KH * KW);
+    const TapsOf<KH * KW> taps(ft, KH * KW);
     const int oh = h - KH + 1, ow = w - KW + 1;
     // SBM strips overlap (the partial sums of the first KW-1 PEs come from the strip to
     // the left, so those lanes are redundant); BFS strips are exactly 256 outputs wide and
@@ -856,8 +855,7 @@ hipError_t launch_fbs_static(const float* x, int h, int w, size_t xp, const floa
                              hipStream_t s)
 {
     constexpr int tile_rows = RPW * (kBlock / kWave);
-    Taps2D taps;
-    fill_taps(taps, f, KH * KW);
+    const TapsOf<KH * KW> taps(f, KH * KW);
     const int oh = h - KH + 1, ow = w - KW + 1;
     const int cols = kTile * fbs_static_valid_lanes(KH, KW);
     const int tiles_x = (ow + cols - 1) / cols;
@@ -952,8 +950,7 @@ template <int KH, int KW, int ROWS>
 hipError_t launch_bfs_block(const float* x, int h, int w, size_t xp, const float* f, float* y, size_t yp,
                             hipStream_t s)
 {
-    Taps2D taps;
-    fill_taps(taps, f, KH * KW);
+    const TapsOf<KH * KW> taps(f, KH * KW);
     const int oh = h - KH + 1, ow = w - KW + 1;
     const int strips = (ow + kStrip - 1) / kStrip;
     const int row_blocks = (oh + ROWS - 1) / ROWS;
@@ -972,11 +969,10 @@ template <int KH, int KW, int ROWS>
 hipError_t launch_sbm_block(const float* x, int h, int w, size_t xp, const float* f, float* y, size_t yp,
                             hipStream_t s)
 {
-    Taps2D taps;
     float ft[KH * KW];
     for (int p = 0; p < KH; ++p)
         for (int q = 0; q < KW; ++q) ft[q * KH + p] = f[p * KW + q];      // filter column q contiguous
-    fill_taps(taps, ft, KH * KW);
+    const TapsOf<KH * KW> taps(ft, KH * KW);
     const int oh = h - KH + 1, ow = w - KW + 1;
     const int valid_lanes = strip_valid_lanes(KW);
     const int strips = (ow + kTile * valid_lanes - 1) / (kTile * valid_lanes);

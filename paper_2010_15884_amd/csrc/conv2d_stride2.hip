@@ -118,7 +118,7 @@ __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const 
 
 // The taps (row-major, as the caller gave them) are the first kernel argument.
 template <int KH, int KW, int ROWS>
-__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D taps, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(TapsOf<KH * KW> taps, const float* __restrict__ x,
                                                                           float* __restrict__ y, int w_img,
                                                                           long long xp, int oh, int ow, long long yp,
                                                                           int row_blocks, int strips, int side,
@@ -157,8 +157,7 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(Taps2D
 template <int KH, int KW, int ROWS>
 hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f, float* y, size_t yp, hipStream_t s)
 {
-    Taps2D taps;
-    for (int i = 0; i < kTaps2DLen; ++i) taps.f[i] = i < KH * KW ? f[i] : 0.0f;
+    const TapsOf<KH * KW> taps(f, KH * KW);
     const int oh = (h - KH) / 2 + 1, ow = (w - KW) / 2 + 1;
     const int cols = kTile * (kWave - halo_lanes((KW + 1) / 2));
     const int strips = (ow + cols - 1) / cols;
@@ -259,7 +258,7 @@ __device__ __forceinline__ void stride2_strip_rows(kernarg_floats taps_f, const 
 }
 
 template <int KW, int ROWS>
-__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_strip_kernel(Taps2D taps, const float* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_strip_kernel(TapsOf<kMaxK2D * KW> taps, const float* __restrict__ x,
                                                                           float* __restrict__ y, int w_img,
                                                                           long long xp, int oh, int ow, long long yp,
                                                                           int kh, int row_blocks, int strips, int side,
@@ -294,8 +293,7 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_strip_kernel(Taps2D
 template <int KW, int ROWS>
 hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f, int kh, float* y, size_t yp, hipStream_t s)
 {
-    Taps2D taps;
-    for (int i = 0; i < kTaps2DLen; ++i) taps.f[i] = i < kh * KW ? f[i] : 0.0f;
+    const TapsOf<kMaxK2D * KW> taps(f, kh * KW);
     const int oh = (h - kh) / 2 + 1, ow = (w - KW) / 2 + 1;
     const int cols = kTile * (kWave - halo_lanes((KW + 1) / 2));
     const int strips = (ow + cols - 1) / cols;
