@@ -30,6 +30,7 @@ EXPORTS = ["sys_conv1d", "sys_conv1d_strided", "sys_conv2d", "sys_conv1d_has", "
            "sys_projection_name", "sys_last_hip_error", "sys_version"]
 
 _lib = None
+_calls = None          # the convolution entry points, taps passed as bytes (_entry_points)
 
 
 class SttDesign(ctypes.Structure):
@@ -117,6 +118,34 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _EntryPoints:
+    """The convolutions as the wrappers below call them: the taps go in as a bytes object, whose buffer ctypes passes on as it is
+    (the library copies them before it returns), which costs a tenth of making a ctypes pointer to an array."""
+
+    def __init__(self):
+        import torch
+        lib()
+        own = ctypes.CDLL(LIB_PATH)            # function objects of its own, so that lib()'s keep their argument types
+        vp, taps, sz, ci = ctypes.c_void_p, ctypes.c_char_p, ctypes.c_size_t, ctypes.c_int
+        for name, types in (("sys_conv1d", [vp, sz, taps, ci, vp, ci, vp]),
+                            ("sys_conv1d_strided", [vp, sz, taps, ci, ci, vp, ci, vp]),
+                            ("sys_conv2d", [vp, ci, ci, sz, taps, ci, ci, vp, sz, ci, vp]),
+                            ("sys_conv2d_strided", [vp, ci, ci, sz, taps, ci, ci, ci, vp, sz, ci, vp])):
+            f = getattr(own, name)
+            f.argtypes, f.restype = types, ci
+            setattr(self, name, f)
+        self.Tensor, self.float32, self.empty = torch.Tensor, torch.float32, torch.empty
+        # torch's short ways to the current device and stream, when it has them
+        self.device, self.stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _entry_points() -> _EntryPoints:
+    global _calls
+    if _calls is None:
+        _calls = _EntryPoints()
+    return _calls
+
+
 def status_string(status: int) -> str:
     return lib().sys_status_string(int(status)).decode()
 
@@ -140,23 +169,24 @@ def _proj(projection) -> int:
 
 
 def _taps(w) -> np.ndarray:
-    return np.ascontiguousarray(np.asarray(w, dtype=np.float32))
+    w = np.asarray(w, dtype=np.float32)            # any strides: tobytes() packs them
+    return w if w.ndim else w.reshape(1)
 
 
 def _stream_handle(stream) -> Optional[int]:
     """The hipStream_t to launch on: the caller's, else torch's current stream."""
     if stream is not None:
         return int(stream)
+    c = _entry_points()
+    if c.stream is not None and c.device is not None:
+        return c.stream(c.device())                # (the caller's tensor is on a device, so CUDA is initialised)
     import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # the short way, when this torch has it
-    if raw is not None:
-        return raw(torch.cuda.current_device())
     return torch.cuda.current_stream().cuda_stream
 
 
 def _device_f32(t, what):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.float32:
+    c = _calls or _entry_points()
+    if not isinstance(t, c.Tensor) or not t.is_cuda or t.dtype != c.float32:
         raise TypeError(f"{what} must be a float32 CUDA tensor")
     return t
 
@@ -168,37 +198,43 @@ def _room_1d(d_y, m):
         raise ValueError(f"d_y must be a contiguous 1-D tensor with room for {m} outputs")
 
 
-def sys_conv1d(d_x, h_w, d_y=None, projection="AUTO", stream=None):
-    """y[c] = sum_q x[c+q] w[q].  d_x: 1-D float32 CUDA tensor; h_w: host taps.
-    Returns d_y (allocated with torch if not given)."""
-    import torch
+def _signal(d_x):
     _device_f32(d_x, "d_x")
     if d_x.dim() != 1 or not d_x.is_contiguous():
         raise ValueError("d_x must be a contiguous 1-D tensor")
+
+
+def sys_conv1d(d_x, h_w, d_y=None, projection="AUTO", stream=None):
+    """y[c] = sum_q x[c+q] w[q].  d_x: 1-D float32 CUDA tensor; h_w: host taps.
+    Returns d_y (allocated with torch if not given)."""
+    c = _calls or _entry_points()
+    _signal(d_x)
     w = _taps(h_w)
     n, k = d_x.shape[0], w.shape[0]
+    m = n - k + 1 if n >= k else 0
     if d_y is None:
-        d_y = torch.empty(max(n - k + 1, 0), dtype=torch.float32, device=d_x.device)
-    _room_1d(d_y, max(n - k + 1, 0))
-    _check(lib().sys_conv1d(d_x.data_ptr(), n, w.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), k,
-                            d_y.data_ptr(), _proj(projection), _stream_handle(stream)))
+        d_y = c.empty(m, dtype=c.float32, device=d_x.device)
+    _room_1d(d_y, m)
+    status = c.sys_conv1d(d_x.data_ptr(), n, w.tobytes(), k, d_y.data_ptr(), _proj(projection), _stream_handle(stream))
+    if status:
+        _check(status)
     return d_y
 
 
 def sys_conv1d_strided(d_x, h_w, stride, d_y=None, projection="AUTO", stream=None):
     """y[c] = sum_q x[stride*c+q] w[q], (n-k)//stride + 1 outputs.  Arguments as sys_conv1d."""
-    import torch
-    _device_f32(d_x, "d_x")
-    if d_x.dim() != 1 or not d_x.is_contiguous():
-        raise ValueError("d_x must be a contiguous 1-D tensor")
+    c = _calls or _entry_points()
+    _signal(d_x)
     w = _taps(h_w)
     n, k, stride = d_x.shape[0], w.shape[0], int(stride)
     m = (n - k) // stride + 1 if (stride >= 1 and n >= k) else 0
     if d_y is None:
-        d_y = torch.empty(m, dtype=torch.float32, device=d_x.device)
+        d_y = c.empty(m, dtype=c.float32, device=d_x.device)
     _room_1d(d_y, m)
-    _check(lib().sys_conv1d_strided(d_x.data_ptr(), n, w.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), k, stride,
-                                    d_y.data_ptr(), _proj(projection), _stream_handle(stream)))
+    status = c.sys_conv1d_strided(d_x.data_ptr(), n, w.tobytes(), k, stride, d_y.data_ptr(), _proj(projection),
+                                  _stream_handle(stream))
+    if status:
+        _check(status)
     return d_y
 
 
@@ -213,7 +249,7 @@ def sys_conv1d_stt(d_x, h_w, design: SttDesign, d_y=None, stream=None):
     _device_f32(d_x, "d_x")
     if d_x.dim() != 1 or not d_x.is_contiguous():
         raise ValueError("d_x must be a contiguous 1-D tensor")
-    w = _taps(h_w)
+    w = np.ascontiguousarray(_taps(h_w))
     n, k = d_x.shape[0], w.shape[0]
     if d_y is None:
         d_y = torch.empty(max(n - k + 1, 0), dtype=torch.float32, device=d_x.device)
@@ -223,55 +259,60 @@ def sys_conv1d_stt(d_x, h_w, design: SttDesign, d_y=None, stream=None):
     return d_y
 
 
-def sys_conv2d(d_x, h_f, d_y=None, projection="AUTO", stream=None):
-    """y[r][c] = sum_p sum_q x[r+p][c+q] f[p][q].  d_x: 2-D float32 CUDA tensor whose
-    rows are contiguous (stride(1) == 1; stride(0) is the pitch); h_f: host kh x kw taps."""
-    import torch
+def _image_and_taps(d_x, h_f):
+    """The taps as an array, after the checks that both 2-D calls make."""
     _device_f32(d_x, "d_x")
     if d_x.dim() != 2 or d_x.stride(1) != 1:
         raise ValueError("d_x must be 2-D with unit column stride")
     f = _taps(h_f)
     if f.ndim != 2:
         raise ValueError("h_f must be 2-D")
-    h, w = d_x.shape
-    kh, kw = f.shape
-    if d_y is None:
-        d_y = torch.empty((max(h - kh + 1, 0), max(w - kw + 1, 0)), dtype=torch.float32, device=d_x.device)
+    return f
+
+
+def _room_2d(d_y, oh, ow):
     _device_f32(d_y, "d_y")
     if d_y.dim() != 2 or d_y.stride(1) != 1:
         raise ValueError("d_y must be 2-D with unit column stride")
-    if d_y.shape[0] < max(h - kh + 1, 0) or d_y.shape[1] < max(w - kw + 1, 0):
-        raise ValueError(f"d_y must have room for {h - kh + 1} x {w - kw + 1} outputs")
-    _check(lib().sys_conv2d(d_x.data_ptr(), h, w, d_x.stride(0),
-                            f.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), kh, kw,
-                            d_y.data_ptr(), d_y.stride(0), _proj(projection), _stream_handle(stream)))
+    have_h, have_w = d_y.shape
+    if have_h < oh or have_w < ow:
+        raise ValueError(f"d_y must have room for {oh} x {ow} outputs")
+
+
+def sys_conv2d(d_x, h_f, d_y=None, projection="AUTO", stream=None):
+    """y[r][c] = sum_p sum_q x[r+p][c+q] f[p][q].  d_x: 2-D float32 CUDA tensor whose
+    rows are contiguous (stride(1) == 1; stride(0) is the pitch); h_f: host kh x kw taps."""
+    c = _calls or _entry_points()
+    f = _image_and_taps(d_x, h_f)
+    h, w = d_x.shape
+    kh, kw = f.shape
+    oh, ow = max(h - kh + 1, 0), max(w - kw + 1, 0)
+    if d_y is None:
+        d_y = c.empty((oh, ow), dtype=c.float32, device=d_x.device)
+    _room_2d(d_y, oh, ow)
+    status = c.sys_conv2d(d_x.data_ptr(), h, w, d_x.stride(0), f.tobytes(), kh, kw, d_y.data_ptr(), d_y.stride(0),
+                          _proj(projection), _stream_handle(stream))
+    if status:
+        _check(status)
     return d_y
 
 
 def sys_conv2d_strided(d_x, h_f, stride, d_y=None, projection="AUTO", stream=None):
     """y[r][c] = sum_p sum_q x[stride*r+p][stride*c+q] f[p][q].  Arguments as sys_conv2d."""
-    import torch
-    _device_f32(d_x, "d_x")
-    if d_x.dim() != 2 or d_x.stride(1) != 1:
-        raise ValueError("d_x must be 2-D with unit column stride")
-    f = _taps(h_f)
-    if f.ndim != 2:
-        raise ValueError("h_f must be 2-D")
+    c = _calls or _entry_points()
+    f = _image_and_taps(d_x, h_f)
     h, w = d_x.shape
     kh, kw = f.shape
     stride = int(stride)
     ok = stride >= 1 and h >= kh and w >= kw
     oh, ow = ((h - kh) // stride + 1, (w - kw) // stride + 1) if ok else (0, 0)
     if d_y is None:
-        d_y = torch.empty((oh, ow), dtype=torch.float32, device=d_x.device)
-    _device_f32(d_y, "d_y")
-    if d_y.dim() != 2 or d_y.stride(1) != 1:
-        raise ValueError("d_y must be 2-D with unit column stride")
-    if d_y.shape[0] < oh or d_y.shape[1] < ow:
-        raise ValueError(f"d_y must have room for {oh} x {ow} outputs")
-    _check(lib().sys_conv2d_strided(d_x.data_ptr(), h, w, d_x.stride(0),
-                                    f.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), kh, kw, stride,
-                                    d_y.data_ptr(), d_y.stride(0), _proj(projection), _stream_handle(stream)))
+        d_y = c.empty((oh, ow), dtype=c.float32, device=d_x.device)
+    _room_2d(d_y, oh, ow)
+    status = c.sys_conv2d_strided(d_x.data_ptr(), h, w, d_x.stride(0), f.tobytes(), kh, kw, stride, d_y.data_ptr(), d_y.stride(0),
+                                  _proj(projection), _stream_handle(stream))
+    if status:
+        _check(status)
     return d_y
 
 
