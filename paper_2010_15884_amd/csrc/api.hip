@@ -184,19 +184,27 @@ int sys_conv2d(const float* d_x, int h, int w, size_t x_pitch, const float* h_f,
         return hip_status(sysconv::launch_conv2d_split(d_x, h, w, x_pitch, h_f, kh, kw, d_y, y_pitch, stream));
     // What the split kernel does not take (conv2d_split_pays has the line and both sides' figures):
     // Measured on MI355X, square images of 1000 .. 10240 columns (us, 5x5: BFS / SBM / FBS): 2996^2 15.8 / 14.3 / 14.3,
-    // 4092^2 25.9 / 28.7 / 27.1, 4604^2 33.9 / 36.4 / 32.5, 5996^2 57.2 / 57.0 / 51.1, 7164^2 81.0 / 83.6 / 75.1,
-    // 8188^2 103 / 104 / 95.5, 10236^2 166 / 170 / 155.  Up to 6x6 the FBS tile kernels win by 3 - 17 % except where
-    // the input pitch is a power of two of at most 16 KB (1024, 2048, 4096 columns): there single-strip order and the
-    // BFS block kernel's 1 KB-aligned strips win by 4 - 12 %.  7x7: SBM by 2 - 12 % on large images and power-of-two
-    // pitches, FBS on others up to 3 M outputs (SBM / FBS: 345x390 5.8 / 4.8, 1494^2 9.05 / 8.67, 1704^2 9.64 / 9.19; but 2613^2 16.4 / 17.1,
-    // 2048^2 12.4 / 13.3).  8x8 .. 11x11: SBM.  The rest: FBS.
+    // 4604^2 33.9 / 36.4 / 32.5, 5996^2 57.2 / 57.0 / 51.1, 7164^2 81.0 / 83.6 / 75.1, 8188^2 103 / 104 / 95.5, 10236^2 166 / 170 / 155.
+    // Up to 6x6 the FBS tile kernels win by 3 - 17 % except where the input pitch is a power of two of at most 16 KB (1024, 2048, 4096
+    // columns): there single-strip order and the BFS block kernel's 1 KB-aligned strips win by 2 - 12 % (4096^2 5x5 23.8 / 24.4 / 25.6, 3x3
+    // 22.6 / 23.5 / 23.4, 2048^2 5x5 9.1 / 10.1 / 9.5), but for up to 3 M outputs of 16 KB rows (700x4096 5x5 7.4 / 7.5 / 7.0, 3x3 6.7 / 6.7 / 6.5) and
+    // 6x6 between 1.5 M and 8 M (2048^2 11.0 / 11.2 / 10.4, 4096x1024 11.4 / 11.2 / 10.5; but 1024^2 5.7 / 6.3 / 6.1, 4096^2 27.4 / 27.0 / 28.6).
+    // 7x7: SBM, but FBS up to 3 M outputs (345x390 SBM 5.8, FBS 4.8; 1494^2 9.05 / 8.67; 700x4096 9.5 / 9.0; but 2613^2 16.4 / 17.1),
+    // and BFS at power-of-two pitches up to 8 KB (1024^2 SBM 7.3, FBS 6.8, BFS 6.0; 2048^2 12.5 / 13.2 / 11.4).
+    // 8x8 .. 11x11: SBM.  The rest: FBS.
     if (proj == SYS_PROJ_AUTO) {
         const size_t pitch_bytes = x_pitch * sizeof(float);
-        const bool short_pow2_pitch = (pitch_bytes & (pitch_bytes - 1)) == 0 && pitch_bytes <= 16384;
-        if (kh == kw && kh >= 2 && kh <= 6) proj = short_pow2_pitch ? SYS_PROJ_BFS : SYS_PROJ_FBS;
-        else if (kh == 7 && kw == 7 && !short_pow2_pitch && (double)oh * ow <= 3e6) proj = SYS_PROJ_FBS;
-        else if (sysconv::has_conv2d_sbm(kh, kw) && kh >= 7) proj = SYS_PROJ_SBM;
-        else proj = SYS_PROJ_FBS;
+        const bool pow2_pitch = (pitch_bytes & (pitch_bytes - 1)) == 0;
+        const double outputs = (double)oh * ow;
+        proj = SYS_PROJ_FBS;
+        if (kh == kw && kh >= 2 && kh <= 6 && pow2_pitch && pitch_bytes <= 16384) {
+            if (!(pitch_bytes == 16384 && kh >= 3 && outputs <= 3e6) && !(kh == 6 && outputs > 1.5e6 && outputs < 8e6)) proj = SYS_PROJ_BFS;
+        } else if (kh == 7 && kw == 7) {
+            if (pow2_pitch && pitch_bytes <= 8192) proj = SYS_PROJ_BFS;
+            else if (outputs > 3e6) proj = SYS_PROJ_SBM;
+        } else if (sysconv::has_conv2d_sbm(kh, kw) && kh >= 8) {
+            proj = SYS_PROJ_SBM;
+        }
     }
     switch (proj) {
     case SYS_PROJ_FBS:

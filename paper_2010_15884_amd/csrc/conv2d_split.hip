@@ -25,13 +25,16 @@
 // groups it belongs to, whose sums wait in registers: no halo row is loaded or split twice within a
 // block, one barrier per chunk, and all indices of the sums are compile-time constants.
 //
-// What bounds it: matrix and vector instructions, which add up.  On 8192^2 11x11 the matrix cores are busy for 57 % of the
-// kernel's clocks (16 clocks an instruction) and other vector instructions for 17 %, with 1.41 of the two wavefronts a SIMD has
-// room for resident on average; on 3001x4003 15x15 45 %, 14 % and 1.17.  Per resident pair of wavefronts that is all of the time: what
-// is missing is the tail, in which row blocks of equal length end at different times.  LDS is busy for 21 to 23 %, its bank
-// conflicts are 1 to 5 % of that, HBM reads are 1.06 and 1.28 times the image.  Measured (us, the vector kernels before / this; the
-// best of eight batches, 11x11 on 8192^2 159 and 15x15 46 on average among other passes): 11x11 on 8192^2 243 / 142, 15x15
-// on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 41.
+// What bounds it: the power of the package.  11x11 on 8192^2 issues 180 GFLOP; a large bf16 matrix product reaches 1.32 PFLOP/s on this
+// card, at 1.87 GHz, and at that rate the instructions alone take 136 us (15x15 on 3001x4003: 50 GFLOP, 38 us).  With random data the clock
+// falls to 1.55 - 1.96 GHz in this kernel (2.38 with an image of zeros, 136 us), and what saves clocks lowers it further.  By the
+// counters the matrix cores are busy for 57 % of the clocks and other vector instructions for 17 %, LDS for 21 to 23 %, HBM reads are
+// 1.06 and 1.28 times the image; the two workgroups of a CU do not share it evenly (ends between 100 and 169 us, half by 112).
+// Measured (us, the vector kernels before / this; the best of eight batches, 11x11 on 8192^2 159 and 15x15 46 on average among other
+// passes): 11x11 on 8192^2 243 / 142, 15x15 on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 41.
+// Tried on that account: the next chunk's split placed between the matrix instructions (an MFMA leaves room for two vector instructions)
+// with the windows read a unit ahead, 162 -> 165 us on 8192^2 and 0 to 7 % slower elsewhere; eight wavefronts a workgroup, one a CU, all
+// in step (they end together, at 1.57 GHz), 158 - 165.
 // Tried: 272 input columns per chunk (one wavefront splits a fifth piece and the others wait: 11x11 190 us with two
 // accumulators an output), one accumulator (2 % faster, but errors of 1.8e-7 instead of 6e-8), stores behind per-lane
 // branches (every chunk then waits for the stores of the one before), three workgroups a CU (spills at NS = 7, level
