@@ -105,8 +105,11 @@ typedef enum {
  *   h_w   host, k floats, 1 <= k <= min(n, SYS_MAX_K1D)
  *   d_y   device, n-k+1 floats (written; nothing else is touched)
  *   projection  a sys_projection_t; every projection accepts every k in range
- *         (sys_conv1d_has reports it).  SYS_PROJ_AUTO is FBS, and BFS from 36 taps on
- *         or for n >= 2^29, where BFS measures faster on MI355X.
+ *         (sys_conv1d_has reports it).  SYS_PROJ_AUTO, from measurements: from 28 taps on the
+ *         matrix cores with inputs and taps split exactly into three bf16 numbers each, on the
+ *         conditions of sys_conv2d (a signal with values that the split does not carry all over
+ *         it takes up to 1.45 times what BFS takes); else FBS, and BFS from 36 taps on or
+ *         for n >= 2^29.
  */
 int sys_conv1d(const float *d_x, size_t n,
                const float *h_w, int k,
@@ -201,8 +204,8 @@ int sys_conv1d_stt(const float *d_x, size_t n,
  *            are taken with plain multiply-adds: an image with a few of them loses part of the
  *            gain, one with such values everywhere takes up to 1.4 times (twice below 3 M
  *            outputs) what the named projections take, which do not look at the values.  Of the rest, square
- *            filters up to 6x6 run FBS, or BFS where x_pitch * 4 is a power of two of at most
- *            16 KB; 7x7 .. 11x11 run SBM; everything else FBS); BFS and SBM are built
+ *            filters up to 6x6 run FBS, or mostly BFS where x_pitch * 4 is a power of two of at most
+ *            16 KB; 7x7 FBS, BFS or SBM by size; 8x8 .. 11x11 SBM; everything else FBS); BFS and SBM are built
  *            for SQUARE filters 2x2 .. 11x11 only (sys_conv2d_has) and return
  *            SYS_ERR_UNSUPPORTED otherwise; BSM, FSM and FFS are 1-D only.  FBS runs
  *            kernels specialised at compile time for every filter of up to 11 rows and
