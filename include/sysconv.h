@@ -108,7 +108,7 @@ typedef enum {
  *         (sys_conv1d_has reports it).  SYS_PROJ_AUTO, from measurements: from 28 taps on the
  *         matrix cores with inputs and taps split exactly into three bf16 numbers each, on the
  *         conditions of sys_conv2d (a signal with values that the split does not carry all over
- *         it takes up to 1.45 times what BFS takes); else FBS, and BFS from 36 taps on or
+ *         it takes 0.9 to 1.35 times what the vector kernels take); else FBS, and BFS from 36 taps on or
  *         for n >= 2^29.
  */
 int sys_conv1d(const float *d_x, size_t n,

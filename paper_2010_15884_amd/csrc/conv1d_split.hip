@@ -11,7 +11,7 @@
 //
 // Precision: three bf16 parts a number, six products, x1f1 summed apart from the small ones (split_bf16.h); off from 64-bit sums by
 // 4.2e-8 where BFS is by 1.4e-7 (20 M, k = 63).  A tile one of whose inputs (or of whose right neighbour's) the split does not carry
-// is left out and computed with plain multiply-adds when the wavefront has been through its run (plain_tiles).
+// is left out and computed with plain multiply-adds when the wavefront has been through its run (plain_sums).
 //
 // Data path.  A wavefront walks along a run of tiles by itself: inputs are loaded 1 KB at a time, four tiles ahead, split once,
 // written to two slots of LDS of its own as three planes of bf16, and read back as 16-byte windows.  No barrier after the taps
@@ -20,8 +20,10 @@
 //
 // What bounds it: HBM up to some 24 M inputs, then HBM and the set-up of a run (taps, first loads).  Measured (us, the best vector kernel / this):
 // k = 63 on 20 M 51 / 28 (5.7 TB/s), k = 64 on 300 K 6.5 / 3.7, on 4 M 14.4 / 9.1, on 2^26 149 / 94; k = 40 on 1 M 6.5 / 4.6, on 16 M 35.6 / 23,
-// on 2^26 113 / 92; k = 28 on 2^26 100 / 93.  Signals with a marked value (NaN) in every tile are up to 1.45 times slower than
-// with BFS (20 M, k = 63 51 / 71; 2^26 152 / 219; 1 M, k = 40 6.5 / 7.8), with one in every sixteenth tile faster (20 M 37).
+// on 2^26 113 / 92; k = 28 on 2^26 100 / 93.  A signal with a marked value (NaN) in every tile takes 0.9 to 1.35 times what the best vector
+// kernel takes (us, vector kernel / two tiles at a time behind the whole run / this: k = 28 on 300 K 4.3 / 5.5 / 4.7, 5 M 10.7 / 16.5 / 14.2,
+// 20 M 31 / 47 / 29, 2^26 97 / 160 / 121, there with one in every other tile 97 / 159 / 132; k = 36 on 20 M 39 / 49 / 34; k = 63 on 20 M 52 / 71 / 50, 2^26
+// 149 / 226 / 158), with one in every sixteenth tile less (k = 63 on 20 M 56 / 35 / 33).
 // Tried: five wavefronts a SIMD for k > 49 (spills, twice the time), three (level to 8 % slower), six or eight tiles ahead (level), two
 // (4 % slower), cacheable stores (level to 10 % slower), plain sums in the middle of the run (spills, or 452 us on 2^26 without LDS).
 #include "bfs_blocks.h"
@@ -44,25 +46,44 @@ constexpr float kHuge = 0x1p80f - 0x1p71f;  // the least number whose first part
 constexpr int kPlane = 2 * (2 * kTileOut + 2 * 16);        // bytes of a plane: two slots of 256 numbers, 16 bytes of padding per 128
 __device__ __forceinline__ constexpr int place(int e) { return 2 * e + 16 * (e >> 7); }    // byte of number e of a plane
 
-// Two tiles of outputs from `at` on with plain multiply-adds: a BFS array, every lane four outputs of each tile from its windows in LDS
-// of the wavefront's own (from memory, one load a step, the latency showed: 2^26, k = 63, a marked value in every tile 452 us).
-constexpr int kPlainTiles = 2;
-constexpr int kStage = kPlainTiles * kTileOut + kMaxK1D + 4;               // inputs of their windows, in whole quads
-static_assert(kStage * 4 <= 3 * kPlane, "they fit where the planes were");
-__device__ __forceinline__ void plain_tiles(kernarg_floats tw, const float* __restrict__ x, long long n, long long at, int lane, int k, float* stage,
-                                            float (&acc)[kPlainTiles][4])
+// Tiles of outputs from `at` on with plain multiply-adds: a BFS array, every lane four outputs of each tile from its windows in LDS of the
+// wavefront's own (from memory, one load a step, the latency showed: 2^26, k = 63, a marked value in every tile 452 us).
+template <int N>
+struct PlainInputs { f4u v[N + 1]; };                                      // the inputs of N tiles and the quads that reach past them
+constexpr int kPastTile = (kMaxK1D + kTile) / kTile;                       // lanes with one
+template <int N> constexpr int kStage = N * kTileOut + kPastTile * kTile;  // their windows in LDS
+
+template <int N>
+__device__ __forceinline__ void plain_load(const float* __restrict__ x, long long n, long long at, int lane, PlainInputs<N>& in)
+{
+    if (at + kStage<N> <= n) {                                             // uniform
+#pragma unroll
+        for (int r = 0; r <= N; ++r)
+            in.v[r] = *reinterpret_cast<const f4u*>(x + at + r * kTileOut + kTile * (r < N ? lane : min(lane, kPastTile - 1)));
+    } else {
+#pragma unroll
+        for (int r = 0; r <= N; ++r) {
+            float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (r < N || lane < kPastTile) load4_guarded<false>(x, at + r * kTileOut + kTile * lane, n, v);
+            in.v[r] = f4u{v[0], v[1], v[2], v[3]};
+        }
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void plain_stage(const PlainInputs<N>& in, int lane, float* stage)
 {
     wave_exchange();
 #pragma unroll
-    for (int r = 0; r <= kPlainTiles; ++r) {
-        const int e = r * kTileOut + kTile * lane;
-        if (e < kStage) {
-            float v[4];
-            load4_guarded<false>(x, at + e, n, v);
-            *reinterpret_cast<f4*>(stage + e) = f4{v[0], v[1], v[2], v[3]};
-        }
-    }
+    for (int r = 0; r <= N; ++r)
+        if (r < N || lane < kPastTile)
+            *reinterpret_cast<f4*>(stage + r * kTileOut + kTile * lane) = f4{in.v[r].x, in.v[r].y, in.v[r].z, in.v[r].w};
     wave_exchange();
+}
+
+template <int N>
+__device__ __forceinline__ void plain_sums(kernarg_floats tw, int k, int lane, const float* stage, float (&acc)[N][4])
+{
     const float* mine = stage + kTile * lane;
     auto weights = [&](int b, float (&wv)[7]) {
 #pragma unroll
@@ -75,7 +96,7 @@ __device__ __forceinline__ void plain_tiles(kernarg_floats tw, const float* __re
     float xa[4], wv[7];
     weights(0, wv);
 #pragma unroll
-    for (int r = 0; r < kPlainTiles; ++r) {
+    for (int r = 0; r < N; ++r) {
         acc[r][0] = acc[r][1] = acc[r][2] = acc[r][3] = 0.0f;
         window(r, 0, xa);
         bfs_block<3, 6>(acc[r], xa, wv);                                   // (k >= 4)
@@ -85,7 +106,7 @@ __device__ __forceinline__ void plain_tiles(kernarg_floats tw, const float* __re
     for (; 4 * b + 3 <= k - 1; ++b) {
         weights(b, wv);
 #pragma unroll
-        for (int r = 0; r < kPlainTiles; ++r) {
+        for (int r = 0; r < N; ++r) {
             window(r, b, xa);
             bfs_block<0, 6>(acc[r], xa, wv);
         }
@@ -93,13 +114,34 @@ __device__ __forceinline__ void plain_tiles(kernarg_floats tw, const float* __re
 #pragma nounroll
     for (; 4 * b <= k + 2; ++b) {
         weights(b, wv);
+        float xs[N][4];
 #pragma unroll
-        for (int r = 0; r < kPlainTiles; ++r) {
-            window(r, b, xa);
-            bfs_block_hi<0>(k + 2 - 4 * b, acc[r], xa, wv);
+        for (int r = 0; r < N; ++r) window(r, b, xs[r]);
+        auto last = [&](auto hi) {
+#pragma unroll
+            for (int r = 0; r < N; ++r) bfs_block<0, decltype(hi)::value>(acc[r], xs[r], wv);
+        };
+        switch (k + 2 - 4 * b) {                                           // uniform
+        case 0: last(std::integral_constant<int, 0>{}); break;
+        case 1: last(std::integral_constant<int, 1>{}); break;
+        case 2: last(std::integral_constant<int, 2>{}); break;
+        case 3: last(std::integral_constant<int, 3>{}); break;
+        case 4: last(std::integral_constant<int, 4>{}); break;
+        case 5: last(std::integral_constant<int, 5>{}); break;
+        default: last(std::integral_constant<int, 6>{}); break;
         }
     }
 }
+
+// Tiles at a time: scattered ones, the rest of a run.  One at a time for the former is ahead on runs of one tile (300 K, k = 28 4.7 / 4.1 us) and behind
+// where pairs are marked (2^26, k = 63, every fourth tile 143 / 157); as a third form beside the two it spills.
+constexpr int kPlainFew = 2, kPlainMany = 4;
+constexpr int kOwnLds = kStage<kPlainMany> * 4 > 3 * kPlane ? kStage<kPlainMany> * 4 : 3 * kPlane;     // bytes of a wavefront
+
+// The rest of a run is left to plain sums where its first two tiles both hold a marked value (one value marks two tiles but lies in one), or
+// where three of four of the `seen` ones are marked: with half of them marked the split still pays (k = 63, a value in every fourth
+// tile, given up at two of five: 20 M 48 / 57 us, 2^26 160 / 196).
+__device__ __forceinline__ bool too_many(int marked, int seen) { return marked >= 4 && 4 * marked >= 3 * seen; }
 
 template <int KS, bool NT>
 __global__ __launch_bounds__(kBlock, 4) void conv1d_split_kernel(Taps1D taps, const float* __restrict__ x, float* __restrict__ y,
@@ -111,7 +153,7 @@ __global__ __launch_bounds__(kBlock, 4) void conv1d_split_kernel(Taps1D taps, co
     constexpr int kPad = 15 + 32 * KS + 1;                                 // w(-15) .. w(32 KS - 1)
     __shared__ float tpad[kPad];
     __shared__ __attribute__((aligned(16))) u4 frags[KS * 3 * kWave];
-    __shared__ __attribute__((aligned(16))) char planes[kWaves * 3 * kPlane];
+    __shared__ __attribute__((aligned(16))) char planes[kWaves * kOwnLds];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = wave_in_block();
@@ -161,7 +203,7 @@ __global__ __launch_bounds__(kBlock, 4) void conv1d_split_kernel(Taps1D taps, co
 #pragma unroll
         for (int j = 0; j < 3; ++j) fa[s][j] = __builtin_bit_cast(b8, frags[(s * 3 + j) * kWave + lane]);
 
-    char* const mine = planes + wave * 3 * kPlane;
+    char* const mine = planes + wave * kOwnLds;
     int window[2][KS];                                                     // bytes of the lane's windows in the first plane
 #pragma unroll
     for (int slot = 0; slot < 2; ++slot)
@@ -201,7 +243,8 @@ __global__ __launch_bounds__(kBlock, 4) void conv1d_split_kernel(Taps1D taps, co
         return __builtin_amdgcn_ballot_w64((tiny < tiny_below) | !(large < kHuge)) != 0;
     };
 
-    unsigned todo = 0;                                                     // tiles left to plain_tiles; a bit per tile of the run
+    unsigned todo = 0;                                                     // tiles left to plain sums; a bit per tile of the run
+    int end = tiles, rest = tiles;                                         // of the loop below; 0 and the first tile left once it is given up
     bool bad = put(0, raw[0], 0);
     load_tile(kAhead, raw[0]);
     bool bad_next = put(1, raw[1], 1);
@@ -242,31 +285,56 @@ __global__ __launch_bounds__(kBlock, 4) void conv1d_split_kernel(Taps1D taps, co
             }
         } else {
             todo |= 1u << t;                                               // rare
+            if (too_many(__builtin_popcount(todo), t + 1)) { rest = t + 1; end = 0; }
         }
         wave_exchange();
         bad = bad_next;
         bad_next = bad_after;
     };
     static_assert(kAhead == 4, "the steps below");
+    if ((bad & bad_next) | ((bad | bad_next) & (tiles == 1))) {
+        if (tiles > kPlainFew) rest = 0;
+        else todo = (1u << tiles) - 1u;
+        end = 0;
+    }
 #pragma nounroll
-    for (int t = 0; t < tiles; t += kAhead) {
+    for (int t = 0; t < end; t += kAhead) {
         step(t, std::integral_constant<int, 0>{});
-        if (t + 1 >= tiles) break;
+        if (t + 1 >= end) break;
         step(t + 1, std::integral_constant<int, 1>{});
-        if (t + 2 >= tiles) break;
+        if (t + 2 >= end) break;
         step(t + 2, std::integral_constant<int, 2>{});
-        if (t + 3 >= tiles) break;
+        if (t + 3 >= end) break;
         step(t + 3, std::integral_constant<int, 3>{});
+    }
+    float* const stage = reinterpret_cast<float*>(mine);
+    if (rest < tiles) {                                                    // uniform; the next tiles' loads in flight
+        PlainInputs<kPlainMany> in;
+        plain_load(x, n, base + (long long)rest * kTileOut, lane, in);
+#pragma nounroll
+        for (int t = rest; t < tiles; t += kPlainMany) {
+            const long long at = base + (long long)t * kTileOut;
+            plain_stage(in, lane, stage);
+            if (t + kPlainMany < tiles) plain_load(x, n, at + kPlainMany * kTileOut, lane, in);
+            float acc[kPlainMany][4];
+            plain_sums(tw, k, lane, stage, acc);
+#pragma unroll
+            for (int r = 0; r < kPlainMany; ++r)
+                if (t + r < tiles) store4_guarded(y, at + r * kTileOut + kTile * lane, m, acc[r]);
+        }
     }
     while (todo != 0) {                                                    // uniform
         const int t = __builtin_ctz(todo);
         const long long at = base + (long long)t * kTileOut;
-        float acc[kPlainTiles][4];
-        plain_tiles(tw, x, n, at, lane, k, reinterpret_cast<float*>(mine), acc);
+        PlainInputs<kPlainFew> in;
+        plain_load(x, n, at, lane, in);
+        plain_stage(in, lane, stage);
+        float acc[kPlainFew][4];
+        plain_sums(tw, k, lane, stage, acc);
 #pragma unroll
-        for (int r = 0; r < kPlainTiles; ++r)
+        for (int r = 0; r < kPlainFew; ++r)
             if (r < 32 - t && (todo >> (t + r) & 1u)) store4_guarded(y, at + r * kTileOut + kTile * lane, m, acc[r]);
-        todo &= t + kPlainTiles < 32 ? ~0u << (t + kPlainTiles) : 0u;
+        todo &= t + kPlainFew < 32 ? ~0u << (t + kPlainFew) : 0u;
     }
 }
 

@@ -88,3 +88,78 @@ def test_taps_the_split_does_not_carry(tap):
     x, w = _case(3000, 40)
     w[7] = tap
     assert torch.equal(B.sys_conv1d(dev(x), w), B.sys_conv1d(dev(x), w, projection="BFS"))
+
+
+# Runs of 3, 5, 9 and 32 tiles and of 8 in the second round; past 37.7 M the non-temporal loads.  The last run is cut.
+LONG_RUNS = [(3_000_007, 33, 3), (5_200_003, 64, 5), (9_300_001, 50, 9), (33_400_003, 64, 32), (38_100_005, 40, 8), (38_100_005, 63, 19)]
+
+
+def _marks(pattern, tiles, run):
+    """Tiles (of 256 outputs) that get a NaN: `tiles` in all, `run` to a wavefront."""
+    whole = max(0, tiles // run // 2) * run                                # a run in the middle
+    last = (tiles - 1) // run * run                                        # the last one, cut
+    if pattern == "scattered":
+        return [0, whole + run // 2, whole + run, last, tiles - 1]
+    if pattern == "last two of a run":
+        return [whole + run - 2, whole + run - 1, last + max(0, tiles - last - 2)]
+    if pattern == "first two of a run":                                    # the run is given up before its first tile
+        return [whole, whole + 1, last, min(last + 1, tiles - 1)]
+    if pattern == "a stretch in a run":                                    # given up on the way, or not, by where it lies
+        return list(range(whole + 1, whole + 1 + max(2, 2 * run // 3))) + list(range(last + 1, tiles, 2))
+    return list(range(whole, whole + run)) + list(range(last, tiles))      # whole runs
+
+
+@pytest.mark.parametrize("pattern", ["scattered", "last two of a run", "first two of a run", "a stretch in a run", "whole runs"])
+@pytest.mark.parametrize("n,k,run", LONG_RUNS)
+def test_marked_tiles_of_long_runs(n, k, run, pattern):
+    """Outputs that see a NaN are BFS's bit for bit (the same order of sums), the others within the tolerance of the oracle's scale."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + k)
+    x = torch.rand(n, dtype=torch.float32, device="cuda", generator=gen) * 2 - 1
+    w = _case(k, k)[1]
+    m = n - k + 1
+    tiles = -(-m // 256)
+    assert -(-tiles // 4096) == run or n > 33_554_432                      # the launch rule this is about
+    at = torch.tensor([min(256 * t + (37 * i) % 256, n - 1) for i, t in enumerate(_marks(pattern, tiles, run))], device="cuda")
+    clean = x.clone()
+    x[at] = float("nan")
+    clean[at] = 0
+    y, plain = B.sys_conv1d(x, w), B.sys_conv1d(x, w, projection="BFS")
+    assert torch.equal(torch.isnan(y), torch.isnan(plain))
+    ok = ~torch.isnan(plain)
+    scale = B.sys_conv1d(clean.abs(), np.abs(w), projection="BFS")
+    assert ((y - plain).abs()[ok] <= TOL * scale[ok]).all()
+    # infinities take the same way and leave numbers to compare
+    x[at] = float("inf")
+    x[at[::2]] = 2.0 ** 81
+    y, plain = B.sys_conv1d(x, w), B.sys_conv1d(x, w, projection="BFS")
+    seen = torch.isnan(B.sys_conv1d(torch.where(x.abs() > 2.0 ** 80, float("nan"), x), w, projection="BFS"))
+    same = (y == plain) | (torch.isnan(y) & torch.isnan(plain))
+    assert same[seen].all()
+
+
+def _us(fn, launches, best_of=7):
+    fn()
+    times = []
+    for _ in range(best_of):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(launches):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / launches)
+    return min(times)
+
+
+@pytest.mark.parametrize("n,k", [(8_000_000, 28), (20_000_000, 28), (20_000_000, 63), (1 << 26, 28), (1 << 26, 63)])
+def test_no_input_makes_auto_much_slower_than_the_vector_kernels(n, k):
+    """A NaN in every tile: measured 0.95 to 1.25 times the best vector kernel (1.27 to 1.69 while every run was gone through first); the bound
+    leaves room for another box's clocks."""
+    x = torch.rand(n, dtype=torch.float32, device="cuda") * 2 - 1
+    x[128::256] = float("nan")
+    w, y = _case(k, k)[1], torch.empty(n - k + 1, dtype=torch.float32, device="cuda")
+    bound = min(_us(lambda: B.sys_conv1d(x, w, y, projection=p), 10) for p in ("FBS", "BFS"))
+    marked = _us(lambda: B.sys_conv1d(x, w, y), 10)
+    print(f"{n} {k}: {marked:.1f} / {bound:.1f}", flush=True)
+    assert marked <= 1.45 * bound, f"a NaN per tile: {marked:.1f} us, vector kernel {bound:.1f} us"
