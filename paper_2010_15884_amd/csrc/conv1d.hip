@@ -50,7 +50,7 @@ __device__ __forceinline__ void fbs_groups_last(int nt, float (&e)[kGroups][4], 
     }
 }
 
-template <int KT, bool NT>
+template <int KT>
 __global__ __launch_bounds__(kBlock) void conv1d_fbs_kernel(const float* __restrict__ x, float* __restrict__ y,
                                                             long long n, long long m, int k_rt, int valid_lanes,
                                                             TapsFor<KT> taps)
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kBlock) void conv1d_fbs_kernel(const float* __restr
     float e[kGroups][4], acc[kGroups][4];
 #pragma unroll
     for (int r = 0; r < kGroups; ++r) {
-        load4_guarded<NT>(x, base + r * per_group + kTile * lane, n, e[r]);
+        load4_guarded(x, base + r * per_group + kTile * lane, n, e[r]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[r][i] = 0.0f;
     }
@@ -377,12 +377,9 @@ int group_valid_lanes(int k)
     return v - v % SYSCONV_1D_LANE_ALIGN;
 }
 
-// FBS reads signals of this many inputs without the non-temporal hint: the few of them that a program goes round stay in the 256 MB
-// memory-side cache (us, with / without: k = 5 16 M, four of them 22.6 / 19.8, 20 M, three 27.5 / 24.4, 30 M, two 39.9 / 35.9; k = 16
-// 23.4 / 20.6, 27.5 / 24.9, 39.8 / 36.3).  Where they do not all fit it is level to 2 % behind (15 M, five 21.5 / 21.7; 24 M, three
-// 32.4 / 32.0); longer signals lose (2^26 86.3 / 89.1), and so do 16 taps and more on 2 M to 4 M (1 to 2 %).
-constexpr size_t kCachedFrom = 14u << 20, kCachedTo = 34u << 20;
-
+// The loads keep the non-temporal hint at every size.  Cacheable ones find inputs that a kernel before has just written, or that a program
+// goes round, in the 256 MB memory-side cache (20 M, k = 5: 28.4 -> 22.4 us behind the kernel that wrote them), but where that cache is full of
+// what else was written they wait for it to be written back (27.8 -> 41.9 us, 30 M 43.4 -> 67; up to 1.55 times).
 template <int KT, bool SBM>
 hipError_t launch_1d(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
 {
@@ -398,8 +395,8 @@ hipError_t launch_1d(const float* x, size_t n, const float* w, int k, float* y, 
         hipLaunchKernelGGL((conv1d_sbm_kernel<KT>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
                            x, y, (long long)n, m, k, valid_lanes, taps);
     else
-        hipLaunchKernelGGL((n >= kCachedFrom && n <= kCachedTo ? conv1d_fbs_kernel<KT, false> : conv1d_fbs_kernel<KT, true>),
-                           dim3((unsigned)blocks), dim3(kBlock), 0, s, x, y, (long long)n, m, k, valid_lanes, taps);
+        hipLaunchKernelGGL((conv1d_fbs_kernel<KT>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+                           x, y, (long long)n, m, k, valid_lanes, taps);
     return hipGetLastError();
 }
 
