@@ -105,8 +105,8 @@ typedef enum {
  *   h_w   host, k floats, 1 <= k <= min(n, SYS_MAX_K1D)
  *   d_y   device, n-k+1 floats (written; nothing else is touched)
  *   projection  a sys_projection_t; every projection accepts every k in range
- *         (sys_conv1d_has reports it).  SYS_PROJ_AUTO, from measurements: from 28 taps on the
- *         matrix cores with inputs and taps split exactly into three bf16 numbers each, on the
+ *         (sys_conv1d_has reports it).  SYS_PROJ_AUTO, from measurements: from 34 taps on, and from 28 on
+ *         below 4 M inputs and above 36 M, the matrix cores with inputs and taps split exactly into three bf16 numbers each, on the
  *         conditions of sys_conv2d (a signal with values that the split does not carry all over
  *         it takes 0.9 to 1.35 times what the vector kernels take); else FBS, and BFS from 36 taps on or
  *         for n >= 2^29.

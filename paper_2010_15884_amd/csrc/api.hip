@@ -53,7 +53,7 @@ int sys_conv1d(const float* d_x, size_t n, const float* h_w, int k, float* d_y, 
 
     switch (projection) {
     case SYS_PROJ_AUTO:
-        if (sysconv::conv1d_split_takes(h_w, k))
+        if (sysconv::conv1d_split_pays(n, k) && sysconv::conv1d_split_takes(h_w, k))
             return hip_status(sysconv::launch_conv1d_split(d_x, n, h_w, k, d_y, stream));
         // What the matrix-core kernel does not take: long filters are bound by the VALUs, where BFS issues the fewest
         // instructions (n = 2^26: k = 34: 110 / 109 us FBS / BFS, k = 36: 113 / 108, k = 48: 146 / 120,

@@ -19,7 +19,7 @@
 // pieces change places in pairs instead, free of them by construction, is level to 2 % slower.
 //
 // What bounds it: HBM up to some 24 M inputs, then HBM and the set-up of a run (taps, first loads).  Measured (us, the best vector kernel / this):
-// k = 63 on 20 M 51 / 28 (5.7 TB/s), k = 64 on 300 K 6.5 / 3.7, on 4 M 14.4 / 9.1, on 2^26 149 / 94; k = 40 on 1 M 6.5 / 4.6, on 16 M 35.6 / 23,
+// k = 63 on 20 M 51 / 28 (three inputs in turn, which the memory-side cache holds in part; in no cache 34), k = 64 on 300 K 6.5 / 3.7, on 4 M 14.4 / 9.1, on 2^26 149 / 94; k = 40 on 1 M 6.5 / 4.6, on 16 M 35.6 / 29,
 // on 2^26 113 / 92; k = 28 on 2^26 100 / 93.  A signal with a marked value (NaN) in every tile takes 0.9 to 1.35 times what the best vector
 // kernel takes (us, vector kernel / two tiles at a time behind the whole run / this: k = 28 on 300 K 4.3 / 5.5 / 4.7, 5 M 10.7 / 16.5 / 14.2,
 // 20 M 31 / 47 / 29, 2^26 97 / 160 / 121, there with one in every other tile 97 / 159 / 132; k = 36 on 20 M 39 / 49 / 34; k = 63 on 20 M 52 / 71 / 50, 2^26
@@ -343,9 +343,13 @@ __global__ __launch_bounds__(kBlock, 4) void conv1d_split_kernel(Taps1D taps, co
 // the set-up is shorter and from the second round on runs of eight are the better ones: 2^26 93 / 97 with 8 / 32, 40 M 58 / 59.
 constexpr long long kPlaces = 4096;
 constexpr int kLongestRun = 32;
-// Up to here the loads are cacheable: a few such inputs that a program goes round stay in the 256 MB memory-side cache (20 M, k = 63, three
-// of them: 34 us with the non-temporal hint, 28 without; 32 M, two: 52 / 43); 40 M and 50 M are level, 2^26 95 / 100.
-constexpr size_t kCached = 36u << 20;
+// Up to here (with two and with three instructions a product) the loads are cacheable.  Inputs that the kernel before has written, or a few that a
+// program goes round, are then found in the 256 MB memory-side cache; where that is full of what else was written, the loads wait for it to be
+// written back.  The lines lie where even then the call takes no longer than the vector kernel's (us, vector kernel / cacheable / non-temporal; in
+// turn behind the kernel that wrote the input, and behind others that wrote 1 GB; k = 50: 14 M 34.7 / 20.6 / 21.9, 37.3 / 33.5 / 25.8; 24 M 54.5 / 35.7 / 37.1,
+// 56.5 / 56.9 / 41.7; 34 M 71.6 / 46.2 / 49.2, 75.5 / 77.2 / 56.6; k = 36: 8 M 18.6 / 12.4 / 14.8, 20.2 / 18.0 / 18.5; 14 M 28.3 / 19.2 / 20.9, 31.3 / 32.6 / 27.1;
+// 20 M 38.8 / 26.4 / 30.2, 41.7 / 46.7 / 36.5).  Three 20 M inputs in turn, k = 63: 28 / 34.
+constexpr size_t kCached2 = 8u << 20, kCached3 = 24u << 20;
 
 template <int KS, bool NT>
 hipError_t launch_split(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
@@ -365,22 +369,29 @@ hipError_t launch_split(const float* x, size_t n, const float* w, int k, float* 
     return hipGetLastError();
 }
 
-template <bool NT>
-hipError_t launch_by_k(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
+template <int KS>
+hipError_t launch_cached(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
 {
-    return k <= 49 ? launch_split<2, NT>(x, n, w, k, y, s) : launch_split<3, NT>(x, n, w, k, y, s);
+    return n <= (KS == 2 ? kCached2 : kCached3) ? launch_split<KS, false>(x, n, w, k, y, s) : launch_split<KS, true>(x, n, w, k, y, s);
 }
 
 }  // namespace
 
-// Where it is the fastest kernel: from 28 taps on, at every size (us, FBS / this; k = 24: 4.3 / 4.2 on 300 K, 6.3 / 5.9 on 2 M, 20.6 / 21.1 on
-// 12 M, 91.7 / 93.3 on 2^26; k = 28: 4.2 / 3.5, 6.8 / 5.9, 21.6 / 21.8, 100.7 / 93.8; k = 32: 4.4 / 3.5, 6.6 / 5.8, 22.6 / 21.6, 109 / 94).
-// Shorter filters sit on the copy rate with FBS from a few million inputs on.
 bool conv1d_split_takes(const float* w, int k) { return k >= 28 && k <= kMaxK1D && split_takes_taps(w, k); }
+
+// Where it is the fastest kernel (us, best vector kernel / this): from 34 taps on, at every size (k = 36: 1 M 7.6 / 4.7, 8 M 19.1 / 16.9, 20 M 40.8 / 35.7, 2^26 113 / 93,
+// 2^29 809 / 758; k = 64 2^30 2309 / 1535, k = 40 2^31 3405 / 3085).  From 28 to 33 taps on short signals and long ones (k = 28: 300 K 4.2 / 3.5, 2 M 6.8 / 5.9,
+// 36 M 57.6 / 51.6, 2^26 100 / 93, 2^27 187 / 181, 2^29 778 / 751, 2^30 1567 / 1524); between them FBS is level or ahead (k = 28: 8 M 16.4 / 16.5, 14 M 24.1 / 25.3, 20 M
+// 31.8 / 34.7, 30 M 45.6 / 48.8; k = 32: 34.3 / 34.8 on 20 M).  Shorter filters sit on the copy rate with FBS from a few million inputs on
+// (k = 24: 4.3 / 4.2 on 300 K, 20.6 / 21.1 on 12 M).
+bool conv1d_split_pays(size_t n, int k)
+{
+    return k >= 34 || (k >= 28 && (n <= (4u << 20) || n >= (36u << 20)));
+}
 
 hipError_t launch_conv1d_split(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s)
 {
-    return n <= kCached ? launch_by_k<false>(x, n, w, k, y, s) : launch_by_k<true>(x, n, w, k, y, s);
+    return k <= 49 ? launch_cached<2>(x, n, w, k, y, s) : launch_cached<3>(x, n, w, k, y, s);
 }
 
 }  // namespace sysconv

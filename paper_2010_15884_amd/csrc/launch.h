@@ -43,6 +43,7 @@ hipError_t launch_conv1d_bfs(const float* x, size_t n, const float* w, int k, fl
 
 // Matrix-core path without conditions on the input (conv1d_split.hip).
 bool conv1d_split_takes(const float* w, int k);
+bool conv1d_split_pays(size_t n, int k);         // where it is the fastest kernel
 hipError_t launch_conv1d_split(const float* x, size_t n, const float* w, int k, float* y, hipStream_t s);
 
 // Generic space-time-transform kernel (conv1d_stt.hip).  A plan is what the host derives

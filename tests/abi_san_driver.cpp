@@ -20,6 +20,7 @@ namespace sysconv {
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw);
 bool conv2d_split_pays(int oh, int ow, int kh, int kw);
 int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);
+bool conv1d_split_pays(size_t n, int k);
 }
 
 static int failures = 0;
@@ -195,6 +196,16 @@ int main()
     EXPECT(sysconv::conv2d_split_pays(2828, 989, 9, 9), 1);
     EXPECT(sysconv::conv2d_split_pays(3857, 380, 11, 11), 1);
     EXPECT(sysconv::conv2d_split_pays(2039, 2039, 10, 10), 1);
+
+    // ---- long 1-D filters: the split kernel from 34 taps on, and from 28 on below 4 Mi and above 36 Mi inputs
+    for (size_t n : {(size_t)64, (size_t)4 << 20, ((size_t)4 << 20) + 1, (size_t)20000000, ((size_t)36 << 20) - 1, (size_t)36 << 20, (size_t)1 << 40}) {
+        const bool ends = n <= (size_t)4 << 20 || n >= (size_t)36 << 20;
+        EXPECT(sysconv::conv1d_split_pays(n, 27), 0);
+        EXPECT(sysconv::conv1d_split_pays(n, 28), ends);
+        EXPECT(sysconv::conv1d_split_pays(n, 33), ends);
+        EXPECT(sysconv::conv1d_split_pays(n, 34), 1);
+        EXPECT(sysconv::conv1d_split_pays(n, SYS_MAX_K1D), 1);
+    }
 
     // ---- stride 2: tiles (0) or strips of two or three rows, all three timed at each shape
     EXPECT(sysconv::conv2d_stride2_strip_rows(1137, 1676, 6, 3), 0);

@@ -45,3 +45,14 @@ def test_fbs_takes_what_a_copy_takes(n, k, other):
     fbs = _cold_us(lambda: B.sys_conv1d(x, w, y, projection="FBS"), other)
     print(f"{n} {k}: {fbs:.1f} / {copy:.1f}", flush=True)
     assert fbs <= 1.25 * copy, f"FBS {fbs:.1f} us, copy {copy:.1f} us"
+
+
+@pytest.mark.parametrize("n,k", [(1_000_000, 28), (4_000_000, 32), (16_000_000, 28), (20_000_000, 33), (8_000_000, 34), (20_000_000, 36), (32_000_000, 40),
+                                 (14_000_000, 50), (25_000_000, 50), (25_000_000, 63), (32_000_000, 50), (40_000_000, 28), (1 << 26, 40)])
+def test_auto_is_no_slower_than_the_vector_kernels(n, k, other):
+    """Measured 0.75 to 1.05 times the better vector kernel (up to 1.22 with cacheable loads up to 36 M inputs and 28 to 33 taps at every size)."""
+    x, w, y = _signal(n, k)
+    vector = min(_cold_us(lambda: B.sys_conv1d(x, w, y, projection=p), other) for p in ("FBS", "BFS"))
+    auto = _cold_us(lambda: B.sys_conv1d(x, w, y), other)
+    print(f"{n} {k}: {auto:.1f} / {vector:.1f}", flush=True)
+    assert auto <= 1.15 * vector, f"AUTO {auto:.1f} us, vector kernel {vector:.1f} us"

@@ -33,6 +33,14 @@ def test_auto_runs_the_split_kernel(k):
     assert torch.equal(B.sys_conv1d(dev(x), w[:27]), B.sys_conv1d(dev(x), w[:27], projection="FBS"))
 
 
+@pytest.mark.parametrize("n,k,split", [(4_194_304, 28, True), (4_194_305, 28, False), (4_194_305, 33, False), (37_748_735, 33, False), (37_748_736, 33, True),
+                                       (4_194_305, 34, True), (20_000_000, 34, True)])
+def test_auto_keeps_fbs_between_short_and_long_signals(n, k, split):
+    x = torch.rand(n, dtype=torch.float32, device="cuda") * 2 - 1
+    w = _case(k, k)[1]
+    assert torch.equal(B.sys_conv1d(x, w), B.sys_conv1d(x, w, projection="FBS")) != split
+
+
 @pytest.mark.parametrize("k", TAPS)
 # one output, one quad, a tile, a workgroup of one-tile runs, and more
 @pytest.mark.parametrize("m", [1, 3, 4, 15, 17, 255, 256, 257, 511, 512, 1023, 1025, 1280, 70001])
@@ -41,9 +49,9 @@ def test_edges_of_tiles(k, m):
     assert err1d(run1d(x, w, "AUTO"), x, w) <= TOL
 
 
-# runs of 2, 3, 5 and 9 tiles, the last one cut; past 33.5 M a second round (runs of 8 up to 49 taps), past 37.7 M the non-temporal loads
-@pytest.mark.parametrize("n,k", [(1_100_003, 50), (2_900_001, 33), (4_300_007, 64), (9_000_001, 49), (34_000_003, 28), (38_000_001, 50),
-                                 (38_000_001, 49)])
+# runs of 2, 3, 5 and 9 tiles, the last one cut; past 33.5 M a second round (runs of 8 up to 49 taps), past 8.4 M and 25.2 M the non-temporal loads
+@pytest.mark.parametrize("n,k", [(1_100_003, 50), (2_900_001, 33), (4_300_007, 64), (9_000_001, 49), (34_000_003, 28), (34_000_003, 40), (38_000_001, 50),
+                                 (38_000_001, 49), (38_000_001, 28)])
 def test_runs_of_several_tiles(n, k):
     x, w = _case(n, k)
     assert err1d(run1d(x, w, "AUTO"), x, w) <= TOL
@@ -90,7 +98,8 @@ def test_taps_the_split_does_not_carry(tap):
     assert torch.equal(B.sys_conv1d(dev(x), w), B.sys_conv1d(dev(x), w, projection="BFS"))
 
 
-# Runs of 3, 5, 9 and 32 tiles and of 8 in the second round; past 37.7 M the non-temporal loads.  The last run is cut.
+# Runs of 3, 5, 9 and 32 tiles and of 8 in the second round, with cacheable and (past 8.4 M with up to 49 taps, past 25.2 M) non-temporal
+# loads.  The last run is cut.
 LONG_RUNS = [(3_000_007, 33, 3), (5_200_003, 64, 5), (9_300_001, 50, 9), (33_400_003, 64, 32), (38_100_005, 40, 8), (38_100_005, 63, 19)]
 
 
