@@ -123,6 +123,25 @@ def test_1d_paper_shape_stride1(signal, proj, k):
     _check_1d(signal, y, w, 1, rng, f"{proj} k={k}")
 
 
+@pytest.mark.parametrize("k", [28, 49, 50, 64])
+def test_1d_paper_shape_long_filters(signal, k):
+    """The matrix-core kernel behind AUTO (both instruction counts); a value that it does not carry lies past output 2^29."""
+    rng = np.random.default_rng(10 + k)
+    w = rng.uniform(-1, 1, k).astype(np.float32)
+    n = OUTPUTS + k - 1
+    at = (1 << 29) + 300
+    kept = float(signal[at])
+    try:
+        signal[at] = 2.0 ** 85
+        y = B.sys_conv1d(signal[:n], w)
+        torch.cuda.synchronize()
+        assert y.shape == (OUTPUTS,)
+        _check_1d(signal, y, w, 1, rng, f"AUTO k={k}")
+        assert torch.equal(y[at - k + 1:at + 1], B.sys_conv1d(signal[at - k + 1:at + k], w, projection="BFS"))
+    finally:
+        signal[at] = kept
+
+
 @pytest.mark.parametrize("k", [2, 5, 16])
 def test_1d_paper_shape_stride2(signal, k):
     rng = np.random.default_rng(20 + k)
