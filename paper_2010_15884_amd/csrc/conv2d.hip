@@ -257,15 +257,17 @@ __device__ __forceinline__ int opaque_zero()
 // A wavefront walks `rows` output rows of one strip; PD input rows are in
 // flight ahead of the one being consumed (PD divides KH so that the slot of a
 // row in the prefetch ring is a compile-time constant of the unrolled loop).
-// EDGE = the strip reaches past the right edge of the image: only then are
-// loads clamped to the row (EdgeQuad; at least 8 columns here) and stores bounds-checked per lane.
+// A strip that reaches past the right edge of the image checks its stores per lane, and its loads in one of two ways: kEdge, where some of its 256
+// columns are missing, loads them clamped to the row (EdgeQuad; at least 8 columns here) and has no halo; kNarrow checks every load, which
+// costs nothing where the 256 columns are all there.
 enum BfsMode { kBfsFirst, kBfsMiddle, kBfsLast, kBfsChecked };
 
-template <int KH, int KW, int PD, bool EDGE>
+template <int KH, int KW, int PD, StripKind KIND>
 struct BfsStrip {
     static_assert(KH % PD == 0, "prefetch depth must divide the filter height");
     static constexpr bool kReloadTaps = KH * KW > 25;
     static constexpr int NH = (KW + 2) / 4;                                // halo float4s: ceil((KW-1)/4)
+    static constexpr bool EDGE = KIND != kInside;
 
     const float* __restrict__ xrow;
     float* __restrict__ yrow;
@@ -284,19 +286,26 @@ struct BfsStrip {
         // Halo: the KW-1 columns right of the strip, fetched by lane 63 alone (one
         // 16-byte access per float4) into the registers that the window hand-overs
         // leave untouched in that lane.
-        if (last_lane) {
+        if (KIND != kEdge && last_lane) {
 #pragma unroll
             for (int j = 0; j < NH; ++j) {
-                const int at = col + 4 * (j + 1);
-                const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? EdgeQuad(at, w_img).at : at));
-                h[j][0] = t.x; h[j][1] = t.y; h[j][2] = t.z; h[j][3] = t.w;
+                if (KIND == kNarrow) {
+                    load4_guarded<false>(p, col + 4 * (j + 1), w_img, h[j]);
+                } else {
+                    const f4u t = *reinterpret_cast<const f4u*>(p + col + 4 * (j + 1));
+                    h[j][0] = t.x; h[j][1] = t.y; h[j][2] = t.z; h[j][3] = t.w;
+                }
             }
+        }
+        if (KIND == kNarrow) {
+            load4_guarded<false>(p, col, w_img, v);
+            return;
         }
         // plain (cacheable) loads: the KH-1 halo rows are read again by the wavefront
         // working on the next row block and should then come from L2 / the memory-side
         // cache, not from HBM (measured on 4096^2, 5x5: 33 us against 43 us with the
         // non-temporal hint)
-        const f4u t = *reinterpret_cast<const f4u*>(p + (EDGE ? EdgeQuad(col, w_img).at : col));
+        const f4u t = *reinterpret_cast<const f4u*>(p + (KIND == kEdge ? EdgeQuad(col, w_img).at : col));
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
 
@@ -322,12 +331,8 @@ struct BfsStrip {
 #pragma unroll
             for (int j = 0; j < NH; ++j)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) hin[j][i] = halo[ph % PD][j][i];
-            if (EDGE) {
-                EdgeQuad(col, w_img).put_right(win[0], win[1], win[2], win[3]);
-#pragma unroll
-                for (int j = 0; j < NH; ++j) EdgeQuad(col + 4 * (j + 1), w_img).put_right(hin[j][0], hin[j][1], hin[j][2], hin[j][3]);
-            }
+                for (int i = 0; i < 4; ++i) hin[j][i] = KIND == kEdge ? 0.0f : halo[ph % PD][j][i];
+            if (KIND == kEdge) EdgeQuad(col, w_img).put_right(win[0], win[1], win[2], win[3]);
             load_row(rho + PD, ring[ph % PD], halo[ph % PD]);
             // X(c) <- X(c+1): lanes 0..62 take the value of the lane above, lane 63 takes
             // the next halo element
@@ -404,7 +409,10 @@ struct BfsStrip {
 // kernel-argument segment; reading them through that segment's pointer keeps
 // run-time-indexed taps on the scalar load path (indexing the by-value struct
 // itself can make the compiler copy it to scratch).
-template <int KH, int KW, int PD>
+// Two kernels, by the right-hand strips (bfs_strip_right): with clamped columns and halo in one body, inside strips lost registers too (us, guarded
+// everywhere / so / this: 8192^2 8x8 159 / 168 / 158, 10x10 217 / 228 / 217, 11x11 254 / 266 / 254, 3001x4003 8x8 38.5 / 37.6 / 34.0, 11x11 67.0 / 59.5 / 57.4,
+// 1500^2 8x8 15.1 / 12.9 / 12.5, 501x703 11x11 14.9 / 11.5 / 10.4).
+template <int KH, int KW, int PD, StripKind RIGHT>
 __global__ __launch_bounds__(kBlock) void conv2d_bfs_kernel(TapsOf<KH * KW> taps, const float* __restrict__ x,
                                                             float* __restrict__ y, int w_img, long long xp, int oh,
                                                             int ow, long long yp, int rows, int row_blocks,
@@ -425,11 +433,11 @@ __global__ __launch_bounds__(kBlock) void conv2d_bfs_kernel(TapsOf<KH * KW> taps
     const bool last_lane = lane == kWave - 1;
     constexpr int halo_cols = kTile * ((KW + 2) / 4);
     if (col0 + kStrip + halo_cols <= w_img) {
-        BfsStrip<KH, KW, PD, false> st{xrow, yrow, col0 + kTile * lane, w_img, ow, rows_out, rows_in,
+        BfsStrip<KH, KW, PD, kInside> st{xrow, yrow, col0 + kTile * lane, w_img, ow, rows_out, rows_in,
                                        xp, yp, last_lane, {}, {}, {}};
         st.run(taps_f);
     } else {
-        BfsStrip<KH, KW, PD, true> st{xrow, yrow, col0 + kTile * lane, w_img, ow, rows_out, rows_in,
+        BfsStrip<KH, KW, PD, RIGHT> st{xrow, yrow, col0 + kTile * lane, w_img, ow, rows_out, rows_in,
                                       xp, yp, last_lane, {}, {}, {}};
         st.run(taps_f);
     }
@@ -778,6 +786,13 @@ void fill_taps(Taps2D& taps, const float* f, int n)
     for (int i = 0; i < kMaxK2D * kMaxK2D + 7; ++i) taps.f[i] = i < n ? f[i] : 0.0f;
 }
 
+// kEdge takes the last strip where some of its columns are missing, as long as the strip before it has its whole halo (in whole quads).
+StripKind bfs_strip_right(int w, int strips, int kw)
+{
+    const int last = (strips - 1) * kStrip;
+    return w - last < kStrip && (strips == 1 || w - last >= kTile * ((kw + 2) / 4)) ? kEdge : kNarrow;
+}
+
 // Shared launcher of the two strip-walking kernels (BFS and SBM).
 template <int KH, int KW, int PD, bool SBM>
 hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f, float* y, size_t yp, hipStream_t s)
@@ -817,7 +832,7 @@ hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f,
                            taps, x, y, w, (long long)xp, oh, ow, (long long)yp, rows, row_blocks, strips, band_width(xp),
                            (int)per_xcd, valid_lanes);
     else
-        hipLaunchKernelGGL((conv2d_bfs_kernel<KH, KW, PD>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL((bfs_strip_right(w, strips, KW) == kEdge ? conv2d_bfs_kernel<KH, KW, PD, kEdge> : conv2d_bfs_kernel<KH, KW, PD, kNarrow>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
                            taps, x, y, w, (long long)xp, oh, ow, (long long)yp, rows, row_blocks, strips, band_width(xp),
                            (int)per_xcd, valid_lanes);
     return hipGetLastError();

@@ -40,3 +40,10 @@ def test_strips_that_end_inside_a_quad(proj, kh, kw, w):
                                           ("SBM", 2, 2, 2), ("SBM", 3, 3, 3)])
 def test_fewer_than_four_columns(proj, kh, kw, w):
     _check(proj, kh, kw, 200, w)
+
+
+@pytest.mark.parametrize("k", [8, 9, 10, 11])
+@pytest.mark.parametrize("w", [11, 12, 255, 256, 257, 263, 264, 265, 266, 267, 268, 269, 511, 512, 520, 522, 523, 524, 700, 1500])
+def test_bfs_strips_with_and_without_a_halo(k, w):
+    """Last strips with all their 256 columns, with fewer, and ones before them whose halo ends inside a quad."""
+    _check("BFS", k, k, 61, w)

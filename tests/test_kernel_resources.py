@@ -1,0 +1,45 @@
+"""Registers and scratch memory of the built kernels, from the code object's own metadata (no GPU).
+
+The vector-ALU kernels hide memory latency with wavefronts, and a second body in a kernel (the right-hand strips) costs the first its registers: lines
+below are what the wavefronts a SIMD were measured with (512 registers a SIMD lane, allocated in eights).
+"""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2010_15884_amd import binding as B
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("code")
+    fat, obj = str(tmp / "fat"), str(tmp / "code.o")
+    subprocess.run([f"{LLVM}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", B.LIB_PATH, str(tmp / "unused")], check=True)
+    data = open(fat, "rb").read()
+    found = {}
+    # one bundle per translation unit
+    starts = [m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data)]
+    for a, b in zip(starts, starts[1:] + [len(data)]):
+        open(fat, "wb").write(data[a:b])
+        subprocess.run([f"{LLVM}/clang-offload-bundler", "--type=o", "--unbundle", f"--input={fat}", f"--output={obj}",
+                        "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", obj], check=True, capture_output=True, text=True).stdout
+        for entry in notes.split("  - .agpr_count")[1:]:
+            field = lambda n: re.search(rf"\.{n}:\s+(\S+)", entry).group(1)
+            found[field("name")] = {n: int(field(n)) for n in ("vgpr_count", "sgpr_count", "private_segment_fixed_size")}
+    assert len(found) > 200
+    return found
+
+
+def test_no_kernel_uses_scratch_memory(kernels):
+    assert not [n for n, r in kernels.items() if r["private_segment_fixed_size"]]
+
+
+@pytest.mark.parametrize("k,most", [(8, 80), (9, 72), (10, 88), (11, 90)])
+def test_bfs_strips_keep_their_wavefronts(kernels, k, most):
+    mine = [r["vgpr_count"] for n, r in kernels.items() if f"conv2d_bfs_kernelILi{k}E" in n]
+    assert mine and max(mine) <= most
