@@ -20,10 +20,12 @@ constexpr int kTaps2DLen = kMaxK2D * kMaxK2D + 7;
 struct Taps2D { float f[kTaps2DLen]; };
 
 // The same for kernels whose filter size is known at compile time: the argument block is written across the bus at every launch, and
-// a launch with 1 KB of arguments costs the host up to 1.2 us more than one with 100 bytes (3.8 / 2.6).
+// a launch with 1 KB of arguments costs the host up to 1.2 us more than one with 100 bytes (3.8 / 2.6).  At least 256 bytes, so that the arguments behind
+// the taps begin a block of their own: every wavefront reads both first (4096^2 5x5 with 64 / 128 / 192 / 256 / 448 / 928 bytes 23.8 / 23.6 / 23.35 / 23.25 / 23.28 /
+// 23.5 us; other sizes level).
 template <int N>
 struct TapsOf {
-    static constexpr int kLen = (N + 15) / 16 * 16;      // whole 64-byte scalar loads
+    static constexpr int kLen = N <= 64 ? 64 : (N + 15) / 16 * 16;       // whole 64-byte scalar loads
     float f[kLen];
     TapsOf(const float* from, int n)
     {

@@ -31,6 +31,8 @@ def kernels(tmp_path_factory):
         for entry in notes.split("  - .agpr_count")[1:]:
             field = lambda n: re.search(rf"\.{n}:\s+(\S+)", entry).group(1)
             found[field("name")] = {n: int(field(n)) for n in ("vgpr_count", "sgpr_count", "private_segment_fixed_size")}
+            sizes = re.search(r"\.args:(.*?)\.group_segment", entry, re.S).group(1)
+            found[field("name")]["first_argument"] = next((int(v) for o, v in re.findall(r"\.offset:\s+(\d+)\s+\.size:\s+(\d+)", sizes) if o == "0"), 0)
     assert len(found) > 200
     return found
 
@@ -43,3 +45,9 @@ def test_no_kernel_uses_scratch_memory(kernels):
 def test_bfs_strips_keep_their_wavefronts(kernels, k, most):
     mine = [r["vgpr_count"] for n, r in kernels.items() if f"conv2d_bfs_kernelILi{k}E" in n]
     assert mine and max(mine) <= most
+
+
+def test_arguments_behind_the_taps_begin_a_block_of_their_own(kernels):
+    taps = {n: r["first_argument"] for n, r in kernels.items() if "TapsOf" in n}
+    assert len(taps) > 100
+    assert not {n: b for n, b in taps.items() if b < 256 or b > 1024}
