@@ -647,7 +647,10 @@ __device__ __forceinline__ void bfs_block_rows(kernarg_floats taps_f, const floa
     }
 }
 
-template <int KH, int KW, int ROWS>
+// Two kernels, by how the right-hand strips load: kNarrow (every load checked) where the width is a multiple of four, as whole quads end at the edge and
+// nobody waits (4096^2 5x5 with clamped loads 24.0 / 24.9 us), and below four columns; kEdge elsewhere.  Both bodies in one kernel cost the
+// first registers (us, one kernel / two: 1024^2 7x7 6.01 / 5.87, 2048^2 5x5 9.25 / 9.17, 4096^2 5x5 23.82 / 23.56, 7x7 33.35 / 32.92, 8192^2 5x5 103.6 / 102.2; others level).
+template <int KH, int KW, int ROWS, StripKind RIGHT>
 __global__ __launch_bounds__(kBlock) void conv2d_bfs_block_kernel(TapsOf<KH * KW> taps, const float* __restrict__ x,
                                                                   float* __restrict__ y, int w_img, long long xp,
                                                                   int oh, int ow, long long yp, int row_blocks,
@@ -670,10 +673,8 @@ __global__ __launch_bounds__(kBlock) void conv2d_bfs_block_kernel(TapsOf<KH * KW
     constexpr int halo_cols = kTile * ((KW + 2) / 4);
     if (col0 + kStrip + halo_cols <= w_img)
         bfs_block_rows<KH, KW, ROWS, kInside>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
-    else if (w_img >= 4 && (w_img & 3) != 0)                               // (whole quads up to the edge: nobody waits, 4096^2 5x5 24.0 / 24.9 us)
-        bfs_block_rows<KH, KW, ROWS, kEdge>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
     else
-        bfs_block_rows<KH, KW, ROWS, kNarrow>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
+        bfs_block_rows<KH, KW, ROWS, RIGHT>(taps_f, xrow, yrow, col0, lane, w_img, xp, ow, yp, rows_out);
 }
 
 // ----------------------------------------------------- SBM 2-D, block form ---
@@ -974,7 +975,8 @@ hipError_t launch_bfs_block(const float* x, int h, int w, size_t xp, const float
     const long long blocks = wide ? tile_workgroups_wide(row_blocks, strips, per_xcd)
                                   : tile_workgroups(row_blocks, strips, per_xcd);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((conv2d_bfs_block_kernel<KH, KW, ROWS>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+    const bool quads = w < 4 || (w & 3) == 0;
+    hipLaunchKernelGGL((quads ? conv2d_bfs_block_kernel<KH, KW, ROWS, kNarrow> : conv2d_bfs_block_kernel<KH, KW, ROWS, kEdge>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
                        taps, x, y, w, (long long)xp, oh, ow, (long long)yp, row_blocks, strips, band_width(xp),
                        (int)per_xcd, wide);
     return hipGetLastError();

@@ -47,6 +47,13 @@ def test_bfs_strips_keep_their_wavefronts(kernels, k, most):
     assert mine and max(mine) <= most
 
 
+@pytest.mark.parametrize("k,vector,scalar", [(2, 22, 43), (3, 28, 50), (4, 38, 62), (5, 51, 65), (6, 68, 92), (7, 89, 106)])
+def test_bfs_blocks_on_whole_quads_keep_their_registers(kernels, k, vector, scalar):
+    """kNarrow (2), the kernel for widths that are multiples of four: what it had before clamped loads came to the others."""
+    mine = [r for n, r in kernels.items() if f"conv2d_bfs_block_kernelILi{k}E" in n and "StripKindE2" in n]
+    assert len(mine) == 1 and mine[0]["vgpr_count"] <= vector and mine[0]["sgpr_count"] <= scalar
+
+
 def test_arguments_behind_the_taps_begin_a_block_of_their_own(kernels):
     taps = {n: r["first_argument"] for n, r in kernels.items() if "TapsOf" in n}
     assert len(taps) > 100
