@@ -74,7 +74,10 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_kernel(const float* __restr
                 const int rr = r0 + k * kWaves;
                 if (rr >= in_rows) break;                                  // uniform
                 float t[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-                if (edge) quad.put_right(t[0], t[1], t[2], t[3]);
+                if (edge) {
+                    asm volatile("");                                      // a branch, not selects in every tile (8192^2 9x9 229 / 217 us)
+                    quad.put_right(t[0], t[1], t[2], t[3]);
+                }
                 *reinterpret_cast<f4*>(tile + rr * kStrip + kTile * lane) = f4{t[0], t[1], t[2], t[3]};
             }
         }
