@@ -27,7 +27,7 @@ constexpr int kCols = 2 * kStrip;                        // input columns of a s
 // load is 1 KB of consecutive addresses) to the array's (lane l: columns 8l .. 8l+7, four PEs), through 2 KB of LDS that
 // belong to the wavefront.  Loaded straight by the lanes that need them, every cache line was asked for twice (us,
 // before / with the exchange: 8192^2 5x5 68.4 / 62.0, 4x4 65.3 / 59.8; 4095x6001 5x5 30.6 / 26.3).  In the strip form
-// below, whose row loop waits for each exchange, it costs more than it gives (4095x6001 7x7 35.9 / 38.1).
+// below, whose row loop waits for each exchange, it costs more than it gives (4095x6001 7x7 30.2 / 30.5, 8192^2 11x11 94 / 101).
 __device__ __forceinline__ void exchange_row(float* __restrict__ slot, int lane, float (&v)[8])
 {
     *reinterpret_cast<f4*>(slot + kTile * lane) = f4{v[0], v[1], v[2], v[3]};
@@ -40,12 +40,11 @@ __device__ __forceinline__ void exchange_row(float* __restrict__ slot, int lane,
 }
 
 // ------------------------------------------------------------ block form ----
-// For the small square filters of the paper's experiment (Section 6) the same array
-// without staged tiles: a wavefront takes ROWS output rows of a strip of 512 input columns,
+// For the small square filters of the paper's experiment (Section 6): a wavefront takes ROWS output rows of a strip of 512 input columns,
 // requests all 2*(ROWS-1)+KH input rows up front (four consecutive inputs of either half of
 // a row per lane) and then, input row by input row, passes the row through its own 2 KB of
 // LDS (exchange_row), builds the shifted windows of the even and of the odd chain once and applies them to every output row whose filter covers that input
-// row (p = rho - 2r).  Strips overlap like the tiles above: the PEs whose even chain
+// row (p = rho - 2r).  Strips overlap: the PEs whose even chain
 // would reach past lane 63 compute values that are never stored.
 template <int KH, int KW, int ROWS, bool EDGE, bool EXCHANGE>
 __device__ __forceinline__ void stride2_block_rows(kernarg_floats taps_f, const float* __restrict__ xrow,
@@ -139,19 +138,15 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_block_kernel(TapsOf
     const bool lane_valid = lane < valid_lanes;
     const int in_col = 2 * out_col0, out_col = out_col0 + kTile * lane;
     // interior strips: all 512 input columns exist, and then so do the valid lanes' outputs
-    // A right-hand strip more than half full of a 2x2 filter loads straight to the lanes: where every load is checked, four rows do
-    // not make up for the exchange (us, straight / exchanged: 266x1790 outputs 5.1 / 6.1, 1211x673 6.2 / 6.8, 442x3324 7.5 / 8.2; but
-    // half full and less 1221x284 6.1 / 5.3, 254x1656 5.2 / 4.9; level on 4 M outputs).
+    // A right-hand strip of a 2x2 filter loads straight to the lanes: four rows do not make up for the exchange (us, straight / exchanged: 250x127
+    // outputs 2.28 / 2.46, 150x230 2.46 / 2.63, 500x500 3.05 / 3.14, 1221x284 3.53 / 3.64; level from 1 M outputs on).
     float* const own = slots[wave_in_block()];
     if (2 * out_col0 + kCols <= w_img)
         stride2_block_rows<KH, KW, ROWS, false, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out,
                                                       lane_valid, own, lane);
-    else if (KH == 2 && 2 * out_col0 + kStrip < w_img)
+    else
         stride2_block_rows<KH, KW, ROWS, true, KH != 2>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out,
                                                         lane_valid, own, lane);
-    else
-        stride2_block_rows<KH, KW, ROWS, true, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, rows_out,
-                                                     lane_valid, own, lane);
 }
 
 template <int KH, int KW, int ROWS>

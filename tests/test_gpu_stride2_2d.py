@@ -162,7 +162,7 @@ def test_stride2_2d_strips_keep_infinities_in_their_windows(kh, kw, h, w):
 
 @pytest.mark.parametrize("w", [200, 257, 505, 508, 511, 512, 513, 761, 1016, 1300])
 def test_stride2_2d_2x2_right_hand_strip(w):
-    """The last strip of 2x2 filters, which loads its lanes straight where it is more than half full (504 input columns a strip)."""
+    """The last strip of 2x2 filters, which loads its lanes straight where the others exchange (504 input columns a strip)."""
     x, f = W.random_case(w, (41, w), (2, 2), x_range=(0.0, 1.0))
     assert err(run(x, f), x, f) <= TOL
 
