@@ -314,11 +314,12 @@ hipError_t launch_strip_by_kw(std::integer_sequence<int, KW0, KW...>, const floa
 
 }  // namespace
 
-// Output rows of a wavefront, filters with a block form aside.  One row reads the most halo rows and gives the most wavefronts and
+// Output rows of a wavefront, filters with a block form aside: 1, 2 or 3.  One row reads the most halo rows and gives the most wavefronts and
 // the shortest, which decides while they do not fill the chip; 250 random shapes, two rows / one row by wavefronts of one row: filters of
 // more than 60 taps up to 2000 1.27 to 1.30, 2000 to 3000 1.21, 3000 to 4096 1.06, above 5000 0.92 to 1.02; 25 to 60 taps 1.24, 1.17, 1.0,
-// 0.88; fewer 1.10, 1.03, 0.93.  So filters of up to kFewTaps taps (0) take one row up to 3000 wavefronts, the others (2) up to one round of
-// the chip, and single-row filters, whose rows share nothing, always (1x14 on 3964x2242 inputs 10.1 / 7.6 us).  Three rows need images large
+// 0.88; fewer 1.10, 1.03, 0.93.  So filters of up to kFewTaps taps take one row up to 3000 wavefronts, the others up to one round of the chip.
+// Single-row filters, whose output rows share no input row, take one at every size (us, three rows / two / one: 1x5 on 3000^2 inputs 8.4 / 8.1 / 6.3, on 8192^2
+// 56.6 / 49.5 / 32.9, 1x11 on 4096^2 14.4 / 12.8 / 10.4; 1x14 two / one 13.1 / 10.6).  Three rows need images large
 // enough to fill the chip with fewer wavefronts and few enough columns that their taps stay in scalar registers (2 rows / 3
 // rows from 2 M outputs on: 8x8 on 892x2450 outputs 14.6 / 12.8 us, 7x7 on 2447^2 29.7 / 27.5).
 // LDS tiles shared by four wavefronts, which smaller images used to take, are slower than two rows on 399 of 400 random shapes
@@ -326,8 +327,11 @@ hipError_t launch_strip_by_kw(std::integer_sequence<int, KW0, KW...>, const floa
 constexpr int kOneRowFew = 3000, kOneRow = 4096, kFewTaps = 40;
 int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw)
 {
+    if (kh == 1) return 1;
     if (kw > 1 && kw <= 11 && (double)oh * ow >= 2e6) return 3;
-    return kh * kw <= kFewTaps ? 0 : 2;
+    const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
+    const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
+    return wavefronts <= (kh * kw <= kFewTaps ? kOneRowFew : kOneRow) ? 1 : 2;
 }
 
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
@@ -345,15 +349,8 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         default: break;
         }
     }
-    const int oh = (h - kh) / 2 + 1, ow = (w - kw) / 2 + 1;
-    int rows = conv2d_stride2_strip_rows(oh, ow, kh, kw);
-    if (rows != 3) {
-        const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
-        const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
-        rows = kh == 1 || wavefronts <= (rows == 0 ? kOneRowFew : kOneRow) ? 1 : 2;
-    }
     using Widths = std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>;
-    switch (rows) {
+    switch (conv2d_stride2_strip_rows((h - kh) / 2 + 1, (w - kw) / 2 + 1, kh, kw)) {
     case 1: return launch_strip_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
     case 2: return launch_strip_by_kw<2>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
     default:

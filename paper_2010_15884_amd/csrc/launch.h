@@ -74,7 +74,7 @@ hipError_t launch_conv1d_stt(const float* x, size_t n, const float* w, int k, fl
 
 hipError_t launch_conv2d_fbs(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                              float* y, size_t yp, hipStream_t s);
-int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);     // 3, or 2 / 0: two or one (conv2d_stride2.hip); filters with a block form aside
+int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);     // output rows of a wavefront, 1 to 3; filters with a block form aside
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                      float* y, size_t yp, hipStream_t s);
 bool has_conv2d_fbs_static(int kh, int kw);      // sizes the FBS tile kernel is specialised for

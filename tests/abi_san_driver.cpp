@@ -207,24 +207,34 @@ int main()
         EXPECT(sysconv::conv1d_split_pays(n, SYS_MAX_K1D), 1);
     }
 
-    // ---- stride 2: tiles (0) or strips of two or three rows, all three timed at each shape
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1137, 1676, 6, 3), 0);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(2910, 100, 2, 5), 0);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1529, 800, 10, 1), 0);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1982, 1115, 1, 14), 0);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(143, 193, 15, 15), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(109, 3025, 6, 8), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(257, 1857, 14, 14), 2);
+    // ---- stride 2: output rows of a wavefront, on both sides of every line
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3000, 200, 4, 10), 1);       // up to 40 taps: 3000 wavefronts of one row
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3001, 200, 4, 10), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1500, 253, 3, 4), 1);        // (strips of 252 columns)
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1501, 253, 3, 4), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1500, 256, 10, 1), 1);       // (of 256 for one column)
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3001, 256, 10, 1), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(4096, 200, 6, 7), 1);        // more taps: 4096
+    EXPECT(sysconv::conv2d_stride2_strip_rows(4097, 200, 6, 7), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(2048, 496, 15, 15), 1);      // (of 248 columns)
+    EXPECT(sysconv::conv2d_stride2_strip_rows(2049, 496, 15, 15), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1000, 1999, 7, 7), 2);       // 2 M outputs
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1000, 2000, 7, 7), 3);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 2, 11), 3);      // 2 to 11 columns
+    EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 2, 12), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 15, 1), 2);
+    for (int kw = 1; kw <= SYS_MAX_K2D; ++kw) EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 1, kw), 1);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1137, 1676, 6, 3), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(2910, 100, 2, 5), 1);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(143, 193, 15, 15), 1);
     EXPECT(sysconv::conv2d_stride2_strip_rows(769, 1865, 7, 7), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(654, 1920, 13, 13), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(2045, 2998, 7, 7), 3);
     EXPECT(sysconv::conv2d_stride2_strip_rows(4089, 4089, 15, 15), 2);
     for (int kh = 1; kh <= SYS_MAX_K2D; ++kh)
         for (int kw = 1; kw <= SYS_MAX_K2D; ++kw)
             for (int oh : {1, 8, 1000, 20000, INT_MAX / 2 + 1})
                 for (int ow : {1, 252, 1000, 20000, INT_MAX / 2 + 1}) {
                     const int rows = sysconv::conv2d_stride2_strip_rows(oh, ow, kh, kw);
-                    if (rows != 0 && rows != 2 && !(rows == 3 && kw >= 2 && kw <= 11)) ++failures;
+                    if (rows != 1 && rows != 2 && !(rows == 3 && kw >= 2 && kw <= 11)) ++failures;
                 }
 
     // ---- queries over their whole domain and beyond

@@ -123,15 +123,16 @@ def test_stride2_2d_unsupported_requests_launch_nothing():
     assert (y == 7.0).all()
 
 
-# Every width the strips are built for, 1 .. 15 columns of two rows and 2 .. 11 of three.  4003 x 4099 has 4.1 M outputs
-# (three rows; the last block of one or two; two rows for 1 and for 12 columns and more), 2801 x 4101 2.9 M (two rows: more tiles
-# than fit the chip at once, whatever the filter's height), 700 x 2301 0.4 M (tiles).
+# Every width and number of rows that the strips are built for: one and two rows of 1 .. 15 columns, three of 2 .. 11.  700 x 2301 inputs take one
+# row, 2401 x 2403 two, 4003 x 4099 and 2801 x 4101 three (the last block of one or two; two rows for 1 and for 12 columns and more), as
+# test_stride2_rules.py checks without a GPU.
 STRIPS = [(15, 1), (1, 1), (9, 2), (13, 3), (3, 4), (4, 5), (1, 6), (6, 6), (7, 7), (2, 8), (9, 9), (5, 10), (4, 11), (11, 11), (2, 12), (3, 13), (6, 14),
           (15, 15)]
+STRIP_IMAGES = [(4003, 4099), (2801, 4101), (2401, 2403), (700, 2301)]
 
 
 @pytest.mark.parametrize("kh,kw", STRIPS)
-@pytest.mark.parametrize("h,w", [(4003, 4099), (2801, 4101), (700, 2301)])
+@pytest.mark.parametrize("h,w", STRIP_IMAGES)
 def test_stride2_2d_strips_of_two_and_three_rows(kh, kw, h, w):
     """Whole strips and the cut one at the right edge, into a pitched output whose surroundings stay untouched."""
     x, f = W.random_case(kh * 100 + kw, (h, w), (kh, kw), x_range=(0.0, 1.0))
@@ -146,7 +147,7 @@ def test_stride2_2d_strips_of_two_and_three_rows(kh, kw, h, w):
 
 
 @pytest.mark.parametrize("kh,kw", [(6, 6), (13, 3), (15, 15), (15, 1), (2, 2), (4, 4)])
-@pytest.mark.parametrize("h,w", [(4003, 4099), (2801, 4101), (700, 1301)])
+@pytest.mark.parametrize("h,w", [(4003, 4099), (2801, 4101), (2401, 2403), (700, 1301)])
 def test_stride2_2d_strips_keep_infinities_in_their_windows(kh, kw, h, w):
     x, f = W.random_case(kh, (h, w), (kh, kw), x_range=(0.0, 1.0))
     bad = [(0, 0), (h - 1, w - 1), (350, 511), (351, 512)]
