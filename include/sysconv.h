@@ -204,7 +204,7 @@ int sys_conv1d_stt(const float *d_x, size_t n,
  *            are taken with plain multiply-adds: an image with a few of them loses part of the
  *            gain, one with such values everywhere takes up to 1.4 times (twice below 3 M
  *            outputs) what the named projections take, which do not look at the values.  Of the rest, square
- *            filters up to 6x6 run FBS, or mostly BFS where x_pitch * 4 is a power of two of at most
+ *            filters up to 6x6 run FBS, or BFS where x_pitch * 4 is a power of two of at most
  *            16 KB; 7x7 FBS, BFS or SBM by size; 8x8 .. 11x11 SBM; everything else FBS); BFS and SBM are built
  *            for SQUARE filters 2x2 .. 11x11 only (sys_conv2d_has) and return
  *            SYS_ERR_UNSUPPORTED otherwise; BSM, FSM and FFS are 1-D only.  FBS runs

@@ -38,6 +38,31 @@ bool too_wide(int w) { return w > INT_MAX - 2048; }
 
 }  // namespace
 
+// What AUTO takes where the split kernel does not (conv2d_split_pays has that line).  Measured on MI355X, square images of 1000 .. 10240 columns (us, 5x5:
+// BFS / SBM / FBS): 2996^2 15.8 / 14.3 / 14.3, 4604^2 33.9 / 36.4 / 32.5, 5996^2 57.2 / 57.0 / 51.1, 7164^2 81.0 / 83.6 / 75.1, 8188^2 103 / 104 / 95.5, 10236^2
+// 166 / 170 / 155.  Up to 6x6 the FBS tile kernels win by 3 - 17 % except where the input pitch is a power of two of at most 16 KB (1024, 2048, 4096
+// columns): there single-strip order and the BFS block kernel's 1 KB-aligned strips win by 2 - 12 % (4096^2 5x5 23.3 / 24.5 / 25.8, 3x3 22.6 / 23.6 / 23.5, 1024x2048
+// 6x6 7.0 / 8.1 / 7.8, 300x4096 6x6 5.5 / 6.4 / 6.1), or lose 1 to 7 % where the images fill the chip by a few wavefronts more than whole rounds (2048^2 6x6 11.1 /
+// 11.3 / 10.4, 700x4096 5x5 7.4 / 7.6 / 7.2; no line by size holds at other sizes).
+// 7x7: FBS up to 0.9 M outputs (300^2 FBS 4.6, SBM 5.1; 700x1024 5.4 / 6.5, BFS 5.8; 2048x256 5.2 / 6.3 / 5.7); then BFS at power-of-two pitches up to 8 KB
+// (BFS / SBM / FBS 2048x512 6.0 / 7.5 / 6.9, 2048x1024 7.9 / 9.5 / 8.9, 30000x1024 60 / 62 / 67, 2048^2 11.4 / 12.6 / 13.3, 5000x2048 23.2 / 23.6 / 24.1), but SBM with 8 KB rows from
+// 16 M outputs on (12000x2048 50.7 / 48.8 / 51.4, 30000x2048 123 / 116 / 125); else FBS up to 3 M outputs (1700^2 FBS 9.1, SBM 9.8; 1800^2 10.5 / 10.9; 2200^2 13.1 / 12.8)
+// and SBM above (6000^2 73 / 67).  8x8 .. 11x11: SBM.  The rest: FBS.
+namespace sysconv {
+int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw)
+{
+    const size_t pitch_bytes = x_pitch * sizeof(float);
+    const bool pow2_pitch = (pitch_bytes & (pitch_bytes - 1)) == 0;
+    const double outputs = (double)oh * ow;
+    if (kh != kw || kh < 2 || kh > 11) return SYS_PROJ_FBS;
+    if (kh <= 6) return pow2_pitch && pitch_bytes <= 16384 ? SYS_PROJ_BFS : SYS_PROJ_FBS;
+    if (kh >= 8) return SYS_PROJ_SBM;
+    if (outputs <= 0.9e6) return SYS_PROJ_FBS;
+    if (pow2_pitch && (pitch_bytes <= 4096 || (pitch_bytes == 8192 && outputs <= 16e6))) return SYS_PROJ_BFS;
+    return outputs <= 3e6 ? SYS_PROJ_FBS : SYS_PROJ_SBM;
+}
+}  // namespace sysconv
+
 extern "C" {
 
 int sys_conv1d(const float* d_x, size_t n, const float* h_w, int k, float* d_y, int projection,
@@ -182,30 +207,7 @@ int sys_conv2d(const float* d_x, int h, int w, size_t x_pitch, const float* h_f,
     if (proj == SYS_PROJ_AUTO && sysconv::conv2d_split_pays(oh, ow, kh, kw)
         && sysconv::conv2d_split_takes(h, w, y_pitch, h_f, kh, kw))
         return hip_status(sysconv::launch_conv2d_split(d_x, h, w, x_pitch, h_f, kh, kw, d_y, y_pitch, stream));
-    // What the split kernel does not take (conv2d_split_pays has the line and both sides' figures):
-    // Measured on MI355X, square images of 1000 .. 10240 columns (us, 5x5: BFS / SBM / FBS): 2996^2 15.8 / 14.3 / 14.3,
-    // 4604^2 33.9 / 36.4 / 32.5, 5996^2 57.2 / 57.0 / 51.1, 7164^2 81.0 / 83.6 / 75.1, 8188^2 103 / 104 / 95.5, 10236^2 166 / 170 / 155.
-    // Up to 6x6 the FBS tile kernels win by 3 - 17 % except where the input pitch is a power of two of at most 16 KB (1024, 2048, 4096
-    // columns): there single-strip order and the BFS block kernel's 1 KB-aligned strips win by 2 - 12 % (4096^2 5x5 23.8 / 24.4 / 25.6, 3x3
-    // 22.6 / 23.5 / 23.4, 2048^2 5x5 9.1 / 10.1 / 9.5), but for up to 3 M outputs of 16 KB rows (700x4096 5x5 7.4 / 7.5 / 7.0, 3x3 6.7 / 6.7 / 6.5) and
-    // 6x6 between 1.5 M and 8 M (2048^2 11.0 / 11.2 / 10.4, 4096x1024 11.4 / 11.2 / 10.5; but 1024^2 5.7 / 6.3 / 6.1, 4096^2 27.4 / 27.0 / 28.6).
-    // 7x7: SBM, but FBS up to 3 M outputs (345x390 SBM 5.8, FBS 4.8; 1494^2 9.05 / 8.67; 700x4096 9.5 / 9.0; but 2613^2 16.4 / 17.1),
-    // and BFS at power-of-two pitches up to 8 KB (1024^2 SBM 7.3, FBS 6.8, BFS 6.0; 2048^2 12.5 / 13.2 / 11.4).
-    // 8x8 .. 11x11: SBM.  The rest: FBS.
-    if (proj == SYS_PROJ_AUTO) {
-        const size_t pitch_bytes = x_pitch * sizeof(float);
-        const bool pow2_pitch = (pitch_bytes & (pitch_bytes - 1)) == 0;
-        const double outputs = (double)oh * ow;
-        proj = SYS_PROJ_FBS;
-        if (kh == kw && kh >= 2 && kh <= 6 && pow2_pitch && pitch_bytes <= 16384) {
-            if (!(pitch_bytes == 16384 && kh >= 3 && outputs <= 3e6) && !(kh == 6 && outputs > 1.5e6 && outputs < 8e6)) proj = SYS_PROJ_BFS;
-        } else if (kh == 7 && kw == 7) {
-            if (pow2_pitch && pitch_bytes <= 8192) proj = SYS_PROJ_BFS;
-            else if (outputs > 3e6) proj = SYS_PROJ_SBM;
-        } else if (sysconv::has_conv2d_sbm(kh, kw) && kh >= 8) {
-            proj = SYS_PROJ_SBM;
-        }
-    }
+    if (proj == SYS_PROJ_AUTO) proj = sysconv::conv2d_vector_projection(oh, ow, x_pitch, kh, kw);
     switch (proj) {
     case SYS_PROJ_FBS:
         return hip_status(sysconv::launch_conv2d_fbs(d_x, h, w, x_pitch, h_f, kh, kw, d_y, y_pitch, stream));

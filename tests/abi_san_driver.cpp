@@ -21,6 +21,7 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 bool conv2d_split_pays(int oh, int ow, int kh, int kw);
 int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);
 bool conv1d_split_pays(size_t n, int k);
+int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw);
 }
 
 static int failures = 0;
@@ -196,6 +197,32 @@ int main()
     EXPECT(sysconv::conv2d_split_pays(2828, 989, 9, 9), 1);
     EXPECT(sysconv::conv2d_split_pays(3857, 380, 11, 11), 1);
     EXPECT(sysconv::conv2d_split_pays(2039, 2039, 10, 10), 1);
+
+    // ---- AUTO without the split kernel, both sides of every line
+    for (int k = 2; k <= 6; ++k)
+        for (int oh : {1, 300, 2000, 100000}) {
+            for (size_t pitch : {(size_t)16, (size_t)1024, (size_t)2048, (size_t)4096})
+                EXPECT(sysconv::conv2d_vector_projection(oh, 10, pitch, k, k), SYS_PROJ_BFS);
+            for (size_t pitch : {(size_t)15, (size_t)1000, (size_t)4095, (size_t)4100, (size_t)8192, (size_t)1 << 20})
+                EXPECT(sysconv::conv2d_vector_projection(oh, 10, pitch, k, k), SYS_PROJ_FBS);
+        }
+    EXPECT(sysconv::conv2d_vector_projection(900, 1000, 1024, 7, 7), SYS_PROJ_FBS);        // 7x7: 0.9 M outputs
+    EXPECT(sysconv::conv2d_vector_projection(901, 1000, 1024, 7, 7), SYS_PROJ_BFS);
+    EXPECT(sysconv::conv2d_vector_projection(901, 1000, 1008, 7, 7), SYS_PROJ_FBS);
+    EXPECT(sysconv::conv2d_vector_projection(30000, 1000, 1024, 7, 7), SYS_PROJ_BFS);
+    EXPECT(sysconv::conv2d_vector_projection(8000, 2000, 2048, 7, 7), SYS_PROJ_BFS);       // 8 KB rows: 16 M
+    EXPECT(sysconv::conv2d_vector_projection(8001, 2000, 2048, 7, 7), SYS_PROJ_SBM);
+    EXPECT(sysconv::conv2d_vector_projection(750, 4000, 4096, 7, 7), SYS_PROJ_FBS);        // 3 M
+    EXPECT(sysconv::conv2d_vector_projection(751, 4000, 4096, 7, 7), SYS_PROJ_SBM);
+    EXPECT(sysconv::conv2d_vector_projection(3000, 1000, 1007, 7, 7), SYS_PROJ_FBS);
+    EXPECT(sysconv::conv2d_vector_projection(3001, 1000, 1007, 7, 7), SYS_PROJ_SBM);
+    for (int k = 8; k <= 11; ++k)
+        for (size_t pitch : {(size_t)1024, (size_t)1000}) EXPECT(sysconv::conv2d_vector_projection(500, 900, pitch, k, k), SYS_PROJ_SBM);
+    for (int kh = 1; kh <= SYS_MAX_K2D; ++kh)
+        for (int kw = 1; kw <= SYS_MAX_K2D; ++kw) {
+            if (kh == kw && kh >= 2 && kh <= 11) continue;
+            EXPECT(sysconv::conv2d_vector_projection(500, 900, 1024, kh, kw), SYS_PROJ_FBS);
+        }
 
     // ---- long 1-D filters: the split kernel from 34 taps on, and from 28 on below 4 Mi and above 36 Mi inputs
     for (size_t n : {(size_t)64, (size_t)4 << 20, ((size_t)4 << 20) + 1, (size_t)20000000, ((size_t)36 << 20) - 1, (size_t)36 << 20, (size_t)1 << 40}) {

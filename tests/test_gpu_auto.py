@@ -1,5 +1,5 @@
-"""SYS_PROJ_AUTO is a measured choice: on each of the five benchmark workloads, and on two images whose pitch is not
-a power of two (where the rule differs), it must be as fast as the fastest projection the library has built for that
+"""SYS_PROJ_AUTO is a measured choice: on each of the five benchmark workloads, on two images whose pitch is not
+a power of two (where the rule differs), on some where it is, and with long 1-D filters, it must be as fast as the fastest projection the library has built for that
 filter (the opt-in matrix-core projection aside, which AUTO never picks because it restricts the input range).
 
 Timing method: batches of back-to-back launches on rotated buffers (past the 256 MB memory-side cache) between two
@@ -38,6 +38,12 @@ EXTRA = {   # away from the benchmark sizes: 20 KB and 24 KB pitches
     "conv2d_5120_5x5": W.Workload("conv2d_5120_5x5", 2, (5120, 5120), (5, 5), _BASE.x_range, _BASE.w_range, _BASE.seed + 11),
     "conv2d_6144_7x7": W.Workload("conv2d_6144_7x7", 2, (6144, 6144), (7, 7), _BASE.x_range, _BASE.w_range, _BASE.seed + 12),
 }
+# power-of-two pitches of few and many rows, and filters that the matrix cores take in 1-D
+EXTRA.update({f"conv2d_{h}x{w}_{k}x{k}": W.Workload(f"conv2d_{h}x{w}_{k}x{k}", 2, (h, w), (k, k), _BASE.x_range, _BASE.w_range, _BASE.seed + h + k)
+              for h, w, k in [(1024, 2048, 6), (300, 4096, 6), (700, 1024, 7), (12000, 2048, 7)]})
+_SIGNAL = W.WORKLOADS["conv1d_64m_k16"]
+EXTRA.update({f"conv1d_{n}_k{k}": W.Workload(f"conv1d_{n}_k{k}", 1, (n,), (k,), _SIGNAL.x_range, _SIGNAL.w_range, _SIGNAL.seed + k)
+              for n, k in [(300_000, 28), (4_000_000, 33), (16_000_000, 28), (6_000_000, 40), (20_000_003, 63), (50_000_000, 30)]})
 
 
 @pytest.mark.parametrize("name", list(W.ORDER) + list(EXTRA))
