@@ -185,7 +185,9 @@ def _stream_handle(stream) -> Optional[int]:
 
 
 def _device_f32(t, what):
-    c = _calls or _entry_points()
+    c = _calls
+    if c is None:                                  # before the first call: the library need not be there to refuse an argument
+        import torch as c
     if not isinstance(t, c.Tensor) or not t.is_cuda or t.dtype != c.float32:
         raise TypeError(f"{what} must be a float32 CUDA tensor")
     return t
@@ -207,8 +209,8 @@ def _signal(d_x):
 def sys_conv1d(d_x, h_w, d_y=None, projection="AUTO", stream=None):
     """y[c] = sum_q x[c+q] w[q].  d_x: 1-D float32 CUDA tensor; h_w: host taps.
     Returns d_y (allocated with torch if not given)."""
-    c = _calls or _entry_points()
     _signal(d_x)
+    c = _calls or _entry_points()
     w = _taps(h_w)
     n, k = d_x.shape[0], w.shape[0]
     m = n - k + 1 if n >= k else 0
@@ -223,8 +225,8 @@ def sys_conv1d(d_x, h_w, d_y=None, projection="AUTO", stream=None):
 
 def sys_conv1d_strided(d_x, h_w, stride, d_y=None, projection="AUTO", stream=None):
     """y[c] = sum_q x[stride*c+q] w[q], (n-k)//stride + 1 outputs.  Arguments as sys_conv1d."""
-    c = _calls or _entry_points()
     _signal(d_x)
+    c = _calls or _entry_points()
     w = _taps(h_w)
     n, k, stride = d_x.shape[0], w.shape[0], int(stride)
     m = (n - k) // stride + 1 if (stride >= 1 and n >= k) else 0
@@ -282,8 +284,8 @@ def _room_2d(d_y, oh, ow):
 def sys_conv2d(d_x, h_f, d_y=None, projection="AUTO", stream=None):
     """y[r][c] = sum_p sum_q x[r+p][c+q] f[p][q].  d_x: 2-D float32 CUDA tensor whose
     rows are contiguous (stride(1) == 1; stride(0) is the pitch); h_f: host kh x kw taps."""
-    c = _calls or _entry_points()
     f = _image_and_taps(d_x, h_f)
+    c = _calls or _entry_points()
     h, w = d_x.shape
     kh, kw = f.shape
     oh, ow = max(h - kh + 1, 0), max(w - kw + 1, 0)
@@ -299,8 +301,8 @@ def sys_conv2d(d_x, h_f, d_y=None, projection="AUTO", stream=None):
 
 def sys_conv2d_strided(d_x, h_f, stride, d_y=None, projection="AUTO", stream=None):
     """y[r][c] = sum_p sum_q x[stride*r+p][stride*c+q] f[p][q].  Arguments as sys_conv2d."""
-    c = _calls or _entry_points()
     f = _image_and_taps(d_x, h_f)
+    c = _calls or _entry_points()
     h, w = d_x.shape
     kh, kw = f.shape
     stride = int(stride)

@@ -151,6 +151,20 @@ def test_binding_rejects_host_tensors():
         B.sys_conv1d(torch.zeros(10), np.ones(3, np.float32))
 
 
+def test_arguments_are_refused_before_the_library_is_looked_for(monkeypatch):
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(B, "LIB_PATH", "/nowhere/libsysconv.so")
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_calls", None)
+    w, f = np.ones(3, np.float32), np.ones((3, 3), np.float32)
+    for call in (lambda: B.sys_conv1d(torch.zeros(10), w), lambda: B.sys_conv1d_strided(torch.zeros(10), w, 2), lambda: B.sys_conv2d(torch.zeros(9, 9), f),
+                 lambda: B.sys_conv2d_strided(torch.zeros(9, 9), f, 2), lambda: B.sys_conv1d(None, w)):
+        with pytest.raises(TypeError):
+            call()
+    with pytest.raises(FileNotFoundError):
+        B.lib()
+
+
 @pytest.mark.parametrize("args,want", [
     ((None, 100, "w", 5, 2, Y, 1), B.SYS_ERR_NULL),
     ((X, 100, "w", 5, 2, None, 0), B.SYS_ERR_NULL),
