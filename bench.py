@@ -489,7 +489,7 @@ def main() -> int:
                and "y_pitch_floats" not in r]
         if alu:
             best = max(alu, key=lambda r: r["Gtap/s"])
-            kern = {"SBM": "conv2d_sbm_kernel<11, 11, 1>", "BFS": "conv2d_bfs_kernel<11, 11, 1>",
+            kern = {"SBM": "conv2d_sbm_kernel<11, 11, 1>", "BFS": "conv2d_bfs_kernel<11, 11, 1, kNarrow>",
                     "FBS": "conv2d_fbs_kernel<2>"}[best["projection"]]
             alu_traffic, alu_prov = _stored_traffic(f"conv2d_{best['projection'].lower()}_11x11_8k")
             # what the vector ALUs sustain with nothing in the way: the register-only yard-stick, 8 wavefronts per SIMD
@@ -556,7 +556,7 @@ def main() -> int:
         c4 = [r for r in also if r["workload"] == "conv2d_4k_5x5" and r["projection"] != "MFMA"]
         if c4:
             tight = min((r for r in c4 if "y_pitch_floats" not in r), key=lambda r: r["kernel_us_mean"])
-            kern = {"BFS": "conv2d_bfs_block_kernel<5, 5, 2>", "SBM": "conv2d_sbm_block_kernel<5, 5, 4>",
+            kern = {"BFS": "conv2d_bfs_block_kernel<5, 5, 2, kNarrow>", "SBM": "conv2d_sbm_block_kernel<5, 5, 4>",
                     "FBS": "conv2d_fbs_static_kernel<5, 5, 2>"}[tight["projection"]]
             t_traffic, t_prov = _stored_traffic(f"conv2d_{tight['projection'].lower()}_5x5_4k")
             obj = {"workload": "conv2d_4k_5x5", "projection": tight["projection"], "kernel": kern, "bound": "hbm",

@@ -19,7 +19,7 @@
 // pieces change places in pairs instead, free of them by construction, is level to 2 % slower.
 //
 // What bounds it: HBM up to some 24 M inputs, then HBM and the set-up of a run (taps, first loads).  Measured (us, the best vector kernel / this):
-// k = 63 on 20 M 51 / 28 (three inputs in turn, which the memory-side cache holds in part; in no cache 34), k = 64 on 300 K 6.5 / 3.7, on 4 M 14.4 / 9.1, on 2^26 149 / 94; k = 40 on 1 M 6.5 / 4.6, on 16 M 35.6 / 29,
+// k = 63 on 20 M 51 / 28 (three inputs in turn, which the memory-side cache holds in part; in no cache 56 / 37 to 48), k = 64 on 300 K 6.5 / 3.7, on 4 M 14.4 / 9.1, on 2^26 149 / 94; k = 40 on 1 M 6.5 / 4.6, on 16 M 35.6 / 29,
 // on 2^26 113 / 92; k = 28 on 2^26 100 / 93.  A signal with a marked value (NaN) in every tile takes 0.9 to 1.35 times what the best vector
 // kernel takes (us, vector kernel / two tiles at a time behind the whole run / this: k = 28 on 300 K 4.3 / 5.5 / 4.7, 5 M 10.7 / 16.5 / 14.2,
 // 20 M 31 / 47 / 29, 2^26 97 / 160 / 121, there with one in every other tile 97 / 159 / 132; k = 36 on 20 M 39 / 49 / 34; k = 63 on 20 M 52 / 71 / 50, 2^26

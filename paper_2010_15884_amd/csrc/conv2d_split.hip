@@ -26,10 +26,10 @@
 // block, one barrier per chunk, and all indices of the sums are compile-time constants.
 //
 // What bounds it: the power of the package.  11x11 on 8192^2 issues 180 GFLOP; a large bf16 matrix product reaches 1.32 PFLOP/s on this
-// card, at 1.87 GHz, and at that rate the instructions alone take 136 us (15x15 on 3001x4003: 50 GFLOP, 38 us).  With random data the clock
-// falls to 1.55 - 1.96 GHz in this kernel (2.38 with an image of zeros, 136 us), and what saves clocks lowers it further.  By the
+// card (1.39 on another), at 1.87 GHz, and at that rate the instructions alone take 136 us (15x15 on 3001x4003: 50 GFLOP, 38 us).  With random
+// data the clock falls to 1.95 GHz in this kernel (2.39 with an image of zeros, 136 us), and what saves clocks lowers it further.  By the
 // counters the matrix cores are busy for 57 % of the clocks and other vector instructions for 17 %, LDS for 21 to 23 %, HBM reads are
-// 1.06 and 1.28 times the image; the two workgroups of a CU do not share it evenly (ends between 100 and 169 us, half by 112).
+// 1.06 and 1.28 times the image; the two workgroups of a CU do not share it evenly (ends between 96 and 176 us, half by 123).
 // Measured (us, the vector kernels before / this; the best of eight batches, 11x11 on 8192^2 159 and 15x15 46 on average among other
 // passes): 11x11 on 8192^2 243 / 142, 15x15 on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 41.
 // Tried on that account: the next chunk's split placed between the matrix instructions (an MFMA leaves room for two vector instructions)
