@@ -93,7 +93,8 @@ __device__ __forceinline__ void load4_guarded(const float* __restrict__ row, lon
     }
 }
 
-// Kinds of strips: all columns that it loads exist; not all do; loads must be checked one by one (fewer than four columns).
+// Kinds of strips: all columns that it loads exist; not all do, and loads are clamped (EdgeQuad); every load is checked (images of fewer than four
+// columns, and where no lane straddles the edge, so that checking costs nothing).
 enum StripKind { kInside, kEdge, kNarrow };
 
 // Columns [col, col+4) of the rows of an image of w >= 4 columns, for lanes that may reach past the right edge: the last
