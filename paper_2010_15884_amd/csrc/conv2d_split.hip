@@ -21,9 +21,14 @@
 // Data path.  A workgroup of four wavefronts walks down a block of rows of a 256-column strip, 16 input
 // rows (a "chunk") at a time.  A chunk is loaded into registers two chunks ahead of its use, split once
 // (not once per overlapping window) and written to LDS as three bf16 planes one chunk ahead; a lane's
-// operand is then 16 bytes of a plane.  Every unit is read from LDS once and applied to all output
+// operand is then 16 bytes of a plane, read a unit ahead of its use (4 x 4 offsets; us, without / with: 11x11 on 8192^2 177 / 166, on 2000^2 16.8 / 16.2,
+// 12x12 on 500^2 7.4 / 7.05; with 8 x 2 the registers are full).  Every unit is read from LDS once and applied to all output
 // groups it belongs to, whose sums wait in registers: no halo row is loaded or split twice within a
-// block, one barrier per chunk, and all indices of the sums are compile-time constants.
+// block, one barrier per chunk, and all indices of the sums are compile-time constants.  A block ends with any group (matrix_block_groups): the
+// chunk it ends in, and the one that only finishes groups, look at run time which groups there are.
+//
+// Order of the six products: from one to the next only one operand changes, x or f.  That saves power, which is what bounds large images: us, x and f
+// changing / one at a time 8192^2 11x11 166 / 161, 4096^2 9x13 41.0 / 40.2; x held over all groups before the next x part is slower (170).
 //
 // What bounds it: the power of the package.  11x11 on 8192^2 issues 180 GFLOP; a large bf16 matrix product reaches 1.32 PFLOP/s on this
 // card (1.39 on another), at 1.87 GHz, and at that rate the instructions alone take 136 us (15x15 on 3001x4003: 50 GFLOP, 38 us).  With random
@@ -40,9 +45,9 @@
 // branches (every chunk then waits for the stores of the one before), three workgroups a CU (spills at NS = 7, level
 // below).  Reads of 16 bytes from LDS at 8-byte alignment are slow: a window is two 8-byte (8 x 2: four 4-byte) reads.
 #include "launch.h"
+#include "matrix_blocks.h"
 #include "split_bf16.h"
 #include "systolic.h"
-#include "tiling.h"
 
 #include <limits.h>
 
@@ -61,18 +66,9 @@ constexpr int kUnits = kChunk / 2;
 constexpr int kRow = 3 * kInCols;           // a row in LDS, in bf16 numbers: 256 first parts, 256 second, 256 third
 constexpr int kBuf = kChunk * kRow;
 constexpr int kMaxChunks = 64;              // chunks of a row block, the one that only finishes groups among them (marks fill 64 bits)
-constexpr int kNonTemporal = 2;             // the nt bit of a buffer store
 constexpr int kPlainRows = 4;               // output rows a wavefront takes together in plain_rows, and input rows in flight
 constexpr unsigned short kHuge = (127 + 80) << 7;          // upper half of the bits of 2^80
 constexpr unsigned kHugeBits = (kHuge << 16) - 0x8000u;    // the least number whose first part is 2^80
-
-// Barrier for what the workgroup exchanges through LDS: the loads from global memory that are in flight stay so.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 template <int JC, int NS>
 struct SplitShape {
@@ -84,11 +80,10 @@ struct SplitShape {
     static constexpr int PARTS = JC == 4 ? 2 : 1;          // sums of an output: x1f1 apart from the small products
     static constexpr int TROWS = 2 * NS + JR - 1;          // rows of the zero-padded taps
     static constexpr int TCOLS = 16 + JC - 1;
+    static constexpr int TAPS = JC == 4 ? (2 * NS - 3) * 13 : (2 * NS - 7) * 15;       // most taps of a filter that the shape serves
     static_assert(NS - 1 < LIVE * UG, "a slot is free again before its next group starts");
     static_assert((LIVE % GROUPS) == 0 || GROUPS == LIVE, "slots repeat over the chunks");
 };
-
-constexpr int kPlaces = 512;                // workgroups the device holds: two a CU (registers allow 256 a lane)
 
 // Where the marked chunks of a row block make the matrix cores' work pointless: the block then ends with plain_rows for
 // all rows from the present chunk on.  Rows of a chunk that hold such values cost the 16 (11x11) to 24 (15x15) output rows they
@@ -103,7 +98,7 @@ __device__ __forceinline__ bool too_many(unsigned long long marks, int seen, int
 }
 
 // The output rows [ra, rb) of the strip with plain multiply-adds, as an FBS array whose width is known at compile time:
-// a wavefront walks down the input rows of kPlainRows output rows, builds each row's window once and applies it to every
+// a wavefront walks down the input rows of up to kPlainRows output rows (an even share of each pass), builds each row's window once and applies it to every
 // output row whose filter covers it.  The filter rows in use are in registers (from tap0, row 0 of the taps in LDS, one
 // a step ahead of its use): two wavefronts a SIMD do not hide the latency of scalar loads (11x11 on 4096^2, a marked value in
 // every chunk: 127 us with taps in scalar registers, 95 this way; 1263 with one output row a wavefront and a load a tap).  On
@@ -113,8 +108,11 @@ __device__ __forceinline__ void plain_rows(const float* tap0, const float* __res
                                            unsigned col_b, int off, long long xp, int col, int ow_strip, long long yp, int kh,
                                            int ra, int rb, bool edge, int wave, PutRight put_right)
 {
-    for (int r = ra + kPlainRows * wave; r < rb; r += kPlainRows * (kBlock / kWave)) {
-        const int rows_out = min(kPlainRows, rb - r), rows_in = rows_out - 1 + kh;
+    if (ra >= rb) return;
+    constexpr int kWaves = kBlock / kWave;
+    const int passes = (rb - ra + kPlainRows * kWaves - 1) / (kPlainRows * kWaves), share = (rb - ra + kWaves * passes - 1) / (kWaves * passes);
+    for (int r = ra + share * wave; r < rb; r += share * kWaves) {
+        const int rows_out = min(share, rb - r), rows_in = rows_out - 1 + kh;
         const float* xrow = x + (long long)r * xp;
         f4u v[kPlainRows];
         auto load_row = [&](int rho, f4u& d) {                             // past the last row: the last row again
@@ -151,7 +149,7 @@ __device__ __forceinline__ void plain_rows(const float* tap0, const float* __res
                 for (int m = 4; m < KW + 3; ++m) win[m] = from_lane_above(win[m - 4]);
 #pragma unroll
                 for (int j = kPlainRows - 1; j >= 0; --j) {
-                    if (rho - j >= 0 && rho - j < kh) {                    // uniform
+                    if (j < rows_out && rho - j >= 0 && rho - j < kh) {    // uniform
 #pragma unroll
                         for (int q = 0; q < KW; ++q)
 #pragma unroll
@@ -174,7 +172,7 @@ __host__ __device__ constexpr int most_width(int jc) { return jc == 4 ? 13 : 15;
 
 template <int JC, int NS>
 __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
-    Taps2D taps, const float* __restrict__ x, float* __restrict__ y, int h, int w_img, long long xp, int oh, int ow,
+    TapsOf<SplitShape<JC, NS>::TAPS> taps, const float* __restrict__ x, float* __restrict__ y, int h, int w_img, long long xp, int oh, int ow,
     long long yp, int kh, int kw, int rows, int row_blocks, int strips, int per_xcd, unsigned tiny_below)
 {
     (void)taps;
@@ -197,6 +195,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
     const int rows_out = min(rows, oh - r0);
     // chunks 0 .. chunks-1 start groups; one more holds the units that only finish them
     const int chunks = (rows_out + kChunk - 1) / kChunk;
+    const int groups = (rows_out + JR - 1) / JR, units = UG * (groups - 1) + NS;
     const int last_row = h - 1;
     const bool edge = c0 + kInCols > w_img;                                // uniform
 
@@ -300,7 +299,6 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
     // that are younger than the loads in flight and wait for the loads alone.
     const unsigned pitch_b = (unsigned)yp * (unsigned)sizeof(float);
     auto store_group = [&](int grp, const f4 (&sums)[NB][S::PARTS], auto edge_tag) {
-        constexpr unsigned kNowhere = 0xffffff00u;
         float* base = y + (long long)(r0 + grp * JR) * yp;                 // uniform
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000);
 #pragma unroll
@@ -320,49 +318,69 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
                     else
                         __builtin_amdgcn_raw_buffer_store_b64(u2{ob[2 * k], ob[2 * k + 1]}, rsrc, to, 0, kNonTemporal);
                 } else {
+                    const int left = row_ok ? ow_strip - col : 0;
+                    if constexpr (JC == 4)
+                        __builtin_amdgcn_raw_buffer_store_b128(ob, rsrc, left >= JC ? off : kNowhere, 0, kNonTemporal);
+                    else
+                        __builtin_amdgcn_raw_buffer_store_b64(u2{ob[2 * k], ob[2 * k + 1]}, rsrc, left >= JC ? off : kNowhere, 0, kNonTemporal);
 #pragma unroll
-                    for (int i = 0; i < JC; ++i)
-                        __builtin_amdgcn_raw_buffer_store_b32(ob[JC * k + i], rsrc,
-                                                              row_ok && col + i < ow_strip ? off + 4u * i : kNowhere, 0, kNonTemporal);
+                    for (int i = 0; i < JC - 1; ++i)
+                        __builtin_amdgcn_raw_buffer_store_b32(ob[JC * k + i], rsrc, i < left && left < JC ? off + 4u * i : kNowhere, 0, kNonTemporal);
                 }
             }
         }
     };
 
-    // One chunk: FIRST has no groups from before it, LAST starts none.  SLOT0: slot of the chunk's first group.
-    auto compute = [&](int c, auto edge_tag, auto first_tag, auto last_tag, auto slot_tag) {
-        constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
+    // One chunk: FIRST has no groups from before it, FULL starts all of its own (else it is looked at run time which groups there are, and how many
+    // units are left).  SLOT0: slot of the chunk's first group.
+    auto compute = [&](int c, auto edge_tag, auto first_tag, auto full_tag, auto slot_tag) {
+        constexpr bool FIRST = decltype(first_tag)::value, FULL = decltype(full_tag)::value;
         constexpr int SLOT0 = decltype(slot_tag)::value;
         int at = (c & 1) * kBuf + win0;
+        const int left = FULL ? kUnits : units - c * kUnits;
+        constexpr int SETS = NB == 1 ? 2 : 1;                              // windows are read a step ahead where registers allow it
+        b8 win[SETS][3];
+        auto read = [&](int t) {                                           // windows of step t = NB unit + nb; a unit's address is current
 #pragma unroll
-        for (int u = 0; u < (LAST ? NS - UG : kUnits); ++u, at += 2 * kRow) {
-            __builtin_amdgcn_sched_barrier(0);                             // (else the reads of many units are hoisted and registers spill)
-            asm("" : "+v"(at));                                            // one running address, not one per unit kept for the loop
+            for (int j = 0; j < 3; ++j)
+                __builtin_memcpy(&win[t % SETS][j], __builtin_assume_aligned(parts + at + (t % NB) * 16 * JC + j * kInCols, 2 * JC), 16);
+        };
+        if constexpr (SETS == 2) read(0);
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            if (!FULL && u >= left) break;                                 // uniform
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                b8 b[3];
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    __builtin_memcpy(&b[j], __builtin_assume_aligned(parts + at + nb * 16 * JC + j * kInCols, 2 * JC), 16);
+                const int t = u * NB + nb;
+                if (SETS == 2 || nb == 0) __builtin_amdgcn_sched_barrier(0);
+                if (SETS == 1) read(t);
+                if (nb + 1 == NB) {
+                    at += 2 * kRow;
+                    asm("" : "+v"(at));
+                }
+                if (SETS == 2 && t + 1 < kUnits * NB) read(t + 1);
+                const b8 (&b)[3] = win[t % SETS];
 #pragma unroll
                 for (int lg = -LIVE; lg < GROUPS; ++lg) {
                     const int s = u - UG * lg;
-                    if (s < 0 || s >= NS || (FIRST && lg < 0) || (LAST && lg >= 0)) continue;
+                    if (s < 0 || s >= NS || (FIRST && lg < 0)) continue;
+                    if (!FULL && (c * GROUPS + lg < 0 || c * GROUPS + lg >= groups)) continue;     // uniform
                     constexpr int kLo = S::PARTS - 1;
                     f4& hi = acc[(lg + SLOT0 + LIVE) % LIVE][nb][0];
                     f4& lo = acc[(lg + SLOT0 + LIVE) % LIVE][nb][kLo];
                     if (s == 0) hi = lo = f4{0.0f, 0.0f, 0.0f, 0.0f};
                     lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][2], b[0], lo, 0, 0, 0);
-                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[2], lo, 0, 0, 0);
-                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][1], b[1], lo, 0, 0, 0);
                     lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][1], b[0], lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][1], b[1], lo, 0, 0, 0);
                     lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[1], lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[2], lo, 0, 0, 0);
                     hi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s][0], b[0], hi, 0, 0, 0);
                 }
             }
 #pragma unroll
             for (int lg = -LIVE; lg < GROUPS; ++lg) {
-                if (u - UG * lg != NS - 1 || (FIRST && lg < 0) || (LAST && lg >= 0)) continue;
+                if (u - UG * lg != NS - 1 || (FIRST && lg < 0)) continue;
+                if (!FULL && (c * GROUPS + lg < 0 || c * GROUPS + lg >= groups)) continue;
                 store_group(c * GROUPS + lg, acc[(lg + SLOT0 + LIVE) % LIVE], edge_tag);
             }
         }
@@ -378,7 +396,7 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         auto advance = [&](int c, auto first_tag, auto slot_tag) {
             store_chunk(c + 1, edge_tag);
             load_chunk(c + 2);
-            compute(c, edge_tag, first_tag, std::false_type{}, slot_tag);
+            compute(c, edge_tag, first_tag, std::true_type{}, slot_tag);
             lds_barrier();
         };
         using Slot0 = std::integral_constant<int, 0>;
@@ -387,23 +405,53 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
             const bool full = (__builtin_amdgcn_readfirstlane(quads[0]) & 15u) == 15u;  // such values all over the first chunk
             if ((full && chunks <= 6) || too_many(1, 1, chunks)) return 0;
         }
-        advance(0, std::true_type{}, Slot0{});
-        int c = 1;
-        for (; c + 2 <= chunks; c += 2) {
-            if (too_many(marked_up_to(c), c + 1, chunks)) return c;
-            advance(c, std::false_type{}, Slot1{});
-            advance(c + 1, std::false_type{}, Slot0{});
+        auto swap_slots = [&]() {
+            if constexpr (Slot1::value != 0) {
+#pragma unroll
+                for (int i = 0; i < Slot1::value; ++i)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int p = 0; p < S::PARTS; ++p) {
+                            const f4 t = acc[i][nb][p];
+                            acc[i][nb][p] = acc[i + Slot1::value][nb][p];
+                            acc[i + Slot1::value][nb][p] = t;
+                        }
+            }
+        };
+        const int full = groups / GROUPS;
+        int c = 0;
+        if (full > 0) {
+            advance(0, std::true_type{}, Slot0{});
+            c = 1;
+            for (; c + 2 <= full; c += 2) {
+                if (too_many(marked_up_to(c), c + 1, chunks)) return c;
+                advance(c, std::false_type{}, Slot1{});
+                advance(c + 1, std::false_type{}, Slot0{});
+            }
+            if (c < full) {
+                advance(c, std::false_type{}, Slot1{});
+                ++c;
+            }
         }
-        if (c < chunks) {
-            advance(c, std::false_type{}, Slot1{});
-            compute(c + 1, edge_tag, std::false_type{}, std::true_type{}, Slot0{});
-        } else {
-            compute(c, edge_tag, std::false_type{}, std::true_type{}, Slot1{});
+        if (c & 1) swap_slots();
+#pragma nounroll
+        for (; c * kUnits < units; ++c) {                                  // (few: one body, slots as in the even chunks)
+            if (c > 0 && c < chunks && too_many(marked_up_to(c), c + 1, chunks)) return c;
+            if ((c + 1) * kUnits < units) {
+                store_chunk(c + 1, edge_tag);
+                if ((c + 2) * kUnits < units) load_chunk(c + 2);
+            }
+            compute(c, edge_tag, std::false_type{}, std::false_type{}, Slot0{});
+            swap_slots();
+            lds_barrier();
         }
         return chunks + 1;
     };
     const int stop = edge ? run(std::true_type{}) : run(std::false_type{});
 
+    unsigned long long todo = marked_up_to(chunks);
+    if (todo == 0) return;
     // The output rows that the marks reach, once more; neighbouring and overlapping ones together.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                       // the stores above are done before any of these
     __syncthreads();
@@ -418,7 +466,6 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
         };
         with(std::integral_constant<int, least_width(JC)>{}, with);
     };
-    unsigned long long todo = marked_up_to(chunks);
     if (stop <= chunks) todo = (todo & ~(~0ull << stop)) | 1ull << stop;   // (from there on: all that is left)
     int k = 0;
     unsigned four = 0;                                                     // marked row quads of chunk k that are still to come
@@ -453,22 +500,12 @@ template <int JC, int NS>
 hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
                         hipStream_t s)
 {
-    Taps2D taps;
-    for (int i = 0; i < kTaps2DLen; ++i) taps.f[i] = i < kh * kw ? f[i] : 0.0f;
+    using S = SplitShape<JC, NS>;
+    const TapsOf<S::TAPS> taps(f, kh * kw);
     const int oh = h - kh + 1, ow = w - kw + 1;
     const int strips = (ow + kCols - 1) / kCols;
-    // Rows of a workgroup's block: whole chunks, so many that the rounds of resident workgroups take the
-    // least time.  A block costs its chunks and about 1.5 more for the taps, the first loads and the units
-    // that only finish groups (11x11: 4.0 us a chunk in every round, on images of 2048^2 to 8192^2).
-    const int all_chunks = (oh + kChunk - 1) / kChunk;
-    int best = 1;
-    double best_cost = 0;
-    for (int m = 1; m < kMaxChunks && m <= all_chunks; ++m) {
-        const long long wgs = (long long)((all_chunks + m - 1) / m) * strips;
-        const double cost = (double)((wgs + kPlaces - 1) / kPlaces) * (m + 1.5);
-        if (m == 1 || cost < best_cost) { best = m; best_cost = cost; }
-    }
-    const long long rows = (long long)best * kChunk;
+    const int all = (oh + S::JR - 1) / S::JR;
+    const long long rows = (long long)S::JR * matrix_block_groups(all, strips, NS, S::UG, S::NB, 12.0, (kMaxChunks - 1) * kChunk / S::JR);
     const int row_blocks = (int)((oh + rows - 1) / rows);
     const long long groups = (long long)row_blocks * strips;
     const long long per_xcd = (groups + kXcds - 1) / kXcds;

@@ -51,6 +51,13 @@ def test_row_blocks_of_several_chunks(kh, kw, h):
     assert err2d(run2d(x, f, "AUTO"), x, f) <= TOL
 
 
+@pytest.mark.parametrize("kh,kw", [(9, 13), (13, 13), (15, 15), (6, 14)])
+@pytest.mark.parametrize("h", [900, 2000, 3400, 4100, 5500, 6200, 6900])       # blocks of 3, 6, 5, 7, 9, 10, 11 groups (8 x 2: 2 .. 6): chunks cut after each group
+def test_blocks_that_end_inside_a_chunk(kh, kw, h):
+    x, f = _case(h, 600, kh, kw, seed=1)
+    assert err2d(run2d(x, f, "AUTO"), x, f) <= TOL
+
+
 @pytest.mark.parametrize("kh,kw,h,w", [(13, 13, 60, 500), (15, 15, 60, 500), (11, 11, 1500, 1700)])
 def test_integers_exact_and_nothing_written_outside(kh, kw, h, w):
     rng = np.random.default_rng(7)
