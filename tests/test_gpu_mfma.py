@@ -243,3 +243,27 @@ def test_mfma_chains_on_a_stream_and_in_a_graph():
         mid_h = mid.cpu().numpy()
         assert err2d(mid_h, xh, f1) <= TOL, f"replay {rep}"
         assert err2d(out.cpu().numpy(), mid_h, f2) <= TOL, f"replay {rep}"
+
+
+# Results through LDS (from 40 M outputs on), blocks that end after each group of a chunk, right edges at every
+# position mod 4: integers below 8 with small integer taps are exact in this projection and in fp32, so the vector kernels say what is right.
+@pytest.mark.parametrize("kh,kw,h,w", [(3, 3, 2100, 2003), (2, 13, 1001, 4312), (1, 1, 4003, 1001), (3, 5, 1207, 3414), (5, 5, 6401, 6404), (13, 13, 6413, 6301),
+                                       (8, 4, 6500, 6306), (11, 11, 7001, 6007), (4, 4, 899, 1003), (9, 9, 1777, 1302), (13, 7, 2503, 1001), (6, 6, 3001, 2048)])
+def test_mfma_rows_through_lds_and_block_ends(kh, kw, h, w):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(h + w)
+    x = torch.randint(-7, 8, (h, w), device="cuda", generator=gen).float()
+    f = np.random.default_rng(kh).integers(-5, 6, (kh, kw)).astype(np.float32)
+    y = torch.full((h - kh + 3, w - kw + 6), 0.5, device="cuda")
+    B.sys_conv2d(x, f, y[1:-1, 2:-3], projection="MFMA")
+    assert torch.equal(y[1:-1, 2:-3], B.sys_conv2d(x, f, projection="FBS"))
+    y[1:-1, 2:-3] = 0.5
+    assert (y == 0.5).all()                                    # nothing outside the window
+
+
+def test_mfma_rows_of_a_group_beyond_a_buffer_descriptor():
+    x, f = W.random_case(3, (14, 500), (5, 5), x_range=(0.0, 1.0))
+    y = torch.empty((10, (1 << 25) + 8), dtype=torch.float32, device="cuda")[:, :496]
+    B.sys_conv2d(dev(x), f, y, projection="MFMA")
+    torch.cuda.synchronize()
+    assert err2d(y.cpu().numpy(), x, f) <= TOL
