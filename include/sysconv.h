@@ -208,8 +208,8 @@ int sys_conv1d_stt(const float *d_x, size_t n,
  *            16 KB; 7x7 FBS, BFS or SBM by size; 8x8 .. 11x11 SBM; everything else FBS); BFS and SBM are built
  *            for SQUARE filters 2x2 .. 11x11 only (sys_conv2d_has) and return
  *            SYS_ERR_UNSUPPORTED otherwise; BSM, FSM and FFS are 1-D only.  FBS runs
- *            kernels specialised at compile time for every filter of up to 11 rows and
- *            columns whose smaller side is at most 7 (square or not; this includes single
+ *            kernels specialised at compile time for every filter
+ *            whose smaller side is at most 7 (square or not; this includes single
  *            rows and columns, 1 x k and k x 1: the two passes of a
  *            separable filter, which run at the rate of a plain copy), and a kernel with
  *            run-time filter sizes otherwise.

@@ -7,7 +7,7 @@
 // not overlap and fetch the kw-1 columns to their right separately.
 //
 //   conv2d_fbs_kernel<RPW>            any kh, kw <= 15: LDS tile, one 1-D FBS pass per filter row
-//   conv2d_fbs_static_kernel<KH,KW,R> kh, kw <= 11 with min(kh, kw) <= 7: the same array with the sizes known
+//   conv2d_fbs_static_kernel<KH,KW,R> min(kh, kw) <= 7: the same array with the sizes known
 //                                     at compile time and each staged row's window shared by the rows it feeds
 //   conv2d_bfs_block_kernel<K,K,ROWS> 2x2 .. 7x7: short row block, all loads up front
 //   conv2d_bfs_kernel<K,K,PD>         8x8 .. 11x11: strip walk with rows in flight
@@ -144,10 +144,10 @@ typedef const float __attribute__((address_space(4)))* kernarg_floats;
 // convolutions instead of repeated per filter row.
 // Lanes of a strip that keep their results.  Single-row filters move as many bytes as a copy, and
 // there strips that start on 64-byte boundaries measure faster (8192^2, 1x5: 98.8 -> 91.5 us), as in
-// the 1-D kernels; with taller filters the rounding does not pay.
+// the 1-D kernels; with taller filters, and rows of more than 11 taps, the rounding does not pay.
 __host__ __device__ constexpr int fbs_static_valid_lanes(int kh, int kw)
 {
-    return kh == 1 ? ((kWave - halo_lanes(kw)) & ~3) : kWave - halo_lanes(kw);
+    return kh == 1 && kw <= 11 ? ((kWave - halo_lanes(kw)) & ~3) : kWave - halo_lanes(kw);
 }
 
 template <int KH, int KW, int RPW>
@@ -891,18 +891,27 @@ hipError_t launch_fbs_static(const float* x, int h, int w, size_t xp, const floa
 
 }  // namespace
 
-// Filters whose size is known at compile time: every kh x kw with 2 <= kh, kw <= 11 of which at
-// least one is at most 7 (4096^2, us, this kernel / the run-time-sized one: 9x3 29.9 / 40.4, 3x9 27.5 / 32.7,
-// 11x5 41.2 / 51.0, 5x11 43.7 / 45.2, 10x4 36.3 / 48.5, 7x11 56.5 / 57.0), single rows 1 x 2..11 and
-// single columns 2..11 x 1 (the two passes of a separable filter).  From 8x8 on the taps no longer
+// Filters whose size is known at compile time: every kh x kw whose smaller side is at most 7 (us, this kernel / the run-time-sized one: 4096^2
+// 9x3 29.9 / 40.4, 3x9 27.5 / 32.7, 11x5 41.2 / 51.0, 5x11 43.7 / 45.2, 10x4 36.3 / 48.5, 7x11 56.5 / 57.0; 3000^2 15x2 17.9 / 25.7, 13x4 21.1 / 29.2, 14x6 32.0 / 39.1, 12x7
+// 31.6 / 37.9, 6x12 28.4 / 32.1, 2x14 16.3 / 16.7; 522x945 7x14 7.4 / 10.2), single rows 1 x 2..15 and single columns 2..15 x 1 (the two passes of a separable
+// filter; 4096^2 15x1 21.9 / 39.7, 1000^2 14x1 4.5 / 6.7).  From 8x8 on the taps no longer
 // fit the scalar registers and the unrolled form loses to the run-time-sized kernel (11x11 on
 // 8192^2: 353 us with 4 rows per wavefront, 423 us with 2, against 313 us).  Output rows per wavefront
 // from a sweep on MI355X (us with 1 / 2 / 3 / 4 rows): 4096^2 3x3 27.1 / 26.4 / 28.0 / 28.2,
-// 5x5 32.3 / 27.7 / 28.1 / 29.6, 7x7 51.7 / 41.2 / 42.1 / 39.6; 8192^2 5x5 115.5 / 95.3 / 96.8 / 102.2.
+// 5x5 32.3 / 27.7 / 28.1 / 29.6, 7x7 51.7 / 41.2 / 42.1 / 39.6; 8192^2 5x5 115.5 / 95.3 / 96.8 / 102.2; columns with 3 / 4 / 6 / 8 rows 2000^2 10x1
+// 8.9 / 8.4 / 8.0 / 7.4, 500^2 15x1 3.8 / 3.9 / 4.5 / 5.1, 8000^2 13x1 level.
 bool has_conv2d_fbs_static(int kh, int kw)
 {
-    if (kh >= 2 && kh <= 11 && kw >= 2 && kw <= 11 && (kh <= 7 || kw <= 7)) return true;
-    return (kh == 1 && kw >= 2 && kw <= 11) || (kw == 1 && kh >= 2 && kh <= 11);
+    const int small = kh < kw ? kh : kw, large = kh < kw ? kw : kh;
+    return small >= 1 && small <= 7 && large >= 2 && large <= kMaxK2D;
+}
+
+// Where the specialised kernel serves them: rows of 12 taps and more, and 7x14 and 7x15, only up to 2 M outputs (1x12 on 1000^2 4.35 / 4.7, on 3000^2 15.3 / 14.9;
+// 7x14 on 522x945 7.4 / 10.2, on 3000^2 42.0 / 40.5).
+bool conv2d_fbs_static_serves(int oh, int ow, int kh, int kw)
+{
+    if (!has_conv2d_fbs_static(kh, kw)) return false;
+    return !((kh == 1 && kw >= 12) || (kh == 7 && kw >= 14)) || (double)oh * ow <= 2e6;
 }
 
 namespace {
@@ -919,19 +928,23 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
     SYSCONV_FBS_STATIC_ROW(2, 2); SYSCONV_FBS_STATIC_ROW(3, 2); SYSCONV_FBS_STATIC_ROW(4, 2);
     SYSCONV_FBS_STATIC_ROW(5, 2); SYSCONV_FBS_STATIC_ROW(6, 4); SYSCONV_FBS_STATIC_ROW(7, 4);
     SYSCONV_FBS_STATIC_ROW(8, 4); SYSCONV_FBS_STATIC_ROW(9, 4); SYSCONV_FBS_STATIC_ROW(10, 4); SYSCONV_FBS_STATIC_ROW(11, 4);
+    SYSCONV_FBS_STATIC_ROW(12, 4); SYSCONV_FBS_STATIC_ROW(13, 4); SYSCONV_FBS_STATIC_ROW(14, 4); SYSCONV_FBS_STATIC_ROW(15, 4);
 #undef SYSCONV_FBS_STATIC_ROW
 #define SYSCONV_FBS_STATIC_WIDE(KH, RPW)                                                                    \
     SYSCONV_FBS_STATIC(KH, 8, RPW); SYSCONV_FBS_STATIC(KH, 9, RPW); SYSCONV_FBS_STATIC(KH, 10, RPW);      \
-    SYSCONV_FBS_STATIC(KH, 11, RPW)
+    SYSCONV_FBS_STATIC(KH, 11, RPW); SYSCONV_FBS_STATIC(KH, 12, RPW); SYSCONV_FBS_STATIC(KH, 13, RPW);            \
+    SYSCONV_FBS_STATIC(KH, 14, RPW); SYSCONV_FBS_STATIC(KH, 15, RPW)
     SYSCONV_FBS_STATIC_WIDE(2, 2); SYSCONV_FBS_STATIC_WIDE(3, 2); SYSCONV_FBS_STATIC_WIDE(4, 2);
     SYSCONV_FBS_STATIC_WIDE(5, 2); SYSCONV_FBS_STATIC_WIDE(6, 4); SYSCONV_FBS_STATIC_WIDE(7, 4);
 #undef SYSCONV_FBS_STATIC_WIDE
     SYSCONV_FBS_STATIC(1, 2, 4); SYSCONV_FBS_STATIC(1, 3, 4); SYSCONV_FBS_STATIC(1, 4, 4); SYSCONV_FBS_STATIC(1, 5, 4);
     SYSCONV_FBS_STATIC(1, 6, 4); SYSCONV_FBS_STATIC(1, 7, 4); SYSCONV_FBS_STATIC(1, 8, 4); SYSCONV_FBS_STATIC(1, 9, 4);
-    SYSCONV_FBS_STATIC(1, 10, 4); SYSCONV_FBS_STATIC(1, 11, 4);
+    SYSCONV_FBS_STATIC(1, 10, 4); SYSCONV_FBS_STATIC(1, 11, 4); SYSCONV_FBS_STATIC(1, 12, 4); SYSCONV_FBS_STATIC(1, 13, 4);
+    SYSCONV_FBS_STATIC(1, 14, 4); SYSCONV_FBS_STATIC(1, 15, 4);
     SYSCONV_FBS_STATIC(2, 1, 4); SYSCONV_FBS_STATIC(3, 1, 4); SYSCONV_FBS_STATIC(4, 1, 4); SYSCONV_FBS_STATIC(5, 1, 4);
     SYSCONV_FBS_STATIC(6, 1, 4); SYSCONV_FBS_STATIC(7, 1, 4); SYSCONV_FBS_STATIC(8, 1, 4); SYSCONV_FBS_STATIC(9, 1, 4);
-    SYSCONV_FBS_STATIC(10, 1, 4); SYSCONV_FBS_STATIC(11, 1, 4);
+    SYSCONV_FBS_STATIC(10, 1, 4); SYSCONV_FBS_STATIC(11, 1, 4); SYSCONV_FBS_STATIC(12, 1, 4); SYSCONV_FBS_STATIC(13, 1, 4);
+    SYSCONV_FBS_STATIC(14, 1, 4); SYSCONV_FBS_STATIC(15, 1, 4);
     return hipErrorInvalidValue;
 }
 #undef SYSCONV_FBS_STATIC
@@ -940,7 +953,7 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
 hipError_t launch_conv2d_fbs(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                              float* y, size_t yp, hipStream_t s)
 {
-    if (has_conv2d_fbs_static(kh, kw)) return launch_fbs_static_any(x, h, w, xp, f, kh, kw, y, yp, s);
+    if (conv2d_fbs_static_serves(h - kh + 1, w - kw + 1, kh, kw)) return launch_fbs_static_any(x, h, w, xp, f, kh, kw, y, yp, s);
     // Output rows per wavefront, measured on MI355X with 1, 2, 3, 4, 6 and 8 (us):
     //   4096^2 5x5   50.7  38.6  34.9  36.9  39.8  43.5      8192^2 5x5    178  127  122  121  125  134
     //   4096^2 7x7   63.3  50.1  48.6  49.9  53.3   -        8192^2 11x11  374  313  313  313  334  349

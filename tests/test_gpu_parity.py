@@ -242,3 +242,22 @@ def test_runs_on_a_side_stream():
         y = B.sys_conv1d(dx, w, projection="FBS")           # binding picks up torch's current stream
     s.synchronize()
     assert err1d(y.cpu().numpy(), x, w) <= TOL
+
+
+# Filters with a side of 12 .. 15 whose smaller side is at most 7: FBS kernels sized at compile time (rows of 12 taps and more, and 7x14 and 7x15, up to
+# 2 M outputs).  One output, one strip and its neighbour (4 (64 - ceil((kw - 1) / 4)) columns), ragged edges, tiles of 8 and 16 rows, and both sides of the 2 M line.
+@pytest.mark.parametrize("long_side", [12, 13, 14, 15])
+@pytest.mark.parametrize("short_side", [1, 2, 3, 4, 5, 6, 7])
+def test_fbs_long_filters_with_a_short_side(short_side, long_side):
+    for kh, kw in ((short_side, long_side), (long_side, short_side)):
+        for oh, ow in ((1, 1), (16, 240), (17, 253), (9, 257), (33, 491), (5, 1003)):
+            x, f = W.random_case(100 * kh + kw, (oh + kh - 1, ow + kw - 1), (kh, kw), x_range=(0.0, 1.0))
+            e = err2d(run2d(x, f, "FBS"), x, f)
+            assert e <= TOL, f"FBS {kh}x{kw} outputs {oh}x{ow}: rel err {e}"
+
+
+@pytest.mark.parametrize("kh,kw", [(1, 12), (1, 15), (7, 14), (7, 15)])
+@pytest.mark.parametrize("oh", [1000, 1001])                           # x 2000 columns: 2 M outputs, and more
+def test_fbs_either_side_of_two_million_outputs(kh, kw, oh):
+    x, f = W.integer_case(kh + kw, (oh + kh - 1, 2000 + kw - 1), (kh, kw), x_max=7, w_max=5)
+    assert np.array_equal(run2d(x, f, "FBS").astype(np.float64), oracle.conv2d(x, f, 16))
