@@ -536,26 +536,23 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
     return split_takes_taps(f, kh * kw);
 }
 
-// Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units NS, theirs with
-// the kh*kw taps, so the line is drawn in taps per unit; measured on 300x400 .. 8192x8192 images (us, vector / split), then
-// held against 2100 random shapes of 30 K to 26 M outputs (three of them lose more than 3 %: 10x10 on 370x6223, where
-// two rounds of workgroups leave most of the second empty, 12.1 / 13.2, and two by 4 %):
-//   filters that only the run-time-sized FBS kernel serves (a side above 11, or 8 .. 11 and not square): from 12 taps
-//   a unit at every size (5x13 7.8 / 6.0 on 300x400, 49 / 41 on 4096^2; 9x13 76 / 42; 12x12 11.0 / 7.3, 100 / 46), with fewer on
-//   images of 2 M outputs and more, the larger the closer they are to 7 (13x5 13.5 / 14.3 on 2.2 M, 56 / 44 on 4096^2; 12x6
-//   15.7 / 14.5 on 2.2 M).  Three rows leave half of the four units they take empty: from 5 M outputs on (3x12 8.6 / 10.4 on
-//   2.0 M, 12.3 / 13.6 on 4.1 M; 3x13 12.2 / 12.9 on 3.7 M, 16.4 / 14.2 on 5.0 M).  With 14 or 15 rows or
-//   columns: from 10 taps a unit (15x15 14.9 / 8.9 on 300x400, 150 / 59 on 4096^2; 6x14 10.9 / 10.4 on 1000^2; 3x15 32 / 37
-//   on 3001x4003), but not tall narrow ones, whose sums over 11 units in one accumulator are no more exact than the
-//   vector kernel's (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
-//   8x8 .. 11x11 (SBM) and other sides up to 11 (compile-time FBS): those kernels are quick on small images, and the
-//   split kernel wins once the image is large enough, the sooner the more taps a unit has: 11x11 (17.3) 9.9 / 9.6 on
-//   1000^2, 243 / 142 on 8192^2; 10x10 (14.3) 20.0 / 16.7 on 2048^2; 9x9 (13.5) 17.2 / 16.1 on 2048^2; 8x8
-//   (10.7) 18.3 / 19.5 on 2000x3000, 33.6 / 32.1 on 3001x4003; 7x11 (15.4) 8.8 / 8.1 on 1000^2; 11x7 (11) 9.7 / 10.0 on 1500x1100,
-//   55 / 42 on 4096^2; 7x7 25.5 / 32.5 on 3001x4003.
-// What the kernels compute for padding counts where it is a third or more beyond the others': strips of 240 columns and chunks of
-// 16 rows here, about 252 columns and 8 rows there (us: 13x5 on 8237x244 outputs 13.5 / 18.3, on 20000x250 22.3 / 27.7; 11x11 on
-// 8x200000 12.7 / 16.3; but 9x9 on 2828x989, a sixth, 14.2 / 13.0).
+// Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units, theirs with
+// the kh*kw taps, so the lines are drawn in taps per unit t; measured on squares of 400 .. 6500 and some other images (us, split / vector):
+//   filters that only the run-time-sized FBS kernel serves (both sides 8 or more, and not a square up to 11x11): at every size
+//   (10x8, t = 11.4, on 700^2 7.2 / 8.7, 300x400 5.2 / 7.9; 8x10 16.2 / 23.7 on 2300^2; 12x12 5.5 / 11.5, 83 / 196 on 5630^2; 15x15 8.4 / 15 on 300x400).  With 14 or 15
+//   columns: from 11 columns and 10 taps a unit on, as sums over 8 to 11 units in one accumulator are no more exact than the
+//   vector kernels' for narrower ones (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
+//   8x8 .. 11x11 (SBM) and filters with one side up to 7 (compile-time FBS): those kernels are quick on small images, and the split kernel wins once the
+//   image is large enough, the sooner the more taps a unit has.  Where the two are level, in M outputs: 8x8 (t = 10.7) 5, 9x9 (13.5) 2.2, 10x10 (14.3) 2,
+//   11x11 (17.3) 0.5 .. 1.3: from 0.11 (18.5 - t)^2 and 1.4 on; 12x6 (9.0) 4, 13x6 (9.8) 3, 12x7, 9x7 (10.5) 3 .. 4, 13x7 (11.4) 1, 4x12 (12) 2.2, 6x10 (12) 3, 7x10 (14) 0.9, 7x11 (15.4)
+//   0.8: from 0.05 (18.5 - t)^2 on, with fewer than 64 taps from 0.075; four and five rows from 2.2 (5x11 on 1275^2 7.6 / 6.8, 5x12 level at 1.5); 6x14, 6x15, 7x14 and 7x15 0.3 .. 1.5 on most images: 0.02 (18.5 - t)^2.  (12x6 on 4500^2
+//   52 / 59, 6x12 41 / 62, 8x8 on 3000x4000 29.6 / 35.1, 9x9 29.2 / 42.2, 11x11 on 1000^2 8.3 / 9.2, 420x1344 7.3 / 7.8, 7x15 on 1612x2405 16.4 / 24.3.)  Below t = 8.1 and below 44
+//   taps they are level at best (11x5 75 / 71 on 5630^2; 6x7 54 / 48 on 6300x4466; 13x5, 8.1, 50 / 52 on 4500^2); three rows leave half of the four units they take empty (3x13
+//   77 / 81 on 6500^2, 3x12 83 / 75), and 7x7 is level (59.5 / 62).
+//   Up to 0.1 M outputs, where either kernel takes less than launching it costs the host (4x13 on 277^2 4.3 / 3.7), filters with a side of 12 or 13 and 12 taps a unit stay with the
+//   split for its smaller error.
+// What the kernels compute for padding counts: strips of 240 columns and chunks of 16 rows here, about 252 columns and 8 rows there, where it is a quarter or
+// more beyond theirs (10x10 on 4082x485 outputs, a third strip for five columns, 13.1 / 10.1; 9x9 on 2828x989, a sixth, 14.2 / 13.0 with the kernels of then).
 bool conv2d_split_pays(int oh, int ow, int kh, int kw)
 {
     const int taps = kh * kw, units = split_units(kh, kw);
@@ -563,12 +560,15 @@ bool conv2d_split_pays(int oh, int ow, int kh, int kw)
     const int cols = kTile * (kWave - halo_lanes(kw));
     const double theirs = (double)(((long long)ow + cols - 1) / cols * 252) * (double)(((long long)oh + 7) / 8 * 8);
     const double ours = (double)(((long long)ow + kCols - 1) / kCols * kCols) * (double)(((long long)oh + kChunk - 1) / kChunk * kChunk);
-    const double worth = taps * (1.5 * theirs < ours ? 1.5 * theirs / ours : 1.0);
-    if (kh > 13 || kw > 13) return kw >= 11 && taps >= 10 * units;
-    const bool run_time_sized = kh > 11 || kw > 11 || (kh >= 8 && kw >= 8 && kh != kw);
-    if (run_time_sized && kh <= 3) return worth >= 8 * units && outputs >= 5e6;
-    if (run_time_sized) return taps >= 12 * units || (worth >= 8 * units && outputs >= 2e6 && outputs * (worth - 7 * units) >= 4e6 * units);
-    return taps >= 64 && outputs * (worth - 9 * units) >= 12e6 * units;
+    const double t = taps * (1.25 * theirs < ours ? 1.25 * theirs / ours : 1.0) / units;
+    const bool eight_by_two = kh > 13 || kw > 13;
+    if (t < 8.1 || (eight_by_two && (kw < 11 || taps < 10 * units))) return false;
+    if (kh <= 3) return t >= 9.5 && taps >= 39 && outputs >= 5e6;
+    if (kh >= 8 && kw >= 8 && (kh != kw || kh > 11)) return true;
+    if (taps < 44 || (kh == 7 && kw == 7)) return false;
+    const double line = eight_by_two ? 0.02e6 : kh == kw ? 0.11e6 : taps < 64 ? 0.075e6 : 0.05e6;
+    if (outputs <= 0.1e6 && t >= 12.0 && (kh > 11 || kw > 11)) return true;
+    return outputs >= (kh <= 5 ? 2.2e6 : kh == kw ? 1.4e6 : 0.5e6) && outputs >= line * (18.5 - t) * (18.5 - t);
 }
 
 hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
