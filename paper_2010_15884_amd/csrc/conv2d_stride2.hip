@@ -9,7 +9,8 @@
 // X(c,q) = X(c+1,q-2) never mixes the two).
 //
 //   conv2d_fbs_stride2_block_kernel<K,K,ROWS> 2x2 .. 5x5: all input rows of two output rows up front
-//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  the rest: the input rows of one to three output rows streamed through registers
+//   conv2d_fbs_stride2_pair_kernel<KW,ROWS>   the rest: the input rows of one to four output rows streamed through registers, two outputs a lane
+//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  single-row filters and images of fewer than four columns: the same with four outputs a lane
 #include "launch.h"
 #include "systolic.h"
 #include "tiling.h"
@@ -167,7 +168,7 @@ hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f,
 }
 
 // ------------------------------------------------------------ strip form ----
-// Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 512
+// Single-row filters, whose output rows share no input row, and images of fewer than four columns.  Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 512
 // input columns and walks down its 2*(ROWS-1)+kh input rows, kAhead of them in flight in registers.  Each row's two
 // windows are built once and applied to every output row whose filter covers it.  What bounds it is the latency of its input rows: the
 // rows requested, (2 (ROWS-1) + kh) / (2 ROWS) times the image, come from L2 for the most part.  A strip that reaches past
@@ -302,6 +303,141 @@ hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f,
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------- pair form ----
+// Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 256 input columns, two outputs a lane, and walks
+// down its 2*(ROWS-1)+kh input rows, four of them in flight.  A row is one load of 1 KB; its two windows are built once and applied to every output row whose
+// filter covers it.  Half as many outputs a lane as in the strips above give twice the wavefronts, less padding at the right edge, loads without gaps, and registers for four output rows.
+// Taps come in a row ahead of their use where a ring of them fits the scalar registers (a row of taps serves output row r two input rows after r - 1).  us, strips of
+// four outputs a lane / this: 4095x6001 7x7 29.5 / 26.6, 8192^2 11x11 98.6 / 89.3, 9x9 80.6 / 74.4, 3302x4516 15x15 41.7 / 37.0, 5564x1164 12x12 18.6 / 14.8, 780^2 12x12 7.1 / 5.7, 453^2 15x14 9.8 / 6.7;
+// 116 random images and filters 0.91 on average (15x15 on 1985x3879, a seventeenth strip for 13 columns, 21.9 / 23.6).
+// What bounds it: large images HBM with 1.2 to 1.3 times the image read (halo rows of neighbouring workgroups that miss L2); small ones the latency of the rows of one wavefront.
+// Tried: eight rows in flight (7x7 28.2 / 31.2), wavefronts of a workgroup side by side (7x7 30.6), six and eight output rows (30.0, 31.1; 12x12 18.8, 22.2).
+template <int KW>
+struct PairShape {
+    static constexpr int KE = (KW + 1) / 2, KO = KW / 2;                   // even and odd taps
+    static constexpr int kLanes = kWave - KE / 2;                          // lanes that keep their results: windows reach KE - 1 inputs of a chain further
+    static constexpr int kOut = 2 * kLanes;                                // output columns of a strip
+};
+
+template <int KW, int ROWS, bool EDGE>
+__device__ __forceinline__ void stride2_pair_rows(kernarg_floats taps_f, const float* __restrict__ xrow, float* __restrict__ yrow, int in_col, int out_col,
+                                                  int w_img, long long xp, int ow, long long yp, int kh, int rows_out, bool lane_valid)
+{
+    constexpr int KE = PairShape<KW>::KE, KO = PairShape<KW>::KO;
+    // filter row p waits in slot p mod RING from input row p - 1 on to input row p + 2 (ROWS - 1)
+    constexpr int RING = ROWS == 1 ? 2 : ROWS == 2 ? (KW <= 11 ? 4 : 0) : (KW <= 9 ? 8 : 0);
+    static_assert(RING == 0 || RING >= 2 * ROWS, "a slot is free again when the next filter row comes in");
+    constexpr int UNROLL = RING > kAhead ? RING : kAhead;
+    const int rows_in = 2 * (rows_out - 1) + kh;
+    const EdgeQuad quad(in_col, w_img);
+
+    f4u v[kAhead];
+    auto load_row = [&](int rho, f4u& d) {                                 // past the last row: the last row again
+        d = *reinterpret_cast<const f4u*>(xrow + (long long)min(rho, rows_in - 1) * xp + (EDGE ? quad.at : in_col));
+    };
+    float wv[RING > 0 ? RING : ROWS][KW];
+    auto load_taps = [&](int p, float (&w)[KW]) {
+        kernarg_floats fp = taps_f + min(max(p, 0), kh - 1) * KW;
+#pragma unroll
+        for (int q = 0; q < KW; ++q) w[q] = fp[q];
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load_row(i, v[i]);
+    if constexpr (RING > 0) load_taps(0, wv[0]);
+    float acc[ROWS][2];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r][0] = acc[r][1] = 0.0f;
+
+    for (int rho0 = 0; rho0 < rows_in; rho0 += UNROLL) {
+#pragma unroll
+        for (int j = 0; j < UNROLL; ++j) {
+            const int rho = rho0 + j;
+            if (rho >= rows_in) break;                                     // uniform
+            if constexpr (RING > 0) {
+                __builtin_amdgcn_sched_barrier(0);                         // (the taps of the next row stay where they are asked for)
+            } else {
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) load_taps(rho - 2 * r, wv[r]);
+            }
+            f4u t = v[j % kAhead];
+            float e0 = t.x, o0 = t.y, e1 = t.z, o1 = t.w;
+            if constexpr (EDGE) quad.put_right(e0, o0, e1, o1);
+            load_row(rho + kAhead, v[j % kAhead]);
+            if constexpr (RING > 0) load_taps(rho + 1, wv[(j + 1) % RING]);
+            float ev[KE + 1] = {e0, e1}, od[KO + 2] = {o0, o1};
+#pragma unroll
+            for (int m = 2; m < KE + 1; ++m) ev[m] = from_lane_above(ev[m - 2]);
+#pragma unroll
+            for (int m = 2; m < KO + 1; ++m) od[m] = from_lane_above(od[m - 2]);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const int p = rho - 2 * r;
+                if (p < 0 || p >= kh) continue;                            // uniform
+                const float (&w)[KW] = wv[RING > 0 ? (j - 2 * r + 2 * RING) % (RING > 0 ? RING : 1) : r];
+#pragma unroll
+                for (int q = 0; q < KW; ++q)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[r][i] = __builtin_fmaf(w[q], (q & 1) ? od[q / 2 + i] : ev[q / 2 + i], acc[r][i]);
+            }
+        }
+    }
+    if (!lane_valid) return;
+    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        if (r >= rows_out) break;                                          // uniform
+        float* to = yrow + (long long)r * yp + out_col;
+        if (!EDGE || out_col + 2 <= ow) {
+            if (SYSCONV_NONTEMPORAL_STORE) __builtin_nontemporal_store(f2u{acc[r][0], acc[r][1]}, reinterpret_cast<f2u*>(to));
+            else *reinterpret_cast<f2u*>(to) = f2u{acc[r][0], acc[r][1]};
+        } else if (out_col < ow) {
+            *to = acc[r][0];
+        }
+    }
+}
+
+template <int KW, int ROWS>
+__global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_pair_kernel(TapsOf<kMaxK2D * KW> taps, const float* __restrict__ x,
+                                                                         float* __restrict__ y, int w_img, long long xp, int oh, int ow,
+                                                                         long long yp, int kh, int row_blocks, int strips, int side,
+                                                                         int per_xcd)
+{
+    (void)taps;
+    using S = PairShape<KW>;
+    kernarg_floats tf = (kernarg_floats)__builtin_amdgcn_kernarg_segment_ptr();
+    int rb, strip;
+    if (!wave_tile(per_xcd, row_blocks, strips, side, rb, strip)) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int out_col0 = strip * S::kOut, r0 = rb * ROWS;
+    const int rows_out = min(ROWS, oh - r0);
+    const float* xrow = x + (long long)(2 * r0) * xp;
+    float* yrow = y + (long long)r0 * yp;
+    const int in_col = 2 * out_col0 + kTile * lane, out_col = out_col0 + 2 * lane;
+    // inside strips: all 256 input columns exist, and then so do the valid lanes' outputs
+    if (2 * out_col0 + kStrip <= w_img)
+        stride2_pair_rows<KW, ROWS, false>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane < S::kLanes);
+    else
+        stride2_pair_rows<KW, ROWS, true>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane < S::kLanes);
+}
+
+template <int KW, int ROWS>
+hipError_t launch_pair(const float* x, int h, int w, size_t xp, const float* f, int kh, float* y, size_t yp, hipStream_t s)
+{
+    const TapsOf<kMaxK2D * KW> taps(f, kh * KW);
+    const int oh = (h - kh) / 2 + 1, ow = (w - KW) / 2 + 1;
+    constexpr int cols = PairShape<KW>::kOut;
+    const int strips = (ow + cols - 1) / cols;
+    const int row_blocks = (oh + ROWS - 1) / ROWS;
+    long long per_xcd;
+    const long long blocks = tile_workgroups(row_blocks, strips, per_xcd);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((conv2d_fbs_stride2_pair_kernel<KW, ROWS>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+                       taps, x, y, w, (long long)xp, oh, ow, (long long)yp, kh, row_blocks, strips, band_width(xp),
+                       (int)per_xcd);
+    return hipGetLastError();
+}
+
 typedef hipError_t (*LaunchStrip)(const float*, int, int, size_t, const float*, int, float*, size_t, hipStream_t);
 template <int ROWS, int KW0, int... KW>
 hipError_t launch_strip_by_kw(std::integer_sequence<int, KW0, KW...>, const float* x, int h, int w, size_t xp, const float* f,
@@ -312,9 +448,31 @@ hipError_t launch_strip_by_kw(std::integer_sequence<int, KW0, KW...>, const floa
     return table[kw - KW0](x, h, w, xp, f, kh, y, yp, s);
 }
 
+template <int ROWS, int KW0, int... KW>
+hipError_t launch_pair_by_kw(std::integer_sequence<int, KW0, KW...>, const float* x, int h, int w, size_t xp, const float* f,
+                             int kh, int kw, float* y, size_t yp, hipStream_t s)
+{
+    static constexpr LaunchStrip table[] = {launch_pair<KW0, ROWS>, launch_pair<KW, ROWS>...};      // widths KW0 and on
+    if (kw < KW0 || kw > KW0 + (int)sizeof...(KW)) return hipErrorInvalidValue;
+    return table[kw - KW0](x, h, w, xp, f, kh, y, yp, s);
+}
+
 }  // namespace
 
-// Output rows of a wavefront, filters with a block form aside: 1, 2 or 3.  One row reads the most halo rows and gives the most wavefronts and
+// Output rows of a wavefront of the pair form, 1 to 4, by the wavefronts that one row each would make: one row gives the most of them and the shortest, which
+// decides while they do not fill the chip, more rows share input rows and windows.  us with 1 / 2 / 3 / 4 rows (wavefronts of one): 12 columns and more 780^2 12x12 (1540)
+// 5.7 / 8.2 / 9.3 / 10.4, 5524x552 12x12 (8271) 11.2 / 11.5 / 11.5 / 13.3, 807x5966 15x15 (9925) 16.6 / 16.5 / 18.2 / 19.3, 2494x4088 15x15 (21080) 29.9 / 27.6 / 26.5 / 30.4, 7344^2 12x12 114 / 92 /
+// 82.6 / 83.5; fewer columns 1340^2 8x8 (4002) 5.3 / 5.7 / 6.2 / 6.7, 1708^2 6x6 (5964) 6.2 / 5.8 / 6.0 / 6.5, 4846x930 7x7 (9680) 9.0 / 7.9 / 8.2 / 8.3, 4136x1480 7x7 (12390) 11.1 / 10.6 /
+// 9.6 / 9.9, 5448x4838 8x8 (54420) 34.8 / 29.1 / 25.2 / 26.4, 4095x6001 7x7 (51125) 37.6 / 32.0 / 27.8 / 26.6, 8192^2 11x11 129 / 107 / 95 / 89: four rows for odd heights only.
+int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw)
+{
+    const int cols = 2 * (kWave - (kw + 1) / 2 / 2);
+    const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
+    if (kw >= 12) return wavefronts <= 8500 ? 1 : wavefronts <= 20000 ? 2 : 3;
+    return wavefronts <= 5000 ? 1 : wavefronts <= 11500 ? 2 : wavefronts <= 45000 || kh % 2 == 0 ? 3 : 4;
+}
+
+// Output rows of a wavefront of the strip form, 1, 2 or 3 (single-row filters take one; the lines of the rest were drawn when other filters took this form too).  One row reads the most halo rows and gives the most wavefronts and
 // the shortest, which decides while they do not fill the chip; 250 random shapes, two rows / one row by wavefronts of one row: filters of
 // more than 60 taps up to 2000 1.27 to 1.30, 2000 to 3000 1.21, 3000 to 4096 1.06, above 5000 0.92 to 1.02; 25 to 60 taps 1.24, 1.17, 1.0,
 // 0.88; fewer 1.10, 1.03, 0.93.  So filters of up to kFewTaps taps take one row up to 3000 wavefronts, the others up to one round of the chip.
@@ -350,11 +508,19 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         }
     }
     using Widths = std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>;
-    switch (conv2d_stride2_strip_rows((h - kh) / 2 + 1, (w - kw) / 2 + 1, kh, kw)) {
+    const int oh = (h - kh) / 2 + 1, ow = (w - kw) / 2 + 1;
+    if (kh > 1 && w >= 4) {
+        switch (conv2d_stride2_pair_rows(oh, ow, kh, kw)) {
+        case 1: return launch_pair_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
+        case 2: return launch_pair_by_kw<2>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
+        case 3: return launch_pair_by_kw<3>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
+        default: return launch_pair_by_kw<4>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+        }
+    }
+    switch (conv2d_stride2_strip_rows(oh, ow, kh, kw)) {                   // more than one row: images of two or three columns
     case 1: return launch_strip_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
-    case 2: return launch_strip_by_kw<2>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
-    default:
-        return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    case 2: return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    default: return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3>{}, x, h, w, xp, f, kh, kw, y, yp, s);
     }
 }
 
