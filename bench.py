@@ -490,7 +490,7 @@ def main() -> int:
         if alu:
             best = max(alu, key=lambda r: r["Gtap/s"])
             kern = {"SBM": "conv2d_sbm_kernel<11, 11, 1>", "BFS": "conv2d_bfs_kernel<11, 11, 1, kNarrow>",
-                    "FBS": "conv2d_fbs_kernel<2>"}[best["projection"]]
+                    "FBS": "conv2d_fbs_strip_kernel<11, 3>"}[best["projection"]]
             alu_traffic, alu_prov = _stored_traffic(f"conv2d_{best['projection'].lower()}_11x11_8k")
             # what the vector ALUs sustain with nothing in the way: the register-only yard-stick, 8 wavefronts per SIMD
             ybuf = torch.empty(2048 * 256, dtype=torch.float32, device="cuda")

@@ -6,9 +6,8 @@
 // the strip compute values that are never stored; the BFS kernels' strips do
 // not overlap and fetch the kw-1 columns to their right separately.
 //
-//   conv2d_fbs_kernel<RPW>            any kh, kw <= 15: LDS tile, one 1-D FBS pass per filter row
-//   conv2d_fbs_static_kernel<KH,KW,R> min(kh, kw) <= 7: the same array with the sizes known
-//                                     at compile time and each staged row's window shared by the rows it feeds
+//   conv2d_fbs_static_kernel<KH,KW,R> min(kh, kw) <= 7: LDS tile, sizes known at compile time, each staged row's window shared by the rows it feeds
+//   conv2d_fbs_strip_kernel<KW,ROWS>  8 .. 15 columns, any height: input rows streamed through registers
 //   conv2d_bfs_block_kernel<K,K,ROWS> 2x2 .. 7x7: short row block, all loads up front
 //   conv2d_bfs_kernel<K,K,PD>         8x8 .. 11x11: strip walk with rows in flight
 //   conv2d_sbm_block_kernel<K,K,ROWS> 2x2 .. 7x7
@@ -19,125 +18,22 @@
 
 #include <stdlib.h>
 
+#include <type_traits>
+
 namespace sysconv {
 namespace {
 
 // ------------------------------------------------------------- FBS 2-D -----
 // Section 6.2 describes the 2-D FBS design as a set of 1-D FBS convolutions, one per
-// filter row, that add into the same partial sums.  A workgroup stages a (4*RPW + kh - 1) x 256 input tile in LDS
-// once; each of its four wavefronts then owns RPW output rows (RPW independent
-// partial-sum vectors; RPW = 3, or 2 for tall filters) and, for every filter row p,
-// re-reads the input rows r+p from LDS and runs the 1-D FBS time loop over q on them.
-// Filter sizes are run-time values.
-
-template <int NT, bool MORE, int RPW>
-__device__ __forceinline__ void fbs_rows(float (&e)[RPW][4], float (&acc)[RPW][4], const float (&w)[4])
-{
-#pragma unroll
-    for (int j = 0; j < RPW; ++j) fbs_steps<NT, MORE>(e[j], acc[j], w);
-}
-
-template <int RPW>
-__global__ __launch_bounds__(kBlock) void conv2d_fbs_kernel(const float* __restrict__ x, float* __restrict__ y,
-                                                            int h, int w_img, long long xp, int oh, int ow,
-                                                            long long yp, int kh, int kw, int tiles_y, int n_tiles,
-                                                            int side, int per_xcd, Taps2D taps)
-{
-    extern __shared__ __attribute__((aligned(16))) float tile[];           // (kFbsTileRows + kh - 1) x kStrip
-    constexpr int kFbsRowsPerWave = RPW;
-    constexpr int kFbsTileRows = RPW * (kBlock / kWave);                   // output rows per workgroup
-
-    const int t = xcd_contiguous(blockIdx.x, per_xcd);
-    if (t >= n_tiles) return;                                              // whole workgroup leaves together
-    int tile_y, tile_x;
-    band_order(t, tiles_y, n_tiles / tiles_y, side, tile_y, tile_x);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = wave_in_block();
-    const int valid_lanes = kWave - halo_lanes(kw);
-    const int col0 = tile_x * kTile * valid_lanes;
-    const int row0 = tile_y * kFbsTileRows;
-
-    // stage: wavefront v copies input rows v, v+4, ... of the tile (1 KB each, coalesced)
-    const int in_rows = min(kFbsTileRows + kh - 1, h - row0);
-    constexpr int kWaves = kBlock / kWave, kBatch = 4;                     // rows of a wavefront in flight
-    if (w_img >= 4) {                                                      // uniform
-        const EdgeQuad quad(col0 + kTile * lane, w_img);
-        const bool edge = col0 + kStrip > w_img;                           // uniform
-#pragma nounroll
-        for (int r0 = wave; r0 < in_rows; r0 += kWaves * kBatch) {
-            f4u v[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k)                               // past the last row: the last row again
-                v[k] = *reinterpret_cast<const f4u*>(x + (long long)(row0 + min(r0 + k * kWaves, in_rows - 1)) * xp + quad.at);
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int rr = r0 + k * kWaves;
-                if (rr >= in_rows) break;                                  // uniform
-                float t[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-                if (edge) {
-                    asm volatile("");                                      // a branch, not selects in every tile (8192^2 9x9 229 / 217 us)
-                    quad.put_right(t[0], t[1], t[2], t[3]);
-                }
-                *reinterpret_cast<f4*>(tile + rr * kStrip + kTile * lane) = f4{t[0], t[1], t[2], t[3]};
-            }
-        }
-    } else {
-        for (int rr = wave; rr < in_rows; rr += kWaves) {
-            float v[4];
-            load4_guarded<false>(x + (long long)(row0 + rr) * xp, col0 + kTile * lane, w_img, v);
-            *reinterpret_cast<f4*>(tile + rr * kStrip + kTile * lane) = f4{v[0], v[1], v[2], v[3]};
-        }
-    }
-    __syncthreads();
-
-    float acc[kFbsRowsPerWave][4];
-#pragma unroll
-    for (int j = 0; j < kFbsRowsPerWave; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[j][i] = 0.0f;
-
-    const int lrow0 = wave * kFbsRowsPerWave;
-#pragma nounroll
-    for (int p = 0; p < kh; ++p) {
-        float e[kFbsRowsPerWave][4];
-#pragma unroll
-        for (int j = 0; j < kFbsRowsPerWave; ++j) {
-            // rows below the staged part of the tile hold stale LDS; they only feed
-            // output rows >= oh, which are not stored
-            const f4 t4 = *reinterpret_cast<const f4*>(tile + (lrow0 + j + p) * kStrip + kTile * lane);
-            e[j][0] = t4.x; e[j][1] = t4.y; e[j][2] = t4.z; e[j][3] = t4.w;
-        }
-        const float* fp = taps.f + p * kw;
-        int q = 0;
-#pragma nounroll
-        for (; q + 4 < kw; q += 4) {
-            const float w[4] = {fp[q], fp[q + 1], fp[q + 2], fp[q + 3]};
-            fbs_rows<4, true, RPW>(e, acc, w);
-        }
-        const float w[4] = {fp[q], fp[q + 1], fp[q + 2], fp[q + 3]};
-        switch (kw - q) {
-        case 4: fbs_rows<4, false, RPW>(e, acc, w); break;
-        case 3: fbs_rows<3, false, RPW>(e, acc, w); break;
-        case 2: fbs_rows<2, false, RPW>(e, acc, w); break;
-        default: fbs_rows<1, false, RPW>(e, acc, w); break;
-        }
-    }
-
-    if (lane < valid_lanes) {
-#pragma unroll
-        for (int j = 0; j < kFbsRowsPerWave; ++j) {
-            const int r = row0 + lrow0 + j;
-            if (r < oh) store4_guarded(y + (long long)r * yp, col0 + kTile * lane, ow, acc[j]);
-        }
-    }
-}
+// filter row, that add into the same partial sums.  Filters whose smaller side is at most 7 run the tile kernel below, all others the strips
+// (conv2d_fbs_strip_kernel).
 
 // Pointer into the kernel-argument segment (constant address space: uniform
 // reads become scalar loads).
 typedef const float __attribute__((address_space(4)))* kernarg_floats;
 
-// The same design with the filter size known at compile time (has_conv2d_fbs_static): every loop
-// below is unrolled, the taps sit in SGPRs for the whole kernel, and the 1-D passes are taken
+// A workgroup stages a (4 RPW + KH - 1) x 256 input tile in LDS; each of its four wavefronts owns RPW output rows.  The filter size is known at compile time
+// (has_conv2d_fbs_static): every loop below is unrolled, the taps sit in SGPRs for the whole kernel, and the 1-D passes are taken
 // input row by input row -- the array hands a staged row's inputs on from PE to PE once
 // (KW-1 DPP moves) and each of the up to min(RPW, KH) output rows that the input row feeds
 // takes its KW products from that one window, so the hand-overs are shared between the 1-D
@@ -785,11 +681,6 @@ __global__ __launch_bounds__(kBlock) void conv2d_sbm_block_kernel(TapsOf<KH * KW
 // 4096^2, 5x5: 28.1 us with 63 lanes, 29.0 with 60, 29.3 with 56.)
 int strip_valid_lanes(int kw) { return kWave - halo_lanes(kw); }
 
-void fill_taps(Taps2D& taps, const float* f, int n)
-{
-    for (int i = 0; i < kMaxK2D * kMaxK2D + 7; ++i) taps.f[i] = i < n ? f[i] : 0.0f;
-}
-
 // kEdge takes the last strip where some of its columns are missing, as long as the strip before it has its whole halo (in whole quads).
 StripKind bfs_strip_right(int w, int strips, int kw)
 {
@@ -845,30 +736,6 @@ hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f,
 }  // namespace
 
 namespace {
-template <int RPW>
-hipError_t launch_fbs_tiles(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
-                            size_t yp, hipStream_t s)
-{
-    constexpr int tile_rows = RPW * (kBlock / kWave);
-    Taps2D taps;
-    fill_taps(taps, f, kh * kw);
-    const int oh = h - kh + 1, ow = w - kw + 1;
-    const int cols = kTile * (kWave - halo_lanes(kw));
-    const int tiles_x = (ow + cols - 1) / cols;
-    const int tiles_y = (oh + tile_rows - 1) / tile_rows;
-    const long long n_tiles = (long long)tiles_x * tiles_y;
-    const long long per_xcd = (n_tiles + kXcds - 1) / kXcds;
-    const long long blocks = per_xcd * kXcds;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const size_t lds = (size_t)(tile_rows + kh - 1) * kStrip * sizeof(float);
-    hipLaunchKernelGGL(conv2d_fbs_kernel<RPW>, dim3((unsigned)blocks), dim3(kBlock), lds, s,
-                       x, y, h, w, (long long)xp, oh, ow, (long long)yp, kh, kw, tiles_y, (int)n_tiles,
-                       band_width(xp), (int)per_xcd, taps);
-    return hipGetLastError();
-}
-}  // namespace
-
-namespace {
 template <int KH, int KW, int RPW>
 hipError_t launch_fbs_static(const float* x, int h, int w, size_t xp, const float* f, float* y, size_t yp,
                              hipStream_t s)
@@ -891,11 +758,11 @@ hipError_t launch_fbs_static(const float* x, int h, int w, size_t xp, const floa
 
 }  // namespace
 
-// Filters whose size is known at compile time: every kh x kw whose smaller side is at most 7 (us, this kernel / the run-time-sized one: 4096^2
-// 9x3 29.9 / 40.4, 3x9 27.5 / 32.7, 11x5 41.2 / 51.0, 5x11 43.7 / 45.2, 10x4 36.3 / 48.5, 7x11 56.5 / 57.0; 3000^2 15x2 17.9 / 25.7, 13x4 21.1 / 29.2, 14x6 32.0 / 39.1, 12x7
-// 31.6 / 37.9, 6x12 28.4 / 32.1, 2x14 16.3 / 16.7; 522x945 7x14 7.4 / 10.2), single rows 1 x 2..15 and single columns 2..15 x 1 (the two passes of a separable
-// filter; 4096^2 15x1 21.9 / 39.7, 1000^2 14x1 4.5 / 6.7).  From 8x8 on the taps no longer
-// fit the scalar registers and the unrolled form loses to the run-time-sized kernel (11x11 on
+// Filters whose size is known at compile time: every kh x kw whose smaller side is at most 7, single rows and columns (the two passes of a separable filter)
+// among them (us, this kernel / one with run-time sizes, which re-read every staged row once per filter row and is gone: 4096^2
+// 9x3 29.9 / 40.4, 3x9 27.5 / 32.7, 11x5 41.2 / 51.0, 10x4 36.3 / 48.5, 15x1 21.9 / 39.7; 3000^2 15x2 17.9 / 25.7, 13x4 21.1 / 29.2, 14x6 32.0 / 39.1, 12x7
+// 31.6 / 37.9, 6x12 28.4 / 32.1, 2x14 16.3 / 16.7; 1000^2 14x1 4.5 / 6.7).  From 8x8 on the taps no longer
+// fit the scalar registers and the unrolled form loses (11x11 on
 // 8192^2: 353 us with 4 rows per wavefront, 423 us with 2, against 313 us).  Output rows per wavefront
 // from a sweep on MI355X (us with 1 / 2 / 3 / 4 rows): 4096^2 3x3 27.1 / 26.4 / 28.0 / 28.2,
 // 5x5 32.3 / 27.7 / 28.1 / 29.6, 7x7 51.7 / 41.2 / 42.1 / 39.6; 8192^2 5x5 115.5 / 95.3 / 96.8 / 102.2; columns with 3 / 4 / 6 / 8 rows 2000^2 10x1
@@ -903,11 +770,11 @@ hipError_t launch_fbs_static(const float* x, int h, int w, size_t xp, const floa
 bool has_conv2d_fbs_static(int kh, int kw)
 {
     const int small = kh < kw ? kh : kw, large = kh < kw ? kw : kh;
-    return small >= 1 && small <= 7 && large >= 2 && large <= kMaxK2D;
+    return small >= 1 && small <= 7 && large <= kMaxK2D;
 }
 
-// Where the specialised kernel serves them: rows of 12 taps and more, and 7x14 and 7x15, only up to 2 M outputs (1x12 on 1000^2 4.35 / 4.7, on 3000^2 15.3 / 14.9;
-// 7x14 on 522x945 7.4 / 10.2, on 3000^2 42.0 / 40.5).
+// Where it serves them: rows of 12 taps and more, and 7x14 and 7x15, only up to 2 M outputs (us, this / the strips: 1x12 on 1000^2 4.35 / 4.7, on 3000^2 15.3 / 15.1;
+// 7x14 on 522x945 7.4 / 8.9, on 3000^2 42.0 / 35.3).
 bool conv2d_fbs_static_serves(int oh, int ow, int kh, int kw)
 {
     if (!has_conv2d_fbs_static(kh, kw)) return false;
@@ -937,7 +804,7 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
     SYSCONV_FBS_STATIC_WIDE(2, 2); SYSCONV_FBS_STATIC_WIDE(3, 2); SYSCONV_FBS_STATIC_WIDE(4, 2);
     SYSCONV_FBS_STATIC_WIDE(5, 2); SYSCONV_FBS_STATIC_WIDE(6, 4); SYSCONV_FBS_STATIC_WIDE(7, 4);
 #undef SYSCONV_FBS_STATIC_WIDE
-    SYSCONV_FBS_STATIC(1, 2, 4); SYSCONV_FBS_STATIC(1, 3, 4); SYSCONV_FBS_STATIC(1, 4, 4); SYSCONV_FBS_STATIC(1, 5, 4);
+    SYSCONV_FBS_STATIC(1, 1, 4); SYSCONV_FBS_STATIC(1, 2, 4); SYSCONV_FBS_STATIC(1, 3, 4); SYSCONV_FBS_STATIC(1, 4, 4); SYSCONV_FBS_STATIC(1, 5, 4);
     SYSCONV_FBS_STATIC(1, 6, 4); SYSCONV_FBS_STATIC(1, 7, 4); SYSCONV_FBS_STATIC(1, 8, 4); SYSCONV_FBS_STATIC(1, 9, 4);
     SYSCONV_FBS_STATIC(1, 10, 4); SYSCONV_FBS_STATIC(1, 11, 4); SYSCONV_FBS_STATIC(1, 12, 4); SYSCONV_FBS_STATIC(1, 13, 4);
     SYSCONV_FBS_STATIC(1, 14, 4); SYSCONV_FBS_STATIC(1, 15, 4);
@@ -950,18 +817,149 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
 #undef SYSCONV_FBS_STATIC
 }  // namespace
 
+// ------------------------------------------------------------ FBS strips ----
+// Filters of 8 to 15 columns: a wavefront takes ROWS output rows of a strip of 256 input columns and walks down their ROWS + kh - 1 input rows, four of them in
+// flight.  Each row's KW-wide window is built once with KW - 1 hand-overs and applied to every output row whose filter covers it; the taps come in a row ahead of
+// their use, in a ring of scalar registers (with 12 and 14 columns a ring is slower: 6130^2 14x14 236 / 232 us, 2500^2 8x12 26.8 / 24.9).  The tile kernel with run-time sizes that served these filters staged its rows in LDS
+// and handed the inputs on once for every filter row: us, that / this: 8192^2 11x11 354 / 257 (SBM 257), 6130^2 14x14 268 / 234, 3109^2 9x9 36.8 / 31.0, 5694x2688 9x15 85.7 / 72.0,
+// 1500^2 15x15 31.0 / 23.9, 491x4731 12x9 16.4 / 12.6, 902^2 9x9 8.6 / 6.5, 415^2 12x12 11.7 / 6.0.
+// What bounds it: the vector ALUs on large images (11x11: 547 instructions for four outputs, 484 of them the multiply-adds), the latency of a wavefront's rows on small ones.
+namespace {
+constexpr int kFbsAhead = 4;
+template <int KW, int ROWS, bool EDGE>
+__device__ __forceinline__ void fbs_strip_rows(kernarg_floats taps_f, const float* __restrict__ xrow, float* __restrict__ yrow, int col,
+                                               int w_img, long long xp, int ow, long long yp, int kh, int rows_out, bool lane_valid)
+{
+    // filter row p waits in slot p mod RING from input row p - 1 on to input row p + ROWS - 1
+    constexpr int RING = ROWS == 1 ? 2 : ROWS <= 3 && KW != 12 && KW != 14 ? 4 : 0;
+    static_assert(RING == 0 || RING >= ROWS + 1, "a slot is free again when the next filter row comes in");
+    const int rows_in = rows_out - 1 + kh;
+    const EdgeQuad quad(col, w_img);
+    f4u v[kFbsAhead];
+    auto load_row = [&](int rho, f4u& d) {                                 // past the last row: the last row again
+        d = *reinterpret_cast<const f4u*>(xrow + (long long)min(rho, rows_in - 1) * xp + (EDGE ? quad.at : col));
+    };
+    float wv[RING > 0 ? RING : ROWS][KW];
+    auto load_taps = [&](int p, float (&w)[KW]) {
+        kernarg_floats fp = taps_f + min(max(p, 0), kh - 1) * KW;
+#pragma unroll
+        for (int q = 0; q < KW; ++q) w[q] = fp[q];
+    };
+#pragma unroll
+    for (int i = 0; i < kFbsAhead; ++i) load_row(i, v[i]);
+    if constexpr (RING > 0) load_taps(0, wv[0]);
+    float acc[ROWS][4];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r][0] = acc[r][1] = acc[r][2] = acc[r][3] = 0.0f;
+    for (int rho0 = 0; rho0 < rows_in; rho0 += kFbsAhead) {
+#pragma unroll
+        for (int j = 0; j < kFbsAhead; ++j) {
+            const int rho = rho0 + j;
+            if (rho >= rows_in) break;                                     // uniform
+            if constexpr (RING > 0) {
+                __builtin_amdgcn_sched_barrier(0);                         // (the taps of the next row stay where they are asked for)
+            } else {
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) load_taps(rho - r, wv[r]);
+            }
+            f4u t = v[j];
+            float win[KW + 3] = {t.x, t.y, t.z, t.w};
+            if constexpr (EDGE) quad.put_right(win[0], win[1], win[2], win[3]);
+            load_row(rho + kFbsAhead, v[j]);
+            if constexpr (RING > 0) load_taps(rho + 1, wv[(j + 1) % (RING > 0 ? RING : 1)]);
+#pragma unroll
+            for (int m = 4; m < KW + 3; ++m) win[m] = from_lane_above(win[m - 4]);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const int p = rho - r;
+                if (p < 0 || p >= kh) continue;                            // uniform
+                const float (&w)[KW] = wv[RING > 0 ? (j - r + RING) % (RING > 0 ? RING : 1) : r];
+#pragma unroll
+                for (int q = 0; q < KW; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[r][i] = __builtin_fmaf(w[q], win[q + i], acc[r][i]);
+            }
+        }
+    }
+    if (!lane_valid) return;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        if (r < rows_out) store4_guarded(yrow + (long long)r * yp, col, ow, acc[r]);
+}
+
+template <int KW, int ROWS>
+__global__ __launch_bounds__(kBlock) void conv2d_fbs_strip_kernel(TapsOf<kMaxK2D * KW> taps, const float* __restrict__ x, float* __restrict__ y,
+                                                                  int w_img, long long xp, int oh, int ow, long long yp, int kh,
+                                                                  int row_blocks, int strips, int side, int per_xcd)
+{
+    (void)taps;
+    kernarg_floats tf = (kernarg_floats)__builtin_amdgcn_kernarg_segment_ptr();
+    int rb, strip;
+    if (!wave_tile(per_xcd, row_blocks, strips, side, rb, strip)) return;
+    constexpr int valid_lanes = kWave - halo_lanes(KW);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int col0 = strip * kTile * valid_lanes, r0 = rb * ROWS;
+    const int rows_out = min(ROWS, oh - r0);
+    const float* xrow = x + (long long)r0 * xp;
+    float* yrow = y + (long long)r0 * yp;
+    const int col = col0 + kTile * lane;
+    if (col0 + kStrip <= w_img) fbs_strip_rows<KW, ROWS, false>(tf, xrow, yrow, col, w_img, xp, ow, yp, kh, rows_out, lane < valid_lanes);
+    else fbs_strip_rows<KW, ROWS, true>(tf, xrow, yrow, col, w_img, xp, ow, yp, kh, rows_out, lane < valid_lanes);
+}
+
+template <int KW, int ROWS>
+hipError_t launch_fbs_strip(const float* x, int h, int w, size_t xp, const float* f, int kh, float* y, size_t yp, hipStream_t s)
+{
+    const TapsOf<kMaxK2D * KW> taps(f, kh * KW);
+    const int oh = h - kh + 1, ow = w - KW + 1;
+    constexpr int cols = kTile * (kWave - halo_lanes(KW));
+    const int strips = (ow + cols - 1) / cols;
+    const int row_blocks = (oh - 1) / ROWS + 1;
+    long long per_xcd;
+    const long long blocks = tile_workgroups(row_blocks, strips, per_xcd);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((conv2d_fbs_strip_kernel<KW, ROWS>), dim3((unsigned)blocks), dim3(kBlock), 0, s,
+                       taps, x, y, w, (long long)xp, oh, ow, (long long)yp, kh, row_blocks, strips, band_width(xp), (int)per_xcd);
+    return hipGetLastError();
+}
+}  // namespace
+
+// Output rows of a wavefront of the strips, by the wavefronts that one row each would make: one row gives the most of them and the shortest, more share input rows and windows.  us with
+// 1 / 2 / 3 / 4 rows (wavefronts of one): 700^2 11x11 (2070) 6.7 / 7.4 / 8.9 / 10.8, 902^2 9x9 (3576) 6.5 / 6.5 / 7.9 / 8.4, 1000x1300 13x13 (5928) 12.4 / 11.6 / 12.1 / 16.6, 1500^2 15x15
+// (10402) 24.6 / 23.9 / 25.4 / 27.5, 4160x1150 10x10 (20755) 23.7 / 21.2 / 20.5 / 23.5, 8192^2 11x11 320 / 267 / 258 / 257.  Single rows: four (3000^2 1x12 16.5 / 15.6 / 16.4 / 15.2).
+int conv2d_fbs_strip_rows(int oh, int ow, int kh, int kw)
+{
+    if (kh == 1) return 4;
+    const int cols = kTile * (kWave - halo_lanes(kw));
+    const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
+    return wavefronts <= 4000 ? 1 : wavefronts <= 15000 ? 2 : 3;
+}
+
 hipError_t launch_conv2d_fbs(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                              float* y, size_t yp, hipStream_t s)
 {
-    if (conv2d_fbs_static_serves(h - kh + 1, w - kw + 1, kh, kw)) return launch_fbs_static_any(x, h, w, xp, f, kh, kw, y, yp, s);
-    // Output rows per wavefront, measured on MI355X with 1, 2, 3, 4, 6 and 8 (us):
-    //   4096^2 5x5   50.7  38.6  34.9  36.9  39.8  43.5      8192^2 5x5    178  127  122  121  125  134
-    //   4096^2 7x7   63.3  50.1  48.6  49.9  53.3   -        8192^2 11x11  374  313  313  313  334  349
-    //   8000^2 15x15  565   532   540   541   580  603       4096^2 3x3   38.6 33.6 33.2 34.0 33.6   -
-    // Short tiles keep the LDS footprint small (more workgroups per CU); below two rows
-    // the halo rows staged per tile dominate.
-    if (kh <= 8) return launch_fbs_tiles<3>(x, h, w, xp, f, kh, kw, y, yp, s);
-    return launch_fbs_tiles<2>(x, h, w, xp, f, kh, kw, y, yp, s);
+    const int oh = h - kh + 1, ow = w - kw + 1;
+    if (conv2d_fbs_static_serves(oh, ow, kh, kw)) return launch_fbs_static_any(x, h, w, xp, f, kh, kw, y, yp, s);
+    const int rows = conv2d_fbs_strip_rows(oh, ow, kh, kw);
+    auto launch = [&](auto width) {
+        constexpr int KW = decltype(width)::value;
+        if constexpr (KW >= 12) {
+            if (rows == 4) return launch_fbs_strip<KW, 4>(x, h, w, xp, f, kh, y, yp, s);
+        }
+        return rows == 1 ? launch_fbs_strip<KW, 1>(x, h, w, xp, f, kh, y, yp, s)
+             : rows == 2 ? launch_fbs_strip<KW, 2>(x, h, w, xp, f, kh, y, yp, s) : launch_fbs_strip<KW, 3>(x, h, w, xp, f, kh, y, yp, s);
+    };
+    switch (kw) {
+    case 8: return launch(std::integral_constant<int, 8>{});
+    case 9: return launch(std::integral_constant<int, 9>{});
+    case 10: return launch(std::integral_constant<int, 10>{});
+    case 11: return launch(std::integral_constant<int, 11>{});
+    case 12: return launch(std::integral_constant<int, 12>{});
+    case 13: return launch(std::integral_constant<int, 13>{});
+    case 14: return launch(std::integral_constant<int, 14>{});
+    case 15: return launch(std::integral_constant<int, 15>{});
+    default: return hipErrorInvalidValue;
+    }
 }
 
 // SYSCONV_TILE_WIDE=1 in the environment (read once) makes the block-form BFS kernels use the

@@ -538,7 +538,7 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 
 // Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units, theirs with
 // the kh*kw taps, so the lines are drawn in taps per unit t; measured on squares of 400 .. 6500 and some other images (us, split / vector):
-//   filters that only the run-time-sized FBS kernel serves (both sides 8 or more, and not a square up to 11x11): at every size
+//   filters that only the FBS strips serve (both sides 8 or more, and not a square up to 11x11): at every size
 //   (10x8, t = 11.4, on 700^2 7.2 / 8.7, 300x400 5.2 / 7.9; 8x10 16.2 / 23.7 on 2300^2; 12x12 5.5 / 11.5, 83 / 196 on 5630^2; 15x15 8.4 / 15 on 300x400).  With 14 or 15
 //   columns: from 11 columns and 10 taps a unit on, as sums over 8 to 11 units in one accumulator are no more exact than the
 //   vector kernels' for narrower ones (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
