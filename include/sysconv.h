@@ -205,14 +205,14 @@ int sys_conv1d_stt(const float *d_x, size_t n,
  *            gain, one with such values everywhere takes up to 1.4 times (twice below 3 M
  *            outputs) what the named projections take, which do not look at the values.  Of the rest, square
  *            filters up to 6x6 run FBS, or BFS where x_pitch * 4 is a power of two of at most
- *            16 KB; 7x7 FBS, BFS or SBM by size; 8x8 .. 11x11 SBM; everything else FBS); BFS and SBM are built
+ *            16 KB; 7x7 FBS, BFS or SBM by size; 8x8 .. 11x11 SBM, and from 9x9 on FBS up to 0.4 M outputs; everything else FBS); BFS and SBM are built
  *            for SQUARE filters 2x2 .. 11x11 only (sys_conv2d_has) and return
  *            SYS_ERR_UNSUPPORTED otherwise; BSM, FSM and FFS are 1-D only.  FBS runs
  *            kernels specialised at compile time for every filter
  *            whose smaller side is at most 7 (square or not; this includes single
  *            rows and columns, 1 x k and k x 1: the two passes of a
- *            separable filter, which run at the rate of a plain copy), and a kernel with
- *            run-time filter sizes otherwise.
+ *            separable filter, which run at the rate of a plain copy), and kernels with the
+ *            width at compile time and the height at run time otherwise.
  *   h, w     at most INT_MAX - 2048 (SYS_ERR_UNSUPPORTED beyond; pitches at most 2^31).
  *
  * SYS_PROJ_MFMA (opt-in; any filter with kh, kw <= 13, square or not) leaves the paper's

@@ -47,7 +47,10 @@ bool too_wide(int w) { return w > INT_MAX - 2048; }
 // 7x7: FBS up to 0.9 M outputs (300^2 FBS 4.6, SBM 5.1; 700x1024 5.4 / 6.5, BFS 5.8; 2048x256 5.2 / 6.3 / 5.7); then BFS at power-of-two pitches up to 8 KB
 // (BFS / SBM / FBS 2048x512 6.0 / 7.5 / 6.9, 2048x1024 7.9 / 9.5 / 8.9, 30000x1024 60 / 62 / 67, 2048^2 11.4 / 12.6 / 13.3, 5000x2048 23.2 / 23.6 / 24.1), but SBM with 8 KB rows from
 // 16 M outputs on (12000x2048 50.7 / 48.8 / 51.4, 30000x2048 123 / 116 / 125); else FBS up to 3 M outputs (1700^2 FBS 9.1, SBM 9.8; 1800^2 10.5 / 10.9; 2200^2 13.1 / 12.8)
-// and SBM above (6000^2 73 / 67).  8x8 .. 11x11: SBM.  The rest: FBS.
+// and SBM above (6000^2 73 / 67).  9x9 .. 11x11: the FBS strips up to 0.4 M outputs, where their wavefronts of one row are the shortest (FBS / SBM 64^2 9x9 3.7 / 4.3, 11x11
+// 4.2 / 5.2; 500x700 9x9 5.0 / 5.4, 10x10 5.4 / 6.1, 11x11 5.9 / 6.7; 800^2 6.4 / 6.1, 7.2 / 7.0, 7.9 / 7.8) and 3000 such wavefronts
+// (4000x100 10x10, 3991 of them, 7.2 / 6.8), SBM above; 8x8: SBM at every size (FBS gains a third of a
+// microsecond on 300x400, and loses from 600^2 on: 800^2 5.8 / 5.4).  The rest: FBS.
 namespace sysconv {
 int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw)
 {
@@ -56,7 +59,7 @@ int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw)
     const double outputs = (double)oh * ow;
     if (kh != kw || kh < 2 || kh > 11) return SYS_PROJ_FBS;
     if (kh <= 6) return pow2_pitch && pitch_bytes <= 16384 ? SYS_PROJ_BFS : SYS_PROJ_FBS;
-    if (kh >= 8) return SYS_PROJ_SBM;
+    if (kh >= 8) return kh >= 9 && outputs <= 0.4e6 && (long long)oh * (((long long)ow + 243) / 244) <= 3000 ? SYS_PROJ_FBS : SYS_PROJ_SBM;
     if (outputs <= 0.9e6) return SYS_PROJ_FBS;
     if (pow2_pitch && (pitch_bytes <= 4096 || (pitch_bytes == 8192 && outputs <= 16e6))) return SYS_PROJ_BFS;
     return outputs <= 3e6 ? SYS_PROJ_FBS : SYS_PROJ_SBM;

@@ -16,8 +16,6 @@ constexpr int kMaxK2D = 15;
 // always be fetched.
 constexpr int kTaps1DLen = kMaxK1D + 12;      // room for a 3-tap lead-in and a 7-wide fetch at the end
 struct Taps1D { float w[kTaps1DLen]; };
-constexpr int kTaps2DLen = kMaxK2D * kMaxK2D + 7;
-struct Taps2D { float f[kTaps2DLen]; };
 
 // The same for kernels whose filter size is known at compile time: the argument block is written across the bus at every launch, and
 // a launch with 1 KB of arguments costs the host up to 1.2 us more than one with 100 bytes (3.8 / 2.6).  At least 256 bytes, so that the arguments behind

@@ -26,3 +26,14 @@ def test_lines():
             few, many = tiles(1000, 2000, kh, kw), tiles(1001, 2000, kh, kw)
             assert few == (min(kh, kw) <= 7)
             assert many == (few and not (kh == 1 and kw >= 12) and not (kh == 7 and kw >= 14))
+
+
+def test_auto_line_to_the_strips():
+    fn = B.lib()["_ZN7sysconv24conv2d_vector_projectionEiimii"]
+    fn.argtypes, fn.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_int], ctypes.c_int
+    for pitch in (1000, 1024):
+        for k in (9, 10, 11):
+            assert fn(400, 1000, pitch, k, k) == B.SYS_PROJ_FBS and fn(1, 1, pitch, k, k) == B.SYS_PROJ_FBS
+            assert fn(401, 1000, pitch, k, k) == B.SYS_PROJ_SBM
+            assert fn(3000, 100, pitch, k, k) == B.SYS_PROJ_FBS and fn(3001, 100, pitch, k, k) == B.SYS_PROJ_SBM
+        assert fn(300, 300, pitch, 8, 8) == B.SYS_PROJ_SBM
