@@ -544,8 +544,8 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 //   vector kernels' for narrower ones (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
 //   8x8 .. 11x11 (SBM) and filters with one side up to 7 (compile-time FBS): those kernels are quick on small images, and the split kernel wins once the
 //   image is large enough, the sooner the more taps a unit has.  Where the two are level, in M outputs: 8x8 (t = 10.7) 5, 9x9 (13.5) 2.2, 10x10 (14.3) 2,
-//   11x11 (17.3) 0.5 .. 1.3: from 0.11 (18.5 - t)^2 and 1.4 on; 12x6 (9.0) 4, 13x6 (9.8) 3, 12x7, 9x7 (10.5) 3 .. 4, 13x7 (11.4) 1, 4x12 (12) 2.2, 6x10 (12) 3, 7x10 (14) 0.9, 7x11 (15.4)
-//   0.8: from 0.05 (18.5 - t)^2 on, with fewer than 64 taps from 0.075; four and five rows from 2.2 (5x11 on 1275^2 7.6 / 6.8, 5x12 level at 1.5); 6x14, 6x15, 7x14 and 7x15 0.3 .. 1.5 on most images: 0.02 (18.5 - t)^2.  (12x6 on 4500^2
+//   11x11 (17.3) 0.5 .. 1.3: from 0.11 (18.5 - t)^2 and 1.4 on; 12x6 (9.0) 4, 13x6 (9.8) 3, 12x7, 9x7 (10.5) 3 .. 4, 13x7 (11.4) 1, 4x12 (12) 2.2, 6x10 (12) 3, 6x11 (13.2) and 7x10 (14) 1.6 (752x2101 9.1 / 8.2 and 9.1 / 8.5,
+//   894x2590 9.3 / 10.1 and 9.4 / 10.5), 7x11 (15.4) 0.8 .. 1.6: from 0.05 (18.5 - t)^2 on, below t = 14.2 from 1.6 on, with fewer than 64 taps from 0.075; four and five rows from 2.2 (5x11 on 1275^2 7.6 / 6.8, 5x12 level at 1.5); 6x14, 6x15, 7x14 and 7x15 0.3 .. 1.5 on most images: 0.02 (18.5 - t)^2.  (12x6 on 4500^2
 //   52 / 59, 6x12 41 / 62, 8x8 on 3000x4000 29.6 / 35.1, 9x9 29.2 / 42.2, 11x11 on 1000^2 8.3 / 9.2, 420x1344 7.3 / 7.8, 7x15 on 1612x2405 16.4 / 24.3.)  Below t = 8.1 and below 44
 //   taps they are level at best (11x5 75 / 71 on 5630^2; 6x7 54 / 48 on 6300x4466; 13x5, 8.1, 50 / 52 on 4500^2); three rows leave half of the four units they take empty (3x13
 //   77 / 81 on 6500^2, 3x12 83 / 75), and 7x7 is level (59.5 / 62).
@@ -568,7 +568,7 @@ bool conv2d_split_pays(int oh, int ow, int kh, int kw)
     if (taps < 44 || (kh == 7 && kw == 7)) return false;
     const double line = eight_by_two ? 0.02e6 : kh == kw ? 0.11e6 : taps < 64 ? 0.075e6 : 0.05e6;
     if (outputs <= 0.1e6 && t >= 12.0 && (kh > 11 || kw > 11)) return true;
-    return outputs >= (kh <= 5 ? 2.2e6 : kh == kw ? 1.4e6 : 0.5e6) && outputs >= line * (18.5 - t) * (18.5 - t);
+    return outputs >= (kh <= 5 ? 2.2e6 : t < 14.2 && !eight_by_two ? 1.6e6 : kh == kw ? 1.4e6 : 0.5e6) && outputs >= line * (18.5 - t) * (18.5 - t);
 }
 
 hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
