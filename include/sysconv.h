@@ -197,7 +197,8 @@ int sys_conv1d_stt(const float *d_x, size_t n,
  *   d_y      device, h-kh+1 rows of w-kw+1 floats, row stride y_pitch elements
  *            (>= w-kw+1); elements between rows are left untouched
  *   projection  AUTO and FBS accept every filter in range (AUTO, from measurements: filters
- *            of many taps, on images large enough, run on the matrix cores with inputs and taps
+ *            of many taps, on images large enough or (from 12 rows or columns on) for the smaller
+ *            error at any size, run on the matrix cores with inputs and taps
  *            split exactly into three bf16 numbers each -- fp32 results for any input, no
  *            promise asked, taps 0 or within 2^-60 .. 2^40 in magnitude.  NaN, infinities, inputs
  *            from 2^80 on and non-zero ones below 2^-100 / smallest |tap| (2^-103 at the least)

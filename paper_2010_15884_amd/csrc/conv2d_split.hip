@@ -536,23 +536,25 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
     return split_takes_taps(f, kh * kw);
 }
 
-// Where the split kernel is faster than the best vector-ALU kernel.  Its time goes with the units, theirs with
-// the kh*kw taps, so the lines are drawn in taps per unit t; measured on squares of 400 .. 6500 and some other images (us, split / vector):
-//   filters that only the FBS strips serve (both sides 8 or more, and not a square up to 11x11): at every size
-//   (10x8, t = 11.4, on 700^2 7.2 / 8.7, 300x400 5.2 / 7.9; 8x10 16.2 / 23.7 on 2300^2; 12x12 5.5 / 11.5, 83 / 196 on 5630^2; 15x15 8.4 / 15 on 300x400).  With 14 or 15
-//   columns: from 11 columns and 10 taps a unit on, as sums over 8 to 11 units in one accumulator are no more exact than the
-//   vector kernels' for narrower ones (14x9: off by 2.3e-7 against 2.2e-7; 14x11 1.9e-7 against 2.05e-7).
-//   8x8 .. 11x11 (SBM) and filters with one side up to 7 (compile-time FBS): those kernels are quick on small images, and the split kernel wins once the
+// Where AUTO takes the split kernel rather than the best vector-ALU kernel: where it is faster, and for filters that only it and the FBS kernels serve also where it is not, for its
+// smaller error (2-norm against 64 bits, images on [0, 1), split / FBS: 3x12 3.2e-8 / 1.2e-7, 4x13 3.5e-8 / 1.3e-7, 5x12 4.3e-8 / 1.9e-7, 6x12 4.5e-8 / 2.0e-7, 7x13 4.5e-8 / 1.2e-7,
+// 13x5 4.3e-8 / 1.8e-7, 12x7 4.8e-8 / 1.5e-7, 6x14 1.2e-7 / 1.5e-7, 7x15 6.6e-8 / 1.1e-7).  Its time goes with the units, theirs with
+// the kh*kw taps, so the lines are drawn in taps per unit t; measured on squares of 277 .. 6500 and some other images (us, split / vector):
+//   14 or 15 rows or columns: from 11 columns and 10 taps a unit on, at every size (15x15 8.4 / 15 on 300x400; 7x15 6.2 / 7.5 on 500^2, 12.8 / 13.8 on 1500^2; 6x14 7.8 / 6.5 on 700^2,
+//   19.8 / 21.2 on 2300^2).  With fewer columns sums over 8 to 11 units in one accumulator are no more exact than the vector kernels' (14x9: off by 2.3e-7 against 2.2e-7;
+//   14x11 1.9e-7 against 2.05e-7).
+//   A side of 12 or 13, or both 8 or more and not a square up to 11x11: from 12 taps a unit on at every size (4x12 4.6 / 3.7 on 500^2, 6.7 / 5.7 on 1000^2, 13.6 / 15.5 on 2300^2; 5x13 6.7 / 6.4 and
+//   13.9 / 18.7; 7x12 4.9 / 6.1 on 500^2, 14.7 / 21.1 on 2300^2), with fewer on images of 2 M outputs and more, the larger the closer they are to 7 (12x7 18.3 / 19.0 on 2200^2;
+//   12x6 18.0 / 17.4 on 2200^2, 27.1 / 30.7 on 3000^2; 13x5 27.0 / 26.2 on 3000^2, 50 / 52 on 4500^2).  Three rows leave half of the four units they take empty: from 5 M outputs on (3x13 19.4 / 18.7 on 3000^2, 35.5 / 37.3 on
+//   4500^2; 3x12 35.5 / 35.3 and 83 / 75 on 6500^2).  10x8 (t = 11.4) at every size (10x8, t = 11.4, on 700^2 7.2 / 8.7, 300x400 5.2 / 7.9; 8x10 16.2 / 23.7 on 2300^2; 12x12 5.5 / 11.5, 83 / 196 on 5630^2).
+//   8x8 .. 11x11 (SBM) and filters of up to 11 with one side up to 7 (compile-time FBS): those kernels are quick on small images, and the split kernel wins once the
 //   image is large enough, the sooner the more taps a unit has.  Where the two are level, in M outputs: 8x8 (t = 10.7) 5, 9x9 (13.5) 2.2, 10x10 (14.3) 2,
-//   11x11 (17.3) 0.5 .. 1.3: from 0.11 (18.5 - t)^2 and 1.4 on; 12x6 (9.0) 4, 13x6 (9.8) 3, 12x7, 9x7 (10.5) 3 .. 4, 13x7 (11.4) 1, 4x12 (12) 2.2, 6x10 (12) 3, 6x11 (13.2) and 7x10 (14) 1.6 (752x2101 9.1 / 8.2 and 9.1 / 8.5,
-//   894x2590 9.3 / 10.1 and 9.4 / 10.5), 7x11 (15.4) 0.8 .. 1.6: from 0.05 (18.5 - t)^2 on, below t = 14.2 from 1.6 on, with fewer than 64 taps from 0.075; four and five rows from 2.2 (5x11 on 1275^2 7.6 / 6.8, 5x12 level at 1.5); 6x14, 6x15, 7x14 and 7x15 0.3 .. 1.5 on most images: 0.02 (18.5 - t)^2.  (12x6 on 4500^2
-//   52 / 59, 6x12 41 / 62, 8x8 on 3000x4000 29.6 / 35.1, 9x9 29.2 / 42.2, 11x11 on 1000^2 8.3 / 9.2, 420x1344 7.3 / 7.8, 7x15 on 1612x2405 16.4 / 24.3.)  Below t = 8.1 and below 44
-//   taps they are level at best (11x5 75 / 71 on 5630^2; 6x7 54 / 48 on 6300x4466; 13x5, 8.1, 50 / 52 on 4500^2); three rows leave half of the four units they take empty (3x13
-//   77 / 81 on 6500^2, 3x12 83 / 75), and 7x7 is level (59.5 / 62).
-//   Up to 0.1 M outputs, where either kernel takes less than launching it costs the host (4x13 on 277^2 4.3 / 3.7), filters with a side of 12 or 13 and 12 taps a unit stay with the
-//   split for its smaller error.
+//   11x11 (17.3) 0.5 .. 1.3: from 0.11 (18.5 - t)^2 and 1.4 on; 9x7 (10.5) 3 .. 4, 6x10 (12) 3, 6x11 (13.2) and 7x10 (14) 1.6 (752x2101 9.1 / 8.2 and 9.1 / 8.5,
+//   894x2590 9.3 / 10.1 and 9.4 / 10.5), 7x11 (15.4) 0.8 .. 1.6: from 0.05 (18.5 - t)^2 on, below t = 14.2 from 1.6 on, with fewer than 64 taps from 0.075; four and five rows from 2.2 (5x11 on 1275^2 7.6 / 6.8).  (8x8 on 3000x4000 29.6 / 35.1,
+//   9x9 29.2 / 42.2, 11x11 on 1000^2 8.3 / 9.2, 420x1344 7.3 / 7.8.)  Below t = 8.1 and below 44
+//   taps they are level at best (11x5 75 / 71 on 5630^2; 6x7 54 / 48 on 6300x4466), and 7x7 is level (59.5 / 62).
 // What the kernels compute for padding counts: strips of 240 columns and chunks of 16 rows here, about 252 columns and 8 rows there, where it is a quarter or
-// more beyond theirs (10x10 on 4082x485 outputs, a third strip for five columns, 13.1 / 10.1; 9x9 on 2828x989, a sixth, 14.2 / 13.0 with the kernels of then).
+// more beyond theirs (10x10 on 4082x485 outputs, a third strip for five columns, 13.1 / 10.1); where the split stays for its error, or its gain is large, a half or more.
 bool conv2d_split_pays(int oh, int ow, int kh, int kw)
 {
     const int taps = kh * kw, units = split_units(kh, kw);
@@ -560,15 +562,18 @@ bool conv2d_split_pays(int oh, int ow, int kh, int kw)
     const int cols = kTile * (kWave - halo_lanes(kw));
     const double theirs = (double)(((long long)ow + cols - 1) / cols * 252) * (double)(((long long)oh + 7) / 8 * 8);
     const double ours = (double)(((long long)ow + kCols - 1) / kCols * kCols) * (double)(((long long)oh + kChunk - 1) / kChunk * kChunk);
-    const double t = taps * (1.25 * theirs < ours ? 1.25 * theirs / ours : 1.0) / units;
-    const bool eight_by_two = kh > 13 || kw > 13;
-    if (t < 8.1 || (eight_by_two && (kw < 11 || taps < 10 * units))) return false;
-    if (kh <= 3) return t >= 9.5 && taps >= 39 && outputs >= 5e6;
-    if (kh >= 8 && kw >= 8 && (kh != kw || kh > 11)) return true;
-    if (taps < 44 || (kh == 7 && kw == 7)) return false;
-    const double line = eight_by_two ? 0.02e6 : kh == kw ? 0.11e6 : taps < 64 ? 0.075e6 : 0.05e6;
-    if (outputs <= 0.1e6 && t >= 12.0 && (kh > 11 || kw > 11)) return true;
-    return outputs >= (kh <= 5 ? 2.2e6 : t < 14.2 && !eight_by_two ? 1.6e6 : kh == kw ? 1.4e6 : 0.5e6) && outputs >= line * (18.5 - t) * (18.5 - t);
+    auto taps_a_unit = [&](double pad) { return taps * (pad * theirs < ours ? pad * theirs / ours : 1.0) / units; };
+    if (kh > 13 || kw > 13) return kw >= 11 && taps >= 10 * units;
+    const bool both = kh >= 8 && kw >= 8;
+    const double loose = taps_a_unit(1.5), t = taps_a_unit(1.25);
+    if (kh > 11 || kw > 11 || (both && kh != kw)) {
+        if (kh <= 3) return loose >= 8.0 && outputs >= 5e6;
+        return taps >= 12 * units || (both && t >= 8.1) || (loose >= 8.0 && outputs >= 2e6 && outputs * (loose - 7.0) >= 4e6);
+    }
+    if (taps >= 64 && outputs * (loose - 9.0) >= 12e6) return true;
+    if (t < 8.1 || taps < 44 || (kh == 7 && kw == 7)) return false;
+    const double line = kh == kw ? 0.11e6 : taps < 64 ? 0.075e6 : 0.05e6;
+    return outputs >= (kh <= 5 ? 2.2e6 : t < 14.2 ? 1.6e6 : kh == kw ? 1.4e6 : 0.5e6) && outputs >= line * (18.5 - t) * (18.5 - t);
 }
 
 hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,

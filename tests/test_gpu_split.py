@@ -37,6 +37,16 @@ def test_auto_runs_the_split_kernel(kh, kw):
             assert (auto != B.sys_conv2d(d, f, projection=proj)).float().mean() > 0.2, proj
 
 
+@pytest.mark.parametrize("kh,kw,oh,ow", [(4, 12, 500, 700), (4, 13, 900, 901), (5, 12, 700, 600), (6, 13, 500, 500), (7, 12, 600, 500), (7, 13, 400, 700),
+                                         (13, 5, 1900, 2101), (12, 7, 1500, 1500), (3, 12, 2300, 2301), (10, 8, 500, 700)])
+def test_auto_errs_less_than_the_vector_kernels(kh, kw, oh, ow):
+    """2-norm of the error against 64 bits: measured 0.22 .. 0.37 of the FBS kernels'."""
+    x, f = _case(oh + kh - 1, ow + kw - 1, kh, kw, seed=14)
+    ref = oracle.conv2d(x, f, ORACLE_THREADS)
+    auto, fbs = (np.linalg.norm(run2d(x, f, p) - ref) for p in ("AUTO", "FBS"))
+    assert auto <= 0.5 * fbs, auto / fbs
+
+
 @pytest.mark.parametrize("kh,kw", FILTERS)
 @pytest.mark.parametrize("oh,ow", [(1, 1), (16, 240), (17, 241), (15, 243), (33, 482), (100, 719)])
 def test_edges_of_strips_and_chunks(kh, kw, oh, ow):

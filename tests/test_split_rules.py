@@ -1,0 +1,23 @@
+"""Which calls AUTO sends to the split matrix-core kernel (the library's own rule, host code without a GPU)."""
+import ctypes
+
+import pytest
+
+from paper_2010_15884_amd import binding as B
+
+
+def split_pays(oh, ow, kh, kw):
+    fn = B.lib()["_ZN7sysconv17conv2d_split_paysEiiii"]
+    fn.argtypes, fn.restype = [ctypes.c_int] * 4, ctypes.c_bool
+    return fn(oh, ow, kh, kw)
+
+
+# The split's sums are two to four times as exact as the vector kernels', and a caller of AUTO has no say in it: filters that it serves from a size on
+# keep it from there on, also on sizes where a vector kernel is a little quicker.
+@pytest.mark.parametrize("kh,kw,least", [(4, 12, 1), (4, 13, 1), (5, 12, 1), (5, 13, 1), (6, 12, 1), (6, 13, 1), (7, 12, 1), (7, 13, 1), (6, 14, 1), (6, 15, 1),
+                                         (7, 14, 1), (7, 15, 1), (3, 12, 2236), (3, 13, 2236), (12, 6, 1440), (12, 7, 1420), (13, 5, 1900), (13, 6, 1420), (13, 7, 1420),
+                                         (8, 9, 1), (9, 8, 1), (10, 9, 1), (12, 9, 1), (15, 15, 1), (14, 11, 1)])
+def test_filters_keep_the_kernel_with_the_smaller_error(kh, kw, least):
+    for s in (1, 17, 100, 277, 317, 500, 700, 900, 1100, 1300, 1600, 2100, 2400, 3000, 4096, 8192):
+        if s >= least:
+            assert split_pays(s, s, kh, kw), s
