@@ -548,13 +548,16 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 //   12x6 18.0 / 17.4 on 2200^2, 27.1 / 30.7 on 3000^2; 13x5 27.0 / 26.2 on 3000^2, 50 / 52 on 4500^2).  Three rows leave half of the four units they take empty: from 5 M outputs on (3x13 19.4 / 18.7 on 3000^2, 35.5 / 37.3 on
 //   4500^2; 3x12 35.5 / 35.3 and 83 / 75 on 6500^2).  10x8 (t = 11.4) at every size (10x8, t = 11.4, on 700^2 7.2 / 8.7, 300x400 5.2 / 7.9; 8x10 16.2 / 23.7 on 2300^2; 12x12 5.5 / 11.5, 83 / 196 on 5630^2).
 //   8x8 .. 11x11 (SBM) and filters of up to 11 with one side up to 7 (compile-time FBS): those kernels are quick on small images, and the split kernel wins once the
-//   image is large enough, the sooner the more taps a unit has.  Where the two are level, in M outputs: 8x8 (t = 10.7) 5, 9x9 (13.5) 2.2, 10x10 (14.3) 2,
-//   11x11 (17.3) 0.5 .. 1.3: from 0.11 (18.5 - t)^2 and 1.4 on; 9x7 (10.5) 3 .. 4, 6x10 (12) 3, 6x11 (13.2) and 7x10 (14) 1.6 (752x2101 9.1 / 8.2 and 9.1 / 8.5,
-//   894x2590 9.3 / 10.1 and 9.4 / 10.5), 7x11 (15.4) 0.8 .. 1.6: from 0.05 (18.5 - t)^2 on, below t = 14.2 from 1.6 on, with fewer than 64 taps from 0.075; four and five rows from 2.2 (5x11 on 1275^2 7.6 / 6.8).  (8x8 on 3000x4000 29.6 / 35.1,
-//   9x9 29.2 / 42.2, 11x11 on 1000^2 8.3 / 9.2, 420x1344 7.3 / 7.8.)  Below t = 8.1 and below 44
-//   taps they are level at best (11x5 75 / 71 on 5630^2; 6x7 54 / 48 on 6300x4466), and 7x7 is level (59.5 / 62).
-// What the kernels compute for padding counts: strips of 240 columns and chunks of 16 rows here, about 252 columns and 8 rows there, where it is a quarter or
-// more beyond theirs (10x10 on 4082x485 outputs, a third strip for five columns, 13.1 / 10.1); where the split stays for its error, or its gain is large, a half or more.
+//   image is large enough, the sooner the more taps a unit has.  Where the two are level, in M outputs: 8x8 (t = 10.7) 5, 9x9 (13.5) 2.2, 10x10 (14.3) 2 (and 2046x1002 outputs,
+//   five strips, 12.1 / 11.05), 11x11 (17.3) 0.5 .. 1.3: from 12 / (t - 9) on, as other filters of 64 taps and more do at the latest; 9x7 (10.5) 3 .. 4, 6x10 (12) 3, 6x11 (13.2) and 7x10 (14) 1.6 (752x2101 9.1 / 8.2 and 9.1 / 8.5,
+//   894x2590 9.3 / 10.1 and 9.4 / 10.5), 7x11 (15.4) 0.8 .. 1.6: from 0.05 (18.5 - t)^2 on, below t = 14.2 from 1.6 on and else from 0.9 (7x11 on 737x850 6.6 / 6.05), with fewer than 64 taps from
+//   0.075; four and five rows from 2.6 (5x11 on 508x4639 9.1 / 8.3, 1089x2229 9.05 / 9.9).  (8x8 on 3000x4000 29.6 / 35.1,
+//   9x9 29.2 / 42.2, 11x11 on 1000^2 8.3 / 9.2, 420x1344 7.3 / 7.8.)  Below t = 8.5 and below 44
+//   taps they are level at best (11x5 75 / 71 on 5630^2; 6x7 54 / 48 on 6300x4466; 9x6 with a thirtieth of padding 19.1 / 17.7 on 2162x3140), and 7x7 is level (59.5 / 62).
+// What the kernels compute for padding counts: strips of 240 columns and chunks of 16 rows here, about 252 columns and 8 rows there.  In full where the two are close: a strip more here than there
+// costs what it computes (5x9 on 7737x723 17.1 / 14.2; 7x8 on 6757x721 16.5 / 14.5; 6x8 on 6483x1203 21.5 / 18.8; 7x9 on 1607x1700 11.5 / 10.05; with any padding
+// up to a quarter let pass, 40 of 228 random calls beyond the first lines were slower by more than 5 %, up to 20 %; with this none of them and one of 120 others, 6766x959 6x8 by 7 %).  Where the gain is large or the split stays for its
+// error, padding of a half (10x8: a quarter) more than theirs is let pass.
 bool conv2d_split_pays(int oh, int ow, int kh, int kw)
 {
     const int taps = kh * kw, units = split_units(kh, kw);
@@ -565,15 +568,14 @@ bool conv2d_split_pays(int oh, int ow, int kh, int kw)
     auto taps_a_unit = [&](double pad) { return taps * (pad * theirs < ours ? pad * theirs / ours : 1.0) / units; };
     if (kh > 13 || kw > 13) return kw >= 11 && taps >= 10 * units;
     const bool both = kh >= 8 && kw >= 8;
-    const double loose = taps_a_unit(1.5), t = taps_a_unit(1.25);
+    const double loose = taps_a_unit(1.5), t = taps_a_unit(1.0);
     if (kh > 11 || kw > 11 || (both && kh != kw)) {
         if (kh <= 3) return loose >= 8.0 && outputs >= 5e6;
-        return taps >= 12 * units || (both && t >= 8.1) || (loose >= 8.0 && outputs >= 2e6 && outputs * (loose - 7.0) >= 4e6);
+        return taps >= 12 * units || (both && taps_a_unit(1.25) >= 8.1) || (loose >= 8.0 && outputs >= 2e6 && outputs * (loose - 7.0) >= 4e6);
     }
     if (taps >= 64 && outputs * (loose - 9.0) >= 12e6) return true;
-    if (t < 8.1 || taps < 44 || (kh == 7 && kw == 7)) return false;
-    const double line = kh == kw ? 0.11e6 : taps < 64 ? 0.075e6 : 0.05e6;
-    return outputs >= (kh <= 5 ? 2.2e6 : t < 14.2 ? 1.6e6 : kh == kw ? 1.4e6 : 0.5e6) && outputs >= line * (18.5 - t) * (18.5 - t);
+    if (kh == kw || t < 8.5 || taps < 44) return false;
+    return outputs >= (kh <= 5 ? 2.6e6 : t < 14.2 ? 1.6e6 : 0.9e6) && outputs >= (taps < 64 ? 0.075e6 : 0.05e6) * (18.5 - t) * (18.5 - t);
 }
 
 hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,

@@ -21,3 +21,13 @@ def test_filters_keep_the_kernel_with_the_smaller_error(kh, kw, least):
     for s in (1, 17, 100, 277, 317, 500, 700, 900, 1100, 1300, 1600, 2100, 2400, 3000, 4096, 8192):
         if s >= least:
             assert split_pays(s, s, kh, kw), s
+
+
+# What the strips of 240 columns and the chunks of 16 rows compute for padding counts in full where the two kernels are close: the first is level or slower on the split
+# (measured 1.04 .. 1.2 times the vector kernel), the second (no padding) faster.
+@pytest.mark.parametrize("kh,kw,padded,even", [(10, 10, (2046, 1002), (2046, 1200)), (5, 9, (7737, 723), (7737, 720)), (7, 8, (6757, 721), (6757, 720)),
+                                               (6, 8, (6483, 1203), (6480, 1440)), (7, 9, (1607, 1700), (2400, 1920)), (9, 6, (4591, 1926), (4592, 1920)),
+                                               (7, 11, (737, 850), (1280, 960)), (5, 11, (508, 4639), (1200, 2400)), (10, 6, (6129, 1483), (6128, 1440))])
+def test_padding_counts_in_full(kh, kw, padded, even):
+    assert not split_pays(*padded, kh, kw)
+    assert split_pays(*even, kh, kw)
