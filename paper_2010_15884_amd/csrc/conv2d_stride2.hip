@@ -307,9 +307,9 @@ hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f,
 // Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 256 input columns, two outputs a lane, and walks
 // down its 2*(ROWS-1)+kh input rows, four of them in flight.  A row is one load of 1 KB; its two windows are built once and applied to every output row whose
 // filter covers it.  Half as many outputs a lane as in the strips above give twice the wavefronts, less padding at the right edge, loads without gaps, and registers for four output rows.
-// Taps come in a row ahead of their use where a ring of them fits the scalar registers (a row of taps serves output row r two input rows after r - 1).  us, strips of
+// Taps come in a row ahead of their use, in a ring, where one fits the scalar registers (a row of taps serves output row r two input rows after r - 1).  us, strips of
 // four outputs a lane / this: 4095x6001 7x7 29.5 / 26.6, 8192^2 11x11 98.6 / 89.3, 9x9 80.6 / 74.4, 3302x4516 15x15 41.7 / 37.0, 5564x1164 12x12 18.6 / 14.8, 780^2 12x12 7.1 / 5.7, 453^2 15x14 9.8 / 6.7;
-// 116 random images and filters 0.91 on average (15x15 on 1985x3879, a seventeenth strip for 13 columns, 21.9 / 23.6).
+// 116 random images and filters 0.91 on average (15x15 on 1985x3879, a seventeenth strip for 13 columns, 21.6 / 22.2).
 // What bounds it: large images HBM with 1.2 to 1.3 times the image read (halo rows of neighbouring workgroups that miss L2); small ones the latency of the rows of one wavefront.
 // Tried: eight rows in flight (7x7 28.2 / 31.2), wavefronts of a workgroup side by side (7x7 30.6), six and eight output rows (30.0, 31.1; 12x12 18.8, 22.2).
 template <int KW>
@@ -325,9 +325,14 @@ __device__ __forceinline__ void stride2_pair_rows(kernarg_floats taps_f, const f
 {
     constexpr int KE = PairShape<KW>::KE, KO = PairShape<KW>::KO;
     // filter row p waits in slot p mod RING from input row p - 1 on to input row p + 2 (ROWS - 1)
-    constexpr int RING = ROWS == 1 ? 2 : ROWS == 2 ? (KW <= 11 ? 4 : 0) : (KW <= 9 ? 8 : 0);
+    constexpr int RING = ROWS == 1 ? 2 : ROWS == 2 ? 4 : (KW <= 9 ? 8 : 0);
     static_assert(RING == 0 || RING >= 2 * ROWS, "a slot is free again when the next filter row comes in");
     constexpr int UNROLL = RING > kAhead ? RING : kAhead;
+    // Left in the middle, the body has its ring copied to vector registers, tap by tap for every row (98 to 110 of them for two rows of 9 to 11 columns, four wavefronts a SIMD, and half of the
+    // multiply-adds read a tap there); with every row guarded instead the ring stays in scalar registers (40, eight wavefronts, few or no spills).  us, left / guarded: 1066x4859 10x11 12.4 / 10.9, 1564x3252 10x10
+    // 11.4 / 10.2, 2724x1940 9x9 11.0 / 9.6, 1985x3879 15x15 (no ring / guarded, with one) 23.7 / 22.2, 8192^2 11x11 90.5 / 87.9; by rows and columns, 2 rows 8 - 9 0.93, 10 - 11 0.91, 12 and more 0.94, 3 rows 0.98
+    // to 0.99.  Single rows (1.04) and fewer columns (1.01 to 1.1: 7x7 on 4095x6001 26.5 / 26.9, 14x4 on 4720x4127 23.4 / 31) are quicker left: their copies are few.
+    constexpr bool GUARDED = ROWS >= 2 && KW >= 8;
     const int rows_in = 2 * (rows_out - 1) + kh;
     const EdgeQuad quad(in_col, w_img);
 
@@ -352,18 +357,20 @@ __device__ __forceinline__ void stride2_pair_rows(kernarg_floats taps_f, const f
 #pragma unroll
         for (int j = 0; j < UNROLL; ++j) {
             const int rho = rho0 + j;
-            if (rho >= rows_in) break;                                     // uniform
+            if (!GUARDED && rho >= rows_in) break;                         // uniform
             if constexpr (RING > 0) {
                 __builtin_amdgcn_sched_barrier(0);                         // (the taps of the next row stay where they are asked for)
+                if constexpr (GUARDED) load_taps(rho + 1, wv[(j + 1) % (RING > 0 ? RING : 1)]);
             } else {
 #pragma unroll
                 for (int r = 0; r < ROWS; ++r) load_taps(rho - 2 * r, wv[r]);
             }
+            if (GUARDED && rho >= rows_in) continue;                       // uniform
             f4u t = v[j % kAhead];
             float e0 = t.x, o0 = t.y, e1 = t.z, o1 = t.w;
             if constexpr (EDGE) quad.put_right(e0, o0, e1, o1);
             load_row(rho + kAhead, v[j % kAhead]);
-            if constexpr (RING > 0) load_taps(rho + 1, wv[(j + 1) % RING]);
+            if constexpr (RING > 0 && !GUARDED) load_taps(rho + 1, wv[(j + 1) % RING]);
             float ev[KE + 1] = {e0, e1}, od[KO + 2] = {o0, o1};
 #pragma unroll
             for (int m = 2; m < KE + 1; ++m) ev[m] = from_lane_above(ev[m - 2]);

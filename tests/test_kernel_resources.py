@@ -30,7 +30,7 @@ def kernels(tmp_path_factory):
         notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", obj], check=True, capture_output=True, text=True).stdout
         for entry in notes.split("  - .agpr_count")[1:]:
             field = lambda n: re.search(rf"\.{n}:\s+(\S+)", entry).group(1)
-            found[field("name")] = {n: int(field(n)) for n in ("vgpr_count", "sgpr_count", "private_segment_fixed_size")}
+            found[field("name")] = {n: int(field(n)) for n in ("vgpr_count", "sgpr_count", "sgpr_spill_count", "private_segment_fixed_size")}
             sizes = re.search(r"\.args:(.*?)\.group_segment", entry, re.S).group(1)
             found[field("name")]["first_argument"] = next((int(v) for o, v in re.findall(r"\.offset:\s+(\d+)\s+\.size:\s+(\d+)", sizes) if o == "0"), 0)
     assert len(found) > 200
@@ -58,3 +58,11 @@ def test_arguments_behind_the_taps_begin_a_block_of_their_own(kernels):
     taps = {n: r["first_argument"] for n, r in kernels.items() if "TapsOf" in n}
     assert len(taps) > 100
     assert not {n: b for n, b in taps.items() if b < 256 or b > 1024}
+
+
+@pytest.mark.parametrize("rows", [2, 3, 4])
+def test_stride2_pairs_keep_their_taps_in_scalar_registers(kernels, rows):
+    """From 8 columns on (up to 64 vector registers leave eight wavefronts a SIMD; four rows of nine columns do not fit the scalar ones, and ten go to lanes of a vector register)."""
+    mine = {n: r for n, r in kernels.items() for k in range(8, 16) if f"conv2d_fbs_stride2_pair_kernelILi{k}ELi{rows}E" in n}
+    assert len(mine) == (4 if rows == 4 else 8)
+    assert not {n: r for n, r in mine.items() if r["vgpr_count"] > 48 or r["sgpr_spill_count"] > 12}
