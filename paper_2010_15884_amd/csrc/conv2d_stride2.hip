@@ -467,16 +467,24 @@ hipError_t launch_pair_by_kw(std::integer_sequence<int, KW0, KW...>, const float
 }  // namespace
 
 // Output rows of a wavefront of the pair form, 1 to 4, by the wavefronts that one row each would make: one row gives the most of them and the shortest, which
-// decides while they do not fill the chip, more rows share input rows and windows.  us with 1 / 2 / 3 / 4 rows (wavefronts of one): 12 columns and more 780^2 12x12 (1540)
-// 5.7 / 8.2 / 9.3 / 10.4, 5524x552 12x12 (8271) 11.2 / 11.5 / 11.5 / 13.3, 807x5966 15x15 (9925) 16.6 / 16.5 / 18.2 / 19.3, 2494x4088 15x15 (21080) 29.9 / 27.6 / 26.5 / 30.4, 7344^2 12x12 114 / 92 /
-// 82.6 / 83.5; fewer columns 1340^2 8x8 (4002) 5.3 / 5.7 / 6.2 / 6.7, 1708^2 6x6 (5964) 6.2 / 5.8 / 6.0 / 6.5, 4846x930 7x7 (9680) 9.0 / 7.9 / 8.2 / 8.3, 4136x1480 7x7 (12390) 11.1 / 10.6 /
-// 9.6 / 9.9, 5448x4838 8x8 (54420) 34.8 / 29.1 / 25.2 / 26.4, 4095x6001 7x7 (51125) 37.6 / 32.0 / 27.8 / 26.6, 8192^2 11x11 129 / 107 / 95 / 89: four rows for odd heights only.
+// decides while they do not fill the chip, more rows share input rows and windows.  Lines by groups of columns from 510 random calls, us with 1 / 2 / 3 / 4 rows (wavefronts of one):
+//   12 and more   780^2 12x12 (1540) 5.7 / 8.2 / 9.3, 5109x507 14x14 (7644) 12.3 / 11.2 / 13.7, 1493x7018 13x13 (21460) 25.4 / 21.7 / 23.5, 1984x5907 14x13 (24650) 29.1 / 25.0 / 26.8,
+//                 3885x6241 13x13 (50388) 53.2 / 43.9 / 42.6
+//   10 and 11     1786x1823 10x10 (7120) 8.6 / 8.0 / 9.7 / 9.3, 3709^2 11x10 (27750) 25.6 / 21.4 / 23.8 / 22.6, 8057x2541 10x10 (44264) 32.2 / 25.0 / 29.9 / 27.3, 6517x6174 8x10 (81375) 62.5 / 51.1 / 49.8 / 44.7,
+//                 4920x5047 11x11 (54032) 47.2 / 39.2 / 36.5 / 35.7
+//   4 to 9        1340^2 8x8 (4002) 5.3 / 5.7 / 6.2 / 6.7, 4846x930 7x7 (9680) 9.0 / 7.9 / 8.2 / 8.3, 4136x1480 7x7 (12390) 11.1 / 10.6 / 9.6 / 9.9, 4095x6001 7x7 (51125) 37.6 / 32.0 / 27.8 / 26.6; even heights gain from
+//                 four rows later, when the image no longer fits the memory-side cache (7206^2 8x8 (108000) 85.5 / 65.9 / 59.3 / 55.7)
+//   1 to 3        3658x293 15x2 (3644) 6.2 / 5.6 / 6.4 / 6.4; up to 22000 (three columns: 32000, 1541x7211 15x3 (22156) 25.6 / 20.3 / 18.8 / 18.0) as those; 3942^2 9x1 (31472) 20.5 / 15.3 / 18.2 / 19.5, 5767^2 7x2 (66263) 35.5 / 26.3 / 30.8 / 34.8, 7138x3115 13x3 (46319) 37.8 / 26.4 / 28.0 / 31.4; beyond 70000 three rows
+//                 (6130^2 14x1 (73416) 74 / 56 / 52 / 54; on 8192 columns two rows are as quick, 10x1 91 / 72 / 77 / 84)
 int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw)
 {
     const int cols = 2 * (kWave - (kw + 1) / 2 / 2);
     const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
-    if (kw >= 12) return wavefronts <= 8500 ? 1 : wavefronts <= 20000 ? 2 : 3;
-    return wavefronts <= 5000 ? 1 : wavefronts <= 11500 ? 2 : wavefronts <= 45000 || kh % 2 == 0 ? 3 : 4;
+    if (wavefronts <= (kw <= 3 ? 3000 : 5000)) return 1;
+    if (kw >= 12) return wavefronts <= 40000 ? 2 : 3;
+    if (kw >= 10) return wavefronts <= 45000 ? 2 : 4;
+    if (kw <= 3) return wavefronts <= 11500 || (wavefronts > (kw == 3 ? 32000 : 22000) && wavefronts <= 70000) ? 2 : 3;
+    return wavefronts <= 11500 ? 2 : wavefronts <= (kh % 2 ? 45000 : 70000) ? 3 : 4;
 }
 
 // Output rows of a wavefront of the strip form, 1, 2 or 3 (single-row filters take one; the lines of the rest were drawn when other filters took this form too).  One row reads the most halo rows and gives the most wavefronts and
@@ -520,8 +528,10 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         switch (conv2d_stride2_pair_rows(oh, ow, kh, kw)) {
         case 1: return launch_pair_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
         case 2: return launch_pair_by_kw<2>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
-        case 3: return launch_pair_by_kw<3>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
-        default: return launch_pair_by_kw<4>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+        case 3:
+            if (kw >= 12) return launch_pair_by_kw<3>(std::integer_sequence<int, 12, 13, 14, 15>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+            return launch_pair_by_kw<3>(std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+        default: return launch_pair_by_kw<4>(std::integer_sequence<int, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
         }
     }
     switch (conv2d_stride2_strip_rows(oh, ow, kh, kw)) {                   // more than one row: images of two or three columns
