@@ -10,7 +10,7 @@
 //
 //   conv2d_fbs_stride2_block_kernel<K,K,ROWS> 2x2 .. 5x5: all input rows of two output rows up front
 //   conv2d_fbs_stride2_pair_kernel<KW,ROWS>   the rest: the input rows of one to four output rows streamed through registers, two outputs a lane
-//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  single-row filters and images of fewer than four columns: the same with four outputs a lane
+//   conv2d_fbs_stride2_strip_kernel<KW,ROWS>  single-row filters, images of fewer than four columns, two columns on large images: the same with four outputs a lane
 #include "launch.h"
 #include "systolic.h"
 #include "tiling.h"
@@ -476,15 +476,28 @@ hipError_t launch_pair_by_kw(std::integer_sequence<int, KW0, KW...>, const float
 //                 four rows later, when the image no longer fits the memory-side cache (7206^2 8x8 (108000) 85.5 / 65.9 / 59.3 / 55.7)
 //   1 to 3        3658x293 15x2 (3644) 6.2 / 5.6 / 6.4 / 6.4; up to 22000 (three columns: 32000, 1541x7211 15x3 (22156) 25.6 / 20.3 / 18.8 / 18.0) as those; 3942^2 9x1 (31472) 20.5 / 15.3 / 18.2 / 19.5, 5767^2 7x2 (66263) 35.5 / 26.3 / 30.8 / 34.8, 7138x3115 13x3 (46319) 37.8 / 26.4 / 28.0 / 31.4; beyond 70000 three rows
 //                 (6130^2 14x1 (73416) 74 / 56 / 52 / 54; on 8192 columns two rows are as quick, 10x1 91 / 72 / 77 / 84)
-int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw)
+static long long pair_wavefronts(int oh, int ow, int kw)
 {
     const int cols = 2 * (kWave - (kw + 1) / 2 / 2);
-    const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
+    return (long long)oh * (((long long)ow + cols - 1) / cols);
+}
+
+int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw)
+{
+    const long long wavefronts = pair_wavefronts(oh, ow, kw);
     if (wavefronts <= (kw <= 3 ? 3000 : 5000)) return 1;
     if (kw >= 12) return wavefronts <= 40000 ? 2 : 3;
     if (kw >= 10) return wavefronts <= 45000 ? 2 : 4;
     if (kw <= 3) return wavefronts <= 11500 || (wavefronts > (kw == 3 ? 32000 : 22000) && wavefronts <= 70000) ? 2 : 3;
     return wavefronts <= 11500 ? 2 : wavefronts <= (kh % 2 ? 45000 : 70000) ? 3 : 4;
+}
+
+// Whether the strips of four outputs a lane take a call: single rows; images of fewer than four columns; and two columns on images that do not fit the memory-side cache (us, pair form with
+// its best rows / strips: 7559^2 3x2 58.1 / 56.7, 8x2 68.0 / 63.7, 12x2 77.3 / 70.8, 6200x6300 12x2 53.2 / 49.2, 8192^2 6x2 62.2 / 64.3, 9x2 69.4 / 70.6, 15x2 85.2 / 83.7; with one column and three level or the
+// other way round: 7559^2 10x1 70.2 / 72.7, 15x3 81.5 / 79.6).
+bool conv2d_stride2_takes_strips(int w, int oh, int ow, int kh, int kw)
+{
+    return kh == 1 || w < 4 || (kw == 2 && pair_wavefronts(oh, ow, kw) > 70000);
 }
 
 // Output rows of a wavefront of the strip form, 1, 2 or 3 (single-row filters take one; the lines of the rest were drawn when other filters took this form too).  One row reads the most halo rows and gives the most wavefronts and
@@ -524,7 +537,7 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
     }
     using Widths = std::integer_sequence<int, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15>;
     const int oh = (h - kh) / 2 + 1, ow = (w - kw) / 2 + 1;
-    if (kh > 1 && w >= 4) {
+    if (!conv2d_stride2_takes_strips(w, oh, ow, kh, kw)) {
         switch (conv2d_stride2_pair_rows(oh, ow, kh, kw)) {
         case 1: return launch_pair_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
         case 2: return launch_pair_by_kw<2>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
@@ -534,7 +547,7 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         default: return launch_pair_by_kw<4>(std::integer_sequence<int, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
         }
     }
-    switch (conv2d_stride2_strip_rows(oh, ow, kh, kw)) {                   // more than one row: images of two or three columns
+    switch (conv2d_stride2_strip_rows(oh, ow, kh, kw)) {                   // more than one row: filters and images of at most three columns
     case 1: return launch_strip_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
     case 2: return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3>{}, x, h, w, xp, f, kh, kw, y, yp, s);
     default: return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3>{}, x, h, w, xp, f, kh, kw, y, yp, s);

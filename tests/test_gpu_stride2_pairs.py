@@ -32,3 +32,9 @@ def test_every_width_and_number_of_rows(kh, kw, oh, ow):
     assert oracle.max_rel_err(np.ascontiguousarray(y[1:1 + oh, 1:1 + ow]), ref, scale) <= TOL
     y[1:1 + oh, 1:1 + ow] = np.nan
     assert np.isnan(y).all()
+
+
+@pytest.mark.parametrize("kh,oh,ow", [(15, 35003, 129), (3, 23400, 258), (8, 7900, 1025)])
+def test_two_columns_on_large_images(kh, oh, ow):
+    """More than 70000 wavefronts: the strips of four outputs a lane, three rows each (whole, one and two left over), strips of 252 columns inside and at the edge."""
+    test_every_width_and_number_of_rows(kh, 2, oh, ow)

@@ -36,3 +36,13 @@ def test_calls_that_more_rows_slowed_down():
                                (3658, 293, 15, 2, 2), (5109, 507, 14, 14, 2),                               # 5.5 / 6.2 / 5.6, 11.3 / 12.4 / 11.2
                                (6517, 6174, 8, 10, 4), (5413, 5413, 6, 10, 4), (7206, 7206, 8, 8, 4)):             # 46.5 / 49.8 / 44.7, 27.7 / 30.2 / 26.8, 58.1 / 59.5 / 55.7
         assert rows((h - kh) // 2 + 1, (w - kw) // 2 + 1, kh, kw) == best
+
+
+def test_two_columns_on_large_images_take_the_strips():
+    """More than 70000 wavefronts of one row: the pair form is 2 to 23 % slower there with any number of rows."""
+    fn = B.lib()["_ZN7sysconv27conv2d_stride2_takes_stripsEiiiii"]
+    fn.argtypes, fn.restype = [ctypes.c_int] * 5, ctypes.c_bool
+    for oh, ow in ((35000, 129), (35001, 129), (70000, 128), (70001, 1)):
+        for kw in (1, 2, 3, 4, 15):
+            assert fn(2 * ow + kw + 8, oh, ow, 9, kw) == (kw == 2 and oh in (35001, 70001))
+    assert fn(3, 5, 1, 9, 2) and fn(3, 5, 1, 9, 3) and not fn(4, 5, 1, 9, 3) and fn(4000, 5, 2000, 1, 3)
