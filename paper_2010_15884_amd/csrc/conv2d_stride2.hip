@@ -168,13 +168,11 @@ hipError_t launch_block(const float* x, int h, int w, size_t xp, const float* f,
 }
 
 // ------------------------------------------------------------ strip form ----
-// Single-row filters, whose output rows share no input row, and images of fewer than four columns.  Any filter height at run time, the width at compile time: a wavefront takes ROWS output rows of a strip of 512
+// Single-row filters, whose output rows share no input row; images of fewer than four columns; two columns on large images (conv2d_stride2_takes_strips).  Any filter height at run time, the width at
+// compile time: a wavefront takes ROWS output rows of a strip of 512
 // input columns and walks down its 2*(ROWS-1)+kh input rows, kAhead of them in flight in registers.  Each row's two
-// windows are built once and applied to every output row whose filter covers it.  What bounds it is the latency of its input rows: the
-// rows requested, (2 (ROWS-1) + kh) / (2 ROWS) times the image, come from L2 for the most part.  A strip that reaches past
-// the right edge must not wait for each row by itself: with loads behind per-lane branches its wavefronts lived 28 us where the
-// others took 9, and the launch ended with them (4095x6001 7x7 37.1 us, with EdgeQuad's loads 30.5; 8192^2 11x11 118 / 94, 3000^2 9x9
-// 22.6 / 16.4).  Six or eight rows in flight are 1 to 5 % and 6 to 10 % slower than four.
+// windows are built once and applied to every output row whose filter covers it.  What bounds it: HBM on large images (7559^2 8x2 63 us), the latency of its input rows on narrow ones.
+// Six or eight rows in flight are 1 to 5 % and 6 to 10 % slower than four.
 constexpr int kAhead = 4;
 
 template <int KW, int ROWS, StripKind KIND>
@@ -273,16 +271,18 @@ __global__ __launch_bounds__(kBlock) void conv2d_fbs_stride2_strip_kernel(TapsOf
     float* yrow = y + (long long)r0 * yp;
     const bool lane_valid = lane < valid_lanes;
     const int in_col = 2 * out_col0 + 2 * kTile * lane, out_col = out_col0 + kTile * lane;
-    if (2 * out_col0 + kCols <= w_img) {
-        stride2_strip_rows<KW, ROWS, kInside>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
-    } else {
-        if constexpr (KW < 4) {
-            if (w_img < 4) {
-                stride2_strip_rows<KW, ROWS, kNarrow>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
-                return;
-            }
+    constexpr bool WIDE = ROWS == 1 || (ROWS == 3 && KW == 2);             // more rows of other widths: narrow images only
+    if constexpr (KW < 4) {
+        if (!WIDE || w_img < 4) {
+            stride2_strip_rows<KW, ROWS, kNarrow>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+            return;
         }
-        stride2_strip_rows<KW, ROWS, kEdge>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+    }
+    if constexpr (WIDE) {
+        if (2 * out_col0 + kCols <= w_img)
+            stride2_strip_rows<KW, ROWS, kInside>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
+        else
+            stride2_strip_rows<KW, ROWS, kEdge>(tf, xrow, yrow, in_col, out_col, w_img, xp, ow, yp, kh, rows_out, lane_valid);
     }
 }
 
@@ -500,24 +500,15 @@ bool conv2d_stride2_takes_strips(int w, int oh, int ow, int kh, int kw)
     return kh == 1 || w < 4 || (kw == 2 && pair_wavefronts(oh, ow, kw) > 70000);
 }
 
-// Output rows of a wavefront of the strip form, 1, 2 or 3 (single-row filters take one; the lines of the rest were drawn when other filters took this form too).  One row reads the most halo rows and gives the most wavefronts and
-// the shortest, which decides while they do not fill the chip; 250 random shapes, two rows / one row by wavefronts of one row: filters of
-// more than 60 taps up to 2000 1.27 to 1.30, 2000 to 3000 1.21, 3000 to 4096 1.06, above 5000 0.92 to 1.02; 25 to 60 taps 1.24, 1.17, 1.0,
-// 0.88; fewer 1.10, 1.03, 0.93.  So filters of up to kFewTaps taps take one row up to 3000 wavefronts, the others up to one round of the chip.
-// Single-row filters, whose output rows share no input row, take one at every size (us, three rows / two / one: 1x5 on 3000^2 inputs 8.4 / 8.1 / 6.3, on 8192^2
-// 56.6 / 49.5 / 32.9, 1x11 on 4096^2 14.4 / 12.8 / 10.4; 1x14 two / one 13.1 / 10.6).  Three rows need images large
-// enough to fill the chip with fewer wavefronts and few enough columns that their taps stay in scalar registers (2 rows / 3
-// rows from 2 M outputs on: 8x8 on 892x2450 outputs 14.6 / 12.8 us, 7x7 on 2447^2 29.7 / 27.5).
-// LDS tiles shared by four wavefronts, which smaller images used to take, are slower than two rows on 399 of 400 random shapes
-// (1.37 times on average; with their loads in flight together too).
-constexpr int kOneRowFew = 3000, kOneRow = 4096, kFewTaps = 40;
-int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw)
+// Output rows of a wavefront of the strip form.  Single rows take one at every size (us, three rows / two / one: 1x5 on 3000^2 inputs 8.4 / 8.1 / 6.3, on 8192^2
+// 56.6 / 49.5 / 32.9, 1x11 on 4096^2 14.4 / 12.8 / 10.4; 1x14 two / one 13.1 / 10.6), two columns on large images three (12x2 on 7559^2 with two 84, with three 71).  Narrow images have one strip, whose wavefronts are the output
+// rows: one row while they do not fill the chip, then two, then three (one / two / three: 3x3 on 6500x3 - / 3.8 / 4.2, 20000x3 6.5 / 5.7 / 5.6, 200000x3 45 / 38 / 32; 9x1 on 20000x3 7.8 / 6.6 / 7.0, 200000x3 56 / 43 / 41; 15x3 on
+// 6500x3 7.5 / - / 8.6: from 41 taps on one row up to 4096).
+int conv2d_stride2_strip_rows(int w, int oh, int kh, int kw)
 {
     if (kh == 1) return 1;
-    if (kw > 1 && kw <= 11 && (double)oh * ow >= 2e6) return 3;
-    const int cols = kTile * (kWave - halo_lanes((kw + 1) / 2));
-    const long long wavefronts = (long long)oh * (((long long)ow + cols - 1) / cols);
-    return wavefronts <= (kh * kw <= kFewTaps ? kOneRowFew : kOneRow) ? 1 : 2;
+    if (w >= 4 || oh > 100000) return 3;
+    return oh <= (kh * kw <= 40 ? 3000 : 4096) ? 1 : 2;
 }
 
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
@@ -547,10 +538,11 @@ hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, co
         default: return launch_pair_by_kw<4>(std::integer_sequence<int, 4, 5, 6, 7, 8, 9, 10, 11>{}, x, h, w, xp, f, kh, kw, y, yp, s);
         }
     }
-    switch (conv2d_stride2_strip_rows(oh, ow, kh, kw)) {                   // more than one row: filters and images of at most three columns
+    using Narrow = std::integer_sequence<int, 1, 2, 3>;
+    switch (conv2d_stride2_strip_rows(w, oh, kh, kw)) {
     case 1: return launch_strip_by_kw<1>(Widths{}, x, h, w, xp, f, kh, kw, y, yp, s);
-    case 2: return launch_strip_by_kw<2>(std::integer_sequence<int, 1, 2, 3>{}, x, h, w, xp, f, kh, kw, y, yp, s);
-    default: return launch_strip_by_kw<3>(std::integer_sequence<int, 2, 3>{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    case 2: return launch_strip_by_kw<2>(Narrow{}, x, h, w, xp, f, kh, kw, y, yp, s);
+    default: return launch_strip_by_kw<3>(Narrow{}, x, h, w, xp, f, kh, kw, y, yp, s);
     }
 }
 

@@ -72,7 +72,9 @@ hipError_t launch_conv1d_stt(const float* x, size_t n, const float* w, int k, fl
 
 hipError_t launch_conv2d_fbs(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                              float* y, size_t yp, hipStream_t s);
-int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);     // output rows of a wavefront, 1 to 3; filters with a block form aside
+bool conv2d_stride2_takes_strips(int w, int oh, int ow, int kh, int kw);   // four outputs a lane (else two); square filters of 2 to 5 have kernels of their own where w >= 4
+int conv2d_stride2_strip_rows(int w, int oh, int kh, int kw);              // output rows of a wavefront of these strips, 1 to 3
+int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw);              // and of the others, 1 to 4
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                      float* y, size_t yp, hipStream_t s);
 int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw);      // AUTO without the split kernel (api.hip)

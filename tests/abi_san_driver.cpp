@@ -19,7 +19,9 @@
 namespace sysconv {
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw);
 bool conv2d_split_pays(int oh, int ow, int kh, int kw);
-int conv2d_stride2_strip_rows(int oh, int ow, int kh, int kw);
+bool conv2d_stride2_takes_strips(int w, int oh, int ow, int kh, int kw);
+int conv2d_stride2_strip_rows(int w, int oh, int kh, int kw);
+int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw);
 bool conv1d_split_pays(size_t n, int k);
 int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw);
 }
@@ -234,34 +236,36 @@ int main()
         EXPECT(sysconv::conv1d_split_pays(n, SYS_MAX_K1D), 1);
     }
 
-    // ---- stride 2: output rows of a wavefront, on both sides of every line
-    EXPECT(sysconv::conv2d_stride2_strip_rows(3000, 200, 4, 10), 1);       // up to 40 taps: 3000 wavefronts of one row
-    EXPECT(sysconv::conv2d_stride2_strip_rows(3001, 200, 4, 10), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1500, 253, 3, 4), 1);        // (strips of 252 columns)
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1501, 253, 3, 4), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1500, 256, 10, 1), 1);       // (of 256 for one column)
-    EXPECT(sysconv::conv2d_stride2_strip_rows(3001, 256, 10, 1), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(4096, 200, 6, 7), 1);        // more taps: 4096
-    EXPECT(sysconv::conv2d_stride2_strip_rows(4097, 200, 6, 7), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(2048, 496, 15, 15), 1);      // (of 248 columns)
-    EXPECT(sysconv::conv2d_stride2_strip_rows(2049, 496, 15, 15), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1000, 1999, 7, 7), 2);       // 2 M outputs
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1000, 2000, 7, 7), 3);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 2, 11), 3);      // 2 to 11 columns
-    EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 2, 12), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 15, 1), 2);
-    for (int kw = 1; kw <= SYS_MAX_K2D; ++kw) EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 1, kw), 1);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(1137, 1676, 6, 3), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(2910, 100, 2, 5), 1);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(143, 193, 15, 15), 1);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(769, 1865, 7, 7), 2);
-    EXPECT(sysconv::conv2d_stride2_strip_rows(4089, 4089, 15, 15), 2);
+    // ---- stride 2: strips of four outputs a lane, output rows of a wavefront, on both sides of every line
+    for (int kw = 1; kw <= SYS_MAX_K2D; ++kw) {
+        EXPECT(sysconv::conv2d_stride2_takes_strips(4000, 4000, 4000, 1, kw), 1);      // single rows
+        EXPECT(sysconv::conv2d_stride2_strip_rows(4000, 4000, 1, kw), 1);
+        EXPECT(sysconv::conv2d_stride2_takes_strips(4000, 1000, 1000, 2, kw), 0);
+        EXPECT(sysconv::conv2d_stride2_takes_strips(30000, 30000, 10000, 2, kw), kw == 2);   // two columns on large images
+    }
+    EXPECT(sysconv::conv2d_stride2_strip_rows(30000, 30000, 2, 2), 3);
+    EXPECT(sysconv::conv2d_stride2_takes_strips(3, 100, 1, 9, 3), 1);      // narrow images
+    EXPECT(sysconv::conv2d_stride2_takes_strips(4, 100, 1, 9, 3), 0);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3, 3000, 13, 3), 1);         // up to 40 taps: 3000 wavefronts of one row
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3, 3001, 13, 3), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3, 4096, 14, 3), 1);         // more taps: 4096
+    EXPECT(sysconv::conv2d_stride2_strip_rows(3, 4097, 14, 3), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1, 100000, 2, 1), 2);
+    EXPECT(sysconv::conv2d_stride2_strip_rows(1, 100001, 2, 1), 3);
+    // every call has a kernel that is built: pairs with three rows of 10 or 11 columns or four of 1 to 3 or 12 and more are not
     for (int kh = 1; kh <= SYS_MAX_K2D; ++kh)
         for (int kw = 1; kw <= SYS_MAX_K2D; ++kw)
-            for (int oh : {1, 8, 1000, 20000, INT_MAX / 2 + 1})
-                for (int ow : {1, 252, 1000, 20000, INT_MAX / 2 + 1}) {
-                    const int rows = sysconv::conv2d_stride2_strip_rows(oh, ow, kh, kw);
-                    if (rows != 1 && rows != 2 && !(rows == 3 && kw >= 2 && kw <= 11)) ++failures;
+            for (int oh : {1, 8, 1000, 4000, 20000, 100001, INT_MAX / 2 + 1})
+                for (int ow : {1, 2, 124, 252, 1000, 20000, INT_MAX / 2 + 1}) {
+                    const int w = 2 * (ow < INT_MAX / 4 ? ow - 1 : INT_MAX / 4) + kw;
+                    if (sysconv::conv2d_stride2_takes_strips(w, oh, ow, kh, kw)) {
+                        const int rows = sysconv::conv2d_stride2_strip_rows(w, oh, kh, kw);
+                        if (rows != 1 && !((rows == 2 || rows == 3) && kw <= 3)) ++failures;
+                        if (w >= 4 && rows != 1 && !(rows == 3 && kw == 2)) ++failures;
+                    } else {
+                        const int rows = sysconv::conv2d_stride2_pair_rows(oh, ow, kh, kw);
+                        if (rows != 1 && rows != 2 && !(rows == 3 && kw != 10 && kw != 11) && !(rows == 4 && kw >= 4 && kw <= 11)) ++failures;
+                    }
                 }
 
     // ---- queries over their whole domain and beyond

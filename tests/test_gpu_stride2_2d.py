@@ -123,9 +123,7 @@ def test_stride2_2d_unsupported_requests_launch_nothing():
     assert (y == 7.0).all()
 
 
-# Every width and number of rows that the strips are built for: one and two rows of 1 .. 15 columns, three of 2 .. 11.  700 x 2301 inputs take one
-# row, 2401 x 2403 two, 4003 x 4099 and 2801 x 4101 three (the last block of one or two; two rows for 1 and for 12 columns and more), as
-# test_stride2_rules.py checks without a GPU.
+# Filters of every width on images that fill the chip and more (which kernels run on them: test_stride2_pair_rules.py and test_stride2_rules.py, for images of their own).
 STRIPS = [(15, 1), (1, 1), (9, 2), (13, 3), (3, 4), (4, 5), (1, 6), (6, 6), (7, 7), (2, 8), (9, 9), (5, 10), (4, 11), (11, 11), (2, 12), (3, 13), (6, 14),
           (15, 15)]
 STRIP_IMAGES = [(4003, 4099), (2801, 4101), (2401, 2403), (700, 2301)]

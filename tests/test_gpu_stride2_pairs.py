@@ -16,10 +16,12 @@ FILTERS = [(5, 1), (3, 2), (7, 3), (9, 4), (3, 5), (7, 6), (7, 7), (9, 8), (9, 9
 OUTPUTS = [(701, 145), (4001, 145), (9002, 145), (23001, 145)]
 
 
-@pytest.mark.parametrize("kh,kw", FILTERS)
-@pytest.mark.parametrize("oh,ow", OUTPUTS)
-def test_every_width_and_number_of_rows(kh, kw, oh, ow):
-    h, w = 2 * (oh - 1) + kh + (kw & 1), 2 * (ow - 1) + kw + (kh & 1)
+# more than 70000 wavefronts of one row: the strips of four outputs a lane, three rows each (whole, one and two left over), strips of 252 columns inside and at the edge
+LARGE_TWO_COLUMNS = [(15, 35003, 129), (3, 23400, 258), (8, 7900, 1025)]
+
+
+def run_in_a_region(kh, kw, h, w):
+    oh, ow = (h - kh) // 2 + 1, (w - kw) // 2 + 1
     x, f = W.random_case(kh * 100 + kw, (h, w), (kh, kw), x_range=(0.0, 1.0))
     big = torch.full((h, w + 5), float("nan"), dtype=torch.float32, device="cuda")
     big[:, 2:2 + w] = dev(x)
@@ -34,7 +36,12 @@ def test_every_width_and_number_of_rows(kh, kw, oh, ow):
     assert np.isnan(y).all()
 
 
-@pytest.mark.parametrize("kh,oh,ow", [(15, 35003, 129), (3, 23400, 258), (8, 7900, 1025)])
+@pytest.mark.parametrize("kh,kw", FILTERS)
+@pytest.mark.parametrize("oh,ow", OUTPUTS)
+def test_every_width_and_number_of_rows(kh, kw, oh, ow):
+    run_in_a_region(kh, kw, 2 * (oh - 1) + kh + (kw & 1), 2 * (ow - 1) + kw + (kh & 1))
+
+
+@pytest.mark.parametrize("kh,oh,ow", LARGE_TWO_COLUMNS)
 def test_two_columns_on_large_images(kh, oh, ow):
-    """More than 70000 wavefronts: the strips of four outputs a lane, three rows each (whole, one and two left over), strips of 252 columns inside and at the edge."""
-    test_every_width_and_number_of_rows(kh, 2, oh, ow)
+    run_in_a_region(kh, 2, 2 * (oh - 1) + kh, 2 * (ow - 1) + 2 + (kh & 1))
