@@ -820,7 +820,9 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
 // ------------------------------------------------------------ FBS strips ----
 // Filters of 8 to 15 columns: a wavefront takes ROWS output rows of a strip of 256 input columns and walks down their ROWS + kh - 1 input rows, four of them in
 // flight.  Each row's KW-wide window is built once with KW - 1 hand-overs and applied to every output row whose filter covers it; the taps come in a row ahead of
-// their use, in a ring of scalar registers (with 12 and 14 columns a ring is slower: 6130^2 14x14 236 / 232 us, 2500^2 8x12 26.8 / 24.9).  The tile kernel with run-time sizes that served these filters staged its rows in LDS
+// their use, in a ring.  Left in the middle, the body has the ring copied to vector registers (92 to 150 of them with two and three rows); with every row guarded instead it stays in scalar registers (44 to 52).  us, left (12 and 14
+// columns without a ring, which was slower) / guarded: 6130^2 14x14 238 / 230, 415^2 12x12 6.05 / 5.1, 2500^2 8x12 24.9 / 24.1, 3109^2 9x9 31.4 / 30.5; 12 columns and more 0.97 with one row, 0.985 with two, 0.975 with three, 8 and 9
+// with three 0.97.  The others are quicker left: 10 and 11 columns (three rows 1.01, 5952x796 14x10 28.9 / 30.3; two 1.01), 8 and 9 with one (902^2 9x9 6.45 / 6.65) and level with two.  The tile kernel with run-time sizes that served these filters staged its rows in LDS
 // and handed the inputs on once for every filter row: us, that / this: 8192^2 11x11 354 / 257 (SBM 257), 6130^2 14x14 268 / 234, 3109^2 9x9 36.8 / 31.0, 5694x2688 9x15 85.7 / 72.0,
 // 1500^2 15x15 31.0 / 23.9, 491x4731 12x9 16.4 / 12.6, 902^2 9x9 8.6 / 6.5, 415^2 12x12 11.7 / 6.0.
 // What bounds it: the vector ALUs on large images (11x11: 547 instructions for four outputs, 484 of them the multiply-adds), the latency of a wavefront's rows on small ones.
@@ -831,7 +833,8 @@ __device__ __forceinline__ void fbs_strip_rows(kernarg_floats taps_f, const floa
                                                int w_img, long long xp, int ow, long long yp, int kh, int rows_out, bool lane_valid)
 {
     // filter row p waits in slot p mod RING from input row p - 1 on to input row p + ROWS - 1
-    constexpr int RING = ROWS == 1 ? 2 : ROWS <= 3 && KW != 12 && KW != 14 ? 4 : 0;
+    constexpr int RING = ROWS == 1 ? 2 : ROWS <= 3 ? 4 : 0;
+    constexpr bool GUARDED = KW >= 12 || (KW <= 9 && ROWS == 3);
     static_assert(RING == 0 || RING >= ROWS + 1, "a slot is free again when the next filter row comes in");
     const int rows_in = rows_out - 1 + kh;
     const EdgeQuad quad(col, w_img);
@@ -855,18 +858,20 @@ __device__ __forceinline__ void fbs_strip_rows(kernarg_floats taps_f, const floa
 #pragma unroll
         for (int j = 0; j < kFbsAhead; ++j) {
             const int rho = rho0 + j;
-            if (rho >= rows_in) break;                                     // uniform
+            if (!GUARDED && rho >= rows_in) break;                         // uniform
             if constexpr (RING > 0) {
                 __builtin_amdgcn_sched_barrier(0);                         // (the taps of the next row stay where they are asked for)
+                if constexpr (GUARDED) load_taps(rho + 1, wv[(j + 1) % (RING > 0 ? RING : 1)]);
             } else {
 #pragma unroll
                 for (int r = 0; r < ROWS; ++r) load_taps(rho - r, wv[r]);
             }
+            if (GUARDED && rho >= rows_in) continue;                       // uniform
             f4u t = v[j];
             float win[KW + 3] = {t.x, t.y, t.z, t.w};
             if constexpr (EDGE) quad.put_right(win[0], win[1], win[2], win[3]);
             load_row(rho + kFbsAhead, v[j]);
-            if constexpr (RING > 0) load_taps(rho + 1, wv[(j + 1) % (RING > 0 ? RING : 1)]);
+            if constexpr (RING > 0 && !GUARDED) load_taps(rho + 1, wv[(j + 1) % (RING > 0 ? RING : 1)]);
 #pragma unroll
             for (int m = 4; m < KW + 3; ++m) win[m] = from_lane_above(win[m - 4]);
 #pragma unroll
