@@ -496,6 +496,15 @@ __global__ __launch_bounds__(kBlock, 2) void conv2d_split_kernel(
     }
 }
 
+// Output rows of a workgroup's block: whole groups, at most kMaxChunks - 1 chunks.
+template <int JC, int NS>
+int block_rows(int oh, int ow)
+{
+    using S = SplitShape<JC, NS>;
+    const int strips = (ow + kCols - 1) / kCols, all = (oh + S::JR - 1) / S::JR;
+    return S::JR * matrix_block_groups(all, strips, NS, S::UG, S::NB, 12.0, (kMaxChunks - 1) * kChunk / S::JR);
+}
+
 template <int JC, int NS>
 hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y, size_t yp,
                         hipStream_t s)
@@ -504,8 +513,7 @@ hipError_t launch_split(const float* x, int h, int w, size_t xp, const float* f,
     const TapsOf<S::TAPS> taps(f, kh * kw);
     const int oh = h - kh + 1, ow = w - kw + 1;
     const int strips = (ow + kCols - 1) / kCols;
-    const int all = (oh + S::JR - 1) / S::JR;
-    const long long rows = (long long)S::JR * matrix_block_groups(all, strips, NS, S::UG, S::NB, 12.0, (kMaxChunks - 1) * kChunk / S::JR);
+    const long long rows = block_rows<JC, NS>(oh, ow);
     const int row_blocks = (int)((oh + rows - 1) / rows);
     const long long groups = (long long)row_blocks * strips;
     const long long per_xcd = (groups + kXcds - 1) / kXcds;
@@ -578,25 +586,40 @@ bool conv2d_split_pays(int oh, int ow, int kh, int kw)
     return outputs >= (kh <= 5 ? 2.6e6 : t < 14.2 ? 1.6e6 : 0.9e6) && outputs >= (taps < 64 ? 0.075e6 : 0.05e6) * (18.5 - t) * (18.5 - t);
 }
 
-hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
-                               size_t yp, hipStream_t s)
+namespace {
+template <class F>
+auto with_shape(int kh, int kw, F&& f)           // f<JC, NS> of the kernel that serves the filter
 {
     const int units = split_units(kh, kw);
+    using Four = std::integral_constant<int, 4>;
+    using Two = std::integral_constant<int, 2>;
     if (kh <= 13 && kw <= 13) {
         switch (units) {
-        case 4: return launch_split<4, 4>(x, h, w, xp, f, kh, kw, y, yp, s);
-        case 5: return launch_split<4, 5>(x, h, w, xp, f, kh, kw, y, yp, s);
-        case 6: return launch_split<4, 6>(x, h, w, xp, f, kh, kw, y, yp, s);
-        case 7: return launch_split<4, 7>(x, h, w, xp, f, kh, kw, y, yp, s);
-        default: return launch_split<4, 8>(x, h, w, xp, f, kh, kw, y, yp, s);
+        case 4: return f(Four{}, std::integral_constant<int, 4>{});
+        case 5: return f(Four{}, std::integral_constant<int, 5>{});
+        case 6: return f(Four{}, std::integral_constant<int, 6>{});
+        case 7: return f(Four{}, std::integral_constant<int, 7>{});
+        default: return f(Four{}, std::integral_constant<int, 8>{});
         }
     }
     switch (units) {
-    case 8: return launch_split<2, 8>(x, h, w, xp, f, kh, kw, y, yp, s);
-    case 9: return launch_split<2, 9>(x, h, w, xp, f, kh, kw, y, yp, s);
-    case 10: return launch_split<2, 10>(x, h, w, xp, f, kh, kw, y, yp, s);
-    default: return launch_split<2, 11>(x, h, w, xp, f, kh, kw, y, yp, s);
+    case 8: return f(Two{}, std::integral_constant<int, 8>{});
+    case 9: return f(Two{}, std::integral_constant<int, 9>{});
+    case 10: return f(Two{}, std::integral_constant<int, 10>{});
+    default: return f(Two{}, std::integral_constant<int, 11>{});
     }
+}
+}  // namespace
+
+int conv2d_split_block_rows(int oh, int ow, int kh, int kw)
+{
+    return with_shape(kh, kw, [&](auto jc, auto ns) { return block_rows<decltype(jc)::value, decltype(ns)::value>(oh, ow); });
+}
+
+hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
+                               size_t yp, hipStream_t s)
+{
+    return with_shape(kh, kw, [&](auto jc, auto ns) { return launch_split<decltype(jc)::value, decltype(ns)::value>(x, h, w, xp, f, kh, kw, y, yp, s); });
 }
 
 }  // namespace sysconv

@@ -95,6 +95,7 @@ hipError_t launch_conv2d_mfma(const float* x, int h, int w, size_t xp, const flo
 // Matrix-core path without conditions on the input (conv2d_split.hip).
 bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw);
 bool conv2d_split_pays(int oh, int ow, int kh, int kw);     // where it is the fastest kernel
+int conv2d_split_block_rows(int oh, int ow, int kh, int kw);      // output rows of a workgroup
 hipError_t launch_conv2d_split(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                float* y, size_t yp, hipStream_t s);
 

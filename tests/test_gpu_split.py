@@ -126,12 +126,18 @@ def _same_as_fbs(d, f):
     assert ((want - got).abs()[ok] <= TOL * scale[ok]).all()
 
 
-# Row blocks of 1 .. 63 chunks (the rule takes so many that the workgroups fill the chip in whole rounds), with one marked
-# chunk early, late or in the last place, neighbouring ones, so many that a block is given up at once or half way, and marks in
-# each four rows of a chunk (53 rows apart), whose output rows overlap or do not.
+# Row blocks of 1 .. 56 chunks (32 with 4 x 4 offsets: the most that the rule takes; test_split_rules.py checks the heights), with one marked
+# chunk early, late or in the last place, on either side of the 32nd and in the one that only finishes groups (row 16 n of n chunks), neighbouring ones, so many that a block is given up at once,
+# half way or past the 32nd, and marks in each four rows of a chunk (53 rows apart), whose output rows overlap or do not.
+MARKED_IMAGES = [(13, 13, 300, 500), (13, 13, 2900, 600), (10, 12, 30000, 600), (13, 13, 104000, 600), (15, 15, 171000, 600),
+                 (13, 13, 63500, 741), (15, 15, 128000, 600), (15, 15, 143000, 600)]
+
+
 @pytest.mark.parametrize("rows", [[3], [16 * 30], [16 * 62 + 5], [16 * 63], [40, 60, 900], list(range(500, 600, 16)), list(range(0, 1100, 16)),
-                                  list(range(0, 1100, 96)), list(range(15, 1100, 112)), list(range(16, 32)), [7, 8], list(range(11, 1100, 53))])
-@pytest.mark.parametrize("kh,kw,h,w", [(13, 13, 300, 500), (13, 13, 2900, 600), (10, 12, 30000, 600), (13, 13, 104000, 600), (15, 15, 171000, 600)])
+                                  list(range(0, 1100, 96)), list(range(15, 1100, 112)), list(range(16, 32)), [7, 8], list(range(11, 1100, 53)),
+                                  [2, 16 * 31 + 2], [16 * 32], [16 * 31 + 15, 16 * 32 + 9, 16 * 33], [16 * 47 + 3, 16 * 48 + 1], [16 * 55 + 15], [5, 16 * 56], [16 * 32 - 1, 16 * 56 + 14],
+                                  list(range(16 * 33, 16 * 57, 16))])
+@pytest.mark.parametrize("kh,kw,h,w", MARKED_IMAGES)
 def test_marked_chunks_in_blocks_of_every_length(rows, kh, kw, h, w):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(kh)

@@ -4,6 +4,7 @@ import ctypes
 import pytest
 
 from paper_2010_15884_amd import binding as B
+from test_gpu_split import MARKED_IMAGES
 
 
 def split_pays(oh, ow, kh, kw):
@@ -31,3 +32,18 @@ def test_filters_keep_the_kernel_with_the_smaller_error(kh, kw, least):
 def test_padding_counts_in_full(kh, kw, padded, even):
     assert not split_pays(*padded, kh, kw)
     assert split_pays(*even, kh, kw)
+
+
+def test_images_with_marked_chunks_have_blocks_of_every_length():
+    """Chunks (16 rows) of a row block on the images of the GPU test: the first mark word alone, both, and the most there can be."""
+    fn = B.lib()["_ZN7sysconv23conv2d_split_block_rowsEiiii"]
+    fn.argtypes, fn.restype = [ctypes.c_int] * 4, ctypes.c_int
+
+    def chunks(kh, kw, h, w):
+        return -(-fn(h - kh + 1, w - kw + 1, kh, kw) // 16)
+
+    assert [chunks(*i) for i in MARKED_IMAGES] == [1, 2, 12, 12, 14, 32, 48, 56]
+    # no image has longer blocks: what the marks have room for, with the chunk that only finishes groups
+    for kh, kw, most in ((13, 13, 32), (4, 13, 32), (15, 15, 56), (6, 14, 56)):
+        seen = {chunks(kh, kw, h, w) for w in (100, 250, 600, 1201, 5000, 40000) for h in range(1000, 200000, 500)}
+        assert max(seen) == most
