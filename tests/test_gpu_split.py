@@ -1,7 +1,7 @@
 """The split matrix-core kernel behind AUTO: filters and images at the edges of its strips (240 columns), chunks (16 rows)
 and row blocks, and the inputs that its three-part split does not carry.
 
-Every filter below is one that AUTO sends to the kernel at any image size (or, where said, from the size used on).
+Every call below is one that AUTO sends to the kernel (test_split_rules.py checks that without a GPU).
 Tolerance: the split is exact, six of nine products are kept and accumulated in fp32; the parity metric's 1e-5 covers
 225 roundings of 2^-24 (1.3e-5 would need them all worst and of one sign).  Integers whose products and sums stay below
 2^24 need one part each and come out bit for bit.
@@ -18,6 +18,9 @@ pytestmark = pytest.mark.gpu
 
 # one filter for each number of units, both operand shapes
 FILTERS = [(4, 13), (5, 13), (7, 12), (9, 13), (10, 12), (13, 13), (12, 12), (9, 14), (11, 15), (13, 14), (15, 15), (14, 11)]
+EDGES = [(1, 1), (16, 240), (17, 241), (15, 243), (33, 482), (100, 719)]                   # outputs
+SEVERAL_CHUNKS = [5000, 8000, 10500, 13001]                                               # rows of 600 columns: row blocks of 2 .. 5 chunks, odd and even, whole and cut
+CUT_CHUNKS = [900, 2000, 3400, 4100, 5500, 6200, 6900]                                    # blocks of 3, 6, 5, 7, 9, 10, 11 groups (8 x 2: 1 .. 6): chunks cut after each group
 
 
 def _case(h, w, kh, kw, seed=0, top=1.0):
@@ -48,21 +51,21 @@ def test_auto_errs_less_than_the_vector_kernels(kh, kw, oh, ow):
 
 
 @pytest.mark.parametrize("kh,kw", FILTERS)
-@pytest.mark.parametrize("oh,ow", [(1, 1), (16, 240), (17, 241), (15, 243), (33, 482), (100, 719)])
+@pytest.mark.parametrize("oh,ow", EDGES)
 def test_edges_of_strips_and_chunks(kh, kw, oh, ow):
     x, f = _case(oh + kh - 1, ow + kw - 1, kh, kw, top=255.0)
     assert err2d(run2d(x, f, "AUTO"), x, f) <= TOL
 
 
 @pytest.mark.parametrize("kh,kw", [(9, 13), (13, 13), (15, 15)])
-@pytest.mark.parametrize("h", [5000, 8000, 10500, 13001])      # row blocks of 2 .. 5 chunks: odd and even, whole and cut
+@pytest.mark.parametrize("h", SEVERAL_CHUNKS)
 def test_row_blocks_of_several_chunks(kh, kw, h):
     x, f = _case(h, 600, kh, kw)
     assert err2d(run2d(x, f, "AUTO"), x, f) <= TOL
 
 
 @pytest.mark.parametrize("kh,kw", [(9, 13), (13, 13), (15, 15), (6, 14)])
-@pytest.mark.parametrize("h", [900, 2000, 3400, 4100, 5500, 6200, 6900])       # blocks of 3, 6, 5, 7, 9, 10, 11 groups (8 x 2: 2 .. 6): chunks cut after each group
+@pytest.mark.parametrize("h", CUT_CHUNKS)
 def test_blocks_that_end_inside_a_chunk(kh, kw, h):
     x, f = _case(h, 600, kh, kw, seed=1)
     assert err2d(run2d(x, f, "AUTO"), x, f) <= TOL

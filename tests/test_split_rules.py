@@ -4,7 +4,7 @@ import ctypes
 import pytest
 
 from paper_2010_15884_amd import binding as B
-from test_gpu_split import MARKED_IMAGES
+from test_gpu_split import CUT_CHUNKS, EDGES, FILTERS, MARKED_IMAGES, SEVERAL_CHUNKS
 
 
 def split_pays(oh, ow, kh, kw):
@@ -34,13 +34,33 @@ def test_padding_counts_in_full(kh, kw, padded, even):
     assert split_pays(*even, kh, kw)
 
 
-def test_images_with_marked_chunks_have_blocks_of_every_length():
-    """Chunks (16 rows) of a row block on the images of the GPU test: the first mark word alone, both, and the most there can be."""
+def block_rows(oh, ow, kh, kw):
     fn = B.lib()["_ZN7sysconv23conv2d_split_block_rowsEiiii"]
     fn.argtypes, fn.restype = [ctypes.c_int] * 4, ctypes.c_int
+    return fn(oh, ow, kh, kw)
+
+
+def test_calls_of_the_gpu_tests_run_the_split_kernel():
+    for kh, kw in FILTERS:
+        assert all(split_pays(oh, ow, kh, kw) for oh, ow in EDGES)
+    for kh, kw in [(9, 13), (13, 13), (15, 15), (6, 14)]:
+        assert all(split_pays(h - kh + 1, 601 - kw, kh, kw) for h in SEVERAL_CHUNKS + CUT_CHUNKS)
+    for kh, kw, h, w in [(13, 13, 60, 500), (15, 15, 60, 500), (11, 11, 1500, 1700), (9, 13, 70, 500), (13, 13, 8000, 600), (15, 15, 8000, 600), (9, 13, 300, 700),
+                         (13, 13, 150, 500), (15, 15, 150, 500), (13, 13, 80, 500), (13, 13, 300, 700), *MARKED_IMAGES]:
+        assert split_pays(h - kh + 1, w - kw + 1, kh, kw), (kh, kw, h, w)
+
+
+def test_blocks_of_the_gpu_tests_end_everywhere_in_a_chunk():
+    for kh, kw, rows in [(9, 13, 4), (13, 13, 4), (15, 15, 8), (6, 14, 8)]:
+        assert [block_rows(h - kh + 1, 601 - kw, kh, kw) for h in SEVERAL_CHUNKS] == [32, 48, 64, 80]
+        assert {block_rows(h - kh + 1, 601 - kw, kh, kw) // rows % (16 // rows) for h in CUT_CHUNKS + SEVERAL_CHUNKS} == set(range(16 // rows))
+
+
+def test_images_with_marked_chunks_have_blocks_of_every_length():
+    """Chunks (16 rows) of a row block on the images of the GPU test: the first mark word alone, both, and the most there can be."""
 
     def chunks(kh, kw, h, w):
-        return -(-fn(h - kh + 1, w - kw + 1, kh, kw) // 16)
+        return -(-block_rows(h - kh + 1, w - kw + 1, kh, kw) // 16)
 
     assert [chunks(*i) for i in MARKED_IMAGES] == [1, 2, 12, 12, 14, 32, 48, 56]
     # no image has longer blocks: what the marks have room for, with the chunk that only finishes groups
