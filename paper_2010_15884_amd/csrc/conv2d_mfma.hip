@@ -330,6 +330,23 @@ float largest_finite_magnitude(const float* f, int n)
     return amax;
 }
 
+// Output rows of a workgroup's block: whole groups.
+// Filters of up to three rows, whose groups end in the chunk they start in or the next: short blocks once they fill the device, one chunk's (NS = 2: four groups, eight units) or two (NS = 3: eight groups, 17 units, the
+// last in a third chunk; us, blocks of the model's heights / this: 1775x7797 1x13 26.5 / 21.4, 5180^2 3x7 42.5 / 35.6, 7233x407 1x1 8.1 / 7.5.  Seven groups, which end with the second chunk, are 7 % quicker on some images and up to 16 % slower
+// on others: 2110x1828 2x7 10.4 / 9.7, 5180^2 3x7 37.3 / 35.6, 1289x2854 3x1 8.5 / 9.9; 0.994 on average over 60).
+// The model's set-up of a block is 8 steps.  With results through LDS it is a fit and no set-up: large images are bound by memory, and with more blocks under way their loads and stores spread better than the model
+// says, the more so the fewer rows a filter has.  2, 1, 0 steps for NS = 2, 3, 4 and 1 .. 4 for 5 .. 8 (us, 8 / this, long runs: 8192^2 1x5 107 / 101, 3x3 108.5 / 102.9, 5x5 108 / 103, 20000x2500 4x4 88.7 / 85.3, 7500^2 4x7 95 / 91.5, 6800x8000
+// 7x7 94.0 / 90.4, 8000^2 7x7 116 / 108, 9000x6000 6x6 96.8 / 91.6, 7899^2 9x9 110.5 / 106.7; the other way round 8192^2 9x9 109.4 / 112.0, 7899^2 12x12 108.1 / 113.4).
+template <int NS, bool ROWS_OUT>
+int block_rows(int oh, int ow)
+{
+    const int strips = (ow + kCols - 1) / kCols;
+    const int all = (oh - 1) / 4 + 1;
+    constexpr int kShort = 4 * (NS - 1);
+    if (NS <= 3 && !ROWS_OUT && (double)((all + kShort - 1) / kShort) * strips > kPlaces) return 4 * kShort;
+    return 4 * matrix_block_groups(all, strips, NS, 2, 1, ROWS_OUT ? (NS > 4 ? NS - 4 : 4 - NS) : 8, 128);
+}
+
 template <int NS, bool ROWS_OUT>
 hipError_t launch_mfma(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw, float* y,
                        size_t yp, hipStream_t s)
@@ -345,12 +362,7 @@ hipError_t launch_mfma(const float* x, int h, int w, size_t xp, const float* f, 
 
     const int oh = h - kh + 1, ow = w - kw + 1;
     const int strips = (ow + kCols - 1) / kCols;
-    const int all = (oh - 1) / 4 + 1;
-    // Filters of up to three rows, whose groups end in the chunk they start in or the next: short blocks, of whole chunks, once they fill the device (us, this / the model's:
-    // 1775x7797 1x13 21.4 / 26.5, 5180^2 3x7 35.6 / 42.5, 7233x407 1x1 7.5 / 8.1).
-    constexpr int kShort = 4 * (NS - 1);
-    const bool few = NS <= 3 && !ROWS_OUT && (double)((all + kShort - 1) / kShort) * strips > kPlaces;
-    const long long rows = 4LL * (few ? kShort : matrix_block_groups(all, strips, NS, 2, 1, ROWS_OUT ? (NS > 4 ? NS - 4 : 4 - NS) : 8, 128));
+    const long long rows = block_rows<NS, ROWS_OUT>(oh, ow);
     const int row_blocks = (int)((oh + rows - 1) / rows);
     const long long groups = (long long)row_blocks * strips;
     const long long per_xcd = (groups + kXcds - 1) / kXcds;
@@ -379,24 +391,37 @@ bool conv2d_mfma_rows_out(int oh, int ow, size_t yp)
     return (double)oh * ow >= 40e6 || yp > ((size_t)1 << 25);
 }
 
+namespace {
+template <class F>
+auto with_units(int kh, F&& f)                  // f<NS>
+{
+    switch ((kh + 4) / 2) {                                    // NS = ceil((kh + 3) / 2)
+    case 2: return f(std::integral_constant<int, 2>{});
+    case 3: return f(std::integral_constant<int, 3>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    case 5: return f(std::integral_constant<int, 5>{});
+    case 6: return f(std::integral_constant<int, 6>{});
+    case 7: return f(std::integral_constant<int, 7>{});
+    default: return f(std::integral_constant<int, 8>{});
+    }
+}
+}  // namespace
+
+int conv2d_mfma_block_rows(int oh, int ow, size_t yp, int kh)
+{
+    const bool rows_out = conv2d_mfma_rows_out(oh, ow, yp);
+    return with_units(kh, [&](auto ns) { return rows_out ? block_rows<decltype(ns)::value, true>(oh, ow) : block_rows<decltype(ns)::value, false>(oh, ow); });
+}
+
 hipError_t launch_conv2d_mfma(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                               float* y, size_t yp, hipStream_t s)
 {
     if (!has_conv2d_mfma(kh, kw)) return hipErrorInvalidValue;
     const bool rows_out = conv2d_mfma_rows_out(h - kh + 1, w - kw + 1, yp);
-    auto launch = [&](auto ns) {
+    return with_units(kh, [&](auto ns) {
         constexpr int NS = decltype(ns)::value;
         return rows_out ? launch_mfma<NS, true>(x, h, w, xp, f, kh, kw, y, yp, s) : launch_mfma<NS, false>(x, h, w, xp, f, kh, kw, y, yp, s);
-    };
-    switch ((kh + 4) / 2) {                                    // NS = ceil((kh + 3) / 2)
-    case 2: return launch(std::integral_constant<int, 2>{});
-    case 3: return launch(std::integral_constant<int, 3>{});
-    case 4: return launch(std::integral_constant<int, 4>{});
-    case 5: return launch(std::integral_constant<int, 5>{});
-    case 6: return launch(std::integral_constant<int, 6>{});
-    case 7: return launch(std::integral_constant<int, 7>{});
-    default: return launch(std::integral_constant<int, 8>{});
-    }
+    });
 }
 
 }  // namespace sysconv

@@ -89,6 +89,8 @@ hipError_t launch_conv2d_sbm(const float* x, int h, int w, size_t xp, const floa
 // Matrix-core path (conv2d_mfma.hip): any filter up to 13 x 13.
 bool has_conv2d_mfma(int kh, int kw);
 bool conv2d_mfma_taps_in_range(const float* f, int n);      // largest |f| is 0 or within [1e-30, 1e30]
+bool conv2d_mfma_rows_out(int oh, int ow, size_t yp);         // results through LDS
+int conv2d_mfma_block_rows(int oh, int ow, size_t yp, int kh);      // output rows of a workgroup
 hipError_t launch_conv2d_mfma(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                               float* y, size_t yp, hipStream_t s);
 
