@@ -247,6 +247,11 @@ def test_mfma_chains_on_a_stream_and_in_a_graph():
 
 # Results through LDS (from 40 M outputs on), blocks that end after each group of a chunk, right edges at every
 # position mod 4: integers below 8 with small integer taps are exact in this projection and in fp32, so the vector kernels say what is right.
+LDS_IMAGES = [(1, 6, 1323, 30372), (2, 3, 1157, 34790), (3, 3, 1691, 23898), (3, 13, 11821, 3560), (6, 5, 1164, 34612), (7, 7, 1162, 34683), (7, 4, 11575, 3640),
+              (4, 5, 2718, 14900), (9, 9, 2094, 19366), (11, 11, 1676, 24074), (13, 13, 1941, 20778)]         # test_mfma_rules.py: every NS, blocks and images that end inside a chunk
+WIDE_PITCH = [(kh, kw) for kh in range(1, 14) for kw in (1, 6, 13)]
+
+
 @pytest.mark.parametrize("kh,kw,h,w", [(3, 3, 2100, 2003), (2, 13, 1001, 4312), (1, 1, 4003, 1001), (3, 5, 1207, 3414), (5, 5, 6401, 6404), (13, 13, 6413, 6301),
                                        (8, 4, 6500, 6306), (11, 11, 7001, 6007), (4, 4, 899, 1003), (9, 9, 1777, 1302), (13, 7, 2503, 1001), (6, 6, 3001, 2048)])
 def test_mfma_rows_through_lds_and_block_ends(kh, kw, h, w):
@@ -259,6 +264,25 @@ def test_mfma_rows_through_lds_and_block_ends(kh, kw, h, w):
     assert torch.equal(y[1:-1, 2:-3], B.sys_conv2d(x, f, projection="FBS"))
     y[1:-1, 2:-3] = 0.5
     assert (y == 0.5).all()                                    # nothing outside the window
+
+
+@pytest.mark.parametrize("kh,kw,h,w", LDS_IMAGES)
+def test_mfma_rows_through_lds_for_every_number_of_units(kh, kw, h, w):
+    test_mfma_rows_through_lds_and_block_ends(kh, kw, h, w)
+
+
+@pytest.mark.parametrize("kh,kw", WIDE_PITCH)
+def test_mfma_rows_through_lds_on_a_wide_pitch(kh, kw):
+    """Small images whose output rows are more than 2^25 floats apart (a few times 128 MB of which are touched): single blocks of one chunk."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(kh)
+    x = torch.randint(-7, 8, (11 + kh, 490 + kw), device="cuda", generator=gen).float()
+    f = np.random.default_rng(kw).integers(-5, 6, (kh, kw)).astype(np.float32)
+    y = torch.empty((12, (1 << 25) + 8), dtype=torch.float32, device="cuda")
+    y[:, :500] = 0.5
+    B.sys_conv2d(x, f, y[:, 1:492], projection="MFMA")
+    assert torch.equal(y[:, 1:492], B.sys_conv2d(x, f, projection="FBS"))
+    assert (y[:, 0] == 0.5).all() and (y[:, 492:500] == 0.5).all()
 
 
 def test_mfma_rows_of_a_group_beyond_a_buffer_descriptor():
