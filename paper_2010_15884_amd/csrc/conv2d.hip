@@ -767,7 +767,7 @@ hipError_t launch_fbs_static(const float* x, int h, int w, size_t xp, const floa
 // from a sweep on MI355X (us with 1 / 2 / 3 / 4 rows): 4096^2 3x3 27.1 / 26.4 / 28.0 / 28.2,
 // 5x5 32.3 / 27.7 / 28.1 / 29.6, 7x7 51.7 / 41.2 / 42.1 / 39.6; 8192^2 5x5 115.5 / 95.3 / 96.8 / 102.2; columns with 3 / 4 / 6 / 8 rows 2000^2 10x1
 // 8.9 / 8.4 / 8.0 / 7.4, 500^2 15x1 3.8 / 3.9 / 4.5 / 5.1, 8000^2 13x1 level.
-bool has_conv2d_fbs_static(int kh, int kw)
+static bool has_conv2d_fbs_static(int kh, int kw)
 {
     const int small = kh < kw ? kh : kw, large = kh < kw ? kw : kh;
     return small >= 1 && small <= 7 && large <= kMaxK2D;
@@ -823,8 +823,8 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
 // their use, in a ring.  Left in the middle, the body has the ring copied to vector registers (92 to 150 of them with two and three rows); with every row guarded instead it stays in scalar registers (44 to 52).  us, left (12 and 14
 // columns without a ring, which was slower) / guarded: 6130^2 14x14 238 / 230, 415^2 12x12 6.05 / 5.1, 2500^2 8x12 24.9 / 24.1, 3109^2 9x9 31.4 / 30.5; 12 columns and more 0.97 with one row, 0.985 with two, 0.975 with three, 8 and 9
 // with three 0.97.  The others are quicker left: 10 and 11 columns (three rows 1.01, 5952x796 14x10 28.9 / 30.3; two 1.01), 8 and 9 with one (902^2 9x9 6.45 / 6.65) and level with two.  The tile kernel with run-time sizes that served these filters staged its rows in LDS
-// and handed the inputs on once for every filter row: us, that / this: 8192^2 11x11 354 / 257 (SBM 257), 6130^2 14x14 268 / 234, 3109^2 9x9 36.8 / 31.0, 5694x2688 9x15 85.7 / 72.0,
-// 1500^2 15x15 31.0 / 23.9, 491x4731 12x9 16.4 / 12.6, 902^2 9x9 8.6 / 6.5, 415^2 12x12 11.7 / 6.0.
+// and handed the inputs on once for every filter row: us, that / this: 8192^2 11x11 354 / 257 (SBM 257), 6130^2 14x14 268 / 230, 3109^2 9x9 36.8 / 30.5, 5694x2688 9x15 85.7 / 72.0,
+// 1500^2 15x15 31.0 / 23.9, 491x4731 12x9 16.4 / 12.6, 902^2 9x9 8.6 / 6.5, 415^2 12x12 11.7 / 5.1.
 // What bounds it: the vector ALUs on large images (11x11: 547 instructions for four outputs, 484 of them the multiply-adds), the latency of a wavefront's rows on small ones.
 namespace {
 constexpr int kFbsAhead = 4;
@@ -930,8 +930,8 @@ hipError_t launch_fbs_strip(const float* x, int h, int w, size_t xp, const float
 }  // namespace
 
 // Output rows of a wavefront of the strips, by the wavefronts that one row each would make: one row gives the most of them and the shortest, more share input rows and windows.  us with
-// 1 / 2 / 3 / 4 rows (wavefronts of one): 700^2 11x11 (2070) 6.7 / 7.4 / 8.9 / 10.8, 902^2 9x9 (3576) 6.5 / 6.5 / 7.9 / 8.4, 1000x1300 13x13 (5928) 12.4 / 11.6 / 12.1 / 16.6, 1500^2 15x15
-// (10402) 24.6 / 23.9 / 25.4 / 27.5, 4160x1150 10x10 (20755) 23.7 / 21.2 / 20.5 / 23.5, 8192^2 11x11 320 / 267 / 258 / 257.  Single rows: four (3000^2 1x12 16.5 / 15.6 / 16.4 / 15.2).
+// 1 / 2 / 3 / 4 rows (wavefronts of one): 700^2 11x11 (2070) 6.7 / 7.4 / 8.9 / 10.8, 902^2 9x9 (3576) 6.5 / 6.5 / 7.9 / 8.4, 1000x1300 13x13 (5928) 12.4 / 11.9 / 12.4, 2631x749 9x15
+// (10492) 17.0 / 16.5 / 16.6, 4160x1150 10x10 (20755) 23.7 / 21.2 / 20.5 / 23.5, 8192^2 11x11 320 / 267 / 258 / 257.  Single rows: four (3000^2 1x12 16.5 / 15.6 / 16.4 / 15.2).
 int conv2d_fbs_strip_rows(int oh, int ow, int kh, int kw)
 {
     if (kh == 1) return 4;

@@ -33,7 +33,7 @@
 // belongs to, whose sums wait in registers: no halo row is loaded or split twice within a block, and there is one barrier per chunk.  A block ends with
 // any group (matrix_block_groups).  Before, a workgroup of twelve wavefronts stepped through four rows at a time in lock-step and every lane split its own windows,
 // four times an input: us, so / this: 300^2 3x3 5.8 / 3.3, 585^2 12x12 10.4 / 6.2, 1222^2 11x11 10.1 / 7.8, 2021^2 12x9 15.5 / 12.5, 4096^2 9x9 33 / 28.5,
-// 6000^2 9x9 66 / 60, 8192^2 11x11 123 / 116; 150 random images and filters 0.74 on average; 8192^2 5x5 103.5 / 105.
+// 6000^2 9x9 66 / 60, 8192^2 11x11 121 / 114, 5x5 103 / 103, 7x7 108 / 109; 150 random images and filters 0.74 on average.
 //
 // Stores.  A group's row is 256 bytes of a wavefront; where output rows start anywhere in a 128-byte line, that is three lines, two of them shared
 // with the neighbours, and on large images these pieces reach memory one by one.  ROWS_OUT passes the results through LDS and stores 1 KB of a row at a
@@ -41,11 +41,12 @@
 // 8.0 / 8.5, 4096^2 9x9 28.8 / 29.8).  A strip at the right edge stores whole quads, and column by column only where a quad straddles the edge: four strided dwords for
 // every quad ended the launch with these strips (6000^2 9x9 69 / 58).
 //
-// What bounds it: large images the way of the stores and loads (a copy kernel with this walk takes 109 us on 8192^2, one of 256 columns 100, with rows on 64-byte boundaries 91:
-// strips shifted row by row onto those boundaries were tried here, 224 or 240 columns wide, and cost more in strips and edges than they gave, 124 - 128 us),
-// then the clock, which power lowers; small ones the chain taps - first chunk - units of one block.
+// What bounds it: large images how this walk's loads and stores reach memory, not how many they are (8192^2: 1.06 times the bytes of inputs and results, which the FBS kernel for 5x5 moves in 95 us; 11x11 takes
+// 111 us with an image of zeros, where the clock is high, and 3x3, with a third of the matrix instructions, 103), then the clock, which power lowers; small ones the chain taps - first chunk - units of one block.
+// Strips shifted row by row onto 64-byte boundaries, 224 or 240 columns wide, cost more in strips and edges than they give, 124 - 128 us.
 // Tried: strips of 256 columns with the 16 columns beyond as a fifth load (8192^2 112 - 117 us, 4096^2 30 - 33 and 1222^2 8.9), three or four workgroups a CU and
-// two chunks in flight (level to 10 % slower: it is not latency), cacheable stores (8192^2 111 without ROWS_OUT, but 4096^2 28 / 33).
+// two chunks in flight (level to 10 % slower: it is not latency), cacheable stores (long runs, us, this / through LDS / without: 8192^2 5x5 103 / 105 / 118, 11x11 114 / 116 / 116, 6401x6404
+// 5x5 65.5 / 69.5 / 70.7, 8000^2 11x11 116 / 115 / 119; without it is ahead for single rows, 8192^2 1x5 101 / 103 / 91; 4096^2 28 / - / 33).
 #include "launch.h"
 #include "matrix_blocks.h"
 #include "split_bf16.h"

@@ -15,8 +15,9 @@
 // The chunk (16 input rows x 256 columns) that holds such a value is marked, and which four of its rows, and the outputs
 // these rows reach are taken again with ordinary multiply-adds before the workgroup ends (plain_rows).  Measured (us; the
 // vector kernel / no such value / one in the image / in every twelfth chunk down a column / in every fourth / in every one):
-// 11x11 on 4096^2 71 / 43 / 48 / 51 / 68 / 92, on 8192^2 242 / 148 / 155 / 174 / 230 / 326, on 1500^2 14.7 / 13.8 / 17 / 20 / 22 / 23;
-// 15x15 on 3001x4003 107 / 46 / 51 / 69 / 93 / 100, on 300x400 15 / 8.8 / 19 / 19 / 19 / 16.
+// 11x11 on 4096^2 69 / 43 / 46 / 53 / 68 / 95, on 8192^2 256 / 141 / 162 / 191 / 244 / 349, on 1500^2 14.7 / 12.5 / 21 / 22 / 23 / 22;
+// 15x15 on 3001x4003 87 / 44 / 61 / 64 / 86 / 103, on 300x400 6.7 / 8.3 / 14.8 / 15.8 / 15.9 / 12.5.  At worst over 13 filters on 300x400 .. 4096^2: 1.7 times the vector kernel from 3 M outputs on (9x9 on
+// 2500^2), 2.5 times below (14x11 on 700^2).
 //
 // Data path.  A workgroup of four wavefronts walks down a block of rows of a 256-column strip, 16 input
 // rows (a "chunk") at a time.  A chunk is loaded into registers two chunks ahead of its use, split once
@@ -32,13 +33,12 @@
 //
 // What bounds it: the power of the package.  11x11 on 8192^2 issues 180 GFLOP; a large bf16 matrix product reaches 1.32 PFLOP/s on this
 // card (1.39 on another), at 1.87 GHz, and at that rate the instructions alone take 136 us (15x15 on 3001x4003: 50 GFLOP, 38 us).  With random
-// data the clock falls to 1.95 GHz in this kernel (2.39 with an image of zeros, 136 us), and what saves clocks lowers it further.  By the
-// counters the matrix cores are busy for 57 % of the clocks and other vector instructions for 17 %, LDS for 21 to 23 %, HBM reads are
-// 1.06 and 1.28 times the image; the two workgroups of a CU do not share it evenly (ends between 96 and 176 us, half by 123).
-// Measured (us, the vector kernels before / this; the best of eight batches, 11x11 on 8192^2 159 and 15x15 46 on average among other
-// passes): 11x11 on 8192^2 243 / 142, 15x15 on 3001x4003 106 / 44, 13x13 on 8192^2 406 / 156, 9x13 on 4096^2 76 / 41.
-// Tried on that account: the next chunk's split placed between the matrix instructions (an MFMA leaves room for two vector instructions)
-// with the windows read a unit ahead, 162 -> 165 us on 8192^2 and 0 to 7 % slower elsewhere; eight wavefronts a workgroup, one a CU, all
+// data the clock falls to 1.86 GHz in this kernel (155 us; 2.38 with an image of zeros, 123), and what saves clocks lowers it further.  By the
+// counters the matrix cores are busy for 62 % of the clocks and other vector instructions for 21 %, LDS for 26 %, HBM reads are
+// 1.12 and 1.24 times the image.
+// Measured (us, the best vector kernel / this, short runs): 11x11 on 8192^2 256 / 141, 15x15 on 3001x4003 87 / 44, 12x12 on 5630^2 146 / 78, 9x13 on 4096^2 72 / 42.
+// Tried on that account: the next chunk's split placed between the matrix instructions (an MFMA leaves room for two vector instructions),
+// 162 -> 165 us on 8192^2 and 0 to 7 % slower elsewhere; eight wavefronts a workgroup, one a CU, all
 // in step (they end together, at 1.57 GHz), 158 - 165.
 // Tried: 272 input columns per chunk (one wavefront splits a fifth piece and the others wait: 11x11 190 us with two
 // accumulators an output), one accumulator (2 % faster, but errors of 1.8e-7 instead of 6e-8), stores behind per-lane
@@ -548,13 +548,15 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
 // smaller error (2-norm against 64 bits, images on [0, 1), split / FBS: 3x12 3.2e-8 / 1.2e-7, 4x13 3.5e-8 / 1.3e-7, 5x12 4.3e-8 / 1.9e-7, 6x12 4.5e-8 / 2.0e-7, 7x13 4.5e-8 / 1.2e-7,
 // 13x5 4.3e-8 / 1.8e-7, 12x7 4.8e-8 / 1.5e-7, 6x14 1.2e-7 / 1.5e-7, 7x15 6.6e-8 / 1.1e-7).  Its time goes with the units, theirs with
 // the kh*kw taps, so the lines are drawn in taps per unit t; measured on squares of 277 .. 6500 and some other images (us, split / vector):
-//   14 or 15 rows or columns: from 11 columns and 10 taps a unit on, at every size (15x15 8.4 / 15 on 300x400; 7x15 6.2 / 7.5 on 500^2, 12.8 / 13.8 on 1500^2; 6x14 7.8 / 6.5 on 700^2,
-//   19.8 / 21.2 on 2300^2).  With fewer columns sums over 8 to 11 units in one accumulator are no more exact than the vector kernels' (14x9: off by 2.3e-7 against 2.2e-7;
+//   14 or 15 rows or columns: from 11 columns and 10 taps a unit on, at every size (15x15 8.3 / 6.7 on 300x400, 9.7 / 9.5 on 700^2, 25.2 / 47.2 on 2300^2; 14x11 9.7 / 7.8 on 700^2, 24.6 / 32.3 on 2300^2; 7x15 6.2 / 7.5
+//   on 500^2, 12.9 / 13.5 on 1500^2; 6x14 7.8 / 6.4 on 700^2, 19.7 / 21.1 on 2300^2).  With fewer columns sums over 8 to 11 units in one accumulator are no more exact than the vector kernels' (14x9: off by 2.3e-7 against 2.2e-7;
 //   14x11 1.9e-7 against 2.05e-7).
 //   A side of 12 or 13, or both 8 or more and not a square up to 11x11: from 12 taps a unit on at every size (4x12 4.6 / 3.7 on 500^2, 6.7 / 5.7 on 1000^2, 13.6 / 15.5 on 2300^2; 5x13 6.7 / 6.4 and
 //   13.9 / 18.7; 7x12 4.9 / 6.1 on 500^2, 14.7 / 21.1 on 2300^2), with fewer on images of 2 M outputs and more, the larger the closer they are to 7 (12x7 18.3 / 19.0 on 2200^2;
 //   12x6 18.0 / 17.4 on 2200^2, 27.1 / 30.7 on 3000^2; 13x5 27.0 / 26.2 on 3000^2, 50 / 52 on 4500^2).  Three rows leave half of the four units they take empty: from 5 M outputs on (3x13 19.4 / 18.7 on 3000^2, 35.5 / 37.3 on
-//   4500^2; 3x12 35.5 / 35.3 and 83 / 75 on 6500^2).  10x8 (t = 11.4) at every size (10x8, t = 11.4, on 700^2 7.2 / 8.7, 300x400 5.2 / 7.9; 8x10 16.2 / 23.7 on 2300^2; 12x12 5.5 / 11.5, 83 / 196 on 5630^2).
+//   4500^2; 3x12 35.5 / 35.3 and 83 / 75 on 6500^2).  With both sides 8 or more at
+//   every size: the FBS strips are up to 30 % quicker below 1 M outputs (10x8, t = 11.4, 5.1 / 4.3 on 300x400, 7.2 / 5.5 on 700^2, 8.2 / 7.7 on 1000^2, 17.4 / 19.9 on 2300^2; 8x10 6.8 / 5.4, 7.7 / 7.9, 16.1 / 20.3 on the last three; 12x12 5.5 / 5.2,
+//   7.7 / 7.3, 8.9 / 10.9, 18.9 / 31.3, 78 / 146 on 5630^2), but their error is three times as large (10x8 on 600^2 1.7e-7 / 4.8e-8).
 //   8x8 .. 11x11 (SBM) and filters of up to 11 with one side up to 7 (compile-time FBS): those kernels are quick on small images, and the split kernel wins once the
 //   image is large enough, the sooner the more taps a unit has.  Where the two are level, in M outputs: 8x8 (t = 10.7) 5, 9x9 (13.5) 2.2, 10x10 (14.3) 2 (and 2046x1002 outputs,
 //   five strips, 12.1 / 11.05), 11x11 (17.3) 0.5 .. 1.3: from 12 / (t - 9) on, as other filters of 64 taps and more do at the latest; 9x7 (10.5) 3 .. 4, 6x10 (12) 3, 6x11 (13.2) and 7x10 (14) 1.6 (752x2101 9.1 / 8.2 and 9.1 / 8.5,

@@ -308,8 +308,8 @@ hipError_t launch_strip(const float* x, int h, int w, size_t xp, const float* f,
 // down its 2*(ROWS-1)+kh input rows, four of them in flight.  A row is one load of 1 KB; its two windows are built once and applied to every output row whose
 // filter covers it.  Half as many outputs a lane as in the strips above give twice the wavefronts, less padding at the right edge, loads without gaps, and registers for four output rows.
 // Taps come in a row ahead of their use, in a ring, where one fits the scalar registers (a row of taps serves output row r two input rows after r - 1).  us, strips of
-// four outputs a lane / this: 4095x6001 7x7 29.5 / 26.6, 8192^2 11x11 98.6 / 89.3, 9x9 80.6 / 74.4, 3302x4516 15x15 41.7 / 37.0, 5564x1164 12x12 18.6 / 14.8, 780^2 12x12 7.1 / 5.7, 453^2 15x14 9.8 / 6.7;
-// 116 random images and filters 0.91 on average (15x15 on 1985x3879, a seventeenth strip for 13 columns, 21.6 / 22.2).
+// four outputs a lane / this: 4095x6001 7x7 28.9 / 26.5, 8192^2 11x11 93.5 / 92, 9x9 79.8 / 74.7, 3302x4516 15x15 39.6 / 36.2, 5564x1164 12x12 18.6 / 13.9, 780^2 12x12 7.1 / 5.7, 453^2 15x14 9.7 / 6.8;
+// 200 random images and filters 0.91 on average (15x15 on 1985x3879, a seventeenth strip for 13 columns, 21.6 / 22.0).
 // What bounds it: large images HBM with 1.2 to 1.3 times the image read (halo rows of neighbouring workgroups that miss L2); small ones the latency of the rows of one wavefront.
 // Tried: eight rows in flight (7x7 28.2 / 31.2), wavefronts of a workgroup side by side (7x7 30.6), six and eight output rows (30.0, 31.1; 12x12 18.8, 22.2).
 template <int KW>

@@ -78,7 +78,6 @@ int conv2d_stride2_pair_rows(int oh, int ow, int kh, int kw);              // an
 hipError_t launch_conv2d_fbs_stride2(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                                      float* y, size_t yp, hipStream_t s);
 int conv2d_vector_projection(int oh, int ow, size_t x_pitch, int kh, int kw);      // AUTO without the split kernel (api.hip)
-bool has_conv2d_fbs_static(int kh, int kw);      // sizes the FBS tile kernel is specialised for
 bool has_conv2d_bfs(int kh, int kw);
 hipError_t launch_conv2d_bfs(const float* x, int h, int w, size_t xp, const float* f, int kh, int kw,
                              float* y, size_t yp, hipStream_t s);

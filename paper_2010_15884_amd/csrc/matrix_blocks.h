@@ -6,7 +6,7 @@
 
 namespace sysconv {
 
-constexpr int kPlaces = 512;                // workgroups of four wavefronts the device holds at two a CU
+constexpr int kPlaces = 512;                // workgroups of four wavefronts a whole device of 256 CUs holds at two a CU (a partition of one holds fewer: the heights are then chosen for a larger device, the results are the same)
 constexpr int kNonTemporal = 2;             // the nt bit of a buffer store
 constexpr unsigned kNowhere = 0xffffff00u;  // offset of a buffer store that is dropped
 
