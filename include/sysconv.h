@@ -203,7 +203,7 @@ int sys_conv1d_stt(const float *d_x, size_t n,
  *            promise asked, taps 0 or within 2^-60 .. 2^40 in magnitude.  NaN, infinities, inputs
  *            from 2^80 on and non-zero ones below 2^-100 / smallest |tap| (2^-103 at the least)
  *            are taken with plain multiply-adds: an image with a few of them loses part of the
- *            gain, one with such values everywhere takes up to 1.7 times (2.5 below 3 M
+ *            gain, one with such values everywhere takes up to 1.75 times (2.5 below 3 M
  *            outputs) what the named projections take, which do not look at the values.  Of the rest, square
  *            filters up to 6x6 run FBS, or BFS where x_pitch * 4 is a power of two of at most
  *            16 KB; 7x7 FBS, BFS or SBM by size; 8x8 .. 11x11 SBM, and from 9x9 on FBS up to 0.4 M outputs; everything else FBS); BFS and SBM are built

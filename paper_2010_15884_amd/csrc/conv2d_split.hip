@@ -16,8 +16,8 @@
 // these rows reach are taken again with ordinary multiply-adds before the workgroup ends (plain_rows).  Measured (us; the
 // vector kernel / no such value / one in the image / in every twelfth chunk down a column / in every fourth / in every one):
 // 11x11 on 4096^2 69 / 43 / 46 / 53 / 68 / 95, on 8192^2 256 / 141 / 162 / 191 / 244 / 349, on 1500^2 14.7 / 12.5 / 21 / 22 / 23 / 22;
-// 15x15 on 3001x4003 87 / 44 / 61 / 64 / 86 / 103, on 300x400 6.7 / 8.3 / 14.8 / 15.8 / 15.9 / 12.5.  At worst over 13 filters on 300x400 .. 4096^2: 1.7 times the vector kernel from 3 M outputs on (9x9 on
-// 2500^2), 2.5 times below (14x11 on 700^2).
+// 15x15 on 3001x4003 87 / 44 / 61 / 64 / 86 / 103, on 300x400 6.7 / 8.3 / 14.8 / 15.8 / 15.9 / 12.5.  At worst over 13 filters on 300x400 .. 4096^2: 1.75 times the vector kernel from 3 M outputs on (11x11 on
+// 2048^2 23 / 40), 2.5 times below (14x11 on 700^2 7.9 / 20).
 //
 // Data path.  A workgroup of four wavefronts walks down a block of rows of a 256-column strip, 16 input
 // rows (a "chunk") at a time.  A chunk is loaded into registers two chunks ahead of its use, split once
@@ -544,7 +544,8 @@ bool conv2d_split_takes(int h, int w, size_t yp, const float* f, int kh, int kw)
     return split_takes_taps(f, kh * kw);
 }
 
-// Where AUTO takes the split kernel rather than the best vector-ALU kernel: where it is faster, and for filters that only it and the FBS kernels serve also where it is not, for its
+// Where AUTO takes the split kernel rather than the best vector-ALU kernel: where it is faster, and for filters with a side of 12 to 15 or with both of 8 and more (squares that SBM is built for aside), which it has
+// served longest, also where it is not, for its
 // smaller error (2-norm against 64 bits, images on [0, 1), split / FBS: 3x12 3.2e-8 / 1.2e-7, 4x13 3.5e-8 / 1.3e-7, 5x12 4.3e-8 / 1.9e-7, 6x12 4.5e-8 / 2.0e-7, 7x13 4.5e-8 / 1.2e-7,
 // 13x5 4.3e-8 / 1.8e-7, 12x7 4.8e-8 / 1.5e-7, 6x14 1.2e-7 / 1.5e-7, 7x15 6.6e-8 / 1.1e-7).  Its time goes with the units, theirs with
 // the kh*kw taps, so the lines are drawn in taps per unit t; measured on squares of 277 .. 6500 and some other images (us, split / vector):
