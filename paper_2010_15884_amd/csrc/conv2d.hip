@@ -821,9 +821,10 @@ hipError_t launch_fbs_static_any(const float* x, int h, int w, size_t xp, const 
 // Filters of 8 to 15 columns: a wavefront takes ROWS output rows of a strip of 256 input columns and walks down their ROWS + kh - 1 input rows, four of them in
 // flight.  Each row's KW-wide window is built once with KW - 1 hand-overs and applied to every output row whose filter covers it; the taps come in a row ahead of
 // their use, in a ring.  Left in the middle, the body has the ring copied to vector registers (92 to 150 of them with two and three rows); with every row guarded instead it stays in scalar registers (44 to 52).  us, left (12 and 14
-// columns without a ring, which was slower) / guarded: 6130^2 14x14 238 / 230, 415^2 12x12 6.05 / 5.1, 2500^2 8x12 24.9 / 24.1, 3109^2 9x9 31.4 / 30.5; 12 columns and more 0.97 with one row, 0.985 with two, 0.975 with three, 8 and 9
-// with three 0.97.  The others are quicker left: 10 and 11 columns (three rows 1.01, 5952x796 14x10 28.9 / 30.3; two 1.01), 8 and 9 with one (902^2 9x9 6.45 / 6.65) and level with two.  The tile kernel with run-time sizes that served these filters staged its rows in LDS
-// and handed the inputs on once for every filter row: us, that / this: 8192^2 11x11 354 / 257 (SBM 257), 6130^2 14x14 268 / 230, 3109^2 9x9 36.8 / 30.5, 5694x2688 9x15 85.7 / 72.0,
+// columns without a ring, which was slower) / guarded: 6130^2 14x14 238 / 230, 415^2 12x12 6.05 / 5.1, 2500^2 8x12 24.9 / 24.1; 12 columns and more 0.97 with one row, 0.985 with two, 0.975 with three.
+// Fewer columns are level or quicker left: 10 and 11 (three rows 1.01, 5952x796 14x10 28.9 / 30.3; two 1.01), 8 and 9 with one (902^2 9x9 6.45 / 6.65), with two, and with three (8 to 11 rows a filter 0.97, 3109^2 9x9 31.4 / 30.5; 13 and 14
+// 1.035, 2748x4017 13x9 43.8 / 46.2).  The tile kernel with run-time sizes that served these filters staged its rows in LDS
+// and handed the inputs on once for every filter row: us, that / this: 8192^2 11x11 354 / 257 (SBM 257), 6130^2 14x14 268 / 230, 3109^2 9x9 36.8 / 31.4, 5694x2688 9x15 85.7 / 72.0,
 // 1500^2 15x15 31.0 / 23.9, 491x4731 12x9 16.4 / 12.6, 902^2 9x9 8.6 / 6.5, 415^2 12x12 11.7 / 5.1.
 // What bounds it: the vector ALUs on large images (11x11: 547 instructions for four outputs, 484 of them the multiply-adds), the latency of a wavefront's rows on small ones.
 namespace {
@@ -834,7 +835,7 @@ __device__ __forceinline__ void fbs_strip_rows(kernarg_floats taps_f, const floa
 {
     // filter row p waits in slot p mod RING from input row p - 1 on to input row p + ROWS - 1
     constexpr int RING = ROWS == 1 ? 2 : ROWS <= 3 ? 4 : 0;
-    constexpr bool GUARDED = KW >= 12 || (KW <= 9 && ROWS == 3);
+    constexpr bool GUARDED = KW >= 12;
     static_assert(RING == 0 || RING >= ROWS + 1, "a slot is free again when the next filter row comes in");
     const int rows_in = rows_out - 1 + kh;
     const EdgeQuad quad(col, w_img);

@@ -42,7 +42,7 @@
 // every quad ended the launch with these strips (6000^2 9x9 69 / 58).
 //
 // What bounds it: large images how this walk's loads and stores reach memory, not how many they are (8192^2: 1.06 times the bytes of inputs and results, which the FBS kernel for 5x5 moves in 95 us; 11x11 takes
-// 111 us with an image of zeros, where the clock is high, and 3x3, with a third of the matrix instructions, 103), then the clock, which power lowers; small ones the chain taps - first chunk - units of one block.
+// 111 us with an image of zeros, where the clock is high, and 3x3, with three sevenths of the matrix instructions, 103), then the clock, which power lowers; small ones the chain taps - first chunk - units of one block.
 // Strips shifted row by row onto 64-byte boundaries, 224 or 240 columns wide, cost more in strips and edges than they give, 124 - 128 us.
 // Tried: strips of 256 columns with the 16 columns beyond as a fifth load (8192^2 112 - 117 us, 4096^2 30 - 33 and 1222^2 8.9), three or four workgroups a CU and
 // two chunks in flight (level to 10 % slower: it is not latency), cacheable stores (long runs, us, this / through LDS / without: 8192^2 5x5 103 / 105 / 118, 11x11 114 / 116 / 116, 6401x6404

@@ -20,7 +20,8 @@ __device__ __forceinline__ void lds_barrier()
 
 // Output groups (of 4 or 8 rows) of a workgroup's block, at most `most`: those whose modelled time is least.  A block of m groups takes
 // u = steps * (units_per_group (m - 1) + units) steps, one a unit of two input rows and column of matrix instructions.  One workgroup a CU
-// takes u, two 6 + 1.1 u (in time of a step); beyond that workgroups follow one another freely, no rounds are seen, a block costs its steps and `setup` more (taps, first
+// takes u, two 6 steps + 1.1 u (in time of a step; with 8 x 2 offsets, two columns, blocks of one group and two or of two groups and one a CU: us 744x580 11x14 9.6 / 8.7, 739x747 10x14 9.8 / 8.9, 1473x288 12x15
+// 10.3 / 9.45; where one group leaves one a CU 500^2 14x14 8.6 / 9.4); beyond that workgroups follow one another freely, no rounds are seen, a block costs its steps and `setup` more (taps, first
 // loads, units that only finish groups apart), and the launch ends with blocks that are still under way (u / 2).  Fitted to sweeps over all heights on 101 random and listed images and
 // filters (256 .. 8192 rows and columns): the height chosen is 0.8 % slower than the best one on average (MFMA: 60 images, 2 %), 8 % at most.  Whole chunks of 16
 // rows in whole rounds, as blocks were chosen before, lost 15 % on 2000^2 11x11 (9 groups of four rows 15.7 us, 8 18.8, 12 16.8), 17 % on 3001x4003 15x15 (13 groups of eight rows 45.2,
@@ -34,7 +35,7 @@ inline int matrix_block_groups(int all, int strips, int units, int units_per_gro
         if (m > most || (m > 1 && m > all)) break;
         const double places = (double)((all + m - 1) / m) * strips * (1.0 / kPlaces);
         const double u = steps * (units_per_group * (m - 1) + units);
-        const double cost = places > 1.0 ? places * (setup + u) + 0.5 * u : places > 0.5 ? 6.0 + 1.1 * u : u;
+        const double cost = places > 1.0 ? places * (setup + u) + 0.5 * u : places > 0.5 ? 6.0 * steps + 1.1 * u : u;
         if (m == 1 || cost < least) { best = m; least = cost; }
     }
     const int blocks = (all + best - 1) / best;

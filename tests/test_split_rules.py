@@ -67,3 +67,10 @@ def test_images_with_marked_chunks_have_blocks_of_every_length():
     for kh, kw, most in ((13, 13, 32), (4, 13, 32), (15, 15, 56), (6, 14, 56)):
         seen = {chunks(kh, kw, h, w) for w in (100, 250, 600, 1201, 5000, 40000) for h in range(1000, 200000, 500)}
         assert max(seen) == most
+
+
+@pytest.mark.parametrize("kh,kw,h,w,groups", [(11, 14, 744, 580, 2), (13, 14, 304, 2677, 2), (10, 14, 739, 747, 2), (12, 15, 1473, 288, 2),      # one group: more than 256 workgroups
+                                              (14, 14, 500, 500, 1), (15, 15, 300, 400, 1), (9, 15, 282, 797, 1)])
+def test_eight_by_two_prefers_one_workgroup_a_cu(kh, kw, h, w, groups):
+    """Blocks of one group, two a CU, are 10 % slower than blocks of two groups, one a CU; one a CU they are 6 to 8 % faster."""
+    assert block_rows(h - kh + 1, w - kw + 1, kh, kw) == 8 * groups
